@@ -17,73 +17,127 @@
 
 namespace lbm {
 
+// 1 / a and sqrt(a) from the hardware estimates and Newton steps.  The
+// compiler's IEEE forms also scale by powers of two for operands near the
+// ends of the exponent range; here 1 / a is taken of porosities, heat
+// capacities and momentum denominators (1e-3 .. 1e3), and the root's operand
+// is bounded from below: a root below the bound's root comes out too small,
+// never NaN, which no result can feel (it is a speed that is added to 1/2).
+// FP32: 3 and 6 instructions instead of 10 and 16, FP64: 5 and 11 instead of
+// 10 and 20; results within 1 ulp.  NaN and infinity come out as NaN.  Used
+// by the reverse step only: the forward step's roundings are IEEE's.
+__device__ __forceinline__ float fast_rcp(float a) {
+  const float y = __builtin_amdgcn_rcpf(a);
+  return __builtin_fmaf(__builtin_fmaf(-a, y, 1.0f), y, y);
+}
+__device__ __forceinline__ double fast_rcp(double a) {
+  double y = __builtin_amdgcn_rcp(a);
+  y = __builtin_fma(__builtin_fma(-a, y, 1.0), y, y);
+  return __builtin_fma(__builtin_fma(-a, y, 1.0), y, y);
+}
+__device__ __forceinline__ float fast_sqrt(float a) {
+  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(a, 1.17549435e-38f));
+  const float s = a * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, a), 0.5f * y, s);
+}
+__device__ __forceinline__ double fast_sqrt(double a) {
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(a, 1e-300));
+  double g = a * y, h = 0.5 * y;
+  double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  r = __builtin_fma(-g, g, a);
+  g = __builtin_fma(r, h, g);
+  r = __builtin_fma(-g, g, a);
+  return __builtin_fma(r, h, g);
+}
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+
+// Sum of the five populations g of a scalar lattice, and the temperature
+// rise from the five temperature populations (isig: 1 / sigma, 1 without the
+// heat-capacity ratio).
+template <typename R>
+__device__ __forceinline__ R sum5(const R* g) {
+  return g[0] + ((g[1] + g[3]) + (g[2] + g[4]));
+}
+template <typename R>
+__device__ __forceinline__ R theta_of(const R* g, R isig) {
+  return sum5(g) * isig;
+}
+
+// The forward step's material with what the reverse step takes of it:
+// 1 / phi, the linear drag coefficient dl = phi nu / K, the equilibrium
+// weights a = (4 + b) / 20 of a moving scalar population and the reciprocals
+// of rho c_p and sigma.
+template <typename R>
+struct AdjMat : Mat<R> {
+  R iphi, dl, aT, aC, irc, isig;
+};
+template <typename R>
+__device__ __forceinline__ AdjMat<R> adj_material(const Consts<R>& k, const R* __restrict__ phi_f,
+                                                  const R* __restrict__ invk_f, const R* __restrict__ d_f, int x,
+                                                  int y) {
+  AdjMat<R> m;
+  static_cast<Mat<R>&>(m) = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, x, y);
+  m.iphi = fast_rcp(m.phi);
+  m.dl = m.phi * k.nu * m.invk;
+  m.aT = fma_(R(0.05), m.bT, R(0.2));
+  m.aC = fma_(R(0.05), m.bC, R(0.2));
+  m.irc = fast_rcp(m.rhocp);
+  m.isig = (k.flags & F_SIGMA_ENERGY) ? k.rhocp_f * m.irc : R(1);
+  return m;
+}
+// outlet_scalar_material with the reverse step's quantities.
+template <typename R>
+__device__ __forceinline__ void outlet_scalar_adj_material(AdjMat<R>& mb, const AdjMat<R>& mp) {
+  outlet_scalar_material(mb, mp);
+  mb.aT = mp.aT;
+  mb.aC = mp.aC;
+  mb.irc = mp.irc;
+  mb.isig = mp.isig;
+}
+
 // EXT: the instances of the reverse step that also cover Boussinesq
-// buoyancy, the energy equation with the heat-capacity ratio sigma and the
-// pressure-driven inlet; the default instances leave their terms out (and
-// their registers free).
+// buoyancy, the energy equation with the heat-capacity ratio sigma, the
+// pressure-driven inlet and the thin-film CL; the default instances leave
+// their terms out (and their registers free).
+//
+// Adjoints of the medium's quantities as the forward step uses them.
 template <typename R>
 struct MatAdj {
-  R phi = R(0), invk = R(0), sqk = R(0), fphi = R(0), l0 = R(0), l1 = R(0), bT = R(0), bC = R(0), rhocp = R(0);
+  R phi = R(0), dl = R(0), l0 = R(0), l1 = R(0), aT = R(0), aC = R(0), rhocp = R(0);
   R sig = R(0);  // heat-capacity ratio (EXT only)
 };
 
 // Chain the adjoints of the derived material quantities to (phi, 1/K, D).
 template <typename R, bool EXT = false>
-__device__ __forceinline__ void material_adj(const Consts<R>& k, const Mat<R>& m, const MatAdj<R>& a, R& g_phi,
+__device__ __forceinline__ void material_adj(const Consts<R>& k, const AdjMat<R>& m, const MatAdj<R>& a, R& g_phi,
                                              R& g_invk, R& g_d) {
-  const R phi = m.phi;
-  const R iphi = R(1) / phi, irc = R(1) / m.rhocp;
-  R lphi = a.phi, linvk = a.invk, lsqk = a.sqk, lfphi = a.fphi;
-  // l1 = phi fphi sqk / 2
-  lphi += a.l1 * m.fphi * m.sqk * R(0.5);
-  lfphi += a.l1 * phi * m.sqk * R(0.5);
-  lsqk += a.l1 * phi * m.fphi * R(0.5);
-  // l0 = 1/2 + phi nu invk / 4
-  lphi += a.l0 * k.nu * m.invk * R(0.25);
-  linvk += a.l0 * phi * k.nu * R(0.25);
-  // fphi = 0.143 phi^-1.5
-  lphi += lfphi * R(-1.5) * m.fphi * iphi;
-  // sqk = sqrt(invk); derivative taken as 0 at invk = 0 (clear fluid)
-  if (m.sqk > R(0)) linvk += lsqk * R(0.5) / m.sqk;
-  // rhocp = phi rhocp_f + (1 - phi) rhocp_s; alpha (Eq. 19) -> bT = 20 sqrt3 alpha - 4
-  const R c20s3 = R(34.64101615137754587);
-  const R alpha = (m.bT + R(4)) * R(0.028867513459481288225);  // 1 / (20 sqrt 3)
-  const R drc = k.rhocp_f - k.rhocp_s;
-  const R lalpha = a.bT * c20s3;
-  if (EXT && (k.flags & F_SIGMA_ENERGY)) {
-    // alpha = k_eff alpha_scale / rhocp_f, sigma = rhocp / rhocp_f
-    lphi += lalpha * (k.k_f - k.k_s) * k.alpha_scale / k.rhocp_f;
-    lphi += (a.rhocp + a.sig / k.rhocp_f) * drc;
+  // dl = phi nu / K, l0 = 1/2 + dl / 4, l1 = c phi^-1/2 K^-1/2 (its
+  // derivative in 1/K taken as 0 at 1/K = 0, the clear fluid)
+  const R ldl = fma_(R(0.25), a.l0, a.dl);
+  R lphi = a.phi + k.nu * m.invk * ldl - R(0.5) * a.l1 * m.l1 * m.iphi;
+  R linvk = m.phi * k.nu * ldl;
+  if (m.invk > R(0)) linvk += R(0.5) * a.l1 * m.l1 / m.invk;
+  // rho c_p = phi rhocp_f + (1 - phi) rhocp_s; aT = sqrt 3 alpha (Eq. 19)
+  const R drc = k.rhocp_f - k.rhocp_s, dk = k.aT_f - k.aT_s;
+  if (EXT && (k.flags & F_SIGMA_ENERGY)) {  // aT = k_eff / (rho c_p)_f, sigma = rho c_p / (rho c_p)_f
+    lphi += a.aT * dk * k.irc_f + (a.rhocp + a.sig * k.irc_f) * drc;
   } else {
-    lphi += lalpha * ((k.k_f - k.k_s) * k.alpha_scale - alpha * drc) * irc;
-    lphi += a.rhocp * drc;
+    lphi += a.aT * (dk - m.aT * drc) * m.irc + a.rhocp * drc;
   }
   g_phi += lphi;
   g_invk += linvk;
-  g_d += a.bC * c20s3;
+  g_d += a.aC * R(1.7320508075688772935);
 }
 
-// Adjoint of meq_shifted(p, ux, uy, phi) given the adjoint lm[1..8] of the
-// moments; iphi = 1 / phi.
-template <typename R>
-__device__ __forceinline__ void meq_adj(R p, R ux, R uy, R phi, R iphi, const R (&lm)[9], R& lp, R& lux, R& luy,
-                                        R& lphi) {
-  const R u2 = ux * ux + uy * uy;
-  lp += R(6) * phi * lm[1] - R(9) * phi * lm[2];
-  lphi += R(6) * p * lm[1] - R(9) * p * lm[2] + (lm[2] - lm[1]) * R(3) * u2 * iphi * iphi -
-          (ux * ux - uy * uy) * iphi * iphi * lm[7] - ux * uy * iphi * iphi * lm[8];
-  const R a12 = R(6) * iphi * (lm[1] - lm[2]);
-  lux += a12 * ux + lm[3] - lm[4] + R(2) * ux * iphi * lm[7] + uy * iphi * lm[8];
-  luy += a12 * uy + lm[5] - lm[6] - R(2) * uy * iphi * lm[7] + ux * iphi * lm[8];
-}
-
-// Forward intermediates of flow_macros kept for its adjoint, with the
-// reciprocals the adjoint divides by (each taken once per node).
+// Forward intermediates of flow_macros kept for its adjoint.
 template <typename R>
 struct MacroTape {
-  R vx, vy, vm, r, den, ux, uy, um, drag, s18, p, Fx, Fy;
-  R iphi, iden, ir;  // 1 / phi, 1 / den, 1 / r
-  R ax, ay, thb;     // acceleration, and the temperature rise buoyancy takes it from (EXT)
+  R vx, vy, vm, ir, iden, ux, uy, u2, Fx, Fy, drag;  // ir: 1 / sqrt(l0^2 + l1 |v|)
+  R ax, ay, thb;  // acceleration, and the temperature rise buoyancy takes it from (EXT)
 };
 
 // The acceleration a of flow_macros is on when the test-mode body force is,
@@ -93,197 +147,87 @@ __device__ __forceinline__ bool accelerated(const Consts<R>& k) {
   return (k.flags & F_BODY_FORCE) || (EXT && (k.flags & F_BUOYANCY));
 }
 
-template <typename R, bool EXT = false>
-__device__ __forceinline__ MacroTape<R> flow_macros_tape(const R (&f)[19], const Mat<R>& m, const Consts<R>& k) {
+// f: the nine flow populations; th: the node's temperature rise (EXT).
+template <typename R, bool EXT>
+__device__ __forceinline__ MacroTape<R> flow_macros_tape(const R* f, R th, const AdjMat<R>& m, const Consts<R>& k) {
   MacroTape<R> t;
-  t.vx = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
-  t.vy = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
-  if constexpr (EXT) {
-    t.ax = R(0);
-    t.ay = R(0);
-    t.thb = R(0);
+  const R b57 = f[5] - f[7], b68 = f[6] - f[8];
+  t.vx = (f[1] - f[3]) + (b57 - b68);
+  t.vy = (f[2] - f[4]) + (b57 + b68);
+  t.ax = t.ay = t.thb = R(0);
+  if (accelerated<R, EXT>(k)) {
     if (k.flags & F_BODY_FORCE) {
       t.ax = k.ax;
       t.ay = k.ay;
     }
-    if (k.flags & F_BUOYANCY) {
-      t.thb = theta_of(f + 9, m.sig, k);
-      t.ax += k.bx * t.thb;
-      t.ay += k.by * t.thb;
+    if (EXT && (k.flags & F_BUOYANCY)) {
+      t.thb = th;
+      t.ax += k.bx * th;
+      t.ay += k.by * th;
     }
-    if (accelerated<R, EXT>(k)) {
-      t.vx += R(0.5) * m.phi * t.ax;
-      t.vy += R(0.5) * m.phi * t.ay;
-    }
-  } else if (k.flags & F_BODY_FORCE) {
-    t.vx += R(0.5) * m.phi * k.ax;
-    t.vy += R(0.5) * m.phi * k.ay;
+    t.vx += R(0.5) * m.phi * t.ax;
+    t.vy += R(0.5) * m.phi * t.ay;
   }
-  t.vm = dsqrt(t.vx * t.vx + t.vy * t.vy);
-  t.r = dsqrt(m.l0 * m.l0 + m.l1 * t.vm);
-  t.den = m.l0 + t.r;
-  t.iden = R(1) / t.den;
-  t.ir = R(1) / t.r;
+  t.vm = fast_sqrt(fma_(t.vx, t.vx, t.vy * t.vy));
+  const R r = fast_sqrt(fma_(m.l1, t.vm, m.l0 * m.l0));
+  t.ir = fast_rcp(r);
+  t.iden = fast_rcp(m.l0 + r);
   t.ux = t.vx * t.iden;
   t.uy = t.vy * t.iden;
-  const R u2 = t.ux * t.ux + t.uy * t.uy;
-  t.um = dsqrt(u2);
-  t.drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * t.um);
+  t.u2 = fma_(t.ux, t.ux, t.uy * t.uy);
+  t.drag = fma_(R(2) * m.l1, t.vm * t.iden, m.dl);
   t.Fx = -t.drag * t.ux;
   t.Fy = -t.drag * t.uy;
-  if constexpr (EXT) {
-    if (accelerated<R, EXT>(k)) {
-      t.Fx += m.phi * t.ax;
-      t.Fy += m.phi * t.ay;
-    }
-  } else if (k.flags & F_BODY_FORCE) {
-    t.Fx += m.phi * k.ax;
-    t.Fy += m.phi * k.ay;
+  if (accelerated<R, EXT>(k)) {
+    t.Fx += m.phi * t.ax;
+    t.Fy += m.phi * t.ay;
   }
-  t.s18 = f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
-  t.iphi = R(1) / m.phi;
-  t.p = R(0.6) * t.iphi * t.s18 - R(0.4) * u2 * t.iphi * t.iphi;
   return t;
 }
 
-// Adjoint of flow_macros: given the adjoints of (ux, uy, p, Fx, Fy), add the
-// adjoints of the flow populations to lf[0..8] (with buoyancy also of the
-// temperature populations, lf[9..13]) and of the material to ma.
-template <typename R, bool EXT = false>
-__device__ __forceinline__ void flow_macros_adj(const MacroTape<R>& t, const Mat<R>& m, const Consts<R>& k, R lux,
-                                                R luy, R lp, R lFx, R lFy, R* lf, MatAdj<R>& ma) {
-  const R iphi = t.iphi;
-  const R u2 = t.ux * t.ux + t.uy * t.uy;
-  // p = 0.6 iphi s18 - 0.4 u2 iphi^2
-  const R ls18 = R(0.6) * iphi * lp;
-  R lu2 = R(-0.4) * iphi * iphi * lp;
-  R liphi = (R(0.6) * t.s18 - R(0.8) * u2 * iphi) * lp;
-  // F = -drag u (+ phi a)
-  R lax = R(0), lay = R(0);
-  if constexpr (EXT) {
-    if (accelerated<R, EXT>(k)) {
-      ma.phi += t.ax * lFx + t.ay * lFy;
-      lax += m.phi * lFx;
-      lay += m.phi * lFy;
-    }
-  } else if (k.flags & F_BODY_FORCE) {
-    ma.phi += k.ax * lFx + k.ay * lFy;
-  }
-  const R ldrag = -(t.ux * lFx + t.uy * lFy);
-  lux += -t.drag * lFx;
-  luy += -t.drag * lFy;
-  // drag = phi (nu invk + fphi sqk um)
-  ma.phi += (k.nu * m.invk + m.fphi * m.sqk * t.um) * ldrag;
-  ma.invk += m.phi * k.nu * ldrag;
-  ma.fphi += m.phi * m.sqk * t.um * ldrag;
-  ma.sqk += m.phi * m.fphi * t.um * ldrag;
-  const R lum = m.phi * m.fphi * m.sqk * ldrag;
-  if (t.um > R(0)) lu2 += lum * R(0.5) / t.um;  // one division (vm, um > 0 only in moving cells)
-  lux += R(2) * t.ux * lu2;
-  luy += R(2) * t.uy * lu2;
-  ma.phi += -iphi * iphi * liphi;
-  // u = v / den, den = l0 + r, r = sqrt(l0^2 + l1 vm)
-  R lvx = lux * t.iden, lvy = luy * t.iden;
-  const R lden = -(t.ux * lux + t.uy * luy) * t.iden;
+// Adjoint of v -> (u, F): from the adjoints of u and F the adjoints lvx, lvy
+// of v = sum e f; the material's added to ma.  With buoyancy (EXT) the
+// adjoint of the temperature rise is added to lth.
+template <typename R, bool EXT>
+__device__ __forceinline__ void flow_macros_adj(const MacroTape<R>& t, const AdjMat<R>& m, const Consts<R>& k, R lux,
+                                                R luy, R lFx, R lFy, R& lvx, R& lvy, R& lth, MatAdj<R>& ma) {
+  // F = -drag u (+ phi a), drag = dl + 2 l1 |v| / den
+  const R um = t.vm * t.iden;
+  const R ldrag = -fma_(t.ux, lFx, t.uy * lFy);
+  lux = fma_(-t.drag, lFx, lux);
+  luy = fma_(-t.drag, lFy, luy);
+  ma.dl += ldrag;
+  ma.l1 = fma_(R(2) * um, ldrag, ma.l1);
+  const R lum = R(2) * m.l1 * ldrag;
+  // u = v / den, |u| = |v| / den, den = l0 + r, r = sqrt(l0^2 + l1 |v|)
+  const R lden = -t.iden * fma_(um, lum, fma_(t.ux, lux, t.uy * luy));
   const R ldr = lden * t.ir;
-  ma.l0 += lden + ldr * m.l0;
-  ma.l1 += ldr * t.vm * R(0.5);
-  const R lvm = ldr * m.l1 * R(0.5);
-  if (t.vm > R(0)) {
+  ma.l0 += fma_(ldr, m.l0, lden);
+  ma.l1 = fma_(R(0.5) * t.vm, ldr, ma.l1);
+  const R lvm = fma_(R(0.5) * m.l1, ldr, lum * t.iden);
+  lvx = lux * t.iden;
+  lvy = luy * t.iden;
+  if (t.vm > R(0)) {  // |v| of a cell at rest: derivative taken as 0
     const R q = lvm / t.vm;
-    lvx += q * t.vx;
-    lvy += q * t.vy;
+    lvx = fma_(q, t.vx, lvx);
+    lvy = fma_(q, t.vy, lvy);
   }
-  if constexpr (EXT) {
-    if (accelerated<R, EXT>(k)) {
-      ma.phi += R(0.5) * (t.ax * lvx + t.ay * lvy);
-      lax += R(0.5) * m.phi * lvx;
-      lay += R(0.5) * m.phi * lvy;
-    }
-  } else if (k.flags & F_BODY_FORCE) {
-    ma.phi += R(0.5) * (k.ax * lvx + k.ay * lvy);
+  if (accelerated<R, EXT>(k)) {  // a enters F as phi a and v as phi a / 2
+    const R lx = fma_(R(0.5), lvx, lFx), ly = fma_(R(0.5), lvy, lFy);
+    ma.phi += t.ax * lx + t.ay * ly;
+    if (EXT && (k.flags & F_BUOYANCY)) lth += m.phi * (k.bx * lx + k.by * ly);
   }
-  if (EXT && (k.flags & F_BUOYANCY)) {  // a = ... + b theta, theta = sum g_T (/ sigma)
-    R lth = k.bx * lax + k.by * lay;
-    if (k.flags & F_SIGMA_ENERGY) {
-      const R isg = R(1) / m.sig;
-      ma.sig += -t.thb * isg * lth;
-      lth *= isg;
-    }
-#pragma unroll
-    for (int i = 9; i < 14; ++i) lf[i] += lth;
+}
+
+// Share of the adjoint of theta = (sum g) / sigma that goes onto every
+// population; sigma's own part to ma.
+template <typename R, bool EXT>
+__device__ __forceinline__ R theta_adj(R lth, R th, const AdjMat<R>& m, const Consts<R>& k, MatAdj<R>& ma) {
+  if (EXT && (k.flags & F_SIGMA_ENERGY)) {
+    ma.sig -= th * m.isig * lth;
+    return lth * m.isig;
   }
-  // v = sum e f, s18 = sum_{1..8} f
-  lf[1] += lvx + ls18;
-  lf[2] += lvy + ls18;
-  lf[3] += -lvx + ls18;
-  lf[4] += -lvy + ls18;
-  lf[5] += lvx + lvy + ls18;
-  lf[6] += -lvx + lvy + ls18;
-  lf[7] += -lvx - lvy + ls18;
-  lf[8] += lvx - lvy + ls18;
-}
-
-// (M^T y)_i = sum_k M[k][i] y_k: the columns of the Eq. 3 matrix (integer
-// coefficients, additions only).
-template <typename R>
-__device__ __forceinline__ void mt_times(const R (&y)[9], R* out) {
-  const R b14 = y[0] - y[1] - R(2) * y[2];
-  const R b58 = y[0] + R(2) * y[1] + y[2];
-  out[0] = y[0] - R(4) * y[1] + R(4) * y[2];
-  out[1] = b14 + y[3] - R(2) * y[4] + y[7];
-  out[2] = b14 + y[5] - R(2) * y[6] - y[7];
-  out[3] = b14 - y[3] + R(2) * y[4] + y[7];
-  out[4] = b14 - y[5] + R(2) * y[6] - y[7];
-  out[5] = b58 + y[3] + y[4] + y[5] + y[6] + y[8];
-  out[6] = b58 - y[3] - y[4] + y[5] + y[6] - y[8];
-  out[7] = b58 - y[3] - y[4] - y[5] - y[6] + y[8];
-  out[8] = b58 + y[3] + y[4] - y[5] - y[6] - y[8];
-}
-
-// 1 / diag(M M^T): M^{-T} a = (M a) / diag(M M^T).
-template <typename R>
-__device__ __forceinline__ R inv_mmt(int i) {
-  constexpr double d[9] = {1.0 / 9, 1.0 / 36, 1.0 / 36, 1.0 / 6, 1.0 / 12, 1.0 / 6, 1.0 / 12, 0.25, 0.25};
-  return R(d[i]);
-}
-
-template <typename R>
-__device__ __forceinline__ void m_times(const R* a, R (&out)[9]) {
-  R f[19];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) f[i] = a[i];
-  moments9(f, out);
-}
-
-// Adjoint of add_geq(X, ux, uy, b, sgn, g): given lg (adjoint of g) add the
-// adjoints of X, ux, uy, b.
-template <typename R>
-__device__ __forceinline__ void geq_adj(R X, R ux, R uy, R b, R sgn, const R* lg, R& lX, R& lux, R& luy, R& lb) {
-  const R n0 = (lg[0] + lg[1] + lg[2] + lg[3] + lg[4]) * R(0.2);
-  const R n1 = (lg[1] - lg[3]) * R(0.5);
-  const R n2 = (lg[2] - lg[4]) * R(0.5);
-  const R n3 = (R(-4) * lg[0] + lg[1] + lg[2] + lg[3] + lg[4]) * R(0.05);
-  lX += sgn * (n0 + ux * n1 + uy * n2 + b * n3);
-  lux += sgn * X * n1;
-  luy += sgn * X * n2;
-  lb += sgn * X * n3;
-}
-
-// The same with the heat-capacity ratio of add_geq (rest moment sigma X,
-// energy moment (b + 4 (1 - sigma)) X); also adds the adjoint of sigma.
-template <typename R>
-__device__ __forceinline__ void geq_adj_sig(R X, R ux, R uy, R b, R sig, R sgn, const R* lg, R& lX, R& lux, R& luy,
-                                            R& lb, R& lsig) {
-  const R n0 = (lg[0] + lg[1] + lg[2] + lg[3] + lg[4]) * R(0.2);
-  const R n1 = (lg[1] - lg[3]) * R(0.5);
-  const R n2 = (lg[2] - lg[4]) * R(0.5);
-  const R n3 = (R(-4) * lg[0] + lg[1] + lg[2] + lg[3] + lg[4]) * R(0.05);
-  lX += sgn * (sig * n0 + ux * n1 + uy * n2 + (b + R(4) * (R(1) - sig)) * n3);
-  lux += sgn * X * n1;
-  luy += sgn * X * n2;
-  lb += sgn * X * n3;
-  lsig += sgn * X * (n0 - R(4) * n3);
+  return lth;
 }
 
 // Reaction sensitivities: ds_c/dc, ds_c/dtheta, and S_T's.
@@ -322,7 +266,7 @@ __device__ __forceinline__ ReactAdj<R> reaction_tape(R theta, R c, R rhocp, cons
 }
 
 // Tape of the thin-film reaction (surface_reaction: the populations g_t, g_c
-// that cross the reactive wall, wall values g / a with a = (4 + b) / 20)
+// that cross the reactive wall, wall values g / a)
 // and its derivatives with respect to the wall temperature T, g_c and a_c.
 template <typename R>
 struct FilmTape {
@@ -330,10 +274,10 @@ struct FilmTape {
 };
 
 template <typename R>
-__device__ __forceinline__ FilmTape<R> film_tape(R g_t, R g_c, const Mat<R>& m, const Consts<R>& k) {
+__device__ __forceinline__ FilmTape<R> film_tape(R g_t, R g_c, const AdjMat<R>& m, const Consts<R>& k) {
   FilmTape<R> f;
-  f.a_t = (R(4) + m.bT) / R(20);
-  const R a_c = (R(4) + m.bC) / R(20);
+  f.a_t = m.aT;
+  const R a_c = m.aC;
   f.T = k.T_in + g_t / f.a_t;
   const R iT = R(1) / f.T;
   const R eta = k.V_op - (k.U0_slope * f.T + k.U0_icept);
@@ -362,7 +306,7 @@ __device__ __forceinline__ FilmTape<R> film_tape(R g_t, R g_c, const Mat<R>& m, 
 // ls, le: adjoints of s and of the heat factor from other uses (the seed
 // of J takes ls = its weight).
 template <typename R>
-__device__ __forceinline__ void film_adj(const FilmTape<R>& f, const Mat<R>& m, const Consts<R>& k, R ls, R& l13,
+__device__ __forceinline__ void film_adj(const FilmTape<R>& f, const AdjMat<R>& m, const Consts<R>& k, R ls, R& l13,
                                          R& l18, MatAdj<R>& ma) {
   const R sg = (k.flags & F_SIGMA_ENERGY) ? m.sig : R(1);
   const R irc = R(1) / m.rhocp;
@@ -374,202 +318,188 @@ __device__ __forceinline__ void film_adj(const FilmTape<R>& f, const Mat<R>& m, 
   const R lT = ls * f.ds_dT + lehs * f.dehs_dT;
   l13 += lT / f.a_t;
   l18 += -ls * f.em;
-  // T = T_in + g_t / a_t, a = (4 + b) / 20
-  ma.bT += -lT * (f.T - k.T_in) / f.a_t * R(0.05);
-  ma.bC += ls * f.ds_dac * R(0.05);
+  // T = T_in + g_t / a_t
+  ma.aT += -lT * (f.T - k.T_in) / f.a_t;
+  ma.aC += ls * f.ds_dac;
 }
 
-// Collision adjoint of one node.  In: pre-collision f, material, adjoint of
-// the post-collision populations la.  Out: adjoint of the pre-collision
-// populations mu; material adjoints accumulated in ma.
-// With the heat-capacity ratio (EXT) the temperature lattice conserves
-// sigma theta: theta = sum g_T / sigma, the rest moment takes sigma S_T, the
-// energy moment relaxes with b_T + 4 (1 - sigma); the adjoint of theta is
-// then divided by sigma onto the populations and its sigma part goes to ma.
-template <typename R, bool EXT = false>
-__device__ __forceinline__ void collide_adj(const R (&f)[19], const Mat<R>& mt, const Consts<R>& k, bool cl,
-                                            const R (&la)[19], R (&mu)[19], MatAdj<R>& ma) {
-  const MacroTape<R> t = flow_macros_tape<R, EXT>(f, mt, k);
-  R lux = R(0), luy = R(0);
-#pragma unroll
-  for (int i = 0; i < 19; ++i) mu[i] = R(0);
-
-  // ---- scalars (reverse of the D2Q5 collisions and the CL source) ----
+// Adjoint of the two scalar collisions of one node and of the CL source.
+// g[0..4] temperature, g[5..9] O2 (pre-collision), la their post-collision
+// adjoints; out: mu[0..9], the adjoints lux, luy of the velocity, the
+// material's in ma.  The rest population is the conserved sum minus the
+// moving ones, so its adjoint passes to every population unchanged and is
+// taken off the moving ones' before they are relaxed.
+template <typename R, bool EXT>
+__device__ __forceinline__ void scalars_adj(const R (&g)[10], R ux, R uy, const AdjMat<R>& mt, const Consts<R>& k,
+                                            bool cl, const R (&la)[10], R (&mu)[10], R& lux, R& luy, MatAdj<R>& ma) {
   const bool sigma = EXT && (k.flags & F_SIGMA_ENERGY);
-  const R thsum = f[9] + f[10] + f[11] + f[12] + f[13];
-  const R th = sigma ? thsum / mt.sig : thsum;
-  const R c = f[14] + f[15] + f[16] + f[17] + f[18];
-  R ln0T = R(0);  // sigma: adjoint of the conserved temperature moment, apart from theta's
+  const R q1 = R(1.2679491924311228), q3 = R(0.9282032302755092);
+  const R k1 = R(0.5) * (R(1) - q1), k3 = R(0.5) * (R(1) - q3), h1 = R(0.5) * q1;
+  const R X[2] = {theta_of(g, mt.isig), sum5(g + 5)};
   ReactAdj<R> rx{};
-  if (cl) rx = reaction_tape(th, c, mt.rhocp, k);
-  const R srcT = cl ? rx.S_T : R(0), srcC = cl ? -rx.s_c : R(0);
-  const R q1 = R(1.2679491924311228);
-  const R q3 = R(0.9282032302755092);
-  R lsrc[2], lX[2];
+  if (cl) rx = reaction_tape(X[0], X[1], mt.rhocp, k);
+  const R src[2] = {cl ? rx.S_T : R(0), cl ? -rx.s_c : R(0)};
+  R lX[2], lsrc[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const R* a = la + 9 + 5 * s;
-    const R* g = f + 9 + 5 * s;
-    const R X = s == 0 ? th : c;
-    const R b = s == 0 ? (sigma ? mt.bT + R(4) * (R(1) - mt.sig) : mt.bT) : mt.bC;
-    const R src = s == 0 ? srcT : srcC;
-    // g* = N^-1 n*: adjoint of n* is (N a) / (5, 2, 2, 20, 4)
-    // Divided (not multiplied by fl(0.2)): the uniform component of the
-    // adjoint is carried unchanged, without a relative 1.5e-8 gain per step.
-    const R ln0 = (a[0] + a[1] + a[2] + a[3] + a[4]) / R(5);
-    const R ln1 = (a[1] - a[3]) * R(0.5);
-    const R ln2 = (a[2] - a[4]) * R(0.5);
-    const R ln3 = (R(-4) * a[0] + a[1] + a[2] + a[3] + a[4]) * R(0.05);
-    const R ln4 = (a[1] - a[2] + a[3] - a[4]) * R(0.25);
-    const R lb = q3 * X * ln3 + src * ln3;
-    if (sigma && s == 0) {  // n0 = sum g_T + sigma S_T; b = b_T + 4 (1 - sigma)
-      ln0T = ln0;
-      lX[s] = q1 * t.ux * ln1 + q1 * t.uy * ln2 + q3 * b * ln3;
-      lsrc[s] = mt.sig * ln0 + b * ln3;
-      ma.sig += src * ln0 - R(4) * lb;
-    } else {
-      lX[s] = ln0 + q1 * t.ux * ln1 + q1 * t.uy * ln2 + q3 * b * ln3;
-      lsrc[s] = ln0 + b * ln3;
-    }
-    if (s == 0) ma.bT += lb; else ma.bC += lb;
-    lux += q1 * X * ln1;
-    luy += q1 * X * ln2;
-    const R m1 = (R(1) - q1) * ln1, m2 = (R(1) - q1) * ln2, m3 = (R(1) - q3) * ln3, m4 = (R(1) - q3) * ln4;
-    R* o = mu + 9 + 5 * s;
-    o[0] = R(-4) * m3;
-    o[1] = m1 + m3 + m4;
-    o[2] = m2 + m3 - m4;
-    o[3] = -m1 + m3 + m4;
-    o[4] = -m2 + m3 - m4;
-    (void)g;
+    const R* a = la + 5 * s;
+    R* o = mu + 5 * s;
+    const R a1 = a[1] - a[0], a2 = a[2] - a[0], a3 = a[3] - a[0], a4 = a[4] - a[0];
+    const R le1 = a1 + a3, le2 = a2 + a4, lo1 = a1 - a3, lo2 = a2 - a4, le = le1 + le2;
+    const R aw = s == 0 ? mt.aT : mt.aC;
+    const R law = le * fma_(q3, X[s], src[s]);
+    if (s == 0) ma.aT += law; else ma.aC += law;
+    lsrc[s] = fma_(aw, le, (sigma && s == 0) ? mt.sig * a[0] : a[0]);
+    if (sigma && s == 0) ma.sig += src[0] * a[0];
+    lX[s] = fma_(q3 * aw, le, h1 * fma_(ux, lo1, uy * lo2));
+    lux = fma_(h1 * X[s], lo1, lux);
+    luy = fma_(h1 * X[s], lo2, luy);
+    o[0] = a[0];
+    o[1] = fma_(k3, le1, k1 * lo1);
+    o[2] = fma_(k3, le2, k1 * lo2);
+    o[3] = fma_(k3, le1, -k1 * lo1);
+    o[4] = fma_(k3, le2, -k1 * lo2);
   }
-  if (cl) {
-    // src_T = S_T(theta, c, rhocp), src_C = -s_c(theta, c)
-    const R lST = lsrc[0], lSC = lsrc[1];
-    const R irc = R(1) / mt.rhocp;
-    const R lsc = -lSC + k.four_f_cref * rx.ehs * irc * lST;
-    ma.rhocp += -rx.S_T * irc * lST;
-    lX[1] += rx.dsc_dc * lsc;
-    lX[0] += rx.dsc_dth * lsc;
-    if (k.flags & F_PHYSICAL_HEAT) lX[0] += k.four_f_cref * rx.s_c * R(2) * k.U0_slope * irc * lST;
-  }
-  if (sigma) {  // theta = sum g_T / sigma
-    const R isg = R(1) / mt.sig;
-    ma.sig += -th * isg * lX[0];
-    lX[0] = ln0T + lX[0] * isg;
+  if (cl) {  // src_T = S_T(theta, c, rho c_p), src_C = -s_c(theta, c)
+    const R lsc = fma_(k.four_f_cref * rx.ehs * mt.irc, lsrc[0], -lsrc[1]);
+    ma.rhocp -= rx.S_T * mt.irc * lsrc[0];
+    lX[1] = fma_(rx.dsc_dc, lsc, lX[1]);
+    lX[0] = fma_(rx.dsc_dth, lsc, lX[0]);
+    if (k.flags & F_PHYSICAL_HEAT) lX[0] += k.four_f_cref * rx.s_c * R(2) * k.U0_slope * mt.irc * lsrc[0];
   }
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    mu[9 + i] += lX[0];
-    mu[14 + i] += lX[1];
-  }
-
-  // ---- flow (reverse of the MRT collision with porous forcing) ----
-  // f* = M^-1 m*, m* = (1 - S) M f + S m_eq + (1 - S/2) G, M^-1 = M^T
-  // diag(M M^T)^-1: the adjoint of m* is M la times the constants
-  // 1 / diag(M M^T), and the part that goes back through M f is M^T of
-  // (1 - S) times it (integer coefficients, no division).
-  R lms[9];
-  m_times(la, lms);
-  const R se = k.s_e, sq = k.s_q;
-  const R s[9] = {se, se, se, R(0), sq, R(0), sq, se, se};
-  R lm[9], lme[9], lG[9];
+  for (int s = 0; s < 2; ++s) {
+    R* o = mu + 5 * s;
+    const R l = o[0] + (s == 0 ? theta_adj<R, EXT>(lX[0], X[0], mt, k, ma) : lX[1]);
+    o[0] = l;
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    lms[i] *= inv_mmt<R>(i);
-    lm[i] = (R(1) - s[i]) * lms[i];
-    lme[i] = s[i] * lms[i];
-    lG[i] = (R(1) - R(0.5) * s[i]) * lms[i];
+    for (int i = 1; i < 5; ++i) o[i] += l;
   }
-  lme[0] = R(0);  // the density-moment equilibrium is a constant
-  const R iphi = t.iphi;
-  const R uF = t.ux * t.Fx + t.uy * t.Fy;
-  // G(u, F, phi)
-  const R luF = R(6) * iphi * (lG[1] - lG[2]);
-  R lFx = lG[3] - lG[4] + R(2) * t.ux * iphi * lG[7] + t.uy * iphi * lG[8] + t.ux * luF;
-  R lFy = lG[5] - lG[6] - R(2) * t.uy * iphi * lG[7] + t.ux * iphi * lG[8] + t.uy * luF;
-  lux += R(2) * t.Fx * iphi * lG[7] + t.Fy * iphi * lG[8] + t.Fx * luF;
-  luy += R(-2) * t.Fy * iphi * lG[7] + t.Fx * iphi * lG[8] + t.Fy * luF;
-  const R liphi_G = R(6) * uF * (lG[1] - lG[2]) + R(2) * (t.ux * t.Fx - t.uy * t.Fy) * lG[7] +
-                    (t.ux * t.Fy + t.uy * t.Fx) * lG[8];
-  ma.phi += -iphi * iphi * liphi_G;
-  // meq(p, u, phi)
-  R lp = R(0);
-  meq_adj(t.p, t.ux, t.uy, mt.phi, iphi, lme, lp, lux, luy, ma.phi);
-  // m = M f
-  R lfm[9];
-  mt_times(lm, lfm);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) mu[i] += lfm[i];
-  flow_macros_adj<R, EXT>(t, mt, k, lux, luy, lp, lFx, lFy, mu, ma);
 }
 
-// Adjoint of the boundary-column extrapolation of node b fed by node xp.
-// pre_xp: pulled populations of xp; mu_b: adjoint of the boundary node's
-// pre-collision populations.  Adds to mu_xp and to the material adjoints of
-// xp (maxp) and of b (mab).
-// EXT: also the pressure-driven inlet (p_in fixed, u taken from xp) and the
-// heat-capacity ratio in the inlet's temperature extrapolation.
-template <typename R, bool EXT = false>
-__device__ __forceinline__ void boundary_adj(const R (&pre_xp)[19], const Mat<R>& mxp, const Mat<R>& mb,
-                                             const Consts<R>& k, bool inlet, R ubx, R uby, const R (&mu_b)[19],
-                                             R (&mu_xp)[19], MatAdj<R>& maxp, MatAdj<R>& mab) {
-  const MacroTape<R> t = flow_macros_tape<R, EXT>(pre_xp, mxp, k);
-  const bool pressure = EXT && inlet && (k.flags & F_PRESSURE_INLET);
+// Adjoints of the flow sums of a node, onto its populations.
+template <typename R>
+__device__ __forceinline__ void flow_sums_adj(R l0, R lS, R lA, R lN, R lM, R lJx, R lJy, R lqx, R lqy, R (&mu)[9]) {
+  const R l13 = lS + (lA + lN), l24 = lS + (lA - lN), l57 = lS + lM, l68 = lS - lM;
+  const R b13 = fma_(R(-2), lqx, lJx), b24 = fma_(R(-2), lqy, lJy);
+  const R dx = lJx + lqx, dy = lJy + lqy, b57 = dx + dy, b68 = dy - dx;
+  mu[0] = l0;
+  mu[1] = l13 + b13;
+  mu[3] = l13 - b13;
+  mu[2] = l24 + b24;
+  mu[4] = l24 - b24;
+  mu[5] = l57 + b57;
+  mu[7] = l57 - b57;
+  mu[6] = l68 + b68;
+  mu[8] = l68 - b68;
+}
+
+// Adjoint of the flow collision of one node in the sums of `collide`, S the
+// sum of its moving populations: la[0..8] the post-collision adjoints, lux,
+// luy the velocity's from the scalars; out: mu[0..8].
+template <typename R, bool EXT>
+__device__ __forceinline__ void flow_adj(const MacroTape<R>& t, const AdjMat<R>& mt, const Consts<R>& k,
+                                         const R (&la)[9], R lux, R luy, R (&mu)[9], R& lth, MatAdj<R>& ma) {
+  const R se = k.s_e, sq = k.s_q;
+  const R ke = R(1) - se, kq = R(1) - sq, he = R(1) - R(0.5) * se, hq = R(1) - R(0.5) * sq;
+  const R iphi = mt.iphi;
+  // outputs -> S', A', N', M', j', q'
+  const R s13 = la[1] + la[3], s24 = la[2] + la[4], s57 = la[5] + la[7], s68 = la[6] + la[8];
+  const R d13 = la[1] - la[3], d24 = la[2] - la[4], d57 = la[5] - la[7], d68 = la[6] - la[8];
+  const R lB = R(0.25) * (s57 + s68);
+  const R lA = fma_(R(0.25), s13 + s24, -lB), lN = R(0.25) * (s13 - s24), lM2 = R(0.125) * (s57 - s68);
+  const R c6 = R(1.0 / 6.0);
+  const R gx = c6 * (d57 - d68), gy = c6 * (d57 + d68);
+  const R ljx = fma_(c6, d13, gx), ljy = fma_(c6, d24, gy);
+  const R lqx = fma_(-c6, d13, R(0.5) * gx), lqy = fma_(-c6, d24, R(0.5) * gy);
+  const R lS = fma_(se, fma_(R(0.8), lA, -la[0]), lB);
+  const R lz = (R(4.0 / 3.0) * he) * (fma_(R(0.5), lA, lB) - la[0]);  // of (u F) / phi
+  const R lw = R(-0.2) * se * lA;                                      // of u^2 / phi
+  // N and M: u_i P_j with P = (s_e u + (2 - s_e) F) / phi
+  const R Px = iphi * fma_(R(2) * he, t.Fx, se * t.ux), Py = iphi * fma_(R(2) * he, t.Fy, se * t.uy);
+  const R lPx = fma_(lN, t.ux, lM2 * t.uy), lPy = fma_(-lN, t.uy, lM2 * t.ux);
+  const R uF = fma_(t.ux, t.Fx, t.uy * t.Fy);
+  ma.phi -= iphi * (fma_(lPx, Px, lPy * Py) + iphi * fma_(lw, t.u2, lz * uF));
+  const R e = se * iphi, h = R(2) * he * iphi, z = lz * iphi, w2 = R(2) * lw * iphi;
+  R lFx = ljx - hq * lqx + h * lPx + z * t.ux;
+  R lFy = ljy - hq * lqy + h * lPy + z * t.uy;
+  lux += lN * Px + lM2 * Py + e * lPx + z * t.Fx + w2 * t.ux - sq * lqx;
+  luy += lM2 * Px - lN * Py + e * lPy + z * t.Fy + w2 * t.uy - sq * lqy;
+  R lvx, lvy;
+  flow_macros_adj<R, EXT>(t, mt, k, lux, luy, lFx, lFy, lvx, lvy, lth, ma);
+  flow_sums_adj(ke * la[0], lS, ke * lA, ke * lN, R(2) * ke * lM2, ljx + lvx, ljy + lvy, kq * lqx, kq * lqy, mu);
+}
+
+// Transposed extrapolation of a boundary node b from the column xp next to
+// it.  Both take part: mu_b is the adjoint of b's pre-collision populations,
+// (ux, uy, pp) xp's velocity and phi p.  Per boundary kind the extrapolated
+// equilibrium takes the velocity (velocity inlet: fixed) and phi p
+// (velocity inlet: phi_b p of xp; else phi_b times a given pressure pb).
+//
+// Scalar part (inlet only): mu_b[0..9], th1 and c1 of xp; adds the adjoints
+// of xp's populations to lth1 and lc1 (per population) and of its velocity to
+// lux, luy, and the materials'.
+template <typename R, bool EXT>
+__device__ __forceinline__ void inlet_scalars_adj(const R (&mu_b)[10], R ux, R uy, R th1, R c1, R ubx, bool pressure,
+                                                  const AdjMat<R>& mxp, const Consts<R>& k, R& lux, R& luy, R& lth1,
+                                                  R& lc1, MatAdj<R>& maxp, MatAdj<R>& mab) {
 #pragma unroll
-  for (int i = 0; i < 19; ++i) mu_xp[i] += mu_b[i];  // identity part (scalars at the outlet: a copy)
-  R ldm[9];
-  m_times(mu_b, ldm);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) ldm[i] *= inv_mmt<R>(i);
-  ldm[0] = R(0);
-  const R iphi_b = R(1) / mb.phi;
-  R lp1 = R(0), lux1 = R(0), luy1 = R(0);
-  // + meq(pb, ub; phi_b): inlet pb = p1 (ub fixed); outlet pb = p_out, ub = u1.
-  R dumx = R(0), dumy = R(0);
-  if (pressure) {  // pb = p_in, ub = u1
-    R dp = R(0);
-    meq_adj(k.p_in, t.ux, t.uy, mb.phi, iphi_b, ldm, dp, lux1, luy1, mab.phi);
-  } else if (inlet) {
-    meq_adj(t.p, ubx, uby, mb.phi, iphi_b, ldm, lp1, dumx, dumy, mab.phi);
-  } else {
-    R dp = R(0);
-    meq_adj(k.p_out, t.ux, t.uy, mb.phi, iphi_b, ldm, dp, lux1, luy1, mab.phi);
-  }
-  // - meq(p1, u1; phi_xp)
-  R nldm[9];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) nldm[i] = -ldm[i];
-  meq_adj(t.p, t.ux, t.uy, mxp.phi, t.iphi, nldm, lp1, lux1, luy1, maxp.phi);
-  if (inlet) {
-    const bool sigma = EXT && (k.flags & F_SIGMA_ENERGY);
-    const R th1sum = pre_xp[9] + pre_xp[10] + pre_xp[11] + pre_xp[12] + pre_xp[13];
-    const R th1 = sigma ? th1sum / mxp.sig : th1sum;
-    const R c1 = pre_xp[14] + pre_xp[15] + pre_xp[16] + pre_xp[17] + pre_xp[18];
-    R lth1 = R(0), lc1 = R(0), dX = R(0);
-    // + geq(0, ub; bT_b): no dependence.  - geq(theta1, u1; bT_xp)
-    if (sigma) {
-      geq_adj_sig(th1, t.ux, t.uy, mxp.bT, mxp.sig, R(-1), mu_b + 9, lth1, lux1, luy1, maxp.bT, maxp.sig);
-      const R isg = R(1) / mxp.sig;  // theta1 = sum g_T / sigma
-      maxp.sig += -th1 * isg * lth1;
-      lth1 *= isg;
+  for (int s = 0; s < 2; ++s) {
+    const R* m = mu_b + 5 * s;
+    const R X = s == 0 ? th1 : c1, aw = s == 0 ? mxp.aT : mxp.aC;
+    const R d1 = R(0.5) * (m[1] - m[3]), d2 = R(0.5) * (m[2] - m[4]);
+    const R la = ((m[1] + m[3]) + (m[2] + m[4])) - R(4) * m[0];
+    const R sig = (EXT && s == 0) ? mxp.sig : R(1);
+    const R lX = -(fma_(aw, la, sig * m[0]) + fma_(ux, d1, uy * d2));
+    lux = fma_(-X, d1, lux);
+    luy = fma_(-X, d2, luy);
+    if (s == 0) {
+      maxp.aT = fma_(-X, la, maxp.aT);
+      if (EXT) maxp.sig = fma_(-X, m[0], maxp.sig);
+      lth1 = theta_adj<R, EXT>(lX, th1, mxp, k, maxp);
     } else {
-      geq_adj(th1, t.ux, t.uy, mxp.bT, R(-1), mu_b + 9, lth1, lux1, luy1, maxp.bT);
-    }
-    // + geq(c_in, ub; bC_b): ub = u1 with the pressure-driven inlet
-    if (pressure)
-      geq_adj(k.c_in, t.ux, t.uy, mb.bC, R(1), mu_b + 14, dX, lux1, luy1, mab.bC);
-    else
-      geq_adj(k.c_in, ubx, uby, mb.bC, R(1), mu_b + 14, dX, dumx, dumy, mab.bC);
-    // - geq(c1, u1; bC_xp)
-    geq_adj(c1, t.ux, t.uy, mxp.bC, R(-1), mu_b + 14, lc1, lux1, luy1, maxp.bC);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      mu_xp[9 + i] += lth1;
-      mu_xp[14 + i] += lc1;
+      maxp.aC = fma_(-X, la, maxp.aC);
+      mab.aC = fma_(k.c_in, la, mab.aC);  // + geq(c_in, u_b; aC_b)
+      if (pressure) {
+        lux = fma_(k.c_in, d1, lux);
+        luy = fma_(k.c_in, d2, luy);
+      }
+      lc1 = lX;
     }
   }
-  flow_macros_adj<R, EXT>(t, mxp, k, lux1, luy1, lp1, R(0), R(0), mu_xp, maxp);
+}
+
+// Flow part: mu_b[0..8]; adds to the velocity's adjoint and to lpp (of phi p
+// of xp).
+template <typename R>
+__device__ __forceinline__ void boundary_flow_adj(const R (&m)[9], R ux, R uy, R pp, bool fixed_u, R ubx, R pb,
+                                                  const AdjMat<R>& mxp, R phi_b, R iphi_b, R& lux, R& luy, R& lpp,
+                                                  MatAdj<R>& maxp, MatAdj<R>& mab) {
+  const R s13 = m[1] + m[3], s24 = m[2] + m[4], s57 = m[5] + m[7], s68 = m[6] + m[8];
+  const R d13 = m[1] - m[3], d24 = m[2] - m[4], d57 = m[5] - m[7], d68 = m[6] - m[8];
+  const R c12 = R(1.0 / 12.0), c3 = R(1.0 / 3.0);
+  const R lA = s13 + s24, lB = s57 + s68;
+  const R ldpp = fma_(R(-5.0 / 3.0), m[0], fma_(c3, lA, c12 * lB));
+  const R ldu2 = fma_(R(-2.0 / 3.0), m[0], c12 * (lA + lB));
+  const R dN = R(0.25) * (s13 - s24);
+  const R lxx = ldu2 + dN, lyy = ldu2 - dN, lxy = R(0.25) * (s57 - s68);
+  const R ldx = fma_(c3, d13, c12 * (d57 - d68)), ldy = fma_(c3, d24, c12 * (d57 + d68));
+  const R gx = fma_(R(2) * ux, lxx, uy * lxy), gy = fma_(R(2) * uy, lyy, ux * lxy);
+  const R e2 = fma_(ux * ux, lxx, fma_(uy * uy, lyy, ux * uy * lxy));
+  // - (xp's equilibrium)
+  lux -= fma_(mxp.iphi, gx, ldx);
+  luy -= fma_(mxp.iphi, gy, ldy);
+  maxp.phi = fma_(mxp.iphi * mxp.iphi, e2, maxp.phi);
+  lpp -= ldpp;
+  if (fixed_u) {  // velocity u_b = (ubx, 0), phi p = phi_b (phi p)_xp / phi_xp
+    lpp = fma_(ldpp * mxp.iphi, phi_b, lpp);
+    maxp.phi -= ldpp * pp * phi_b * mxp.iphi * mxp.iphi;
+    mab.phi += ldpp * pp * mxp.iphi - iphi_b * iphi_b * ubx * ubx * lxx;
+  } else {  // xp's velocity, phi p = phi_b pb
+    lux += fma_(iphi_b, gx, ldx);
+    luy += fma_(iphi_b, gy, ldy);
+    mab.phi += ldpp * pb - iphi_b * iphi_b * e2;
+  }
 }
 
 }  // namespace lbm

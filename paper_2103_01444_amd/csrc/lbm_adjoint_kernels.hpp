@@ -6,262 +6,347 @@
 
 namespace lbm {
 
-// Adjoint of the observable J = mean current density on the pre-collision
-// populations: for CL nodes dJ/dc and dJ/dtheta on every scalar population.
-// With the heat-capacity ratio (EXT) theta = sum g_T / sigma.
-template <typename R, bool EXT>
-__device__ __forceinline__ void seed_mu(const R (&pre)[19], const Mat<R>& mt, const Consts<R>& k, bool cl, R w,
-                                        R (&mu)[19], MatAdj<R>& ma) {
-#pragma unroll
-  for (int i = 0; i < 19; ++i) mu[i] = R(0);
-  if (!cl) return;
-  const bool sigma = EXT && (k.flags & F_SIGMA_ENERGY);
-  const R thsum = pre[9] + pre[10] + pre[11] + pre[12] + pre[13];
-  const R th = sigma ? thsum / mt.sig : thsum;
-  const R c = pre[14] + pre[15] + pre[16] + pre[17] + pre[18];
-  const ReactAdj<R> r = reaction_tape(th, c, mt.rhocp, k);
-  R lth = w * r.dsc_dth;
-  if (sigma) {
-    const R isg = R(1) / mt.sig;
-    ma.sig += -th * isg * lth;
-    lth *= isg;
-  }
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    mu[9 + i] = lth;
-    mu[14 + i] = w * r.dsc_dc;
-  }
-}
-
-// a += (first ? b1 : b2), field by field (selecting values, not objects,
-// keeps both operands in registers).
+// Wave-uniform bases of one 19-plane buffer: five raw buffer resources of
+// four planes each (at most 2^31 elements in all, so three planes and a
+// neighbour shift stay below 4 GiB), each based one row and one element
+// before its first plane so that every neighbour shift is a non-negative
+// scalar byte offset.  One 32-bit lane offset serves all planes, and a plane
+// costs one scalar register (its own resource would cost four: at 57 planes
+// that spilled scalar registers).
 template <typename R>
-__device__ __forceinline__ void add_mat_adj(MatAdj<R>& a, bool first, const MatAdj<R>& b1, const MatAdj<R>& b2) {
-  a.phi += first ? b1.phi : b2.phi;
-  a.invk += first ? b1.invk : b2.invk;
-  a.sqk += first ? b1.sqk : b2.sqk;
-  a.fphi += first ? b1.fphi : b2.fphi;
-  a.l0 += first ? b1.l0 : b2.l0;
-  a.l1 += first ? b1.l1 : b2.l1;
-  a.bT += first ? b1.bT : b2.bT;
-  a.bC += first ? b1.bC : b2.bC;
-  a.rhocp += first ? b1.rhocp : b2.rhocp;
-  a.sig += first ? b1.sig : b2.sig;
-}
-
-template <typename R>
-__device__ __forceinline__ void load_node(const R* __restrict__ a, const Consts<R>& k, int x, int y, R (&v)[19]) {
-  const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
+struct PlaneBuffer {
+  __amdgpu_buffer_rsrc_t r[5];
+  uint32_t plane, pitch;  // bytes
+  __device__ __forceinline__ PlaneBuffer(const R* p, const Consts<R>& k) {
+    plane = uint32_t(k.plane) * uint32_t(sizeof(R));
+    pitch = uint32_t(k.pitch) * uint32_t(sizeof(R));
 #pragma unroll
-  for (int q = 0; q < 19; ++q) v[q] = buffer_load<R, 0>(a + int64_t(q) * k.plane, ob);
+    for (int g = 0; g < 5; ++g) r[g] = buffer_of(p + (int64_t(4 * g) * k.plane - k.pitch - 1));
+  }
+  // byte offset of population q of the node displaced by (dx, dy)
+  __device__ __forceinline__ uint32_t off(int q, int dx, int dy) const {
+    return uint32_t(q & 3) * plane + uint32_t(1 + dy) * pitch + uint32_t(1 + dx) * uint32_t(sizeof(R));
+  }
+  template <int AUX>
+  __device__ __forceinline__ R load(int q, int dx, int dy, uint32_t ob) const {
+    if constexpr (sizeof(R) == 4)
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
+    else
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
+  }
+  __device__ __forceinline__ void store(int q, int dx, int dy, uint32_t ob, R v) const {
+    if constexpr (sizeof(R) == 4) {
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r[q >> 2], int(ob), int(off(q, dx, dy)), 0);
+    } else {
+      using U2 = uint32_t __attribute__((ext_vector_type(2)));
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r[q >> 2], int(ob), int(off(q, dx, dy)), 0);
+    }
+  }
+};
+
+// Element offset the pull of population q at (x, y) reads, and the push of
+// its adjoint writes.
+template <typename R>
+__device__ __forceinline__ int pull_offset(const Consts<R>& k, int q, int x, int y) {
+  int xs = x - EX[q];
+  int ys = y - EY[q];
+  if (k.flags & F_PERIODIC_X) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
+  if (k.flags & F_PERIODIC_Y) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
+  const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny;
+  return in ? (q * k.plane + ys * k.pitch + xs) : (OPP[q] * k.plane + y * k.pitch + x);
 }
 
-// Adjoint of node b's collision (or of J when SEED) given b's pre-collision populations.
-template <typename R, bool SEED, bool EXT>
-__device__ __forceinline__ void node_mu(const R (&pre)[19], const Mat<R>& mt, const Consts<R>& k, bool cl,
-                                        const R* __restrict__ lam_in, int x, int y, R w, R (&mu)[19],
-                                        MatAdj<R>& ma) {
-  if constexpr (SEED) {
-    seed_mu<R, EXT>(pre, mt, k, cl, w, mu, ma);
+// Populations [Q0, Q1) of node (x, y): inner (the wavefront lies one node or
+// more inside the lattice) through the wave-uniform bases.
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void pull_part(const R* __restrict__ S, const PlaneBuffer<R>& b, const Consts<R>& k,
+                                          bool inner, int x, int y, R* f) {
+  if (inner) {
+    const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) f[q - Q0] = b.template load<2>(q, -EX[q], -EY[q], ob);
   } else {
-    R la[19];
-    load_node(lam_in, k, x, y, la);
-    collide_adj<R, EXT>(pre, mt, k, cl, la, mu, ma);
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) f[q - Q0] = __builtin_nontemporal_load(S + pull_offset(k, q, x, y));
   }
 }
+
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void push_part(R* __restrict__ lam, const PlaneBuffer<R>& b, const Consts<R>& k,
+                                          bool inner, int x, int y, const R* mu) {
+  if (inner) {
+    const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) b.store(q, -EX[q], -EY[q], ob, mu[q - Q0]);
+  } else {
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) lam[pull_offset(k, q, x, y)] = mu[q - Q0];
+  }
+}
+
+// Lane shift of the reverse step: lane l of a row's first workgroup holds
+// x = l - shift, so that columns nx - 2 and nx - 1 share a wavefront (as
+// columns 0 and 1 do) at every width.
+__host__ __device__ inline int adj_lane_shift(int nx) { return ((nx - 1) & 63) == 0 ? 1 : 0; }
 
 // One reverse step: lam_out = (dS'/dS)^T lam_in at the state S, gradients
 // accumulated into grad (planes phi, 1/K, D_eff).  SEED: lam_out = dJ/dS
 // (times w = dJ dx / nx * 4 F C_ref / dt), no lam_in.
-// The first and last wavefront of a row carry the boundary nodes and the
-// columns feeding them, whose chain is the longest.  A boundary lane runs
-// its own collision adjoint in the common pass of the wavefront (on its
-// extrapolated populations) and the feeding lane reads it across lanes, so
-// that wavefront pays one collision adjoint plus the transposed
-// extrapolation.  Per reverse step of the 1024x256 adjoint: 28.5 us at four
-// waves per SIMD (128 VGPRs, 64 bytes spilled per lane), 29.7-30.1 us at
-// three; 29.3-29.9 us when the feeding lane recomputed the boundary node's
-// collision adjoint, 34.4 us when the boundary and feeding lanes took
-// separate divergent passes.
-// Registers: the instances are held to four waves per SIMD (the default
-// FP32 one at 128 VGPRs with 64 bytes per lane spilled), except the FP32
-// instances with the model options (EXT), which are left to the registers
-// they need (162 VGPRs, three waves per SIMD, no spill).  Compiled for four
-// waves, that instance spilled 100 bytes per lane and its gradients with the
-// thin-film CL and Butler-Volmer kinetics varied from run to run on
-// identical inputs (some runs NaN); unspilled it gives the same bits in
-// every run.  The FP64 EXT instances stay at four waves: left free, the
-// compiler moved part of their state into accumulation registers and their
-// gradients departed from the oracle by 1e-6 to 2e-5, while at four waves
-// (scratch spills) they match it within 1e-12 in every run.
+//
+// Two passes per node: the ten scalar populations (pull, adjoint of their
+// collisions, push), which leave the velocity's adjoint, then the nine flow
+// ones, so that about 30 values are live at once.  A boundary lane runs its
+// own node's collision adjoint in the common passes on its extrapolated
+// populations; the lane of the feeding column takes the boundary node's
+// result across lanes and runs the transposed extrapolation, while the
+// boundary lane keeps what belongs to its own material.
+//
+// Small lattices are bound by one wavefront's chain, large ones by HBM (in
+// FP32 S, lambda in and out, the gradient twice, the fields: 264 bytes a
+// node).  Holding all nineteen populations, the moment-matrix transposes and
+// 57 four-register buffer resources at once took 128 VGPRs and spilled: 544
+// bytes of scratch per lane in FP64 and 482 scalar-register spills.  Now 71
+// (FP32) and 135 (FP64) VGPRs without a spill; per reverse step at 200x40
+// FP64 29.8 -> 9.2 us, at 1024x256 FP32 (beside the replay) 18.0 -> 17.2 us.
+// The compiler places spills of scalar registers into vector lanes, and the
+// spilled forms' gradients have differed from run to run; every instance
+// here, with and without the model options, is free of them.
 template <typename R, bool SEED, bool EXT = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT && sizeof(R) == 4 ? 1 : 4))) void k_adj_step(const R* __restrict__ S, const R* __restrict__ lam_in,
+__global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, const R* __restrict__ lam_in,
                                                      R* __restrict__ lam_out, R* __restrict__ grad,
                                                      const R* __restrict__ phi_f, const R* __restrict__ invk_f,
                                                      const R* __restrict__ d_f, Consts<R> k, R w) {
   int bx, by;
   xcd_tile(gridDim.x, gridDim.y, bx, by);
-  const int x = bx * kBlock + threadIdx.x;
+  const int shift = adj_lane_shift(k.nx);
+  const int x = bx * kBlock + int(threadIdx.x) - shift;
   const int y = by;
-  if (x >= k.nx) return;
+  if ((unsigned)x >= (unsigned)k.nx) return;
   const bool open = !(k.flags & F_PERIODIC_X);
   const bool react = !(k.flags & F_NO_REACTION);
   const bool cl = react && y >= k.y_cl0;
-  const bool inlet = open && x == 0 && y < k.ny_ch;
+  const bool in_row = open && y < k.ny_ch;
+  const bool inlet = in_row && x == 0;
   const bool outlet = open && x == k.nx - 1;
+  const bool bnode = inlet || outlet;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
+  const int l0 = (x + shift) & ~63;  // first lane of the wavefront, as an x + shift
+  const bool w_in = in_row && l0 == 0, w_out = open && l0 == ((k.nx - 1 + shift) & ~63);
+  const int lane_out = (k.nx - 1 + shift) & 63;
+  const bool pressure = EXT && (k.flags & F_PRESSURE_INLET);
+  const bool inner = __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2);
+  const int o = y * k.pitch + x;
+  const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
+  const PlaneBuffer<R> bS(S, k), bi(lam_in, k), bo(lam_out, k);
 
-  R p[19];
-  pull<R, true, true>(S, k, xp, y, p);
-  const Mat<R> mxp = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, xp, y);
+  AdjMat<R> m = adj_material<R>(k, phi_f, invk_f, d_f, xp, y);
+  R f[9], g[10];
+  pull_part<R, 9, 19>(S, bS, k, inner, xp, y, g);
+  pull_part<R, 0, 9>(S, bS, k, inner, xp, y, f);
   // Thin-film CL (EXT): the bottom row's wall-crossing populations react as
   // the forward pull left them (column nx - 2's film for the outlet).
   const bool film = EXT && (k.flags & F_THIN_CL) && react && y == k.ny - 1;
   FilmTape<R> ft{};
   if (film) {
-    ft = film_tape(p[13], p[18], mxp, k);
-    p[13] += ft.S_T * mxp.sig;
-    p[18] -= ft.s;
+    ft = film_tape(g[4], g[9], m, k);
+    g[4] += ft.S_T * m.sig;
+    g[9] -= ft.s;
   }
+  // Boundary lanes: their extrapolated populations and their own material.
+  if (bnode) {
+    R p[19];
+#pragma unroll
+    for (int q = 0; q < 19; ++q) p[q] = q < 9 ? f[q] : g[q - 9];
+    AdjMat<R> mc = adj_material<R>(k, phi_f, invk_f, d_f, x, y);
+    boundary_column(p, k, y, inlet, m, mc);
+    if (outlet) outlet_scalar_adj_material(mc, m);
+    m = mc;
+#pragma unroll
+    for (int q = 0; q < 19; ++q) (q < 9 ? f[q] : g[q - 9]) = p[q];
+  }
+
   MatAdj<R> ma{};
-  R mu[19];
-  const int o = y * k.pitch + x;
-  const bool bnode = inlet || outlet;
+  MacroTape<R> t = flow_macros_tape<R, EXT>(f, theta_of(g, m.isig), m, k);
+  const R S18 = ((f[1] + f[3]) + (f[2] + f[4])) + ((f[5] + f[7]) + (f[6] + f[8]));
+  R lux = R(0), luy = R(0), lth = R(0), lpp = R(0);
+  R blx = R(0), bly = R(0);  // velocity's adjoint from the transposed extrapolation
+  const R ubx = w_in ? inlet_velocity(k, y) : R(0);
 
-  // One collision adjoint per lane: its own node's, for an inlet / outlet
-  // node on the populations extrapolated from the column next to it.
-  {
-    Mat<R> mc = mxp;
-    if (bnode) {
-      mc = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, x, y);
-      boundary_column(p, k, y, inlet, mxp, mc);
-      if (outlet) outlet_scalar_material(mc, mxp);
-    }
-    node_mu<R, SEED, EXT>(p, mc, k, cl, lam_in, x, y, w, mu, ma);
-  }
-  if (bnode) {  // the column's own populations again
-    pull<R, true, false>(S, k, xp, y, p);
-    if (film) {
-      p[13] += ft.S_T * mxp.sig;
-      p[18] -= ft.s;
-    }
-  }
-
-  // Transpose of the extrapolation of a boundary node from the column next
-  // to it: the boundary node needs it for its own material, the feeding
-  // column for its populations and material.  Both lanes pulled that
-  // column; the feeding lane takes the boundary node's collision adjoint
-  // from its lane by a cross-lane read, and the two run the block together.
-  if (open && y < k.ny_ch && x < 64) {  // the wavefront holding x = 0 and 1
-    R mub[19];
+  // ---- scalars ----
+  R mus[10];
+  if constexpr (SEED) {
+    // J's adjoint: w ds_c / d(theta, c) on the CL's populations
 #pragma unroll
-    for (int q = 0; q < 19; ++q) mub[q] = __shfl(mu[q], 0, 64);
+    for (int q = 0; q < 10; ++q) mus[q] = R(0);
+    if (cl) {
+      const R th = theta_of(g, m.isig);
+      const ReactAdj<R> r = reaction_tape(th, sum5(g + 5), m.rhocp, k);
+      const R lt = theta_adj<R, EXT>(w * r.dsc_dth, th, m, k, ma);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        mus[q] = lt;
+        mus[5 + q] = w * r.dsc_dc;
+      }
+    }
+  } else {
+    R la[10];
+#pragma unroll
+    for (int q = 0; q < 10; ++q) la[q] = bi.template load<0>(9 + q, 0, 0, ob);
+    scalars_adj<R, EXT>(g, t.ux, t.uy, m, k, cl, la, mus, lux, luy, ma);
+  }
+  // With buoyancy the boundary nodes' temperature adjoint also has a share
+  // from the flow pass, so both passes of a boundary wavefront precede the
+  // exchange there.
+  const bool buoyant = EXT && (k.flags & F_BUOYANCY);
+  R muf[9];
+  auto flow_pass = [&]() {
+    if constexpr (SEED) {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) muf[q] = R(0);
+    } else {
+      R la[9];
+#pragma unroll
+      for (int q = 0; q < 9; ++q) la[q] = bi.template load<0>(q, 0, 0, ob);
+      flow_adj<R, EXT>(t, m, k, la, lux, luy, muf, lth, ma);
+      if (buoyant) {
+        const R l = theta_adj<R, EXT>(lth, t.thb, m, k, ma);
+        lth = R(0);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) mus[q] += l;
+      }
+    }
+  };
+  if (EXT) flow_pass();
+
+  // Exchange of the scalars' part.
+  if (w_in) {
+    R mub[10];
+#pragma unroll
+    for (int q = 0; q < 10; ++q) mub[q] = __shfl(mus[q], shift, 64);
+    const R uxp = __shfl(t.ux, shift + 1, 64), uyp = __shfl(t.uy, shift + 1, 64);
     if (x <= 1) {
-      const Mat<R> mb = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, 0, y);
       MatAdj<R> axp{}, ab{};
-      boundary_adj<R, EXT>(p, mxp, mb, k, true, inlet_velocity(k, y), R(0), mub, mu, axp, ab);
-      add_mat_adj(ma, x == 0, ab, axp);
-    }
-  }
-  if (open) {
-    const int xo = k.nx - 1;
-    if ((xo & 63) != 0) {  // x = nx - 2 and nx - 1 in one wavefront
-      if ((x & ~63) == (xo & ~63)) {
-        const int src = xo & 63;
-        R mub[19];
+      R lt1 = R(0), lc1 = R(0);
+      inlet_scalars_adj<R, EXT>(mub, uxp, uyp, theta_of(g, m.isig), sum5(g + 5), ubx, pressure, m, k, blx, bly, lt1,
+                                lc1, axp, ab);
+      if (x == 0) {
+        ma.aC += ab.aC;
+      } else {
+        ma.aT += axp.aT;
+        ma.aC += axp.aC;
+        if (EXT) ma.sig += axp.sig;
 #pragma unroll
-        for (int q = 0; q < 19; ++q) mub[q] = __shfl(mu[q], src, 64);
-        const R sbT = __shfl(ma.bT, src, 64), sbC = __shfl(ma.bC, src, 64), src_p = __shfl(ma.rhocp, src, 64);
-        const R ssg = EXT ? __shfl(ma.sig, src, 64) : R(0);
-        if (x >= xo - 1) {
-          Mat<R> mb = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, xo, y);
-          outlet_scalar_material(mb, mxp);
-          if (!outlet) {  // the outlet node collides with column nx - 2's scalar material
-            ma.bT += sbT;
-            ma.bC += sbC;
-            ma.rhocp += src_p;
-            if (EXT) ma.sig += ssg;
-          }
-          MatAdj<R> axp{}, ab{};
-          boundary_adj<R, EXT>(p, mxp, mb, k, false, R(0), R(0), mub, mu, axp, ab);
-          add_mat_adj(ma, outlet, ab, axp);
+        for (int q = 0; q < 5; ++q) {
+          mus[q] += mub[q] + lt1;
+          mus[5 + q] += mub[5 + q] + lc1;
         }
       }
-    } else if (x >= xo - 1) {  // the pair straddles two wavefronts: each lane on its own
-      Mat<R> mb = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, xo, y);
-      R mub[19];
-      if (outlet) {
+    }
+  }
+  if (w_out) {  // the outlet's scalars are copies, collided with column nx - 2's scalar material
+    R mub[10];
 #pragma unroll
-        for (int q = 0; q < 19; ++q) mub[q] = mu[q];
-        outlet_scalar_material(mb, mxp);
-      } else {
-        R pre[19];
+    for (int q = 0; q < 10; ++q) mub[q] = __shfl(mus[q], lane_out, 64);
+    const R sT = __shfl(ma.aT, lane_out, 64), sC = __shfl(ma.aC, lane_out, 64);
+    const R sr = __shfl(ma.rhocp, lane_out, 64), ss = EXT ? __shfl(ma.sig, lane_out, 64) : R(0);
+    if (x == k.nx - 2) {
 #pragma unroll
-        for (int q = 0; q < 19; ++q) pre[q] = p[q];
-        boundary_column(pre, k, y, false, mxp, mb);
-        outlet_scalar_material(mb, mxp);
-        MatAdj<R> mab{};
-        node_mu<R, SEED, EXT>(pre, mb, k, cl, lam_in, xo, y, w, mub, mab);
-        ma.bT += mab.bT;
-        ma.bC += mab.bC;
-        ma.rhocp += mab.rhocp;
-        if (EXT) ma.sig += mab.sig;
+      for (int q = 0; q < 10; ++q) mus[q] += mub[q];
+      ma.aT += sT;
+      ma.aC += sC;
+      ma.rhocp += sr;
+      if (EXT) ma.sig += ss;
+    }
+  }
+  // A boundary node's pulled sources were never read by the forward step:
+  // their adjoint is 0.
+  auto push_scalars = [&]() {
+    if (bnode) {
+#pragma unroll
+      for (int q = 0; q < 10; ++q) mus[q] = R(0);
+    }
+    push_part<R, 9, 19>(lam_out, bo, k, inner, x, y, mus);
+  };
+  if (!EXT) push_scalars();
+
+  // ---- flow ----
+  if (!EXT) flow_pass();
+  if (w_in || w_out) {
+    const R pp = fma_(R(0.6), S18, R(-0.4) * (t.u2 * m.iphi));
+    // both boundaries in turn (nx = 3: one column feeds both)
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      if (!(side == 0 ? w_in : w_out)) continue;
+      const int lb = side == 0 ? shift : lane_out, lp = side == 0 ? shift + 1 : lane_out - 1;
+      R mub[9];
+#pragma unroll
+      for (int q = 0; q < 9; ++q) mub[q] = __shfl(muf[q], lb, 64);
+      const R uxp = __shfl(t.ux, lp, 64), uyp = __shfl(t.uy, lp, 64), ppp = __shfl(pp, lp, 64);
+      const R ip = __shfl(m.iphi, lp, 64), phi_b = __shfl(m.phi, lb, 64), iphi_b = __shfl(m.iphi, lb, 64);
+      const int xb = side == 0 ? 0 : k.nx - 1, xf = side == 0 ? 1 : k.nx - 2;
+      if (x == xb || x == xf) {
+        AdjMat<R> mx = m;
+        mx.iphi = ip;
+        MatAdj<R> axp{}, ab{};
+        R lx = R(0), ly = R(0), lp1 = R(0);
+        boundary_flow_adj(mub, uxp, uyp, ppp, side == 0 && !pressure, ubx, side == 0 ? k.p_in : k.p_out, mx, phi_b,
+                          iphi_b, lx, ly, lp1, axp, ab);
+        if (x == xb) {
+          ma.phi += ab.phi;
+        } else {
+          ma.phi += axp.phi;
+          blx += lx;
+          bly += ly;
+          lpp += lp1;
+#pragma unroll
+          for (int q = 0; q < 9; ++q) muf[q] += mub[q];
+        }
       }
-      MatAdj<R> axp{}, ab{};
-      boundary_adj<R, EXT>(p, mxp, mb, k, false, R(0), R(0), mub, mu, axp, ab);
-      add_mat_adj(ma, outlet, ab, axp);
+    }
+    if (!bnode && (x == 1 || x == k.nx - 2)) {
+      // xp's macros: phi p = 0.6 S - 0.4 u^2 / phi, u = v / den
+      const R c = R(0.8) * lpp * m.iphi;
+      ma.phi += R(0.4) * lpp * t.u2 * m.iphi * m.iphi;
+      R lvx, lvy, lt = R(0), mx[9];
+      flow_macros_adj<R, EXT>(t, m, k, fma_(-c, t.ux, blx), fma_(-c, t.uy, bly), R(0), R(0), lvx, lvy, lt, ma);
+      flow_sums_adj(R(0), R(0.6) * lpp, R(0), R(0), R(0), lvx, lvy, R(0), R(0), mx);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) muf[q] += mx[q];
+      if (buoyant) {
+        const R l = theta_adj<R, EXT>(lt, t.thb, m, k, ma);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) mus[q] += l;
+      }
     }
   }
   // Transpose of the film's update in the column that pulled it (the
-  // outlet's copy came back through the boundary transpose above); the seed
-  // adds J's dependence on the film, which counts column nx - 2 twice (the
-  // outlet carries its film).
+  // outlet's copy came back through the exchange above); the seed adds J's
+  // dependence on the film, which counts column nx - 2 twice (the outlet
+  // carries its film).
   if (film && !bnode) {
     const R ls = SEED ? ((open && x == k.nx - 2) ? R(2) * w : w) : R(0);
-    film_adj(ft, mxp, k, ls, mu[13], mu[18], ma);
+    film_adj(ft, m, k, ls, mus[4], mus[9], ma);
   }
-  if (outlet) {  // its scalar material terms belong to column nx - 2
-    ma.bT = R(0);
-    ma.bC = R(0);
+  if (EXT) push_scalars();
+  if (bnode) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) muf[q] = R(0);
+  }
+  push_part<R, 0, 9>(lam_out, bo, k, inner, x, y, muf);
+
+  // The gradient of this node's own material; the outlet's scalar-material
+  // terms went to column nx - 2.
+  if (outlet) {
+    ma.aT = R(0);
+    ma.aC = R(0);
     ma.rhocp = R(0);
     ma.sig = R(0);
   }
-  if (bnode) {  // its pulled sources were never read: their adjoint is 0
-#pragma unroll
-    for (int q = 0; q < 19; ++q) mu[q] = R(0);
-  }
-  // The gradient of this node's own material (a boundary node's is read
-  // again; its scalar-material terms are zero, so the outlet's copy of
-  // column nx - 2's scalar material does not enter).
   R g0 = R(0), g1 = R(0), g2 = R(0);
-  material_adj<R, EXT>(k, bnode ? material<R, MAT_FULL>(k, phi_f, invk_f, d_f, x, y) : mxp, ma, g0, g1, g2);
+  material_adj<R, EXT>(k, m, ma, g0, g1, g2);
   grad[o] += g0;
   grad[k.plane + o] += g1;
   grad[2 * k.plane + o] += g2;
-  // Push: the adjoint of the pulled element (x - e_q, q) (or of the
-  // bounced-back (x, opp q)) is mu[q].  Interior wavefronts store through
-  // wave-uniform bases, as the pull loads (30.0 -> 29.2 us per reverse step
-  // together with the buffer loads of lambda; at four waves per SIMD the
-  // same forms had cost more in spilled registers than they saved).
-  if (__all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2)) {
-    const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = 0; q < 19; ++q)
-      buffer_store(lam_out + (int64_t(q) * k.plane - int64_t(EY[q]) * k.pitch - EX[q]), ob, mu[q]);
-    return;
-  }
-  const bool px = k.flags & F_PERIODIC_X;
-  const bool py = k.flags & F_PERIODIC_Y;
-#pragma unroll
-  for (int q = 0; q < 19; ++q) {
-    int xs = x - EX[q];
-    int ys = y - EY[q];
-    if (px) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
-    if (py) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
-    const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny;
-    const int off = in ? (q * k.plane + ys * k.pitch + xs) : (OPP[q] * k.plane + y * k.pitch + x);
-    lam_out[off] = mu[q];
-  }
 }
 
 // Gradient through the initial state: the O2 equilibrium at rest depends on

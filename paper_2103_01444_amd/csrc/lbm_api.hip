@@ -750,6 +750,7 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
   const MatPtrs<R> m = mat_ptrs<R>(c);
   const Consts<R> k = consts<R>(c);
   const dim3 grid((c->g.nx + kBlock - 1) / kBlock, c->g.ny);
+  const dim3 agrid((c->g.nx + adj_lane_shift(c->g.nx) + kBlock - 1) / kBlock, c->g.ny);
   R* grad = reinterpret_cast<R*>(ws + A.off_grad);
   R* lam[2] = {reinterpret_cast<R*>(ws + A.off_lam), reinterpret_cast<R*>(ws + A.off_lam + A.state)};
   const int64_t ngrad = int64_t(3) * c->L.plane;
@@ -763,10 +764,10 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
   const bool ext = c->g.flags & (LBM_BUOYANCY | LBM_SIGMA_ENERGY | LBM_PRESSURE_INLET | LBM_THIN_CL);
   const R* S_final = static_cast<const R*>(c->state(c->cur));
   if (ext)
-    hipLaunchKernelGGL((k_adj_step<R, true, true>), grid, dim3(kBlock), 0, c->stream, S_final,
+    hipLaunchKernelGGL((k_adj_step<R, true, true>), agrid, dim3(kBlock), 0, c->stream, S_final,
                        static_cast<const R*>(nullptr), lam[0], grad, m.phi, m.invk, m.d, k, R(w));
   else
-    hipLaunchKernelGGL((k_adj_step<R, true>), grid, dim3(kBlock), 0, c->stream, S_final,
+    hipLaunchKernelGGL((k_adj_step<R, true>), agrid, dim3(kBlock), 0, c->stream, S_final,
                        static_cast<const R*>(nullptr), lam[0], grad, m.phi, m.invk, m.d, k, R(w));
   // Segments are swept from the last to the first.  Segment s - 1 is
   // replayed from its checkpoint into one replay buffer on the second
@@ -818,10 +819,10 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
     for (int j = seg_len(seg) - 1; j >= 0; --j) {
       const R* S = reinterpret_cast<const R*>(buf + size_t(j) * A.state);
       if (ext)
-        hipLaunchKernelGGL((k_adj_step<R, false, true>), grid, dim3(kBlock), 0, c->stream, S, lam[cur],
+        hipLaunchKernelGGL((k_adj_step<R, false, true>), agrid, dim3(kBlock), 0, c->stream, S, lam[cur],
                            lam[cur ^ 1], grad, m.phi, m.invk, m.d, k, R(0));
       else
-        hipLaunchKernelGGL((k_adj_step<R, false>), grid, dim3(kBlock), 0, c->stream, S, lam[cur], lam[cur ^ 1], grad,
+        hipLaunchKernelGGL((k_adj_step<R, false>), agrid, dim3(kBlock), 0, c->stream, S, lam[cur], lam[cur ^ 1], grad,
                            m.phi, m.invk, m.d, k, R(0));
       cur ^= 1;
     }

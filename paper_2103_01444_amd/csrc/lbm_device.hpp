@@ -61,6 +61,8 @@ struct Consts {
   R aFsum_over_R;       // (alpha_a + alpha_c) F / R, Butler-Volmer only
   R ln_thin;            // ln(film thickness / dx), thin-film CL only
   R bx, by;             // buoyancy: acceleration per kelvin of temperature rise
+  // reverse step: sqrt(3) alpha_scale k_f and k_s, 1 / rhocp_f
+  R aT_f, aT_s, irc_f;
 };
 
 template <typename R>

@@ -211,6 +211,9 @@ void fill_consts(Consts<R>& k, const lbm_geometry& g, const lbm_params& p, const
   k.ln_thin = R(std::log((p.thin_cl_cm > 0 ? p.thin_cl_cm : d.dx) / d.dx));
   k.bx = R(p.buoyancy_x);
   k.by = R(p.buoyancy_y);
+  k.aT_f = R(std::sqrt(3.0) * d.alpha_scale * p.k_f);
+  k.aT_s = R(std::sqrt(3.0) * d.alpha_scale * p.k_s);
+  k.irc_f = R(1.0 / p.rhocp_f);
 }
 
 }  // namespace lbm
