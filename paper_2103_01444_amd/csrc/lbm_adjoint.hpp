@@ -51,8 +51,6 @@ __device__ __forceinline__ double fast_sqrt(double a) {
   r = __builtin_fma(-g, g, a);
   return __builtin_fma(r, h, g);
 }
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 
 // Sum of the five populations g of a scalar lattice, and the temperature

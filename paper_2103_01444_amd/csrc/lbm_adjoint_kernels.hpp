@@ -6,44 +6,6 @@
 
 namespace lbm {
 
-// Wave-uniform bases of one 19-plane buffer: five raw buffer resources of
-// four planes each (at most 2^31 elements in all, so three planes and a
-// neighbour shift stay below 4 GiB), each based one row and one element
-// before its first plane so that every neighbour shift is a non-negative
-// scalar byte offset.  One 32-bit lane offset serves all planes, and a plane
-// costs one scalar register (its own resource would cost four: at 57 planes
-// that spilled scalar registers).
-template <typename R>
-struct PlaneBuffer {
-  __amdgpu_buffer_rsrc_t r[5];
-  uint32_t plane, pitch;  // bytes
-  __device__ __forceinline__ PlaneBuffer(const R* p, const Consts<R>& k) {
-    plane = uint32_t(k.plane) * uint32_t(sizeof(R));
-    pitch = uint32_t(k.pitch) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int g = 0; g < 5; ++g) r[g] = buffer_of(p + (int64_t(4 * g) * k.plane - k.pitch - 1));
-  }
-  // byte offset of population q of the node displaced by (dx, dy)
-  __device__ __forceinline__ uint32_t off(int q, int dx, int dy) const {
-    return uint32_t(q & 3) * plane + uint32_t(1 + dy) * pitch + uint32_t(1 + dx) * uint32_t(sizeof(R));
-  }
-  template <int AUX>
-  __device__ __forceinline__ R load(int q, int dx, int dy, uint32_t ob) const {
-    if constexpr (sizeof(R) == 4)
-      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
-    else
-      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
-  }
-  __device__ __forceinline__ void store(int q, int dx, int dy, uint32_t ob, R v) const {
-    if constexpr (sizeof(R) == 4) {
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r[q >> 2], int(ob), int(off(q, dx, dy)), 0);
-    } else {
-      using U2 = uint32_t __attribute__((ext_vector_type(2)));
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r[q >> 2], int(ob), int(off(q, dx, dy)), 0);
-    }
-  }
-};
-
 // Element offset the pull of population q at (x, y) reads, and the push of
 // its adjoint writes.
 template <typename R>
@@ -82,6 +44,13 @@ __device__ __forceinline__ void push_part(R* __restrict__ lam, const PlaneBuffer
 #pragma unroll
     for (int q = Q0; q < Q1; ++q) lam[pull_offset(k, q, x, y)] = mu[q - Q0];
   }
+}
+
+// Population q of the node at element offset o.
+template <typename R>
+__device__ __forceinline__ R load_own(const R* __restrict__ p, const PlaneBuffer<R>& b, const Consts<R>& k, int q,
+                                      int o) {
+  return k.near32 ? b.template load<0>(q, 0, 0, uint32_t(o) * uint32_t(sizeof(R))) : p[q * k.plane + o];
 }
 
 // Lane shift of the reverse step: lane l of a row's first workgroup holds
@@ -134,9 +103,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   const bool w_in = in_row && l0 == 0, w_out = open && l0 == ((k.nx - 1 + shift) & ~63);
   const int lane_out = (k.nx - 1 + shift) & 63;
   const bool pressure = EXT && (k.flags & F_PRESSURE_INLET);
-  const bool inner = __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2);
+  const bool inner = k.near32 && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2);
   const int o = y * k.pitch + x;
-  const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
   const PlaneBuffer<R> bS(S, k), bi(lam_in, k), bo(lam_out, k);
 
   AdjMat<R> m = adj_material<R>(k, phi_f, invk_f, d_f, xp, y);
@@ -191,7 +159,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   } else {
     R la[10];
 #pragma unroll
-    for (int q = 0; q < 10; ++q) la[q] = bi.template load<0>(9 + q, 0, 0, ob);
+    for (int q = 0; q < 10; ++q) la[q] = load_own(lam_in, bi, k, 9 + q, o);
     scalars_adj<R, EXT>(g, t.ux, t.uy, m, k, cl, la, mus, lux, luy, ma);
   }
   // With buoyancy the boundary nodes' temperature adjoint also has a share
@@ -206,7 +174,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
     } else {
       R la[9];
 #pragma unroll
-      for (int q = 0; q < 9; ++q) la[q] = bi.template load<0>(q, 0, 0, ob);
+      for (int q = 0; q < 9; ++q) la[q] = load_own(lam_in, bi, k, q, o);
       flow_adj<R, EXT>(t, m, k, la, lux, luy, muf, lth, ma);
       if (buoyant) {
         const R l = theta_adj<R, EXT>(lth, t.thb, m, k, ma);

@@ -154,36 +154,31 @@ MatPtrs<R> mat_ptrs(lbm_ctx* c) {
           static_cast<const R*>(c->mat_plane(2))};
 }
 
-// Lattices below this many nodes take the wave-uniform addressing form of
-// the step (their launches are bound by each wavefront's own chain).
-constexpr int64_t kUniformMaxCells = int64_t(1) << 20;
+// A state beyond the 256 MB last-level cache.
+constexpr int64_t kStreamBytes = int64_t(256) << 20;
+bool streams(const lbm_ctx* c) { return int64_t(19) * c->L.plane * int64_t(c->L.esize) > kStreamBytes; }
 
 template <typename R, int MAT>
 void launch_step_kernel(lbm_ctx* c, const R* src, R* dst, const MatPtrs<R>& m, const Consts<R>& k,
                         hipStream_t stream) {
   const dim3 grid((c->g.nx + kBlock - 1) / kBlock, c->g.ny);
-  if (int64_t(c->g.nx) * c->g.ny < kUniformMaxCells)
+  if (streams(c))
     hipLaunchKernelGGL((k_step<R, MAT, true>), grid, dim3(kBlock), 0, stream, src, dst, m.phi, m.invk, m.d, k);
   else
     hipLaunchKernelGGL((k_step<R, MAT, false>), grid, dim3(kBlock), 0, stream, src, dst, m.phi, m.invk, m.d, k);
 }
 
-// Lattices of at least kTwoStepMinCells nodes with walls and inlet / outlet
-// columns advance two steps per launch (k_step2: the same states, bit for
-// bit, as two single steps).  Measured per step against single steps,
-// 4096x1024: FP32 99.6 -> 89.6 us, FP64 247.6 -> 177.7 us; 1024x512 5 %
-// faster in both precisions.  Smaller lattices, whose launches are bound by
-// each wavefront's own chain rather than by HBM, run slower in pairs
-// (1024x256 FP32 8.9 -> 12.5 us) and keep single steps.
-constexpr int64_t kTwoStepMinCells = int64_t(1) << 19;
-// FP32 lattices of at least this many nodes take non-temporal loads in
-// step one (k_step2's NT), the others cached loads.
-constexpr int64_t kTwoStepStreamCells = int64_t(1) << 22;
-bool two_step_form_applies(const lbm_ctx* c) {
-  return !(c->g.flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y));
-}
-bool two_steps_per_launch(const lbm_ctx* c) {
-  return int64_t(c->g.nx) * c->g.ny >= kTwoStepMinCells && two_step_form_applies(c);
+// Lattices with walls and inlet / outlet columns advance two steps per
+// launch (k_step2: the same states, bit for bit, as two single steps), which
+// is faster at every size.
+bool two_steps_per_launch(const lbm_ctx* c) { return !(c->g.flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y)); }
+
+template <typename R, int MAT, int TX, int TY, int SAUX>
+void launch_tiles2(lbm_ctx* c, const R* src, R* mid, R* dst, const MatPtrs<R>& m, const Consts<R>& k,
+                   hipStream_t stream) {
+  const dim3 grid((c->g.nx + TX - 1) / TX, (c->g.ny + TY - 1) / TY);
+  hipLaunchKernelGGL((k_step2<R, MAT, TX, TY, SAUX>), grid, dim3(Tile2<TX, TY>::threads), 0, stream, src, mid, dst,
+                     m.phi, m.invk, m.d, k);
 }
 
 // Two steps src -> (mid) -> dst; mid may be null (the middle state is not
@@ -191,13 +186,11 @@ bool two_steps_per_launch(const lbm_ctx* c) {
 template <typename R, int MAT>
 void launch_step_pair(lbm_ctx* c, const R* src, R* mid, R* dst, const MatPtrs<R>& m, const Consts<R>& k,
                       hipStream_t stream) {
-  const dim3 grid((c->g.nx + kT2X - 1) / kT2X, (c->g.ny + kT2Y - 1) / kT2Y);
-  if (sizeof(R) == 4 && int64_t(c->g.nx) * c->g.ny >= kTwoStepStreamCells)
-    hipLaunchKernelGGL((k_step2<R, MAT, true>), grid, dim3(kT2Threads), 0, stream, src, mid, dst, m.phi, m.invk, m.d,
-                       k);
-  else
-    hipLaunchKernelGGL((k_step2<R, MAT, false>), grid, dim3(kT2Threads), 0, stream, src, mid, dst, m.phi, m.invk,
-                       m.d, k);
+  if (int64_t(c->g.nx) * c->g.ny < kT2SmallCells)
+    return launch_tiles2<R, MAT, kT2SmallX, kT2SmallY, 16>(c, src, mid, dst, m, k, stream);
+  if constexpr (sizeof(R) == 4)
+    if (streams(c)) return launch_tiles2<R, MAT, kT2X, kT2Y, 0>(c, src, mid, dst, m, k, stream);
+  launch_tiles2<R, MAT, kT2X, kT2Y, 16>(c, src, mid, dst, m, k, stream);
 }
 
 template <typename R, int MAT>
@@ -708,17 +701,12 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int32_t every) {
 
 // Steps from state(0) to state(n) of a chain of states, storing each: a
 // pair per launch where the lattice allows it, single steps otherwise.
-// overlapped: the chain runs beside other work (the adjoint's replay, on
-// the second stream during a reverse sweep), where pairs pay at any size:
-// they store three states per two steps instead of four, and the latency
-// of a launch is hidden (1024x256 FP32 adjoint 10.28 -> 10.55 GLUPS, the
-// same gradient bits; run alone, pairs at that size are slower).
 template <typename R, typename Slot>
-void launch_step_chain(lbm_ctx* c, Slot state, int n, hipStream_t stream, bool overlapped) {
+void launch_step_chain(lbm_ctx* c, Slot state, int n, hipStream_t stream) {
   const MatPtrs<R> m = mat_ptrs<R>(c);
   const Consts<R> k = consts<R>(c);
   int j = 1;
-  if (overlapped ? two_step_form_applies(c) : two_steps_per_launch(c))
+  if (two_steps_per_launch(c))
     for (; j + 1 <= n; j += 2)
       launch_step_pair<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)),
                                     static_cast<R*>(state(j + 1)), m, k, stream);
@@ -737,7 +725,7 @@ lbm_status forward_last_segment(lbm_ctx* c, const AdjLayout& A, int64_t n) {
     return fail(c, LBM_ERR_DEVICE, "replay buffer copy failed");
   void* last = c->state(c->cur ^ 1);
   launch_step_chain<R>(c, [&](int64_t j) -> void* { return j < n ? buf + size_t(j) * A.state : last; }, int(n),
-                       c->stream, false);
+                       c->stream);
   c->cur ^= 1;
   c->step += n;
   return check_launch(c, "forward_checkpointed");
@@ -797,8 +785,7 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
     if (hipMemcpyAsync(buf, ws + A.off_ck + size_t(seg) * A.state, A.state, hipMemcpyDeviceToDevice, c->aux) !=
         hipSuccess)
       return fail(c, LBM_ERR_DEVICE, "replay restore failed");
-    launch_step_chain<R>(c, [&](int j) -> void* { return buf + size_t(j) * A.state; }, seg_len(seg) - 1, c->aux,
-                         true);
+    launch_step_chain<R>(c, [&](int j) -> void* { return buf + size_t(j) * A.state; }, seg_len(seg) - 1, c->aux);
     if (hipEventRecord(c->ev_rep[b], c->aux) != hipSuccess) return fail(c, LBM_ERR_DEVICE, "replay event failed");
     return LBM_OK;
   };

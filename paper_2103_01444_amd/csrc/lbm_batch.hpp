@@ -30,11 +30,9 @@ struct Tile {
 // interleave (element y * pitch + x of the planes at 19, 20, 21 rows).
 constexpr int kFieldRow = 19;
 
-// Advance cell i (row-major inside the tile) of a tile.  UNIFORM: wave-
-// uniform buffer addressing for the interior pull and the stores (batches
-// of few nodes, whose launches are one round of wavefronts).  MAT: the
-// material of every case, MAT_LAYERED or MAT_FULL (fields at `fields`).
-template <typename R, int MAT, bool UNIFORM = false>
+// Advance cell i (row-major inside the tile) of a tile.  MAT: the material
+// of every case, MAT_LAYERED or MAT_FULL (fields at `fields`).
+template <typename R, int MAT>
 __device__ __forceinline__ void batch_cell(const R* __restrict__ src, R* __restrict__ dst, const Consts<R>& k,
                                            const R* __restrict__ fields, const Tile& t, int i, int tx) {
   const int y = t.y0 + i / tx;
@@ -43,23 +41,15 @@ __device__ __forceinline__ void batch_cell(const R* __restrict__ src, R* __restr
   R f[19];
   const R* invk_f = MAT == MAT_LAYERED ? nullptr : fields + k.plane;
   const R* d_f = MAT == MAT_LAYERED ? nullptr : fields + 2 * k.plane;
-  const Mat<R> mt = pre_collision<R, MAT, false, UNIFORM>(src, k, fields, invk_f, d_f, x, y, f);
+  const int yb = __builtin_amdgcn_readfirstlane(y);  // the wavefront's topmost row
+  const Mat<R> mt = pre_collision<R, MAT, false>(src, k, fields, invk_f, d_f, x, y, f, yb);
   collide(f, mt, k, y >= k.y_cl0 && !(k.flags & F_NO_REACTION));
-  const int o = y * k.pitch + x;
-  if constexpr (UNIFORM) {
-    const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = 0; q < 19; ++q) buffer_store(dst + int64_t(q) * k.plane, ob, f[q]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 19; ++q) dst[q * k.plane + o] = f[q];
-  }
+  store_node<16>(dst, k, x, y, yb, f);
 }
 
 // Advance the cells of one tile (tx x ty cells).  ONE: the tile has exactly
-// one cell per thread (tx ty = kBlock); without the cell loop the kernel
-// needs 59 instead of 76 VGPRs (8 instead of 6 waves per SIMD in FP32).
-template <typename R, int MAT, bool ONE, bool UNIFORM = false>
+// one cell per thread; without the cell loop the kernel needs fewer VGPRs.
+template <typename R, int MAT, bool ONE>
 __device__ __forceinline__ void batch_tile(R* __restrict__ pool, const BatchCase<R>* __restrict__ cases,
                                            const Tile& t, int parity, int tx, int ty) {
   const Consts<R> k = cases[t.c].k;
@@ -68,10 +58,10 @@ __device__ __forceinline__ void batch_tile(R* __restrict__ pool, const BatchCase
   R* dst = pool + o_dst;
   const R* fields = MAT == MAT_LAYERED ? nullptr : pool + cases[t.c].off[0] + int64_t(kFieldRow) * k.plane;
   if constexpr (ONE) {
-    batch_cell<R, MAT, UNIFORM>(src, dst, k, fields, t, threadIdx.x, tx);
+    batch_cell<R, MAT>(src, dst, k, fields, t, threadIdx.x, tx);
   } else {
     const int n = tx * ty;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) batch_cell<R, MAT, UNIFORM>(src, dst, k, fields, t, i, tx);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) batch_cell<R, MAT>(src, dst, k, fields, t, i, tx);
   }
 }
 
@@ -85,23 +75,23 @@ __device__ __forceinline__ int xcd_logical(int flat, int total) {
 
 // BS: workgroup size.  Tiles of exactly BS cells (64, 128 or 256) run one
 // cell per thread; other tiles loop over their cells with 256 threads.
-template <typename R, int MAT, bool ONE, bool UNIFORM, int BS = kBlock>
+template <typename R, int MAT, bool ONE, int BS = kBlock>
 __global__ __launch_bounds__(BS) void k_batch_step(R* __restrict__ pool, const BatchCase<R>* __restrict__ cases,
                                                    const Tile* __restrict__ tiles, int ntiles, int parity, int tx,
                                                    int ty) {
   const int t = xcd_logical(blockIdx.x, gridDim.x);
   if (t >= ntiles) return;
-  batch_tile<R, MAT, ONE, UNIFORM>(pool, cases, tiles[t], parity, tx, ty);
+  batch_tile<R, MAT, ONE>(pool, cases, tiles[t], parity, tx, ty);
 }
 
-// Two steps per launch: one kT2Threads workgroup per tile of kT2X x kT2Y
-// nodes (the tile list of that shape), the body of k_step2 on the tile's
-// case.  Cases with periodic axes are not scheduled so.
+// Two steps per launch: one workgroup per tile of kT2X x kT2Y nodes, the
+// body of k_step2 on the tile's case.  Cases with periodic axes are not
+// scheduled so.
 template <typename R, int MAT>
-__global__ __launch_bounds__(kT2Threads) void k_batch_step2(R* __restrict__ pool,
-                                                            const BatchCase<R>* __restrict__ cases,
-                                                            const Tile* __restrict__ tiles, int ntiles, int parity) {
-  __shared__ R lds[19 * kT2N];
+__global__ __launch_bounds__((Tile2<kT2X, kT2Y>::threads)) void k_batch_step2(
+    R* __restrict__ pool, const BatchCase<R>* __restrict__ cases, const Tile* __restrict__ tiles, int ntiles,
+    int parity) {
+  __shared__ R lds[19 * Tile2<kT2X, kT2Y>::N];
   const int t = xcd_logical(blockIdx.x, gridDim.x);
   if (t >= ntiles) return;  // the whole workgroup: no thread reaches the barrier
   const Tile tl = tiles[t];
@@ -111,7 +101,7 @@ __global__ __launch_bounds__(kT2Threads) void k_batch_step2(R* __restrict__ pool
   const R* fields = MAT == MAT_LAYERED ? nullptr : pool + cases[tl.c].off[0] + int64_t(kFieldRow) * k.plane;
   const R* invk_f = MAT == MAT_LAYERED ? nullptr : fields + k.plane;
   const R* d_f = MAT == MAT_LAYERED ? nullptr : fields + 2 * k.plane;
-  step2_tile<R, MAT, false>(lds, src, nullptr, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
+  step2_tile<R, MAT, kT2X, kT2Y, 16>(lds, src, nullptr, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
 }
 
 // Waves per SIMD the persistent kernel is compiled for (at least): the

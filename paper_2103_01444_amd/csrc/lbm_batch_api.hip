@@ -18,6 +18,9 @@ using namespace lbm;
 namespace {
 
 constexpr size_t kAlign = 256;
+// The schedule that asks for two steps per launch: its workgroup size and
+// tile shape name the form (the kernel's own tiles are kT2X x kT2Y).
+constexpr int kTwoStepBlock = 960, kTwoStepX = 64, kTwoStepY = 12;
 constexpr int kMinTileCells = 64;  // smallest tile the schedule accepts (sizes the tile table)
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -61,7 +64,8 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
       L.state_off[s][i] = e;
       e += (L.rows * plane + 63) / 64 * 64;  // 256-byte aligned per buffer
     }
-    L.max_tiles += int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells);
+    L.max_tiles += std::max(int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells),
+                            ((g[i].nx + kT2X - 1) / kT2X) * ((g[i].ny + kT2Y - 1) / kT2Y));
     L.max_obs_blocks = std::max(L.max_obs_blocks, ((g[i].nx + kBlock - 1) / kBlock) * g[i].ny);
     L.max_nx = std::max(L.max_nx, g[i].nx);
   }
@@ -319,49 +323,34 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
   } else {
     // workgroups of 64 or 128 threads: one cell of the tile (of that many
     // cells) per thread; of 256: one cell per thread for tiles of 256 cells,
-    // a cell loop otherwise.  Batches of few nodes (one round of wavefronts
-    // per launch) take the wave-uniform addressing form.
+    // a cell loop otherwise.
     const int cells = tx * ty;
     const int bs = b->sched.block == 64 || b->sched.block == 128 ? b->sched.block : kBlock;
-    const bool uniform = b->cells < (int64_t(1) << 20);
     const dim3 grid(b->ntiles);
     int64_t s = 0;
-    if (b->sched.block == kT2Threads) {  // two steps per launch; an odd count ends with one step
+    int odd_tx = tx, odd_ty = ty;
+    if (b->sched.block == kTwoStepBlock) {  // two steps per launch; an odd count ends with one step on the same tiles
+      odd_tx = kT2X;
+      odd_ty = kT2Y;
       for (; s + 2 <= nsteps; s += 2) {
-        hipLaunchKernelGGL((k_batch_step2<R, MAT>), grid, dim3(kT2Threads), 0, b->stream, pool, cases, tiles,
-                           b->ntiles, b->parity);
+        hipLaunchKernelGGL((k_batch_step2<R, MAT>), grid, dim3(Tile2<kT2X, kT2Y>::threads), 0, b->stream, pool, cases,
+                           tiles, b->ntiles, b->parity);
         b->parity ^= 1;
       }
     }
     for (; s < nsteps; ++s) {
-      if (bs == 64) {
-        if (uniform)
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, true, 64>), grid, dim3(64), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-        else
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, false, 64>), grid, dim3(64), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-      } else if (bs == 128) {
-        if (uniform)
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, true, 128>), grid, dim3(128), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-        else
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, false, 128>), grid, dim3(128), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-      } else if (cells == kBlock) {
-        if (uniform)
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, true>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-        else
-          hipLaunchKernelGGL((k_batch_step<R, MAT, true, false>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
-                             b->ntiles, b->parity, tx, ty);
-      } else if (uniform) {
-        hipLaunchKernelGGL((k_batch_step<R, MAT, false, true>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
+      if (bs == 64)
+        hipLaunchKernelGGL((k_batch_step<R, MAT, true, 64>), grid, dim3(64), 0, b->stream, pool, cases, tiles,
                            b->ntiles, b->parity, tx, ty);
-      } else {
-        hipLaunchKernelGGL((k_batch_step<R, MAT, false, false>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
+      else if (bs == 128)
+        hipLaunchKernelGGL((k_batch_step<R, MAT, true, 128>), grid, dim3(128), 0, b->stream, pool, cases, tiles,
                            b->ntiles, b->parity, tx, ty);
-      }
+      else if (cells == kBlock)
+        hipLaunchKernelGGL((k_batch_step<R, MAT, true>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
+                           b->ntiles, b->parity, tx, ty);
+      else
+        hipLaunchKernelGGL((k_batch_step<R, MAT, false>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
+                           b->ntiles, b->parity, odd_tx, odd_ty);
       b->parity ^= 1;
     }
     const hipError_t e = hipGetLastError();
@@ -382,16 +371,17 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
     return bfail(b, LBM_ERR_INVALID_ARG, "tile shape out of range");
   if (!(s.block == 0 || s.block == kBlock ||
         ((s.block == 64 || s.block == 128) && s.tile_x * s.tile_y == s.block && !s.persistent) ||
-        (s.block == kT2Threads && s.tile_x == kT2X && s.tile_y == kT2Y && !s.persistent)))
+        (s.block == kTwoStepBlock && s.tile_x == kTwoStepX && s.tile_y == kTwoStepY && !s.persistent)))
     return bfail(b, LBM_ERR_INVALID_ARG,
                  "workgroup size: 0 or 256, 64 / 128 for a per-step tile of as many cells, or 960 for the "
                  "two-step form of 64 x 12 tiles");
-  if (s.block == kT2Threads)
+  if (s.block == kTwoStepBlock)
     for (int i = 0; i < b->n; ++i)
       if (b->g[i].flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y))
         return bfail(b, LBM_ERR_INVALID_ARG, "the two-step form needs walls and inlet / outlet columns (no periodic axis)");
   b->sched = s;
-  if (lbm_status st = build_tiles(b, s.tile_x, s.tile_y); st != LBM_OK) return st;
+  const bool two = s.block == kTwoStepBlock;
+  if (lbm_status st = build_tiles(b, two ? kT2X : s.tile_x, two ? kT2Y : s.tile_y); st != LBM_OK) return st;
   if (s.persistent)
     return b->L.fields ? persistent_grid<R, MAT_FULL>(b, &b->persistent_grid)
                        : persistent_grid<R, MAT_LAYERED>(b, &b->persistent_grid);
@@ -501,7 +491,7 @@ lbm_status autotune_t(lbm_batch* b, int trial_steps, lbm_schedule* best, double*
       const int cells = sh[0] * sh[1];
       if (!persistent && (cells == 64 || cells == 128)) cand.push_back({sh[0], sh[1], 0, cells});
     }
-  cand.push_back({kT2X, kT2Y, 0, kT2Threads});
+  cand.push_back({kTwoStepX, kTwoStepY, 0, kTwoStepBlock});
   for (const lbm_schedule& s : cand) {
     const int persistent = s.persistent;
     if (set_schedule_t<R>(b, s) != LBM_OK) continue;  // shape not usable here
@@ -657,6 +647,8 @@ lbm_status lbm_batch_create(const lbm_geometry* g, const lbm_params* p, int32_t 
     // 19 planes apart.  64-case sweep: 174.5 -> 157.7 us per step.
     b->kf[i].plane = b->kd[i].plane = pitch_of(g[i].nx);
     b->kf[i].pitch = b->kd[i].pitch = b->L.rows * pitch_of(g[i].nx);
+    b->kf[i].near32 = b->kd[i].near32 =
+        near_offsets(b->kf[i].plane, b->kf[i].pitch, int64_t(64) * b->kf[i].pitch, sizeof(double));
   }
   int dev = 0, wall_khz = 0;
   if (hipGetDevice(&dev) != hipSuccess ||

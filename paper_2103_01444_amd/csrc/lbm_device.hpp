@@ -41,6 +41,7 @@ struct Consts {
   uint32_t flags;
   int32_t plane;        // stride between population q and q + 1
   int32_t bv;           // nonzero: Butler-Volmer kinetics (anodic branch), else the printed Tafel form
+  int32_t near32;       // nonzero: the byte offsets of PlaneBuffer fit 32 bits (near_offsets)
   // flow (Section 2.1)
   R s_e, s_q, nu;       // s_e: rate of rho, e, zeta, pxx, pxy; s_q: energy flux
   R u_in_coef;          // 6 U_avg / H_channel^2
@@ -71,8 +72,61 @@ struct Mat {
   R sig;  // heat-capacity ratio (rho c_p)_eff / (rho c_p)_f with F_SIGMA_ENERGY, else 1
 };
 
+// a / b, 1 / b and sqrt(a) to the bits of IEEE's for operands whose result
+// and remainders stay clear of the ends of the exponent range: the steps of
+// the compiler's expansions without their scaling and special cases.
+// Operands here are porosities, heat capacities, drag and momentum sums of
+// order 1e-6 .. 1e6, and velocities: below 2^-100 (2^-900 in FP64), where
+// the remainders leave the range, a quotient or root may be off in its last
+// bits, and a root of less than the smallest normal number comes out too
+// small; no other quantity of the step can feel either (|v| is added to 1/2).
+// A zero denominator or an infinite operand gives NaN.  FP32: 8, 7 and 9
+// instructions instead of 10, 10 and 16.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Reciprocal of b as the quotients below take it.
+__device__ __forceinline__ float rcp_seed(float b) {
+  const float y = __builtin_amdgcn_rcpf(b);
+  return fma_(fma_(-b, y, 1.0f), y, y);
+}
+__device__ __forceinline__ double rcp_seed(double b) {
+  double y = __builtin_amdgcn_rcp(b);
+  y = fma_(fma_(-b, y, 1.0), y, y);
+  return fma_(fma_(-b, y, 1.0), y, y);
+}
+// a / b with y = rcp_seed(b), which quotients of one denominator share.
+__device__ __forceinline__ float div_(float a, float b, float y) {
+  float q = a * y;
+  q = fma_(fma_(-b, q, a), y, q);
+  return fma_(fma_(-b, q, a), y, q);
+}
+__device__ __forceinline__ double div_(double a, double b, double y) {
+  const double q = a * y;
+  return fma_(fma_(-b, q, a), y, q);
+}
 template <typename R>
-__device__ __forceinline__ R dsqrt(R a) { return sqrt(a); }
+__device__ __forceinline__ R div_(R a, R b) { return div_(a, b, rcp_seed(b)); }
+template <typename R>
+__device__ __forceinline__ R rcp_(R b) { return div_(R(1), b, rcp_seed(b)); }
+
+__device__ __forceinline__ float sqrt_(float a) {
+  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(a, 1.17549435e-38f));
+  float s = a * y, h = 0.5f * y;
+  const float e = fma_(-h, s, 0.5f);
+  s = fma_(s, e, s);
+  h = fma_(h, e, h);
+  return fma_(fma_(-s, s, a), h, s);
+}
+__device__ __forceinline__ double sqrt_(double a) {
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(a, 2.2250738585072014e-308));
+  double s = a * y, h = 0.5 * y;
+  const double e = fma_(-h, s, 0.5);
+  s = fma_(s, e, s);
+  h = fma_(h, e, h);
+  s = fma_(fma_(-s, s, a), h, s);
+  return fma_(fma_(-s, s, a), h, s);
+}
 
 // Porous-medium properties of one cell.  Layered: clear channel (phi = 1,
 // 1/K = 0, D = D_f) above the porous rows.  Per-cell porosity: Kozeny-Carman
@@ -92,13 +146,35 @@ __device__ __forceinline__ void base_fields(const Consts<R>& k, const R* __restr
     phi = phi_f[cell];
     if constexpr (MAT == MAT_PHI) {
       const R om = R(1) - phi;
-      invk = om * om * k.kc_inv / (phi * phi * phi);
-      d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * dsqrt(phi) * k.D_f;
+      invk = div_(om * om * k.kc_inv, phi * phi * phi);
+      d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * sqrt_(phi) * k.D_f;
     } else {
       invk = invk_f[cell];
       d = d_f[cell];
     }
   }
+}
+
+// The quantities the update derives from a cell's porosity, 1/K and D_eff.
+template <typename R>
+__device__ __forceinline__ Mat<R> derive_material(const Consts<R>& k, R phi, R invk, R d) {
+  Mat<R> m;
+  m.phi = phi;
+  m.invk = invk;
+  m.sqk = sqrt_(invk);
+  m.fphi = div_(R(0.143), phi * sqrt_(phi));
+  m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
+  m.l1 = phi * m.fphi * m.sqk * R(0.5);
+  m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
+  // Eq. 19; with the heat-capacity ratio the lattice carries k_eff / (rho c_p)_f
+  // and conserves sigma T
+  const bool sigma = k.flags & F_SIGMA_ENERGY;
+  const R alpha = div_((k.k_f * phi + k.k_s * (R(1) - phi)) * k.alpha_scale, sigma ? k.rhocp_f : m.rhocp);
+  m.sig = sigma ? div_(m.rhocp, k.rhocp_f) : R(1);
+  const R c20s3 = R(34.64101615137754587);  // 20 sqrt(3)
+  m.bT = c20s3 * alpha - R(4);
+  m.bC = c20s3 * d - R(4);
+  return m;
 }
 
 template <typename R, int MAT>
@@ -107,35 +183,14 @@ __device__ __forceinline__ Mat<R> material(const Consts<R>& k, const R* __restri
                                            const R* __restrict__ d_f, int x, int y) {
   R phi, invk, d;
   base_fields<R, MAT>(k, phi_f, invk_f, d_f, x, y, phi, invk, d);
-  Mat<R> m;
-  m.phi = phi;
-  m.invk = invk;
-  m.sqk = dsqrt(invk);
-  m.fphi = R(0.143) / (phi * dsqrt(phi));
-  m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
-  m.l1 = phi * m.fphi * m.sqk * R(0.5);
-  m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
-  // Eq. 19; with the heat-capacity ratio the lattice carries k_eff / (rho c_p)_f
-  // and conserves sigma T
-  const bool sigma = k.flags & F_SIGMA_ENERGY;
-  const R alpha = (k.k_f * phi + k.k_s * (R(1) - phi)) * k.alpha_scale / (sigma ? k.rhocp_f : m.rhocp);
-  m.sig = sigma ? m.rhocp / k.rhocp_f : R(1);
-  const R c20s3 = R(34.64101615137754587);  // 20 sqrt(3)
-  m.bT = c20s3 * alpha - R(4);
-  m.bC = c20s3 * d - R(4);
-  return m;
+  return derive_material(k, phi, invk, d);
 }
 
 // Pull the 19 pre-collision populations of node (x, y) from the
 // post-collision state: f_q(x) = f*_q(x - e_q), or f*_opp(q)(x) where the
 // link crosses a wall (half-way bounce-back).  Every element of the state is
-// read exactly once per step, so on a large lattice the loads carry the
-// non-temporal hint (NT): measured on MI355X the 4096x1024 FP32 step drops
-// from 118.6 us to 112.6 us with it (streamed lines stop displacing the
-// x +- 1 neighbour lines that adjacent wavefronts still need from L2), and
-// it is 9 % slower with plain loads in the final kernel (119.1 against
-// 109.3 us on one GPU).  The batched sweep of many narrow lattices is the
-// other way round: plain loads take it from 182.5 to 175.3 us per step.
+// read exactly once per step; NT gives the loads the non-temporal hint, for
+// states that no cache holds.
 //
 // Wave-uniform addressing: a base address that is the same for every lane
 // of the wavefront is held as a raw buffer resource in scalar registers and
@@ -168,23 +223,71 @@ __device__ __forceinline__ void buffer_store(R* base, uint32_t byte_off, R v) {
   }
 }
 
-//
-// UNIFORM: a wavefront whose nodes all lie one node or more inside the
-// lattice (no wall link, no periodic wrap) folds each population's plane and
-// neighbour shift into a wave-uniform base.  The reverse step, whose
-// register-bound collision adjoint leaves little issue slack, gains from it
-// (per reverse step of the 1024x256 adjoint 34.3 against 35.0 us, on another
-// GPU 33.4 against 34.9 us); the forward kernels run 0.5-1.5 % slower with
-// it (A/B on one GPU) and keep the per-lane form.
-template <typename R, bool NT = true, bool UNIFORM = false>
-__device__ __forceinline__ void pull(const R* __restrict__ src, const Consts<R>& k, int x, int y,
-                                     R (&f)[19]) {
-  if (UNIFORM && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2)) {
-    const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
+// Wave-uniform bases of one 19-plane buffer: five raw buffer resources of
+// four planes each, each based one row and one element
+// before row yb of its first plane so that every neighbour shift is a
+// non-negative scalar byte offset.  One 32-bit lane offset (of the node from
+// (0, yb)) serves all planes, and a plane costs one scalar register (its own
+// resource would cost four: at 57 planes that spilled scalar registers).
+template <typename R>
+struct PlaneBuffer {
+  __amdgpu_buffer_rsrc_t r[5];
+  uint32_t plane, pitch;  // bytes
+  __device__ __forceinline__ PlaneBuffer(const R* p, const Consts<R>& k, int yb = 0) {
+    p += int64_t(yb - 1) * k.pitch - 1;
+    plane = uint32_t(k.plane) * uint32_t(sizeof(R));
+    pitch = uint32_t(k.pitch) * uint32_t(sizeof(R));
 #pragma unroll
-    for (int q = 0; q < 19; ++q) {
-      f[q] = buffer_load<R, NT ? 2 : 0>(src + (int64_t(q) * k.plane - int64_t(EY[q]) * k.pitch - EX[q]), ob);
+    for (int g = 0; g < 5; ++g) r[g] = buffer_of(p + int64_t(4 * g) * k.plane);
+  }
+  // byte offset of population q of the node displaced by (dx, dy)
+  __device__ __forceinline__ uint32_t off(int q, int dx, int dy) const {
+    return uint32_t(q & 3) * plane + uint32_t(1 + dy) * pitch + uint32_t(1 + dx) * uint32_t(sizeof(R));
+  }
+  template <int AUX>
+  __device__ __forceinline__ R load(int q, int dx, int dy, uint32_t ob) const {
+    if constexpr (sizeof(R) == 4)
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
+    else
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
+  }
+  template <int AUX = 0>
+  __device__ __forceinline__ void store(int q, int dx, int dy, uint32_t ob, R v) const {
+    if constexpr (sizeof(R) == 4) {
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r[q >> 2], int(ob), int(off(q, dx, dy)), AUX);
+    } else {
+      using U2 = uint32_t __attribute__((ext_vector_type(2)));
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r[q >> 2], int(ob), int(off(q, dx, dy)), AUX);
     }
+  }
+};
+
+// A wavefront whose nodes all lie one node or more inside the lattice (no
+// wall link, no periodic wrap) folds each population's plane and neighbour
+// shift into a wave-uniform offset.  yb: a wave-uniform row at or above the
+// nodes' rows, at most 64 rows away (their lane offsets count from there).
+template <int AUX = 0, typename R>
+__device__ __forceinline__ void store_node(R* __restrict__ dst, const Consts<R>& k, int x, int y, int yb,
+                                           const R (&f)[19]) {
+  if (!k.near32) {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) dst[q * k.plane + y * k.pitch + x] = f[q];
+    return;
+  }
+  const PlaneBuffer<R> b(dst, k, yb);
+  const uint32_t ob = uint32_t((y - yb) * k.pitch + x) * uint32_t(sizeof(R));
+#pragma unroll
+  for (int q = 0; q < 19; ++q) b.template store<AUX>(q, 0, 0, ob, f[q]);
+}
+
+template <typename R, bool NT>
+__device__ __forceinline__ void pull(const R* __restrict__ src, const Consts<R>& k, int x, int y,
+                                     R (&f)[19], int yb) {
+  if (k.near32 && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2)) {
+    const PlaneBuffer<R> b(src, k, yb);
+    const uint32_t ob = uint32_t((y - yb) * k.pitch + x) * uint32_t(sizeof(R));
+#pragma unroll
+    for (int q = 0; q < 19; ++q) f[q] = b.template load<NT ? 2 : 0>(q, -EX[q], -EY[q], ob);
     return;
   }
   const bool px = k.flags & F_PERIODIC_X;
@@ -209,7 +312,7 @@ __device__ __forceinline__ void pull(const R* __restrict__ src, const Consts<R>&
 template <typename R, typename K>
 __device__ __forceinline__ R theta_of(const R* g, R sig, const K& k) {
   const R s = g[0] + g[1] + g[2] + g[3] + g[4];
-  return (k.flags & F_SIGMA_ENERGY) ? s / sig : s;
+  return (k.flags & F_SIGMA_ENERGY) ? div_(s, sig) : s;
 }
 
 template <typename R>
@@ -240,13 +343,14 @@ __device__ __forceinline__ Macro<R> flow_macros(const R (&f)[19], const Mat<R>& 
     vx += R(0.5) * m.phi * ax;
     vy += R(0.5) * m.phi * ay;
   }
-  const R vmag = dsqrt(vx * vx + vy * vy);
-  const R den = m.l0 + dsqrt(m.l0 * m.l0 + m.l1 * vmag);
+  const R vmag = sqrt_(vx * vx + vy * vy);
+  const R den = m.l0 + sqrt_(m.l0 * m.l0 + m.l1 * vmag);
+  const R iden = rcp_seed(den);
   Macro<R> o;
-  o.ux = vx / den;
-  o.uy = vy / den;
+  o.ux = div_(vx, den, iden);
+  o.uy = div_(vy, den, iden);
   const R u2 = o.ux * o.ux + o.uy * o.uy;
-  const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * dsqrt(u2));
+  const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * sqrt_(u2));
   o.Fx = -drag * o.ux;
   o.Fy = -drag * o.uy;
   if (body) {
@@ -254,7 +358,7 @@ __device__ __forceinline__ Macro<R> flow_macros(const R (&f)[19], const Mat<R>& 
     o.Fy += m.phi * ay;
   }
   const R s18 = f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
-  const R iphi = R(1) / m.phi;
+  const R iphi = rcp_(m.phi);
   o.p = R(0.6) * iphi * s18 - R(0.4) * u2 * iphi * iphi;
   return o;
 }
@@ -262,7 +366,7 @@ __device__ __forceinline__ Macro<R> flow_macros(const R (&f)[19], const Mat<R>& 
 // Eq. 5 equilibrium moments minus the rest-state moments (rho0, -4 rho0, 4 rho0, 0...).
 template <typename R>
 __device__ __forceinline__ void meq_shifted(R p, R ux, R uy, R phi, R (&me)[9]) {
-  const R iphi = R(1) / phi;
+  const R iphi = rcp_(phi);
   const R u2 = ux * ux + uy * uy;
   me[0] = R(0);
   me[1] = R(6) * phi * p + R(3) * u2 * iphi;
@@ -354,17 +458,17 @@ __device__ __forceinline__ void thin_film(R (&f)[19], const Mat<R>& mp, const Co
   }
 }
 
-template <typename R, int MAT, bool NT = true, bool UNIFORM = false>
+template <typename R, int MAT, bool NT>
 __device__ __forceinline__ Mat<R> pre_collision(const R* __restrict__ src, const Consts<R>& k,
                                                 const R* __restrict__ phi_f,
                                                 const R* __restrict__ invk_f,
                                                 const R* __restrict__ d_f, int x, int y,
-                                                R (&f)[19]) {
+                                                R (&f)[19], int yb) {
   const bool open = !(k.flags & F_PERIODIC_X);
   const bool inlet = open && x == 0 && y < k.ny_ch;
   const bool outlet = open && x == k.nx - 1;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
-  pull<R, NT, UNIFORM>(src, k, xp, y, f);
+  pull<R, NT>(src, k, xp, y, f, yb);
   Mat<R> mp = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y);
   thin_film(f, mp, k, y);
   if (!(inlet || outlet)) return mp;
@@ -501,7 +605,7 @@ __device__ __forceinline__ void collide(R (&f)[19], const Mat<R>& mt, const Cons
   R m[9], me[9];
   moments9(f, m);
   meq_shifted(a.p, a.ux, a.uy, mt.phi, me);
-  const R iphi = R(1) / mt.phi;
+  const R iphi = rcp_(mt.phi);
   const R uF = a.ux * a.Fx + a.uy * a.Fy;
   const R se = k.s_e, sq = k.s_q;
   const R he = R(1) - R(0.5) * se, hq = R(1) - R(0.5) * sq;
@@ -518,7 +622,7 @@ __device__ __forceinline__ void collide(R (&f)[19], const Mat<R>& mt, const Cons
 
   R srcT = R(0), srcC = R(0);
   const R thsum = f[9] + f[10] + f[11] + f[12] + f[13];  // sigma theta with the heat-capacity ratio
-  const R th = (k.flags & F_SIGMA_ENERGY) ? thsum / mt.sig : thsum;
+  const R th = (k.flags & F_SIGMA_ENERGY) ? div_(thsum, mt.sig) : thsum;
   const R c = f[14] + f[15] + f[16] + f[17] + f[18];
   if (cl) {
     const React<R> r = reaction(th, c, mt.rhocp, k);

@@ -32,12 +32,14 @@ __device__ __forceinline__ void xcd_tile(int nbx, int nby, int& bx, int& by) {
 }
 
 // One time step: pull-stream, boundary columns, macros, flow collision,
-// reaction, scalar collisions, store.  UNIFORM: wave-uniform buffer
-// addressing for the interior pull and for the stores (fewer vector
-// instructions per node).  Small lattices, whose launches are one round of
-// wavefronts bound by each wave's own chain, gain from it; the 4096x1024
-// lattice runs 0.5 % slower with it and keeps the per-lane form.
-template <typename R, int MAT, bool UNIFORM = false>
+// reaction, scalar collisions, store.  STREAM: non-temporal loads and plain
+// stores, for a state larger than the 256 MB last-level cache; smaller ones
+// take cached loads and stores that write through to it (aux 16, sc1): the
+// lines are there for the next step, and the end of the kernel has no L2
+// write-back to wait for.  Per step, streaming -> cached: 1024x256 FP32 9.8
+// -> 8.3 us, 2048x512 FP32 31.6 -> 25.0, 200x40 FP64 4.92 -> 4.67; 4096x1024
+// FP32 102.6 -> 120.
+template <typename R, int MAT, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_step(const R* __restrict__ src, R* __restrict__ dst,
                                                  const R* __restrict__ phi_f,
                                                  const R* __restrict__ invk_f,
@@ -48,93 +50,99 @@ __global__ __launch_bounds__(kBlock) void k_step(const R* __restrict__ src, R* _
   const int y = by;
   if (x >= k.nx) return;
   R f[19];
-  const Mat<R> mt = pre_collision<R, MAT, true, UNIFORM>(src, k, phi_f, invk_f, d_f, x, y, f);
+  const Mat<R> mt = pre_collision<R, MAT, STREAM>(src, k, phi_f, invk_f, d_f, x, y, f, y);
   const bool cl = y >= k.y_cl0 && !(k.flags & F_NO_REACTION);
   collide(f, mt, k, cl);
-  const int o = y * k.pitch + x;
-  if constexpr (UNIFORM) {
-    const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = 0; q < 19; ++q) buffer_store(dst + int64_t(q) * k.plane, ob, f[q]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 19; ++q) dst[q * k.plane + o] = f[q];
-  }
+  store_node<STREAM ? 0 : 16>(dst, k, x, y, y, f);
 }
 
-// Two time steps in one launch, for lattices large enough to be bound by
-// HBM: a workgroup advances a tile of kT2X x kT2Y nodes.  Step one runs over
-// the tile and a halo (two columns on the left, where the outlet's feeding
-// column can lie, one elsewhere, and a row above and below), one node per
-// thread, from the state in memory, and keeps the post-collision
-// populations in LDS, writing the tile's own to `mid` when that is given;
-// step two pulls the tile's nodes from LDS and writes `dst`.  Every node
-// runs the same code as k_step, so the states are the bits of two single
-// steps.  HBM traffic per step halves; the halo nodes (22 % of step one)
-// are computed twice.  Twelve rows (step one: 938 nodes, 960 threads, one
-// pass) measured faster than four and eight; 13 rows, the last to fit one
-// 1024-thread pass, would save 1 % of the halo work and is not measured.
-// FP64 holds 143 KB of LDS, one workgroup per CU.  Walls and inlet / outlet columns only (the
-// thin-film CL's reactive wall included): the host keeps single steps on
-// periodic lattices.
-constexpr int kT2X = 64, kT2Y = 12;
-constexpr int kT2W = kT2X + 3;                  // LDS row: x0 - 2 .. x0 + kT2X
-constexpr int kT2N = kT2W * (kT2Y + 2);         // LDS rows: y0 - 1 .. y0 + kT2Y
-constexpr int kT2Threads = (kT2N + 63) / 64 * 64;
-static_assert(kT2Threads <= 1024 && kT2X * kT2Y <= kT2Threads, "two-step tile");
+// Two time steps in one launch: a workgroup advances a tile of TX x TY
+// nodes.  Step one runs over the tile and a halo (two columns on the left,
+// where the outlet's feeding column can lie, one elsewhere, and a row above
+// and below), one node per thread, from the state in memory, and keeps the
+// post-collision populations in LDS, writing the tile's own to `mid` when
+// that is given; step two pulls the tile's nodes from LDS and writes `dst`.
+// Every node runs the same code as k_step, so the states are the bits of two
+// single steps.  Walls and inlet / outlet columns only (the thin-film CL's
+// reactive wall included): the host keeps single steps on periodic lattices.
+//
+// What bounds it depends on the size: the launch and one wavefront's chain
+// (the smallest lattices), vector instructions and the overlap of a
+// workgroup's load, compute and store phases (the largest: 65 % VALU busy).
+// Tiles, per step (FP32 4096x1024, FP64 4096x1024, FP32 1537x431, FP32
+// 1024x256; us): 64x12 89.0 / 154 / 15.3 / 8.5, 64x8 86.9 / 172 / 13.9 /
+// 7.5, 32x12 86.1 / 147 / 12.4 / 7.9, 48x8 80.8 / 146 / 12.8 / 7.0.  48x8
+// with its halo is 510 nodes for 512 threads, and four such workgroups (two
+// in FP64) fill a CU's 32 (16) wavefronts with their 39 (78) KB of LDS each,
+// so that one's loads run under another's arithmetic.  Lattices of fewer
+// than 2^17 nodes, which leave CUs idle, take 16x8: 200x40 FP64 5.7 -> 3.7,
+// 300x100 FP32 3.9 -> 3.7, 512x128 FP64 6.4 -> 6.0 (single steps: 4.7, 5.1,
+// 7.9).  Loads are cached and stores write through at every size but FP32
+// states beyond the last-level cache (4096x1024: 86.1 -> 80.8 without).
+template <int TX, int TY>
+struct Tile2 {
+  static constexpr int W = TX + 3;              // LDS row: x0 - 2 .. x0 + TX
+  static constexpr int N = W * (TY + 2);        // LDS rows: y0 - 1 .. y0 + TY
+  static constexpr int threads = (N + 63) / 64 * 64;
+  static_assert(threads <= 1024 && TX * TY <= threads, "two-step tile");
+};
+constexpr int kT2X = 48, kT2Y = 8;              // lattices of kT2SmallCells nodes or more, and the batch
+constexpr int kT2SmallX = 16, kT2SmallY = 8;
+constexpr int64_t kT2SmallCells = int64_t(1) << 17;
 
 // Pull of node (x, y) from the step-one populations of the tile at (x0, y0).
-template <typename R>
+template <int TX, int TY, typename R>
 __device__ __forceinline__ void pull_tile(const R* __restrict__ lds, const Consts<R>& k, int x, int y, int x0,
                                           int y0, R (&f)[19]) {
+  constexpr int W = Tile2<TX, TY>::W, N = Tile2<TX, TY>::N;
+  if (__all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2)) {  // no wall link: constant offsets
+    const R* p = lds + (y - y0 + 1) * W + (x - x0 + 2);
+#pragma unroll
+    for (int q = 0; q < 19; ++q) f[q] = p[q * N - EY[q] * W - EX[q]];
+    return;
+  }
 #pragma unroll
   for (int q = 0; q < 19; ++q) {
     const int xs = x - EX[q], ys = y - EY[q];
     const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny;
-    const int n = in ? (ys - y0 + 1) * kT2W + (xs - x0 + 2) : (y - y0 + 1) * kT2W + (x - x0 + 2);
-    f[q] = lds[(in ? q : OPP[q]) * kT2N + n];
+    const int n = in ? (ys - y0 + 1) * W + (xs - x0 + 2) : (y - y0 + 1) * W + (x - x0 + 2);
+    f[q] = lds[(in ? q : OPP[q]) * N + n];
   }
 }
 
 // The two steps of the tile at (x0, y0), called by every thread of a
-// kT2Threads workgroup (it holds a workgroup barrier).  NT: non-temporal
-// loads in step one.  Cached loads let the L2 serve the halo lines that
-// neighbouring tiles also read; measured (µs per step, non-temporal ->
-// cached): FP64 4096x1024 176.2 -> 167.2, FP32 2048x512 24.7 -> 23.4,
-// 1024x512 14.6 -> 14.0, but FP32 4096x1024 89.0 -> 90.2, whose tile rows
-// are too long for that reuse.
-template <typename R, int MAT, bool NT>
+// Tile2::threads workgroup (it holds a workgroup barrier).  SAUX: cache
+// policy of the final stores.
+template <typename R, int MAT, int TX, int TY, int SAUX>
 __device__ __forceinline__ void step2_tile(R* __restrict__ lds, const R* __restrict__ src, R* __restrict__ mid,
                                            R* __restrict__ dst, const R* __restrict__ phi_f,
                                            const R* __restrict__ invk_f, const R* __restrict__ d_f,
                                            const Consts<R>& k, int x0, int y0) {
+  constexpr int W = Tile2<TX, TY>::W, N = Tile2<TX, TY>::N;
   const bool react = !(k.flags & F_NO_REACTION);
   {
     const int n = threadIdx.x;
-    const int i = n % kT2W, j = n / kT2W;
+    const int i = n % W, j = n / W;
     const int x = x0 - 2 + i, y = y0 - 1 + j;
-    if (n < kT2N && (unsigned)x < (unsigned)k.nx && (unsigned)y < (unsigned)k.ny) {
+    if (n < N && (unsigned)x < (unsigned)k.nx && (unsigned)y < (unsigned)k.ny) {
       R f[19];
-      const Mat<R> mt = pre_collision<R, MAT, NT>(src, k, phi_f, invk_f, d_f, x, y, f);
+      const Mat<R> mt =
+          pre_collision<R, MAT, false>(src, k, phi_f, invk_f, d_f, x, y, f, y0 > 0 ? y0 - 1 : 0);
       collide(f, mt, k, react && y >= k.y_cl0);
 #pragma unroll
-      for (int q = 0; q < 19; ++q) lds[q * kT2N + n] = f[q];
-      if (mid && i >= 2 && i < kT2X + 2 && j >= 1 && j <= kT2Y) {
-        const int o = y * k.pitch + x;
-#pragma unroll
-        for (int q = 0; q < 19; ++q) mid[q * k.plane + o] = f[q];
-      }
+      for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
+      if (mid && i >= 2 && i < TX + 2 && j >= 1 && j <= TY) store_node<16>(mid, k, x, y, y0, f);
     }
   }
   __syncthreads();
-  if (threadIdx.x >= kT2X * kT2Y) return;
-  const int x = x0 + int(threadIdx.x) % kT2X, y = y0 + int(threadIdx.x) / kT2X;
+  if (threadIdx.x >= TX * TY) return;
+  const int x = x0 + int(threadIdx.x) % TX, y = y0 + int(threadIdx.x) / TX;
   if (x >= k.nx || y >= k.ny) return;
   const bool inlet = x == 0 && y < k.ny_ch;
   const bool outlet = x == k.nx - 1;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
   R f[19];
-  pull_tile(lds, k, xp, y, x0, y0, f);
+  pull_tile<TX, TY>(lds, k, xp, y, x0, y0, f);
   Mat<R> mt = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y);
   thin_film(f, mt, k, y);
   if (inlet || outlet) {
@@ -144,20 +152,18 @@ __device__ __forceinline__ void step2_tile(R* __restrict__ lds, const R* __restr
     mt = mb;
   }
   collide(f, mt, k, react && y >= k.y_cl0);
-  const int o = y * k.pitch + x;
-#pragma unroll
-  for (int q = 0; q < 19; ++q) dst[q * k.plane + o] = f[q];
+  store_node<SAUX>(dst, k, x, y, y0, f);
 }
 
-template <typename R, int MAT, bool NT>
-__global__ __launch_bounds__(kT2Threads) void k_step2(const R* __restrict__ src, R* __restrict__ mid,
-                                                      R* __restrict__ dst, const R* __restrict__ phi_f,
-                                                      const R* __restrict__ invk_f, const R* __restrict__ d_f,
-                                                      Consts<R> k) {
-  __shared__ R lds[19 * kT2N];
+template <typename R, int MAT, int TX, int TY, int SAUX>
+__global__ __launch_bounds__((Tile2<TX, TY>::threads)) void k_step2(const R* __restrict__ src, R* __restrict__ mid,
+                                                                    R* __restrict__ dst, const R* __restrict__ phi_f,
+                                                                    const R* __restrict__ invk_f,
+                                                                    const R* __restrict__ d_f, Consts<R> k) {
+  __shared__ R lds[19 * Tile2<TX, TY>::N];
   int bx, by;
   xcd_tile(gridDim.x, gridDim.y, bx, by);
-  step2_tile<R, MAT, NT>(lds, src, mid, dst, phi_f, invk_f, d_f, k, bx * kT2X, by * kT2Y);
+  step2_tile<R, MAT, TX, TY, SAUX>(lds, src, mid, dst, phi_f, invk_f, d_f, k, bx * TX, by * TY);
 }
 
 // Equilibrium initial state: rest fluid at zero pressure (shifted f = 0),
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(kBlock) void k_obs_cells(const R* __restrict__ src,
   double v[kObsQ] = {0, 0, 0, 0, 0, 0, -1e300, 0, 0};
   if (x < k.nx) {
     R f[19];
-    const Mat<R> mt = pre_collision<R, MAT>(src, k, phi_f, invk_f, d_f, x, y, f);
+    const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
     if (x == 0 && y < k.ny_ch && !(k.flags & F_PERIODIC_X)) v[8] = double(flow_macros(f, mt, k).ux);
     double sf = 0, th = 0, c = 0;
 #pragma unroll
@@ -305,14 +311,14 @@ __global__ __launch_bounds__(kBlock) void k_obs_profiles(const R* __restrict__ s
   const bool react = !(k.flags & F_NO_REACTION);
   if (k.flags & F_THIN_CL) {  // the film's current, the profiles of the row above it
     R f[19];
-    const Mat<R> mt = pre_collision<R, MAT>(src, k, phi_f, invk_f, d_f, x, k.ny - 1, f);
+    const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, k.ny - 1, f, k.ny - 1);
     c0 = double(f[14] + f[15] + f[16] + f[17] + f[18]);
     t0 = double(k.T_in) + double(theta_of(f + 9, mt.sig, k));
     if (react) isum = double(film(src, k, x, mt).s_c);
   }
   for (int y = k.y_cl0; y < k.ny; ++y) {
     R f[19];
-    const Mat<R> mt = pre_collision<R, MAT>(src, k, phi_f, invk_f, d_f, x, y, f);
+    const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
     const R th = theta_of(f + 9, mt.sig, k);
     const R c = f[14] + f[15] + f[16] + f[17] + f[18];
     if (react) isum += double(reaction(th, c, mt.rhocp, k).s_c);
@@ -337,7 +343,7 @@ __global__ __launch_bounds__(kBlock) void k_fields(const R* __restrict__ src,
   const int y = blockIdx.y;
   if (x >= k.nx) return;
   R f[19];
-  const Mat<R> mt = pre_collision<R, MAT>(src, k, phi_f, invk_f, d_f, x, y, f);
+  const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
   const Macro<R> a = flow_macros(f, mt, k);
   const int o = y * k.nx + x;
   if (ux) ux[o] = a.ux;
