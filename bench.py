@@ -26,9 +26,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 BYTES_PER_LU_POPS = 19 * 4 * 2  # 19 FP32 populations read and written per lattice update
 BYTES_PER_LU_PHI = 4            # per-cell porosity read
-# The library advances lattices of at least this many nodes (with walls and
-# inlet / outlet columns: no periodic axis) two steps per launch (k_step2).
-TWO_STEP_MIN_CELLS = 1 << 19
+# The library advances lattices with walls and inlet / outlet columns (no
+# periodic axis) two steps per launch (k_step2).
+STEPS_PER_LAUNCH = 2
 # Committed rocprofv3 counter summaries (HBM bytes per launch) and the
 # sources of the kernel each one measured.
 COUNTERS = {
@@ -189,7 +189,7 @@ def bench_fp64(steps_large: int) -> dict:
         sim.step(20)
         wall, ev = _timed(sim.stream, lambda: sim.step(steps_large))
     cells = w["nx"] * w["ny"]
-    spl = 2 if cells >= TWO_STEP_MIN_CELLS else 1
+    spl = STEPS_PER_LAUNCH
     launches = steps_large // spl + steps_large % spl
     launch_s = ev / launches
     bpl = BYTES_PER_LU_FP64 + 8
@@ -462,7 +462,7 @@ def main():
     obs = sim.observables()
     cells = w["nx"] * w["ny"]
     mlups = cells * args.steps / (wall) / 1e6
-    spl = 2 if cells >= TWO_STEP_MIN_CELLS else 1  # steps per launch
+    spl = STEPS_PER_LAUNCH
     launches = args.steps // spl + args.steps % spl  # an odd count ends with one single step
     launch_s = ev_ms / 1e3 / launches
     bpu = BYTES_PER_LU_POPS + BYTES_PER_LU_PHI

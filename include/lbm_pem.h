@@ -213,7 +213,7 @@ lbm_status lbm_set_params(lbm_ctx* ctx, const lbm_params* p, const void* phi, co
 lbm_status lbm_init_equilibrium(lbm_ctx* ctx);
 
 /* Advance nsteps time steps (Eq. 1 and the scalar equation of Eq. 10 with
- * the CL source).  Lattices of 2^19 nodes or more without periodic axes
+ * the CL source).  Lattices without periodic axes
  * advance two steps per kernel launch (an odd count ends with a single
  * step); the states are bit-identical to single steps.
  * Async; never synchronizes. */
@@ -339,8 +339,8 @@ typedef struct lbm_schedule {
   int32_t block;           /* threads per workgroup of the per-step form: 0 or 256 (cells of a tile in a
                             * loop, or one per thread when the tile has 256), or 64 / 128 when the tile has
                             * exactly that many cells (one per thread); the persistent form uses 256.
-                            * 960 with 64 x 12 tiles and persistent = 0: two steps per launch (a tile and
-                            * its halo in LDS; an odd count ends with one step), for batches without
+                            * 960 with 64 x 12 tiles and persistent = 0: two steps per launch (tiles and
+                            * their halos in LDS, of the library's own shape; an odd count ends with one step), for batches without
                             * periodic axes */
 } lbm_schedule;
 

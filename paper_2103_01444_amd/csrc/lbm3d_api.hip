@@ -321,7 +321,7 @@ lbm_status observables3_t(lbm3d_ctx* c, lbm_obs* o) {
     hipLaunchKernelGGL((k3_obs_cells<R, MAT>), c->grid3(), dim3(kBlock3), 0, c->stream, src, m.phi, m.invk, m.d,
                        consts3<R>(c), c->partial());
   });
-  hipLaunchKernelGGL(lbm::k_obs_final<kObsQ3>, dim3(kObsQ3), dim3(lbm::kBlock), 0, c->stream, c->partial(),
+  hipLaunchKernelGGL(lbm::k_obs_final<kObsQ3>, dim3(kObsQ3), dim3(lbm::kFinal), 0, c->stream, c->partial(),
                      c->L.nblocks_obs, c->out());
   if (lbm_status s = check3(c, "observables"); s != LBM_OK) return s;
   double h[kObsQ3];

@@ -52,10 +52,9 @@ Layout make_layout(const lbm_geometry* g) {
   o += align_up(size_t(3) * L.plane * L.esize);
   L.off_partial = o;
   o += align_up(size_t(L.nblocks_obs) * kObsQ * sizeof(double));
-  L.off_prof = o;
-  o += align_up(size_t(3) * g->nx * sizeof(double));
-  L.off_out = o;
-  o += align_up(16 * sizeof(double));
+  L.off_out = o;  // the reduced values and the profiles behind them: one copy reads both
+  L.off_prof = o + 16 * sizeof(double);
+  o += align_up((16 + size_t(3) * g->nx) * sizeof(double));
   L.total = o;
   return L;
 }
@@ -77,6 +76,7 @@ struct lbm_ctx {
   Consts<double> kd{};
   Derived d;
   std::string err;
+  std::vector<double> host_obs;  // the observables' landing place
   // checkpointed forward run held for lbm_backward
   char* adj_ws = nullptr;
   int64_t adj_nsteps = 0;
@@ -239,8 +239,8 @@ void launch_init(lbm_ctx* c) {
 
 // Where the observable reduction keeps its intermediate results: the
 // per-workgroup partial sums (nblocks_obs x kObsQ), the reduced values
-// (kObsQ) and the three CL profiles (3 nx).  Every element is written
-// before it is read, so the buffers need no clearing.
+// (kObsQ) and, behind them, the three CL profiles (3 nx).  Every element is
+// written before it is read, so the buffers need no clearing.
 struct ObsBuffers {
   double* partial;
   double* out;
@@ -248,24 +248,25 @@ struct ObsBuffers {
 };
 
 template <typename R, int MAT>
-void launch_obs_mat(lbm_ctx* c, double i_scale, const ObsBuffers& b) {
+void launch_obs_mat(lbm_ctx* c, double i_scale, const ObsBuffers& b, bool profiles) {
   const MatPtrs<R> m = mat_ptrs<R>(c);
   const R* src = static_cast<const R*>(c->state(c->cur));
   const dim3 grid((c->g.nx + kBlock - 1) / kBlock, c->g.ny);
   hipLaunchKernelGGL((k_obs_cells<R, MAT>), grid, dim3(kBlock), 0, c->stream, src, m.phi, m.invk, m.d,
                      consts<R>(c), b.partial);
-  hipLaunchKernelGGL(k_obs_final<kObsQ>, dim3(kObsQ), dim3(kBlock), 0, c->stream, b.partial, c->L.nblocks_obs, b.out);
-  const dim3 pgrid((c->g.nx + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL((k_obs_profiles<R, MAT>), pgrid, dim3(kBlock), 0, c->stream, src, m.phi, m.invk, m.d,
+  hipLaunchKernelGGL(k_obs_final<kObsQ>, dim3(kObsQ), dim3(kFinal), 0, c->stream, b.partial, c->L.nblocks_obs, b.out);
+  if (!profiles) return;
+  const dim3 pgrid((c->g.nx + 63) / 64);
+  hipLaunchKernelGGL((k_obs_profiles<R, MAT>), pgrid, dim3(64 * kProfRows<R>), 0, c->stream, src, m.phi, m.invk, m.d,
                      consts<R>(c), i_scale, b.prof);
 }
 
 template <typename R>
-void launch_obs(lbm_ctx* c, double i_scale, const ObsBuffers& b) {
+void launch_obs(lbm_ctx* c, double i_scale, const ObsBuffers& b, bool profiles) {
   switch (c->mat) {
-    case MAT_LAYERED: launch_obs_mat<R, MAT_LAYERED>(c, i_scale, b); break;
-    case MAT_PHI: launch_obs_mat<R, MAT_PHI>(c, i_scale, b); break;
-    default: launch_obs_mat<R, MAT_FULL>(c, i_scale, b); break;
+    case MAT_LAYERED: launch_obs_mat<R, MAT_LAYERED>(c, i_scale, b, profiles); break;
+    case MAT_PHI: launch_obs_mat<R, MAT_PHI>(c, i_scale, b, profiles); break;
+    default: launch_obs_mat<R, MAT_FULL>(c, i_scale, b, profiles); break;
   }
 }
 
@@ -356,18 +357,22 @@ lbm_status observables_t(lbm_ctx* c, lbm_obs* o, double* pi, double* pc, double*
   const lbm_params& p = c->p;
   const double four_fc = 4.0 * p.faraday * p.C_ref;
   const double i_scale = four_fc / c->d.dt * c->d.dx;  // i(x) = sum_CL (4 F C_ref s_c / dt) dx
-  launch_obs<R>(c, i_scale, b);
+  const bool profiles = pi || pc || pT;
+  launch_obs<R>(c, i_scale, b, profiles);
   if (lbm_status s = check_launch(c, "observables"); s != LBM_OK) return s;
-  double h[kObsQ];
-  if (hipMemcpyAsync(h, b.out, sizeof(h), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+  const size_t nx = size_t(c->g.nx), behind = size_t(b.prof - b.out);
+  std::vector<double>& h = c->host_obs;
+  try {
+    h.resize(profiles ? behind + 3 * nx : kObsQ);
+  } catch (const std::bad_alloc&) {
+    return fail(c, LBM_ERR_DEVICE, "out of host memory");
+  }
+  if (hipMemcpyAsync(h.data(), b.out, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
     return fail(c, LBM_ERR_DEVICE, "observable copy failed");
-  const size_t nx = size_t(c->g.nx);
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(c, LBM_ERR_DEVICE, "observables sync failed");
   double* const dst[3] = {pi, pc, pT};
   for (int i = 0; i < 3; ++i)
-    if (dst[i] && hipMemcpyAsync(dst[i], b.prof + i * nx, nx * sizeof(double), hipMemcpyDeviceToHost,
-                                 c->stream) != hipSuccess)
-      return fail(c, LBM_ERR_DEVICE, "profile copy failed");
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(c, LBM_ERR_DEVICE, "observables sync failed");
+    if (dst[i]) std::memcpy(dst[i], h.data() + behind + i * nx, nx * sizeof(double));
   const double ncell = double(c->g.nx) * c->g.ny;
   lbm_obs r{};
   r.step = c->step;

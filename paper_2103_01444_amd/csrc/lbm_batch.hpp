@@ -65,6 +65,48 @@ __device__ __forceinline__ void batch_tile(R* __restrict__ pool, const BatchCase
   }
 }
 
+// Field pointers of a case (MAT_FULL) or none.
+template <typename R, int MAT>
+__device__ __forceinline__ const R* case_fields(const R* pool, const BatchCase<R>& c) {
+  return MAT == MAT_LAYERED ? nullptr : pool + c.off[0] + int64_t(kFieldRow) * c.k.plane;
+}
+
+// Initial state of every case: blockIdx.y the case, blockIdx.x its blocks of
+// kBlock nodes of a row (a grid as wide as the largest case's; one launch
+// for the batch instead of one per case).
+template <typename R, int MAT>
+__global__ __launch_bounds__(kBlock) void k_batch_init(R* __restrict__ pool, const BatchCase<R>* __restrict__ cases) {
+  const BatchCase<R>& c = cases[blockIdx.y];
+  const Consts<R> k = c.k;
+  const int nbx = (k.nx + kBlock - 1) / kBlock, y = blockIdx.x / nbx, bx = blockIdx.x - y * nbx;
+  if (y >= k.ny) return;
+  const R* f = case_fields<R, MAT>(pool, c);
+  init_node<R, MAT>(pool + c.off[0], f, f + k.plane, f + 2 * k.plane, k, bx * kBlock + int(threadIdx.x), y);
+}
+
+// Observable partials of every case, laid out and launched likewise:
+// partials of block b of case i at (i * gridDim.x + b) * kObsQ.
+template <typename R, int MAT>
+__global__ __launch_bounds__(kBlock) void k_batch_obs(const R* __restrict__ pool,
+                                                      const BatchCase<R>* __restrict__ cases, int parity,
+                                                      double* __restrict__ partial) {
+  const BatchCase<R>& c = cases[blockIdx.y];
+  const Consts<R> k = c.k;
+  const int nbx = (k.nx + kBlock - 1) / kBlock, y = blockIdx.x / nbx, bx = blockIdx.x - y * nbx;
+  if (y >= k.ny) return;  // the whole workgroup
+  const R* f = case_fields<R, MAT>(pool, c);
+  obs_cells<R, MAT>(pool + c.off[parity], f, f + k.plane, f + 2 * k.plane, k, bx, y,
+                    partial + (size_t(blockIdx.y) * gridDim.x + blockIdx.x) * kObsQ);
+}
+template <typename R>
+__global__ __launch_bounds__(kFinal) void k_batch_obs_final(const double* __restrict__ partial, int stride,
+                                                            const BatchCase<R>* __restrict__ cases,
+                                                            double* __restrict__ out) {
+  const Consts<R>& k = cases[blockIdx.y].k;
+  obs_final<kObsQ>(partial + size_t(blockIdx.y) * stride * kObsQ, (k.nx + kBlock - 1) / kBlock * k.ny, blockIdx.x,
+                   out + size_t(blockIdx.y) * kObsQ);
+}
+
 // Logical index of this workgroup such that each XCD (workgroups are dealt
 // to the 8 XCDs round-robin) owns a contiguous range of logical indices.
 __device__ __forceinline__ int xcd_logical(int flat, int total) {

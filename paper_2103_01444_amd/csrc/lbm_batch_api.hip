@@ -21,18 +21,20 @@ constexpr size_t kAlign = 256;
 // The schedule that asks for two steps per launch: its workgroup size and
 // tile shape name the form (the kernel's own tiles are kT2X x kT2Y).
 constexpr int kTwoStepBlock = 960, kTwoStepX = 64, kTwoStepY = 12;
+constexpr int kMaxGridY = 65535;
+constexpr int kObsCases = 256;  // cases per launch of the observables, at most (bounds their scratch)
 constexpr int kMinTileCells = 64;  // smallest tile the schedule accepts (sizes the tile table)
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct BatchLayout {
   std::vector<int64_t> state_off[2];  // element offsets per case
   int64_t pool_elems = 0;
-  size_t off_pool = 0, off_backup = 0, off_cases = 0, off_tiles = 0, off_partial = 0, off_prof = 0, off_out = 0;
+  size_t off_pool = 0, off_backup = 0, off_cases = 0, off_tiles = 0, off_partial = 0, off_out = 0;
   size_t off_sync = 0;  // the persistent kernel's barrier: its counts (256 B apart), then the failure flag
   size_t total = 0;
   int max_tiles = 0;
   int max_obs_blocks = 0;
-  int max_nx = 0;
+  int obs_cases = 0;  // cases one launch of the observables covers
   size_t esize = 4;
   int rows = 19;        // rows per lattice row of a state buffer: 19 populations (+ 3 field rows)
   bool fields = false;  // the cases carry per-cell fields (LBM_CELL_FIELDS)
@@ -67,7 +69,6 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
     L.max_tiles += std::max(int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells),
                             ((g[i].nx + kT2X - 1) / kT2X) * ((g[i].ny + kT2Y - 1) / kT2Y));
     L.max_obs_blocks = std::max(L.max_obs_blocks, ((g[i].nx + kBlock - 1) / kBlock) * g[i].ny);
-    L.max_nx = std::max(L.max_nx, g[i].nx);
   }
   L.pool_elems = e;
   size_t o = 0;
@@ -79,12 +80,11 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
   o += align_up(size_t(n) * (L.esize == 8 ? sizeof(BatchCase<double>) : sizeof(BatchCase<float>)));
   L.off_tiles = o;
   o += align_up(size_t(L.max_tiles) * sizeof(Tile));
+  L.obs_cases = std::min(n, kObsCases);
   L.off_partial = o;
-  o += align_up(size_t(L.max_obs_blocks) * kObsQ * sizeof(double));
-  L.off_prof = o;
-  o += align_up(size_t(3) * L.max_nx * sizeof(double));
+  o += align_up(size_t(L.obs_cases) * L.max_obs_blocks * kObsQ * sizeof(double));
   L.off_out = o;
-  o += align_up(16 * sizeof(double));
+  o += align_up(size_t(L.obs_cases) * kObsQ * sizeof(double));
   L.off_sync = o;
   o += align_up(size_t(kBarrierWords + 1) * 256);
   L.total = o;
@@ -124,7 +124,6 @@ struct lbm_batch {
   size_t state_elems(int i) const { return size_t(L.rows) * plane_elems(int64_t(pitch_of(g[i].nx)) * g[i].ny); }
   Tile* tiles() { return reinterpret_cast<Tile*>(ws + L.off_tiles); }
   double* partial() { return reinterpret_cast<double*>(ws + L.off_partial); }
-  double* prof() { return reinterpret_cast<double*>(ws + L.off_prof); }
   double* out() { return reinterpret_cast<double*>(ws + L.off_out); }
   unsigned int* barrier_count() { return reinterpret_cast<unsigned int*>(ws + L.off_sync); }
   int* barrier_failed() { return reinterpret_cast<int*>(ws + L.off_sync + size_t(kBarrierWords) * 256); }
@@ -390,18 +389,13 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
 
 template <typename R>
 lbm_status init_t(lbm_batch* b) {
-  for (int i = 0; i < b->n; ++i) {
-    const dim3 grid((b->g[i].nx + kBlock - 1) / kBlock, b->g[i].ny);
-    R* dst = b->pool<R>() + b->L.state_off[0][i];
-    if (b->L.fields) {
-      const R* f = b->field_rows<R>(i);
-      const int64_t L = pitch_of(b->g[i].nx);
-      hipLaunchKernelGGL((k_init<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, dst, f, f + L, f + 2 * L,
-                         bconsts<R>(b, i));
-    } else {
-      hipLaunchKernelGGL((k_init<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, dst, nullptr, nullptr, nullptr,
-                         bconsts<R>(b, i));
-    }
+  for (int i = 0; i < b->n; i += kMaxGridY) {
+    const dim3 grid(b->L.max_obs_blocks, std::min(b->n - i, kMaxGridY));
+    if (b->L.fields)
+      hipLaunchKernelGGL((k_batch_init<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(), b->cases<R>() + i);
+    else
+      hipLaunchKernelGGL((k_batch_init<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
+                         b->cases<R>() + i);
   }
   hipLaunchKernelGGL(k_clear_barrier, dim3(1), dim3(64), 0, b->stream, b->barrier_count(), b->barrier_failed(), 1);
   b->parity = 0;
@@ -410,29 +404,38 @@ lbm_status init_t(lbm_batch* b) {
   return e == hipSuccess ? LBM_OK : bfail(b, LBM_ERR_DEVICE, std::string("batch init: ") + hipGetErrorString(e));
 }
 
+// Observables of every case: one reduction over all of them (in groups of
+// kObsCases), one copy and one wait, where a launch, a copy and a wait per
+// case took 45 us each (48 cases: 2.0 ms, now 0.1).
 template <typename R>
 lbm_status observables_t(lbm_batch* b, lbm_obs* out) {
-  if (lbm_status st = barrier_status(b); st != LBM_OK) return st;
+  std::vector<double> host;
+  try {
+    host.resize(size_t(b->n) * kObsQ);
+  } catch (const std::bad_alloc&) {
+    return bfail(b, LBM_ERR_DEVICE, "out of host memory");
+  }
+  for (int i0 = 0; i0 < b->n; i0 += b->L.obs_cases) {
+    const int n = std::min(b->n - i0, b->L.obs_cases);
+    const dim3 grid(b->L.max_obs_blocks, n);
+    if (b->L.fields)
+      hipLaunchKernelGGL((k_batch_obs<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
+                         b->cases<R>() + i0, b->parity, b->partial());
+    else
+      hipLaunchKernelGGL((k_batch_obs<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
+                         b->cases<R>() + i0, b->parity, b->partial());
+    hipLaunchKernelGGL((k_batch_obs_final<R>), dim3(kObsQ, n), dim3(kFinal), 0, b->stream, b->partial(),
+                       b->L.max_obs_blocks, b->cases<R>() + i0, b->out());
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(host.data() + size_t(i0) * kObsQ, b->out(), size_t(n) * kObsQ * sizeof(double),
+                       hipMemcpyDeviceToHost, b->stream) != hipSuccess)
+      return bfail(b, LBM_ERR_DEVICE, "batch observables failed");
+  }
+  if (lbm_status st = barrier_status(b); st != LBM_OK) return st;  // waits for the copies
   for (int i = 0; i < b->n; ++i) {
     const lbm_geometry& g = b->g[i];
     const lbm_params& p = b->p[i];
-    const Consts<R>& k = bconsts<R>(b, i);
-    const R* src = b->pool<R>() + b->L.state_off[b->parity][i];
-    const dim3 grid((g.nx + kBlock - 1) / kBlock, g.ny);
-    if (b->L.fields) {
-      const R* f = b->field_rows<R>(i);
-      hipLaunchKernelGGL((k_obs_cells<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, src, f, f + k.plane,
-                         f + 2 * k.plane, k, b->partial());
-    } else {
-      hipLaunchKernelGGL((k_obs_cells<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, src, nullptr, nullptr,
-                         nullptr, k, b->partial());
-    }
-    hipLaunchKernelGGL(k_obs_final<kObsQ>, dim3(kObsQ), dim3(kBlock), 0, b->stream, b->partial(),
-                       int(grid.x * grid.y), b->out());
-    double h[kObsQ];
-    if (hipMemcpyAsync(h, b->out(), sizeof(h), hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
-        hipStreamSynchronize(b->stream) != hipSuccess)
-      return bfail(b, LBM_ERR_DEVICE, "batch observables failed");
+    const double* h = host.data() + size_t(i) * kObsQ;
     const double i_scale = 4.0 * p.faraday * p.C_ref / b->d[i].dt * b->d[i].dx;
     lbm_obs r{};
     r.step = b->step;

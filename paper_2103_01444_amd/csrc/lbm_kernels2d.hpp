@@ -169,11 +169,9 @@ __global__ __launch_bounds__((Tile2<TX, TY>::threads)) void k_step2(const R* __r
 // Equilibrium initial state: rest fluid at zero pressure (shifted f = 0),
 // theta = 0, O2 at c_in.
 template <typename R, int MAT>
-__global__ __launch_bounds__(kBlock) void k_init(R* __restrict__ dst, const R* __restrict__ phi_f,
-                                                 const R* __restrict__ invk_f,
-                                                 const R* __restrict__ d_f, Consts<R> k) {
-  const int x = blockIdx.x * kBlock + threadIdx.x;
-  const int y = blockIdx.y;
+__device__ __forceinline__ void init_node(R* __restrict__ dst, const R* __restrict__ phi_f,
+                                          const R* __restrict__ invk_f, const R* __restrict__ d_f,
+                                          const Consts<R>& k, int x, int y) {
   if (x >= k.nx) return;
   const Mat<R> mt = material<R, MAT>(k, phi_f, invk_f, d_f, x, y);
   R g[5] = {R(0), R(0), R(0), R(0), R(0)};
@@ -183,6 +181,12 @@ __global__ __launch_bounds__(kBlock) void k_init(R* __restrict__ dst, const R* _
   for (int q = 0; q < 14; ++q) dst[q * k.plane + o] = R(0);
 #pragma unroll
   for (int q = 0; q < 5; ++q) dst[(14 + q) * k.plane + o] = g[q];
+}
+template <typename R, int MAT>
+__global__ __launch_bounds__(kBlock) void k_init(R* __restrict__ dst, const R* __restrict__ phi_f,
+                                                 const R* __restrict__ invk_f,
+                                                 const R* __restrict__ d_f, Consts<R> k) {
+  init_node<R, MAT>(dst, phi_f, invk_f, d_f, k, blockIdx.x * kBlock + threadIdx.x, blockIdx.y);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -212,13 +216,10 @@ __device__ __forceinline__ React<R> film(const R* __restrict__ src, const Consts
 }
 
 template <typename R, int MAT>
-__global__ __launch_bounds__(kBlock) void k_obs_cells(const R* __restrict__ src,
-                                                      const R* __restrict__ phi_f,
-                                                      const R* __restrict__ invk_f,
-                                                      const R* __restrict__ d_f, Consts<R> k,
-                                                      double* __restrict__ partial) {
-  const int x = blockIdx.x * kBlock + threadIdx.x;
-  const int y = blockIdx.y;
+__device__ __forceinline__ void obs_cells(const R* __restrict__ src, const R* __restrict__ phi_f,
+                                          const R* __restrict__ invk_f, const R* __restrict__ d_f,
+                                          const Consts<R>& k, int bx, int y, double* __restrict__ partial) {
+  const int x = bx * kBlock + threadIdx.x;
   double v[kObsQ] = {0, 0, 0, 0, 0, 0, -1e300, 0, 0};
   if (x < k.nx) {
     R f[19];
@@ -264,69 +265,96 @@ __global__ __launch_bounds__(kBlock) void k_obs_cells(const R* __restrict__ src,
     const int i = threadIdx.x;
     double s = red[i][0];
     for (int w = 1; w < kBlock / 64; ++w) s = i == 6 ? fmax(s, red[i][w]) : s + red[i][w];
-    partial[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * kObsQ + i] = s;
+    partial[i] = s;
   }
 }
 
-// Sum the per-workgroup partials in a fixed order: workgroup i reduces
-// quantity i; thread t sums the contiguous chunk t of the partials, then a
-// fixed tree combines the chunks.
-template <int Q = kObsQ>  // a template so that every translation unit may instantiate it
-__global__ __launch_bounds__(kBlock) void k_obs_final(const double* __restrict__ partial, int nblocks,
-                                                      double* __restrict__ out) {
-  const int i = blockIdx.x;
+template <typename R, int MAT>
+__global__ __launch_bounds__(kBlock) void k_obs_cells(const R* __restrict__ src, const R* __restrict__ phi_f,
+                                                      const R* __restrict__ invk_f, const R* __restrict__ d_f,
+                                                      Consts<R> k, double* __restrict__ partial) {
+  obs_cells<R, MAT>(src, phi_f, invk_f, d_f, k, blockIdx.x, blockIdx.y,
+                    partial + size_t(blockIdx.y * gridDim.x + blockIdx.x) * kObsQ);
+}
+
+// Sum quantity i of the per-workgroup partials in a fixed order: thread t
+// takes every kFinal-th from t on, then a fixed tree combines the threads.
+// (With 256 threads that each walked a contiguous chunk, the 16384 partials
+// of a 4096x1024 lattice took 24 us: one chain of dependent, uncoalesced
+// loads per thread.)
+constexpr int kFinal = 1024;
+template <int Q>
+__device__ __forceinline__ void obs_final(const double* __restrict__ partial, int nblocks, int i,
+                                          double* __restrict__ out) {
   const bool is_max = i == 6;
-  const int per = (nblocks + kBlock - 1) / kBlock;
-  const int b0 = threadIdx.x * per;
-  const int b1 = b0 + per < nblocks ? b0 + per : nblocks;
   double s = is_max ? -1e300 : 0.0;
-  for (int b = b0; b < b1; ++b) {
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nblocks; b += kFinal) {
     const double v = partial[(size_t)b * Q + i];
     s = is_max ? fmax(s, v) : s + v;
   }
-  __shared__ double red[kBlock];
-  red[threadIdx.x] = s;
+  s = is_max ? wave_max(s) : wave_sum(s);
+  __shared__ double red[kFinal / 64];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      const double o = red[threadIdx.x + w];
-      red[threadIdx.x] = is_max ? fmax(red[threadIdx.x], o) : red[threadIdx.x] + o;
-    }
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kFinal / 64; ++w) s = is_max ? fmax(s, red[w]) : s + red[w];
+    out[i] = s;
   }
-  if (threadIdx.x == 0) out[i] = red[0];
+}
+
+template <int Q = kObsQ>  // a template so that every translation unit may instantiate it
+__global__ __launch_bounds__(kFinal) void k_obs_final(const double* __restrict__ partial, int nblocks,
+                                                      double* __restrict__ out) {
+  obs_final<Q>(partial, nblocks, blockIdx.x, out);
 }
 
 // Per-column CL profiles: i(x) = sum over CL rows of 4 F C_ref s_c / dt * dx,
-// and c, T on the CL row next to the GDL.
+// and c, T on the CL row next to the GDL.  A workgroup takes 64 columns, a
+// wavefront one CL row at a time; the rows' reactions meet in LDS and are
+// added in the order of the rows.  (One thread per column walked the 51 rows
+// of a 4096x1024 lattice one after the other, 16 workgroups in all: 150 us in
+// FP32, now 16.)  Eight wavefronts in FP64, whose 1024-thread form spills.
+template <typename R>
+constexpr int kProfRows = sizeof(R) == 8 ? 8 : 16;
 template <typename R, int MAT>
-__global__ __launch_bounds__(kBlock) void k_obs_profiles(const R* __restrict__ src,
-                                                         const R* __restrict__ phi_f,
-                                                         const R* __restrict__ invk_f,
-                                                         const R* __restrict__ d_f, Consts<R> k,
-                                                         double i_scale, double* __restrict__ prof) {
-  const int x = blockIdx.x * kBlock + threadIdx.x;
-  if (x >= k.nx) return;
-  double isum = 0, c0 = 0, t0 = 0;
+__global__ __launch_bounds__(64 * kProfRows<R>) void k_obs_profiles(const R* __restrict__ src,
+                                                                 const R* __restrict__ phi_f,
+                                                                 const R* __restrict__ invk_f,
+                                                                 const R* __restrict__ d_f, Consts<R> k,
+                                                                 double i_scale, double* __restrict__ prof) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int x = blockIdx.x * 64 + lane;
   const bool react = !(k.flags & F_NO_REACTION);
-  if (k.flags & F_THIN_CL) {  // the film's current, the profiles of the row above it
+  constexpr int rows = kProfRows<R>;
+  __shared__ double part[rows][64];
+  double isum = 0, c0 = 0, t0 = 0;
+  if ((k.flags & F_THIN_CL) && w == 0 && x < k.nx) {  // the film's current, the profiles of the row above it
     R f[19];
     const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, k.ny - 1, f, k.ny - 1);
     c0 = double(f[14] + f[15] + f[16] + f[17] + f[18]);
     t0 = double(k.T_in) + double(theta_of(f + 9, mt.sig, k));
     if (react) isum = double(film(src, k, x, mt).s_c);
   }
-  for (int y = k.y_cl0; y < k.ny; ++y) {
-    R f[19];
-    const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
-    const R th = theta_of(f + 9, mt.sig, k);
-    const R c = f[14] + f[15] + f[16] + f[17] + f[18];
-    if (react) isum += double(reaction(th, c, mt.rhocp, k).s_c);
-    if (y == k.y_cl0) {
-      c0 = double(c);
-      t0 = double(k.T_in) + double(th);
+  for (int y0 = k.y_cl0; y0 < k.ny; y0 += rows) {
+    const int y = y0 + w;
+    if (y < k.ny && x < k.nx) {
+      R f[19];
+      const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
+      const R th = theta_of(f + 9, mt.sig, k);
+      const R c = f[14] + f[15] + f[16] + f[17] + f[18];
+      part[w][lane] = react ? double(reaction(th, c, mt.rhocp, k).s_c) : 0.0;
+      if (y == k.y_cl0) {  // wavefront 0
+        c0 = double(c);
+        t0 = double(k.T_in) + double(th);
+      }
     }
+    __syncthreads();
+    if (w == 0)
+      for (int r = 0; r < rows && y0 + r < k.ny; ++r) isum += part[r][lane];
+    __syncthreads();
   }
+  if (w != 0 || x >= k.nx) return;
   prof[x] = isum * i_scale;
   prof[k.nx + x] = c0;
   prof[2 * k.nx + x] = t0;
