@@ -11,353 +11,333 @@
 #pragma once
 
 #include "lbm3d_device.hpp"
-#include "lbm_adjoint.hpp"  // reaction_tape, ReactAdj
+#include "lbm_adjoint.hpp"  // reaction_tape, ReactAdj, the primitives
 
 namespace lbm3 {
 
+using lbm::fast_rcp;
+using lbm::fast_sqrt;
+using lbm::fma_;
 using lbm::ReactAdj;
 using lbm::reaction_tape;
 
-template <typename R>
-struct MatAdj3 {
-  R phi = R(0), invk = R(0), sqk = R(0), fphi = R(0), l0 = R(0), l1 = R(0), aT = R(0), aC = R(0), rhocp = R(0);
-};
-
 constexpr double kSqrt3 = 1.7320508075688772935;
 
-// Chain the adjoints of the derived material quantities to (phi, 1/K, D).
+// Adjoints of the medium's quantities as the forward step uses them
+// (dl = phi nu / K).
 template <typename R>
-__device__ __forceinline__ void material_adj(const Consts3<R>& k, const Mat3<R>& m, const MatAdj3<R>& a, R& g_phi,
+struct MatAdj3 {
+  R phi = R(0), dl = R(0), l0 = R(0), l1 = R(0), aT = R(0), aC = R(0), rhocp = R(0);
+};
+
+// The forward step's material with what the reverse step takes of it.
+template <typename R>
+struct AdjMat3 : Mat3<R> {
+  R iphi, dl, irc;
+};
+template <typename R>
+__device__ __forceinline__ AdjMat3<R> adj_material(const Consts3<R>& k, const R* __restrict__ phi_f,
+                                                   const R* __restrict__ invk_f, const R* __restrict__ d_f, int x,
+                                                   int y, int z) {
+  AdjMat3<R> m;
+  static_cast<Mat3<R>&>(m) = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, x, y, z);
+  m.iphi = fast_rcp(m.phi);
+  m.dl = m.phi * k.nu * m.invk;
+  m.irc = fast_rcp(m.rhocp);
+  return m;
+}
+
+// Chain the adjoints of the derived material quantities to (phi, 1/K, D), as
+// in 2D.
+template <typename R>
+__device__ __forceinline__ void material_adj(const Consts3<R>& k, const AdjMat3<R>& m, const MatAdj3<R>& a, R& g_phi,
                                              R& g_invk, R& g_d) {
-  const R phi = m.phi;
-  const R iphi = R(1) / phi, irc = R(1) / m.rhocp;
-  R lphi = a.phi, linvk = a.invk, lsqk = a.sqk, lfphi = a.fphi;
-  lphi += a.l1 * m.fphi * m.sqk * R(0.5);  // l1 = phi fphi sqk / 2
-  lfphi += a.l1 * phi * m.sqk * R(0.5);
-  lsqk += a.l1 * phi * m.fphi * R(0.5);
-  lphi += a.l0 * k.nu * m.invk * R(0.25);  // l0 = 1/2 + phi nu invk / 4
-  linvk += a.l0 * phi * k.nu * R(0.25);
-  lphi += lfphi * R(-1.5) * m.fphi * iphi;  // fphi = 0.143 phi^-1.5
-  if (m.sqk > R(0)) linvk += lsqk * R(0.5) / m.sqk;  // 0 at invk = 0
-  // aT = sqrt3 alpha, alpha = (k_f phi + k_s (1 - phi)) scale / rhocp (Eq. 19)
-  const R alpha = (k.k_f * phi + k.k_s * (R(1) - phi)) * k.alpha_scale * irc;
-  const R drc = k.rhocp_f - k.rhocp_s;
-  const R lalpha = a.aT * R(kSqrt3);
-  lphi += lalpha * ((k.k_f - k.k_s) * k.alpha_scale - alpha * drc) * irc;
-  lphi += a.rhocp * drc;
-  g_phi += lphi;
+  const R ldl = fma_(R(0.25), a.l0, a.dl);
+  R linvk = m.phi * k.nu * ldl;
+  if (m.invk > R(0)) linvk += R(0.5) * a.l1 * m.l1 / m.invk;  // 0 at 1/K = 0
+  const R drc = k.rhocp_f - k.rhocp_s, dk = k.aT_f - k.aT_s;
+  g_phi += a.phi + k.nu * m.invk * ldl - R(0.5) * a.l1 * m.l1 * m.iphi + a.aT * (dk - m.aT * drc) * m.irc +
+           a.rhocp * drc;
   g_invk += linvk;
   g_d += a.aC * R(kSqrt3);  // aC = sqrt3 D
 }
 
-// Forward intermediates of the flow macros, with the reciprocals the
-// adjoint divides by (each taken once per node).
+template <typename R>
+struct Vec3 {
+  R x = R(0), y = R(0), z = R(0);
+};
+template <typename R>
+__device__ __forceinline__ R dot(const Vec3<R>& a, const Vec3<R>& b) {
+  return fma_(a.x, b.x, fma_(a.y, b.y, a.z * b.z));
+}
+template <typename R>
+__device__ __forceinline__ Vec3<R> axpy(R s, const Vec3<R>& a, const Vec3<R>& b) {
+  return {fma_(s, a.x, b.x), fma_(s, a.y, b.y), fma_(s, a.z, b.z)};
+}
+template <typename R>
+__device__ __forceinline__ Vec3<R> scale(R s, const Vec3<R>& a) {
+  return {s * a.x, s * a.y, s * a.z};
+}
+// e_i . a and b += s e_i for velocity i (components 0, 1, -1: additions only).
+template <typename R>
+__device__ __forceinline__ R along(int i, const Vec3<R>& a) {
+  R v = R(0);
+  if (EX[i]) v = EX[i] > 0 ? v + a.x : v - a.x;
+  if (EY[i]) v = EY[i] > 0 ? v + a.y : v - a.y;
+  if (EZ[i]) v = EZ[i] > 0 ? v + a.z : v - a.z;
+  return v;
+}
+template <typename R>
+__device__ __forceinline__ void add_along(int i, R s, Vec3<R>& b) {
+  if (EX[i]) b.x = EX[i] > 0 ? b.x + s : b.x - s;
+  if (EY[i]) b.y = EY[i] > 0 ? b.y + s : b.y - s;
+  if (EZ[i]) b.z = EZ[i] > 0 ? b.z + s : b.z - s;
+}
+
+// Forward intermediates of the flow macros kept for their adjoint; pp: phi p.
 template <typename R>
 struct MacroTape3 {
-  R vx, vy, vz, vm, r, den, ux, uy, uz, um, drag, s, p, Fx, Fy, Fz;
-  R iphi, iden, ir;  // 1 / phi, 1 / den, 1 / r
+  Vec3<R> v, u, F;
+  R vm, ir, iden, u2, drag, pp;
 };
 
 template <typename R>
-__device__ __forceinline__ MacroTape3<R> flow_macros_tape(const R (&f)[33], const Mat3<R>& m, const Consts3<R>& k) {
+__device__ __forceinline__ MacroTape3<R> flow_macros_tape(const R* f, const AdjMat3<R>& m, const Consts3<R>& k) {
   MacroTape3<R> t;
-  t.vx = t.vy = t.vz = t.s = R(0);
+  R s = R(0);
 #pragma unroll
-  for (int q = 1; q < 19; ++q) {
-    t.vx += R(EX[q]) * f[q];
-    t.vy += R(EY[q]) * f[q];
-    t.vz += R(EZ[q]) * f[q];
-    t.s += f[q];
+  for (int i = 1; i < 19; i += 2) {
+    add_along(i, f[i] - f[i + 1], t.v);
+    s += f[i] + f[i + 1];
   }
-  if (k.flags & F_BODY_FORCE) {
-    t.vx += R(0.5) * m.phi * k.ax;
-    t.vy += R(0.5) * m.phi * k.ay;
+  const bool body = k.flags & F_BODY_FORCE;
+  if (body) {
+    t.v.x += R(0.5) * m.phi * k.ax;
+    t.v.y += R(0.5) * m.phi * k.ay;
   }
-  t.vm = sqrt(t.vx * t.vx + t.vy * t.vy + t.vz * t.vz);
-  t.r = sqrt(m.l0 * m.l0 + m.l1 * t.vm);
-  t.den = m.l0 + t.r;
-  t.iden = R(1) / t.den;
-  t.ir = R(1) / t.r;
-  t.ux = t.vx * t.iden;
-  t.uy = t.vy * t.iden;
-  t.uz = t.vz * t.iden;
-  const R u2 = t.ux * t.ux + t.uy * t.uy + t.uz * t.uz;
-  t.um = sqrt(u2);
-  t.drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * t.um);
-  t.Fx = -t.drag * t.ux;
-  t.Fy = -t.drag * t.uy;
-  t.Fz = -t.drag * t.uz;
-  if (k.flags & F_BODY_FORCE) {
-    t.Fx += m.phi * k.ax;
-    t.Fy += m.phi * k.ay;
+  t.vm = fast_sqrt(dot(t.v, t.v));
+  const R r = fast_sqrt(fma_(m.l1, t.vm, m.l0 * m.l0));
+  t.ir = fast_rcp(r);
+  t.iden = fast_rcp(m.l0 + r);
+  t.u = scale(t.iden, t.v);
+  t.u2 = dot(t.u, t.u);
+  t.drag = fma_(R(2) * m.l1, t.vm * t.iden, m.dl);
+  t.F = scale(-t.drag, t.u);
+  if (body) {
+    t.F.x += m.phi * k.ax;
+    t.F.y += m.phi * k.ay;
   }
-  t.iphi = R(1) / m.phi;
-  t.p = (t.s - R(0.5) * u2 * t.iphi) * R(0.5) * t.iphi;
+  t.pp = fma_(R(0.5), s, R(-0.25) * (t.u2 * m.iphi));
   return t;
 }
 
-// Adjoint of flow_macros: from the adjoints of (u, p, F) add the adjoints of
-// the flow populations to lf[1..18] and of the material to ma.
+// Adjoint of v -> (u, F): the adjoint of v from those of u and F.
 template <typename R>
-__device__ __forceinline__ void flow_macros_adj(const MacroTape3<R>& t, const Mat3<R>& m, const Consts3<R>& k, R lux,
-                                                R luy, R luz, R lp, R lFx, R lFy, R lFz, R* lf, MatAdj3<R>& ma) {
-  const R iphi = t.iphi;
-  const R u2 = t.ux * t.ux + t.uy * t.uy + t.uz * t.uz;
-  // p = 0.5 s iphi - 0.25 u2 iphi^2
-  const R ls = R(0.5) * iphi * lp;
-  R lu2 = R(-0.25) * iphi * iphi * lp;
-  const R liphi = (R(0.5) * t.s - R(0.5) * u2 * iphi) * lp;
-  if (k.flags & F_BODY_FORCE) ma.phi += k.ax * lFx + k.ay * lFy;
-  const R ldrag = -(t.ux * lFx + t.uy * lFy + t.uz * lFz);
-  lux += -t.drag * lFx;
-  luy += -t.drag * lFy;
-  luz += -t.drag * lFz;
-  ma.phi += (k.nu * m.invk + m.fphi * m.sqk * t.um) * ldrag;
-  ma.invk += m.phi * k.nu * ldrag;
-  ma.fphi += m.phi * m.sqk * t.um * ldrag;
-  ma.sqk += m.phi * m.fphi * t.um * ldrag;
-  const R lum = m.phi * m.fphi * m.sqk * ldrag;
-  if (t.um > R(0)) lu2 += lum * R(0.5) / t.um;
-  lux += R(2) * t.ux * lu2;
-  luy += R(2) * t.uy * lu2;
-  luz += R(2) * t.uz * lu2;
-  ma.phi += -iphi * iphi * liphi;
-  R lvx = lux * t.iden, lvy = luy * t.iden, lvz = luz * t.iden;
-  const R lden = -(t.ux * lux + t.uy * luy + t.uz * luz) * t.iden;
+__device__ __forceinline__ Vec3<R> flow_macros_adj(const MacroTape3<R>& t, const AdjMat3<R>& m, const Consts3<R>& k,
+                                                   Vec3<R> lu, const Vec3<R>& lF, MatAdj3<R>& ma) {
+  const R um = t.vm * t.iden;
+  const R ldrag = -dot(t.u, lF);
+  lu = axpy(-t.drag, lF, lu);
+  ma.dl += ldrag;
+  ma.l1 = fma_(R(2) * um, ldrag, ma.l1);
+  const R lum = R(2) * m.l1 * ldrag;
+  const R lden = -t.iden * fma_(um, lum, dot(t.u, lu));
   const R ldr = lden * t.ir;
-  ma.l0 += lden + ldr * m.l0;
-  ma.l1 += ldr * t.vm * R(0.5);
-  const R lvm = ldr * m.l1 * R(0.5);
-  if (t.vm > R(0)) {
-    const R q = lvm / t.vm;
-    lvx += q * t.vx;
-    lvy += q * t.vy;
-    lvz += q * t.vz;
-  }
-  if (k.flags & F_BODY_FORCE) ma.phi += R(0.5) * (k.ax * lvx + k.ay * lvy);
-#pragma unroll
-  for (int q = 1; q < 19; ++q) lf[q] += R(EX[q]) * lvx + R(EY[q]) * lvy + R(EZ[q]) * lvz + ls;
+  ma.l0 += fma_(ldr, m.l0, lden);
+  ma.l1 = fma_(R(0.5) * t.vm, ldr, ma.l1);
+  const R lvm = fma_(R(0.5) * m.l1, ldr, lum * t.iden);
+  Vec3<R> lv = scale(t.iden, lu);
+  if (t.vm > R(0)) lv = axpy(lvm / t.vm, t.v, lv);  // a cell at rest: derivative of |v| taken as 0
+  if (k.flags & F_BODY_FORCE)
+    ma.phi += k.ax * fma_(R(0.5), lv.x, lF.x) + k.ay * fma_(R(0.5), lv.y, lF.y);
+  return lv;
 }
 
-// Adjoint of add_feq(p, u, phi, sgn, .) given L[0..18], the adjoint of its output.
+// Adjoint of the two scalar collisions and the CL source: g, la, mu hold the
+// temperature populations in 0..6 and O2's in 7..13 (as lbm::scalars_adj).
 template <typename R>
-__device__ __forceinline__ void feq_adj(R p, R ux, R uy, R uz, R phi, R sgn, const R* L, R& lp, R& lux, R& luy,
-                                        R& luz, R& lphi) {
-  const R iphi = R(1) / phi;
-  const R u2 = ux * ux + uy * uy + uz * uz;
-  R ap = R(-2) * phi * L[0];
-  R aphi = (R(-2) * p + R(0.5) * u2 * iphi * iphi) * L[0];
-  R au2 = R(-0.5) * iphi * L[0];
-  R ax = R(0), ay = R(0), az = R(0);
-#pragma unroll
-  for (int q = 1; q < 19; ++q) {
-    const R w = weight<R>(q);
-    const R eu = R(EX[q]) * ux + R(EY[q]) * uy + R(EZ[q]) * uz;
-    ap += R(3) * w * phi * L[q];
-    aphi += (R(3) * w * p - w * (R(4.5) * eu * eu - R(1.5) * u2) * iphi * iphi) * L[q];
-    au2 += R(-1.5) * w * iphi * L[q];
-    const R leu = w * (R(3) + R(9) * eu * iphi) * L[q];
-    ax += R(EX[q]) * leu;
-    ay += R(EY[q]) * leu;
-    az += R(EZ[q]) * leu;
-  }
-  lp += sgn * ap;
-  lphi += sgn * aphi;
-  lux += sgn * (ax + R(2) * ux * au2);
-  luy += sgn * (ay + R(2) * uy * au2);
-  luz += sgn * (az + R(2) * uz * au2);
-}
-
-// Adjoint of add_geq(X, u, a, sgn, .) given L[0..6].
-template <typename R>
-__device__ __forceinline__ void geq_adj(R X, R ux, R uy, R uz, R a, R sgn, const R* L, R& lX, R& lux, R& luy,
-                                        R& luz, R& la) {
-  R sX = (R(1) - R(6) * a) * L[0];
-  R sa = R(-6) * X * L[0];
-  R ax = R(0), ay = R(0), az = R(0);
-#pragma unroll
-  for (int q = 1; q < 7; ++q) {
-    const R eu = R(EX[19 + q]) * ux + R(EY[19 + q]) * uy + R(EZ[19 + q]) * uz;
-    sX += (a + R(0.5) * eu) * L[q];
-    sa += X * L[q];
-    const R leu = R(0.5) * X * L[q];
-    ax += R(EX[19 + q]) * leu;
-    ay += R(EY[19 + q]) * leu;
-    az += R(EZ[19 + q]) * leu;
-  }
-  lX += sgn * sX;
-  la += sgn * sa;
-  lux += sgn * ax;
-  luy += sgn * ay;
-  luz += sgn * az;
-}
-
-// Collision adjoint of one node.  In: pre-collision f, material, adjoint la
-// of the post-collision populations.  Out: adjoint mu of the pre-collision
-// populations; material adjoints accumulated in ma.
-template <typename R>
-__device__ __forceinline__ void collide_adj(const R (&f)[33], const Mat3<R>& mt, const Consts3<R>& k, bool cl,
-                                            const R (&la)[33], R (&mu)[33], MatAdj3<R>& ma) {
-  const MacroTape3<R> t = flow_macros_tape(f, mt, k);
-  R lux = R(0), luy = R(0), luz = R(0);
-#pragma unroll
-  for (int i = 0; i < 33; ++i) mu[i] = R(0);
-
-  // ---- scalars: two-rate D3Q7 collisions and the CL source ----
-  R th = R(0), c = R(0);
+__device__ __forceinline__ void scalars_adj(const R (&g)[14], const Vec3<R>& u, const AdjMat3<R>& mt,
+                                            const Consts3<R>& k, bool cl, const R (&la)[14], R (&mu)[14], Vec3<R>& lu,
+                                            MatAdj3<R>& ma) {
+  const R qp = R(0.9282032302755092), qm = R(1.2679491924311228);
+  const R kp = R(0.5) * (R(1) - qp), km = R(0.5) * (R(1) - qm), hm = R(0.5) * qm;
+  R X[2] = {R(0), R(0)};
 #pragma unroll
   for (int q = 0; q < 7; ++q) {
-    th += f[19 + q];
-    c += f[26 + q];
+    X[0] += g[q];
+    X[1] += g[7 + q];
   }
   ReactAdj<R> rx{};
-  if (cl) rx = reaction_tape(th, c, mt.rhocp, k);
-  const R srcT = cl ? rx.S_T : R(0), srcC = cl ? -rx.s_c : R(0);
-  const R qp = R(0.9282032302755092), qm = R(1.2679491924311228);
+  if (cl) rx = reaction_tape(X[0], X[1], mt.rhocp, k);
+  const R src[2] = {cl ? rx.S_T : R(0), cl ? -rx.s_c : R(0)};
   R lX[2], lsrc[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const R* a = la + 19 + 7 * s;
-    R* o = mu + 19 + 7 * s;
-    const R X = s == 0 ? th : c;
+    const R* a = la + 7 * s;
+    R* o = mu + 7 * s;
     const R aw = s == 0 ? mt.aT : mt.aC;
-    const R src = s == 0 ? srcT : srcC;
-    // The forward sets the rest population to X + src minus the six moving
-    // ones: its adjoint a[0] goes to X and src, and is taken off the moving.
-    o[0] = R(0);
-    R lx = a[0];
-    R law = R(0);
-    R ls = a[0];
+    R le = R(0), lo = R(0);
 #pragma unroll
-    for (int pr = 0; pr < 3; ++pr) {
-      const int i = 2 * pr + 1, j = i + 1;
-      const R eu = R(EX[19 + i]) * t.ux + R(EY[19 + i]) * t.uy + R(EZ[19 + i]) * t.uz;
+    for (int p = 0; p < 3; ++p) {
+      const int i = 2 * p + 1, j = i + 1;
       const R ai = a[i] - a[0], aj = a[j] - a[0];
       const R lnp = ai + aj, lnm = ai - aj;
-      o[i] = R(0.5) * (R(1) - qp) * lnp + R(0.5) * (R(1) - qm) * lnm;
-      o[j] = R(0.5) * (R(1) - qp) * lnp - R(0.5) * (R(1) - qm) * lnm;
-      lx += qp * aw * lnp + qm * R(0.5) * eu * lnm;
-      law += (qp * X + src) * lnp;
-      ls += aw * lnp;
-      const R leu = qm * R(0.5) * X * lnm;
-      lux += R(EX[19 + i]) * leu;
-      luy += R(EY[19 + i]) * leu;
-      luz += R(EZ[19 + i]) * leu;
+      le += lnp;
+      lo = fma_(along(19 + i, u), lnm, lo);
+      add_along(19 + i, hm * X[s] * lnm, lu);
+      o[i] = fma_(kp, lnp, km * lnm);
+      o[j] = fma_(kp, lnp, -km * lnm);
     }
-    lX[s] = lx;
-    lsrc[s] = ls;
+    const R law = le * fma_(qp, X[s], src[s]);
     if (s == 0) ma.aT += law; else ma.aC += law;
+    lX[s] = a[0] + fma_(qp * aw, le, hm * lo);
+    lsrc[s] = fma_(aw, le, a[0]);
   }
   if (cl) {  // src_T = S_T(theta, c, rhocp), src_C = -s_c(theta, c)
-    const R irc = R(1) / mt.rhocp;
-    const R lsc = -lsrc[1] + k.four_f_cref * rx.ehs * irc * lsrc[0];
-    ma.rhocp += -rx.S_T * irc * lsrc[0];
-    lX[1] += rx.dsc_dc * lsc;
-    lX[0] += rx.dsc_dth * lsc;
-    if (k.flags & lbm::F_PHYSICAL_HEAT) lX[0] += k.four_f_cref * rx.s_c * R(2) * k.U0_slope * irc * lsrc[0];
+    const R lsc = fma_(k.four_f_cref * rx.ehs * mt.irc, lsrc[0], -lsrc[1]);
+    ma.rhocp -= rx.S_T * mt.irc * lsrc[0];
+    lX[1] = fma_(rx.dsc_dc, lsc, lX[1]);
+    lX[0] = fma_(rx.dsc_dth, lsc, lX[0]);
+    if (k.flags & lbm::F_PHYSICAL_HEAT) lX[0] += k.four_f_cref * rx.s_c * R(2) * k.U0_slope * mt.irc * lsrc[0];
   }
 #pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    mu[19 + q] += lX[0];
-    mu[26 + q] += lX[1];
-  }
-
-  // ---- flow: two-rate D3Q19 collision with porous forcing ----
-  const R sp = k.s_plus, sm = k.s_minus;
-  const R hp = R(1) - R(0.5) * sp, hm = R(1) - R(0.5) * sm;
-  const R phi = mt.phi, iphi = t.iphi;
-  const R u2 = t.ux * t.ux + t.uy * t.uy + t.uz * t.uz;
-  const R uF = t.ux * t.Fx + t.uy * t.Fy + t.uz * t.Fz;
-  R lp = R(0), lu2 = R(0), luF = R(0), liphi = R(0);
-  R lFx = R(0), lFy = R(0), lFz = R(0);
-  {  // rest: f0* = (1 - sp) f0 + sp eq0 + hp F0, eq0 = -2 phi p - u2/(2 phi), F0 = -uF / phi
-    const R L0 = la[0];
-    mu[0] += (R(1) - sp) * L0;
-    const R le = sp * L0, lF = hp * L0;
-    lp += R(-2) * phi * le;
-    ma.phi += R(-2) * t.p * le;
-    lu2 += R(-0.5) * iphi * le;
-    liphi += R(-0.5) * u2 * le;
-    luF += -iphi * lF;
-    liphi += -uF * lF;
-  }
+  for (int s = 0; s < 2; ++s) {
+    R* o = mu + 7 * s;
+    o[0] = lX[s];
 #pragma unroll
-  for (int pr = 0; pr < 9; ++pr) {
-    const int i = 2 * pr + 1, j = i + 1;
-    const R w = weight<R>(i);
-    const R ex = R(EX[i]), ey = R(EY[i]), ez = R(EZ[i]);
-    const R eu = ex * t.ux + ey * t.uy + ez * t.uz;
-    const R eF = ex * t.Fx + ey * t.Fy + ez * t.Fz;
-    const R lnp = la[i] + la[j], lnm = la[i] - la[j];
-    mu[i] += R(0.5) * (R(1) - sp) * lnp + R(0.5) * (R(1) - sm) * lnm;
-    mu[j] += R(0.5) * (R(1) - sp) * lnp - R(0.5) * (R(1) - sm) * lnm;
-    const R leqe = sp * lnp, leqo = sm * lnm, lFe = hp * lnp, lFo = hm * lnm;
-    // eq_even = 3 w phi p + w (4.5 eu^2 - 1.5 u2) / phi; eq_odd = 3 w eu
-    lp += R(3) * w * phi * leqe;
-    ma.phi += R(3) * w * t.p * leqe;
-    R leu = R(9) * w * eu * iphi * leqe + R(3) * w * leqo;
-    lu2 += R(-1.5) * w * iphi * leqe;
-    liphi += w * (R(4.5) * eu * eu - R(1.5) * u2) * leqe;
-    // F_even = w (9 eu eF - 3 uF) / phi; F_odd = 3 w eF
-    leu += R(9) * w * eF * iphi * lFe;
-    const R leF = R(9) * w * eu * iphi * lFe + R(3) * w * lFo;
-    luF += R(-3) * w * iphi * lFe;
-    liphi += w * (R(9) * eu * eF - R(3) * uF) * lFe;
-    lux += ex * leu;
-    luy += ey * leu;
-    luz += ez * leu;
-    lFx += ex * leF;
-    lFy += ey * leF;
-    lFz += ez * leF;
+    for (int q = 1; q < 7; ++q) o[q] += lX[s];
   }
-  lux += t.Fx * luF + R(2) * t.ux * lu2;
-  luy += t.Fy * luF + R(2) * t.uy * lu2;
-  luz += t.Fz * luF + R(2) * t.uz * lu2;
-  lFx += t.ux * luF;
-  lFy += t.uy * luF;
-  lFz += t.uz * luF;
-  ma.phi += -iphi * iphi * liphi;
-  flow_macros_adj(t, mt, k, lux, luy, luz, lp, lFx, lFy, lFz, mu, ma);
 }
 
-// Adjoint of the boundary-column extrapolation of node b fed by node xp.
-// pre_xp: pulled populations of xp; mu_b: adjoint of the boundary node's
-// pre-collision populations.  Adds to mu_xp and to the material adjoints of
-// xp (maxp) and of b (mab).  ub: inlet velocity at b.
+// Adjoint of the flow collision of one node.  Per opposite pair the forward
+// step is (1 - s+) even + w (C + (e u)(e H)) and (1 - s-) odd + w (e G) with
+//   C = 3 s+ phi p - (1.5 s+ u^2 + 3 h+ u F) / phi,
+//   H = (4.5 s+ u + 9 h+ F) / phi,  G = 3 (s- u + h- F),  h = 1 - s / 2.
+// la: the post-collision adjoints, lu: the velocity's from the scalars.  A
+// value common to all of la passes to mu unchanged and drops out of the rest
+// (the equilibrium and force terms of a node sum to zero), so la[0] is taken
+// off before the weighted sums rather than left to cancel after them.
 template <typename R>
-__device__ __forceinline__ void boundary_adj(const R (&pre_xp)[33], const Mat3<R>& mxp, const Mat3<R>& mb,
-                                             const Consts3<R>& k, bool inlet, R ub, const R (&mu_b)[33],
-                                             R (&mu_xp)[33], MatAdj3<R>& maxp, MatAdj3<R>& mab) {
-  const MacroTape3<R> t = flow_macros_tape(pre_xp, mxp, k);
+__device__ __forceinline__ void flow_adj(const MacroTape3<R>& t, const AdjMat3<R>& mt, const Consts3<R>& k,
+                                         const R (&la)[19], Vec3<R> lu, R (&mu)[19], MatAdj3<R>& ma) {
+  const R sp = k.s_plus, sm = k.s_minus;
+  const R hp = R(1) - R(0.5) * sp, hm = R(1) - R(0.5) * sm;
+  const R iphi = mt.iphi;
+  const Vec3<R> H = scale(iphi, axpy(R(9) * hp, t.F, scale(R(4.5) * sp, t.u)));
+  // weights in units of 1/36 (2 for an axis pair, 1 for a diagonal one); 3 w
+  // is then rounded as the forward step rounds it, whose small gain of the
+  // conserved momentum per step belongs to the gradient
+  Vec3<R> lH, lG, lT;
+  R lC = R(0);
 #pragma unroll
-  for (int i = 0; i < 33; ++i) mu_xp[i] += mu_b[i];  // identity part (outlet scalars: a copy)
-  R lp1 = R(0), lux1 = R(0), luy1 = R(0), luz1 = R(0);
-  R d0 = R(0), d1 = R(0), d2 = R(0), d3 = R(0);
-  if (inlet) {  // + feq(p1, ub; phi_b)
-    feq_adj(t.p, ub, R(0), R(0), mb.phi, R(1), mu_b, lp1, d0, d1, d2, mab.phi);
-  } else {  // + feq(0, u1; phi_b)
-    feq_adj(R(0), t.ux, t.uy, t.uz, mb.phi, R(1), mu_b, d3, lux1, luy1, luz1, mab.phi);
+  for (int i = 1; i < 19; i += 2) {
+    R le = (la[i] - la[0]) + (la[i + 1] - la[0]), lo = la[i] - la[i + 1];
+    if (i < 7) {
+      le += le;
+      lo += lo;
+    }
+    lC += le;
+    add_along(i, le * along(i, H), lT);
+    add_along(i, le * along(i, t.u), lH);
+    add_along(i, lo, lG);
   }
-  feq_adj(t.p, t.ux, t.uy, t.uz, mxp.phi, R(-1), mu_b, lp1, lux1, luy1, luz1, maxp.phi);  // - feq(p1, u1; phi_xp)
+  const R c36 = R(1.0 / 36.0);
+  lu = axpy(c36, lT, lu);
+  lH = scale(c36, lH);
+  lG = scale(R(1.0 / 12.0), lG);  // three times the weighted sum
+  lC *= R(1.0 / 12.0);            // likewise
+  const R uF = dot(t.u, t.F);
+  const R lpp = sp * lC;
+  const R lw = -fma_(R(0.5) * sp, lC, R(0.25) * lpp);  // of u^2 / phi
+  const R lz = -hp * lC;                               // of (u F) / phi
+  ma.phi -= iphi * (dot(lH, H) + iphi * fma_(lw, t.u2, lz * uF));
+  Vec3<R> lF = axpy(R(9) * hp * iphi, lH, axpy(hm, lG, scale(lz * iphi, t.u)));
+  lu = axpy(R(4.5) * sp * iphi, lH, axpy(sm, lG, axpy(R(2) * lw * iphi, t.u, axpy(lz * iphi, t.F, lu))));
+  const Vec3<R> lv = flow_macros_adj(t, mt, k, lu, lF, ma);
+  const R lS = R(0.5) * lpp, ke = R(0.5) * (R(1) - sp), ko = R(0.5) * (R(1) - sm);
+  mu[0] = (R(1) - sp) * la[0];
+#pragma unroll
+  for (int i = 1; i < 19; i += 2) {
+    const R e = fma_(ke, la[i] + la[i + 1], lS), o = fma_(ko, la[i] - la[i + 1], along(i, lv));
+    mu[i] = e + o;
+    mu[i + 1] = e - o;
+  }
+}
+
+// Transposed extrapolation of the inlet's scalars from column 1 (as
+// lbm::inlet_scalars_adj): u, th1, c1 of column 1.
+template <typename R>
+__device__ __forceinline__ void inlet_scalars_adj(const R (&mu_b)[14], const Vec3<R>& u, R th1, R c1,
+                                                  const AdjMat3<R>& mxp, const Consts3<R>& k, Vec3<R>& lu, R& lth1,
+                                                  R& lc1, MatAdj3<R>& maxp, MatAdj3<R>& mab) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const R* m = mu_b + 7 * s;
+    const R X = s == 0 ? th1 : c1, aw = s == 0 ? mxp.aT : mxp.aC;
+    R sum = R(0);
+    Vec3<R> d;
+#pragma unroll
+    for (int i = 1; i < 7; i += 2) {
+      sum += m[i] + m[i + 1];
+      add_along(19 + i, R(0.5) * (m[i] - m[i + 1]), d);
+    }
+    const R la = fma_(R(-6), m[0], sum);
+    const R lX = -(fma_(aw, la, m[0]) + dot(u, d));
+    lu = axpy(-X, d, lu);
+    if (s == 0) {
+      maxp.aT = fma_(-X, la, maxp.aT);
+      lth1 = lX;
+    } else {
+      maxp.aC = fma_(-X, la, maxp.aC);
+      mab.aC = fma_(k.c_in, la, mab.aC);  // + geq(c_in, u_b; aC_b)
+      lc1 = lX;
+    }
+  }
+}
+
+// Flow part of the transposed extrapolation: adds to the adjoints of xp's
+// velocity and phi p and to the materials'.  inlet: velocity (ub, 0, 0) and
+// xp's pressure at b; else xp's velocity and zero pressure.
+template <typename R>
+__device__ __forceinline__ void boundary_flow_adj(const R (&m)[19], const Vec3<R>& u, R pp, bool inlet, R ub,
+                                                  R iphi_p, R phi_b, R iphi_b, Vec3<R>& lu, R& lpp, MatAdj3<R>& maxp,
+                                                  MatAdj3<R>& mab) {
+  R sum = R(0), xx = R(0), yy = R(0), zz = R(0), xy = R(0), xz = R(0), yz = R(0);
+  Vec3<R> d;
+#pragma unroll
+  for (int i = 1; i < 19; i += 2) {
+    const R w = weight<R>(i);
+    const R le = w * ((m[i] - m[0]) + (m[i + 1] - m[0]));  // a common value drops out, as in flow_adj
+    sum += le;
+    add_along(i, R(3) * w * (m[i] - m[i + 1]), d);
+    if (EX[i]) xx += le;
+    if (EY[i]) yy += le;
+    if (EZ[i]) zz += le;
+    if (EX[i] && EY[i]) xy = EX[i] * EY[i] > 0 ? xy + le : xy - le;
+    if (EX[i] && EZ[i]) xz = EX[i] * EZ[i] > 0 ? xz + le : xz - le;
+    if (EY[i] && EZ[i]) yz = EY[i] * EZ[i] > 0 ? yz + le : yz - le;
+  }
+  const R ldpp = R(3) * sum, lw = R(-1.5) * sum;
+  // gradient T u and value u T u of the quadratic part, T = 4.5 sum w l e e + lw
+  const R c = R(4.5);
+  auto T = [&](const Vec3<R>& a) {
+    return Vec3<R>{fma_(fma_(c, xx, lw), a.x, c * fma_(xy, a.y, xz * a.z)),
+                   fma_(fma_(c, yy, lw), a.y, c * fma_(xy, a.x, yz * a.z)),
+                   fma_(fma_(c, zz, lw), a.z, c * fma_(xz, a.x, yz * a.y))};
+  };
+  const Vec3<R> g = T(u);
+  const R e2 = dot(u, g);
+  lu = axpy(R(-2) * iphi_p, g, axpy(R(-1), d, lu));
+  maxp.phi = fma_(iphi_p * iphi_p, e2, maxp.phi);
+  lpp -= ldpp;
   if (inlet) {
-    R th1 = R(0), c1 = R(0);
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      th1 += pre_xp[19 + q];
-      c1 += pre_xp[26 + q];
-    }
-    R lth1 = R(0), lc1 = R(0), dX = R(0);
-    // + geq(0, ub; aT_b) is a constant; - geq(theta1, u1; aT_xp)
-    geq_adj(th1, t.ux, t.uy, t.uz, mxp.aT, R(-1), mu_b + 19, lth1, lux1, luy1, luz1, maxp.aT);
-    geq_adj(k.c_in, ub, R(0), R(0), mb.aC, R(1), mu_b + 26, dX, d0, d1, d2, mab.aC);  // + geq(c_in, ub; aC_b)
-    geq_adj(c1, t.ux, t.uy, t.uz, mxp.aC, R(-1), mu_b + 26, lc1, lux1, luy1, luz1, maxp.aC);
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      mu_xp[19 + q] += lth1;
-      mu_xp[26 + q] += lc1;
-    }
+    lpp = fma_(ldpp * iphi_p, phi_b, lpp);
+    maxp.phi -= ldpp * pp * phi_b * iphi_p * iphi_p;
+    mab.phi += ldpp * pp * iphi_p - iphi_b * iphi_b * ub * ub * fma_(c, xx, lw);
+  } else {
+    lu = axpy(R(2) * iphi_b, g, axpy(R(1), d, lu));
+    mab.phi -= iphi_b * iphi_b * e2;
   }
-  flow_macros_adj(t, mxp, k, lux1, luy1, luz1, lp1, R(0), R(0), R(0), mu_xp, maxp);
 }
 
 }  // namespace lbm3

@@ -6,283 +6,225 @@
 
 namespace lbm3 {
 
-// Adjoint of J = mean current density on the pre-collision populations: for
-// CL nodes w dJ/dc and w dJ/dtheta on every scalar population.
-template <typename R>
-__device__ __forceinline__ void seed_mu(const R (&pre)[33], const Mat3<R>& mt, const Consts3<R>& k, bool cl, R w,
-                                        R (&mu)[33]) {
+// Post-collision adjoints [Q0, Q1) of node (x, y, z), y and z the
+// wavefront's.
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void load_own(const R* __restrict__ lam, const Consts3<R>& k, int x, int y, int z,
+                                         R (&la)[Q1 - Q0]) {
+  const Planes3<R> b(lam, k, y, z);
 #pragma unroll
-  for (int i = 0; i < 33; ++i) mu[i] = R(0);
-  if (!cl) return;
-  R th = R(0), c = R(0);
-#pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    th += pre[19 + q];
-    c += pre[26 + q];
-  }
-  const ReactAdj<R> r = reaction_tape(th, c, mt.rhocp, k);
-#pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    mu[19 + q] = w * r.dsc_dth;
-    mu[26 + q] = w * r.dsc_dc;
-  }
-}
-
-// Shares of the boundary columns left for the next reverse step (open x).
-// The boundary pass of a step computes, for the column xp_s feeding each
-// boundary node (s = 0: column 1, inlet rows; s = 1: column nx - 2, every
-// row), the share of the adjoint of every element that column pulled, and
-// of the column's gradient.  The 33 shares of node (xp_s - 1 + dx, row) are
-// contiguous (padded to kPendQ) at pend[((s * nrows + row) * 3 + dx) *
-// kPendQ], so that a node near a boundary takes them in a few 16-byte
-// loads; the gradient shares c of row `row` at pend[kPendLam * nrows +
-// (s * nrows + row) * 4 + c].  Each element receives at most one share (a
-// link of the column either crosses a wall or it does not), so the
-// boundary pass writes them and every node adds its own when it loads its
-// adjoint in the next step; the last step's are added by an apply pass.
-// Slots that never receive a share hold zero.
-constexpr int kPendQ = 36;
-constexpr int kPendLam = 2 * 3 * kPendQ;
-constexpr int kPendVals = kPendLam + 2 * 4;
-
-__device__ __forceinline__ int pend_slot(int nrows, int s, int q, int dx, int row) {
-  return ((s * nrows + row) * 3 + dx) * kPendQ + q;
-}
-__device__ __forceinline__ int pend_grad(int nrows, int s, int c, int row) {
-  return kPendLam * nrows + (s * nrows + row) * 4 + c;
-}
-
-template <typename R>
-struct Vec16;  // 16 bytes of R
-template <>
-struct Vec16<float> {
-  using T = float __attribute__((ext_vector_type(4)));
-  static constexpr int n = 4;
-};
-template <>
-struct Vec16<double> {
-  using T = double __attribute__((ext_vector_type(2)));
-  static constexpr int n = 2;
-};
-
-// Add the shares of node (x, row) to the adjoint la it loaded (a node near
-// both ends when nx <= 5 takes both sides').
-template <typename R>
-__device__ __forceinline__ void add_pending(R (&la)[33], const Consts3<R>& k, const R* __restrict__ pend, int x,
-                                            int row) {
-  const int nrows = k.ny * k.nz;
-  constexpr int n = Vec16<R>::n;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int dx = x - (s == 0 ? 0 : k.nx - 3);
-    if ((unsigned)dx <= 2u) {
-      const auto* v = reinterpret_cast<const typename Vec16<R>::T*>(pend + pend_slot(nrows, s, 0, dx, row));
-#pragma unroll
-      for (int i = 0; i < (33 + n - 1) / n; ++i) {
-        const typename Vec16<R>::T w = v[i];
-#pragma unroll
-        for (int j = 0; j < n; ++j)
-          if (i * n + j < 33) la[i * n + j] += w[j];
-      }
-    }
-  }
-}
-
-// The gradient shares of the feeding column at node (x, row).
-template <typename R>
-__device__ __forceinline__ void add_pending_grad(R& g0, R& g1, R& g2, const Consts3<R>& k, const R* __restrict__ pend,
-                                                 int x, int row) {
-  const int nrows = k.ny * k.nz;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    if (x == (s == 0 ? 1 : k.nx - 2)) {
-      g0 += pend[pend_grad(nrows, s, 0, row)];
-      g1 += pend[pend_grad(nrows, s, 1, row)];
-      g2 += pend[pend_grad(nrows, s, 2, row)];
-    }
-  }
-}
-
-template <typename R, bool SEED>
-__device__ __forceinline__ void node_mu(const R (&pre)[33], const Mat3<R>& mt, const Consts3<R>& k, bool cl,
-                                        const R* __restrict__ lam_in, const R* __restrict__ pend, int o, int x,
-                                        int row, R w, R (&mu)[33], MatAdj3<R>& ma) {
-  if constexpr (SEED) {
-    seed_mu(pre, mt, k, cl, w, mu);
-  } else {
-    R la[33];
-#pragma unroll
-    for (int q = 0; q < 33; ++q) la[q] = lbm::buffer_load<R, 0>(lam_in + int64_t(q) * k.plane, uint32_t(o) * uint32_t(sizeof(R)));
-    if (pend) add_pending(la, k, pend, x, row);
-    collide_adj(pre, mt, k, cl, la, mu, ma);
-  }
+  for (int q = Q0; q < Q1; ++q)
+    la[q - Q0] = b.template load<0>(q, 0, 0, 0, uint32_t(x) * uint32_t(sizeof(R)));
 }
 
 // Push: the adjoint of the pulled element (x - e_q, q), or of the
-// bounced-back (x, opp q), is mu[q].  ADD: add to what is there.
-template <typename R, bool ADD>
-__device__ __forceinline__ void push(R* __restrict__ lam_out, const Consts3<R>& k, int x, int y, int z,
-                                     const R (&mu)[33]) {
-  const int rowp = k.pitch * k.ny;
-  const int o = z * rowp + y * k.pitch + x;
-  if (!ADD && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2 && z >= 1 && z <= k.nz - 2)) {
-    const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
+// bounced-back (x, opp q), is mu[q - Q0].
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void push(R* __restrict__ lam, const Consts3<R>& k, int x, int y, int z,
+                                     const R (&mu)[Q1 - Q0]) {
+  if (inside(k, x, y, z)) {
+    const Planes3<R> b(lam, k, y, z);
 #pragma unroll
-    for (int q = 0; q < 33; ++q)
-      lbm::buffer_store(lam_out + (int64_t(q) * k.plane - int64_t(EZ[q]) * rowp - int64_t(EY[q]) * k.pitch - EX[q]),
-                        ob, mu[q]);
+    for (int q = Q0; q < Q1; ++q)
+      b.template store<0>(q, -EX[q], -EY[q], -EZ[q], uint32_t(x) * uint32_t(sizeof(R)), mu[q - Q0]);
     return;
   }
-  const bool px = k.flags & F_PERIODIC_X, py = k.flags & F_PERIODIC_Y, pz = k.flags & F_PERIODIC_Z;
 #pragma unroll
-  for (int q = 0; q < 33; ++q) {
-    int xs = x - EX[q], ys = y - EY[q], zs = z - EZ[q];
-    if (px) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
-    if (py) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
-    if (pz) zs = zs < 0 ? zs + k.nz : (zs >= k.nz ? zs - k.nz : zs);
-    const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny && (unsigned)zs < (unsigned)k.nz;
-    const int off = in ? (q * k.plane + zs * rowp + ys * k.pitch + xs) : (OPP[q] * k.plane + o);
-    if constexpr (ADD) lam_out[off] += mu[q]; else lam_out[off] = mu[q];
-  }
+  for (int q = Q0; q < Q1; ++q) lam[pull_offset(k, q, x, y, z)] = mu[q - Q0];
 }
 
-// One reverse step, interior pass: lam_out = (dS'/dS)^T lam_in at the state
-// S without the boundary-column terms, gradients accumulated into grad
-// (planes phi, 1/K, D_eff).  Boundary nodes push zeros (the values of their
-// own pull are never read by the forward step) and leave their gradient to
-// the boundary pass.  SEED: lam_out = w dJ/dS.
+// One reverse step: lam_out = (dS'/dS)^T lam_in at the state S, gradients
+// accumulated into grad (planes phi, 1/K, D_eff).  SEED: lam_out = w dJ/dS.
+//
+// As the 2D reverse step: the fourteen scalar populations (pull, adjoint of
+// their collisions, push), then the nineteen flow ones; a boundary lane runs
+// its own node on its extrapolated populations, and the lane of the feeding
+// column, which the lane shift keeps in the same wavefront, takes the
+// boundary node's result across lanes and runs the transposed
+// extrapolation.  Bound by HBM (432 bytes a node in FP32).  The former
+// kernel held all 33 populations at once (144 VGPRs) and left the boundary
+// nodes to a second kernel on a second stream, joined by events at every
+// step: 72 us per reverse step at 160x80x40 FP32, now 50 (4.5 TB/s).
 template <typename R, bool SEED>
 __global__ __launch_bounds__(kBlock3) void k3_adj_step(const R* __restrict__ S, const R* __restrict__ lam_in,
                                                        R* __restrict__ lam_out, R* __restrict__ grad,
-                                                       const R* __restrict__ pend,
                                                        const R* __restrict__ phi_f, const R* __restrict__ invk_f,
                                                        const R* __restrict__ d_f, Consts3<R> k, R w) {
+  const int shift = lbm::adj_lane_shift(k.nx);
   int x, y, z;
-  node_of(k, x, y, z);
-  if (x >= k.nx) return;
+  if (!node_of(k, shift, x, y, z)) return;
   const bool open = !(k.flags & F_PERIODIC_X);
   const bool cl = !(k.flags & F_NO_REACTION) && z >= k.z_cl0;
-  const bool boundary = open && ((x == 0 && z < k.nz_ch) || x == k.nx - 1);
-  R mu[33];
-  if (boundary) {
-#pragma unroll
-    for (int q = 0; q < 33; ++q) mu[q] = R(0);
-  } else {
-    const int o = (z * k.ny + y) * k.pitch + x;
-    R p[33];
-    pull<R, true>(S, k, x, y, z, p);
-    const Mat3<R> mt = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, x, y, z);
-    MatAdj3<R> ma{};
-    node_mu<R, SEED>(p, mt, k, cl, lam_in, pend, o, x, z * k.ny + y, w, mu, ma);
-    R g0 = R(0), g1 = R(0), g2 = R(0);
-    material_adj(k, mt, ma, g0, g1, g2);
-    if (pend) add_pending_grad(g0, g1, g2, k, pend, x, z * k.ny + y);
-    grad[o] += g0;
-    grad[k.plane + o] += g1;
-    grad[2 * k.plane + o] += g2;
-  }
-  push<R, false>(lam_out, k, x, y, z, mu);
-}
+  const bool in_row = open && z < k.nz_ch;
+  const bool inlet = in_row && x == 0, outlet = open && x == k.nx - 1, bnode = inlet || outlet;
+  const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
+  const int l0 = (x + shift) & ~63;  // first lane of the wavefront, as an x + shift
+  const bool w_in = in_row && l0 == 0, w_out = open && l0 == ((k.nx - 1 + shift) & ~63);
+  const int lane_out = (k.nx - 1 + shift) & 63;
+  const int o = (z * k.ny + y) * k.pitch + x;
 
-// One reverse step, boundary pass (open x only; reads what the interior
-// pass reads, writes only the boundary nodes' gradient and the shares
-// pend_out, so it may run concurrently with the interior pass): one thread
-// per boundary node b fed by column xp computes b's collision adjoint on b's
-// pre-collision populations and the transposed extrapolation.  pend_in: the
-// previous step's shares (null for the first).
-template <typename R, bool SEED>
-__global__ __launch_bounds__(64) void k3_adj_bnd(const R* __restrict__ S, const R* __restrict__ lam_in,
-                                                 R* __restrict__ grad, const R* __restrict__ pend_in,
-                                                 R* __restrict__ pend_out,
-                                                 const R* __restrict__ phi_f, const R* __restrict__ invk_f,
-                                                 const R* __restrict__ d_f, Consts3<R> k, R w) {
-  // This pass runs beside the interior pass on the same CUs and is the
-  // longer of the two: its waves take instruction-issue priority.
-  __builtin_amdgcn_s_setprio(3);
-  const int nrows = k.ny * k.nz;
-  const int t = blockIdx.x * 64 + threadIdx.x;
-  if (t >= 2 * nrows) return;
-  const bool inlet = t < nrows;
-  const int r = inlet ? t : t - nrows;
-  const int z = r / k.ny, y = r - z * k.ny;
-  if (inlet && z >= k.nz_ch) return;
-  const bool cl = !(k.flags & F_NO_REACTION) && z >= k.z_cl0;
-  const int xb = inlet ? 0 : k.nx - 1, xp = inlet ? 1 : k.nx - 2;
-  const int row = (z * k.ny + y) * k.pitch;
-  R p[33];
-  pull(S, k, xp, y, z, p);
-  const Mat3<R> mxp = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, xp, y, z);
-  Mat3<R> mb = material<R, MAT_FULL>(k, phi_f, invk_f, d_f, xb, y, z);
-  if (!inlet) {  // the outlet node collides with column nx-2's scalar material
-    mb.aT = mxp.aT;
-    mb.aC = mxp.aC;
-    mb.rhocp = mxp.rhocp;
-  }
-  MatAdj3<R> mab{}, maxp{};
-  R mub[33];
+  AdjMat3<R> m = adj_material(k, phi_f, invk_f, d_f, xp, y, z);
+  R g[14];
+  MacroTape3<R> t;
   {
-    R pre[33];
+    R f[19];
+    pull_range<R, 0, 19, false>(S, k, xp, y, z, f);
+    pull_range<R, 19, 33, false>(S, k, xp, y, z, g);
+    if (bnode) {  // the boundary node's extrapolated populations and its own material
+      R p[33];
 #pragma unroll
-    for (int q = 0; q < 33; ++q) pre[q] = p[q];
-    boundary_column(pre, k, y, z, inlet, mxp, mb);
-    node_mu<R, SEED>(pre, mb, k, cl, lam_in, pend_in, row + xb, xb, r, w, mub, mab);
-  }
-  R dmu[33];
+      for (int q = 0; q < 33; ++q) p[q] = q < 19 ? f[q] : g[q - 19];
+      AdjMat3<R> mc = adj_material(k, phi_f, invk_f, d_f, x, y, z);
+      boundary_column(p, k, y, z, inlet, m, mc);
+      if (outlet) {  // the outlet node collides with column nx-2's scalar material
+        mc.aT = m.aT;
+        mc.aC = m.aC;
+        mc.rhocp = m.rhocp;
+        mc.irc = m.irc;
+      }
+      m = mc;
 #pragma unroll
-  for (int q = 0; q < 33; ++q) dmu[q] = R(0);
-  boundary_adj(p, mxp, mb, k, inlet, inlet ? inlet_velocity(k, y, z) : R(0), mub, dmu, maxp, mab);
-  if (!inlet) {
-    maxp.aT += mab.aT;
-    maxp.aC += mab.aC;
-    maxp.rhocp += mab.rhocp;
-    mab.aT = mab.aC = mab.rhocp = R(0);
+      for (int q = 0; q < 33; ++q) (q < 19 ? f[q] : g[q - 19]) = p[q];
+    }
+    t = flow_macros_tape(f, m, k);
   }
-  R g0 = R(0), g1 = R(0), g2 = R(0);
-  material_adj(k, mb, mab, g0, g1, g2);
-  grad[row + xb] += g0;
-  grad[k.plane + row + xb] += g1;
-  grad[2 * k.plane + row + xb] += g2;
-  g0 = g1 = g2 = R(0);
-  material_adj(k, mxp, maxp, g0, g1, g2);
-  // The share of element (q, xp - e_q) of the column's pull, or across a
-  // wall of (opp q, xp) (as the pull reads them).
-  const int s = inlet ? 0 : 1;
-  const bool py = k.flags & F_PERIODIC_Y, pz = k.flags & F_PERIODIC_Z;
-#pragma unroll
-  for (int q = 0; q < 33; ++q) {
-    int ys = y - EY[q], zs = z - EZ[q];
-    if (py) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
-    if (pz) zs = zs < 0 ? zs + k.nz : (zs >= k.nz ? zs - k.nz : zs);
-    const bool in = (unsigned)ys < (unsigned)k.ny && (unsigned)zs < (unsigned)k.nz;
-    const int slot = in ? pend_slot(nrows, s, q, 1 - EX[q], zs * k.ny + ys) : pend_slot(nrows, s, OPP[q], 1, r);
-    pend_out[slot] = dmu[q];
-  }
-  pend_out[pend_grad(nrows, s, 0, r)] = g0;
-  pend_out[pend_grad(nrows, s, 1, r)] = g1;
-  pend_out[pend_grad(nrows, s, 2, r)] = g2;
-}
+  MatAdj3<R> ma{};
+  Vec3<R> lu, bl;  // velocity's adjoints: of the node's collision, of the transposed extrapolation
+  R lpp = R(0);
+  const R ub = w_in ? inlet_velocity(k, y, z) : R(0);
 
-// After the last reverse step: its boundary shares added to the adjoint of
-// the initial state and to the gradient.  One thread per (population or the
-// gradient slot, row) adds both sides in turn (for nx <= 5 they reach the
-// same nodes).
-template <typename R>
-__global__ __launch_bounds__(kBlock3) void k3_adj_apply(const R* __restrict__ pend, R* __restrict__ lam,
-                                                        R* __restrict__ grad, Consts3<R> k) {
-  const int nrows = k.ny * k.nz;
-  const int t = blockIdx.x * kBlock3 + threadIdx.x;
-  if (t >= 34 * nrows) return;
-  const int q = t / nrows, row = t - q * nrows;
-  const int z = row / k.ny, y = row - z * k.ny;
-  const int o = z * k.pitch * k.ny + y * k.pitch;
-  for (int s = 0; s < 2; ++s) {
-    const int x0 = s == 0 ? 0 : k.nx - 3;
-    if (q < 33) {
-      for (int dx = 0; dx < 3; ++dx) lam[q * k.plane + o + x0 + dx] += pend[pend_slot(nrows, s, q, dx, row)];
+  // ---- scalars ----
+  {
+    R mus[14];
+    if constexpr (SEED) {
+#pragma unroll
+      for (int q = 0; q < 14; ++q) mus[q] = R(0);
+      if (cl) {
+        R th = R(0), c = R(0);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+          th += g[q];
+          c += g[7 + q];
+        }
+        const ReactAdj<R> r = reaction_tape(th, c, m.rhocp, k);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+          mus[q] = w * r.dsc_dth;
+          mus[7 + q] = w * r.dsc_dc;
+        }
+      }
     } else {
-      for (int c = 0; c < 3; ++c) grad[c * k.plane + o + x0 + 1] += pend[pend_grad(nrows, s, c, row)];
+      R la[14];
+      load_own<R, 19, 33>(lam_in, k, x, y, z, la);
+      scalars_adj(g, t.u, m, k, cl, la, mus, lu, ma);
+    }
+    if (w_in) {
+      R mub[14];
+#pragma unroll
+      for (int q = 0; q < 14; ++q) mub[q] = __shfl(mus[q], shift, 64);
+      const Vec3<R> up{__shfl(t.u.x, shift + 1, 64), __shfl(t.u.y, shift + 1, 64), __shfl(t.u.z, shift + 1, 64)};
+      if (x <= 1) {
+        MatAdj3<R> axp{}, ab{};
+        R th = R(0), c = R(0), lt1 = R(0), lc1 = R(0);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+          th += g[q];
+          c += g[7 + q];
+        }
+        inlet_scalars_adj(mub, up, th, c, m, k, bl, lt1, lc1, axp, ab);
+        if (x == 0) {
+          ma.aC += ab.aC;
+        } else {
+          ma.aT += axp.aT;
+          ma.aC += axp.aC;
+#pragma unroll
+          for (int q = 0; q < 7; ++q) {
+            mus[q] += mub[q] + lt1;
+            mus[7 + q] += mub[7 + q] + lc1;
+          }
+        }
+      }
+    }
+    if (w_out) {  // the outlet's scalars are copies
+      R mub[14];
+#pragma unroll
+      for (int q = 0; q < 14; ++q) mub[q] = __shfl(mus[q], lane_out, 64);
+      const R sT = __shfl(ma.aT, lane_out, 64), sC = __shfl(ma.aC, lane_out, 64);
+      const R sr = __shfl(ma.rhocp, lane_out, 64);
+      if (x == k.nx - 2) {
+#pragma unroll
+        for (int q = 0; q < 14; ++q) mus[q] += mub[q];
+        ma.aT += sT;
+        ma.aC += sC;
+        ma.rhocp += sr;
+      }
+    }
+    if (bnode) {  // its pulled sources were never read by the forward step
+#pragma unroll
+      for (int q = 0; q < 14; ++q) mus[q] = R(0);
+    }
+    push<R, 19, 33>(lam_out, k, x, y, z, mus);
+  }
+
+  // ---- flow ----
+  R muf[19];
+  if constexpr (SEED) {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) muf[q] = R(0);
+  } else {
+    R la[19];
+    load_own<R, 0, 19>(lam_in, k, x, y, z, la);
+    flow_adj(t, m, k, la, lu, muf, ma);
+  }
+  if (w_in || w_out) {
+    // both boundaries in turn (nx = 3: one column feeds both)
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      if (!(side == 0 ? w_in : w_out)) continue;
+      const int lb = side == 0 ? shift : lane_out, lp = side == 0 ? shift + 1 : lane_out - 1;
+      R mub[19];
+#pragma unroll
+      for (int q = 0; q < 19; ++q) mub[q] = __shfl(muf[q], lb, 64);
+      const Vec3<R> up{__shfl(t.u.x, lp, 64), __shfl(t.u.y, lp, 64), __shfl(t.u.z, lp, 64)};
+      const R ppp = __shfl(t.pp, lp, 64), ip = __shfl(m.iphi, lp, 64);
+      const R phi_b = __shfl(m.phi, lb, 64), iphi_b = __shfl(m.iphi, lb, 64);
+      const int xb = side == 0 ? 0 : k.nx - 1, xf = side == 0 ? 1 : k.nx - 2;
+      if (x == xb || x == xf) {
+        MatAdj3<R> axp{}, ab{};
+        Vec3<R> l;
+        R lp1 = R(0);
+        boundary_flow_adj(mub, up, ppp, side == 0, ub, ip, phi_b, iphi_b, l, lp1, axp, ab);
+        if (x == xb) {
+          ma.phi += ab.phi;
+        } else {
+          ma.phi += axp.phi;
+          bl = axpy(R(1), l, bl);
+          lpp += lp1;
+#pragma unroll
+          for (int q = 0; q < 19; ++q) muf[q] += mub[q];
+        }
+      }
+    }
+    if (!bnode && (x == 1 || x == k.nx - 2)) {
+      // xp's macros: phi p = s / 2 - u^2 / (4 phi), u = v / den
+      ma.phi += R(0.25) * lpp * t.u2 * m.iphi * m.iphi;
+      const Vec3<R> lv = flow_macros_adj(t, m, k, axpy(R(-0.5) * lpp * m.iphi, t.u, bl), Vec3<R>{}, ma);
+#pragma unroll
+      for (int q = 1; q < 19; ++q) muf[q] += R(0.5) * lpp + along(q, lv);
     }
   }
+  if (bnode) {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) muf[q] = R(0);
+  }
+  push<R, 0, 19>(lam_out, k, x, y, z, muf);
+
+  if (outlet) ma.aT = ma.aC = ma.rhocp = R(0);  // went to column nx - 2
+  R g0 = R(0), g1 = R(0), g2 = R(0);
+  material_adj(k, m, ma, g0, g1, g2);
+  grad[o] += g0;
+  grad[k.plane + o] += g1;
+  grad[2 * k.plane + o] += g2;
 }
 
 // Gradient through the initial state: the O2 equilibrium at rest depends on

@@ -104,9 +104,7 @@ struct lbm3d_ctx {
   int32_t adj_every = 0;
   int64_t adj_step = -1;
   bool adj_ready = false;
-  // second stream for the boundary pass of the reverse sweep, and its events
-  hipStream_t aux = nullptr;
-  hipEvent_t ev_in = nullptr, ev_bnd = nullptr;
+  bool adj_last_resident = false;  // the replay buffer holds the last segment's states
 
   void* state(int i) { return ws + L.off_state[i]; }
   void* mat_plane(int i) { return ws + L.off_mat + size_t(i) * L.plane * L.esize; }
@@ -171,6 +169,8 @@ void fill_consts3(Consts3<R>& k, const lbm3d_geometry& g, const lbm_params& p, c
   k.aF_over_R = k2.aF_over_R;
   k.four_f_cref = k2.four_f_cref;
   k.aFsum_over_R = k2.aFsum_over_R;
+  k.aT_f = k2.aT_f;
+  k.aT_s = k2.aT_s;
 }
 
 template <typename R>
@@ -221,17 +221,26 @@ void by_mat(int mat, F&& f) {
   }
 }
 
+// One step src -> dst; a state beyond the 256 MB last-level cache streams
+// past it (per step, streaming -> cached: 97x50x33 FP64 21.9 -> 18.6 us,
+// 160x80x40 FP32 31.5 -> 25.8).
+template <typename R, int MAT>
+void launch_step3_kernel(lbm3d_ctx* c, const R* src, R* dst) {
+  const Mat3Ptrs<R> m = mat3_ptrs<R>(c);
+  const Consts3<R>& k = consts3<R>(c);
+  const dim3 grid(unsigned(row_blocks(c->g.nx, 0) * c->g.ny * c->g.nz));
+  if (c->L.state > (size_t(256) << 20))
+    hipLaunchKernelGGL((k3_step<R, MAT, true>), grid, dim3(kBlock3), 0, c->stream, src, dst, m.phi, m.invk, m.d, k);
+  else
+    hipLaunchKernelGGL((k3_step<R, MAT, false>), grid, dim3(kBlock3), 0, c->stream, src, dst, m.phi, m.invk, m.d, k);
+}
+
 template <typename R>
 void launch_step3(lbm3d_ctx* c, int64_t n) {
-  const Mat3Ptrs<R> m = mat3_ptrs<R>(c);
-  const Consts3<R> k = consts3<R>(c);
-  const dim3 grid(unsigned(c->L.nblocks_obs));
   by_mat(c->mat, [&](auto mode) {
     constexpr int MAT = decltype(mode)::value;
     for (int64_t i = 0; i < n; ++i) {
-      const R* src = static_cast<const R*>(c->state(c->cur));
-      R* dst = static_cast<R*>(c->state(c->cur ^ 1));
-      hipLaunchKernelGGL((k3_step<R, MAT>), grid, dim3(kBlock3), 0, c->stream, src, dst, m.phi, m.invk, m.d, k);
+      launch_step3_kernel<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), static_cast<R*>(c->state(c->cur ^ 1)));
       c->cur ^= 1;
     }
   });
@@ -491,12 +500,6 @@ lbm_status lbm3d_synchronize(lbm3d_ctx* c) {
 
 void lbm3d_destroy(lbm3d_ctx* c) {
   if (!c) return;
-  if (c->aux) {
-    (void)hipStreamSynchronize(c->aux);
-    (void)hipStreamDestroy(c->aux);
-  }
-  if (c->ev_in) (void)hipEventDestroy(c->ev_in);
-  if (c->ev_bnd) (void)hipEventDestroy(c->ev_bnd);
   delete c;
 }
 
@@ -515,7 +518,7 @@ namespace {
 struct AdjLayout3 {
   size_t state = 0;
   int nck = 0;
-  size_t off_ck = 0, off_replay = 0, off_lam = 0, off_grad = 0, off_pend = 0, total = 0;
+  size_t off_ck = 0, off_replay = 0, off_lam = 0, off_grad = 0, total = 0;
 };
 
 AdjLayout3 adj_layout3(const lbm3d_ctx* c, int64_t nsteps, int32_t every) {
@@ -531,97 +534,65 @@ AdjLayout3 adj_layout3(const lbm3d_ctx* c, int64_t nsteps, int32_t every) {
   o += 2 * A.state;
   A.off_grad = o;
   o += align3(size_t(3) * c->L.plane * c->L.esize);
-  A.off_pend = o;  // two buffers of boundary shares (written by one step, added by the next)
-  o += 2 * align3(size_t(kPendVals) * c->g.ny * c->g.nz * c->L.esize);
   A.total = o;
   return A;
 }
 
-// One reverse step: interior pass on the context stream and, for an open
-// channel, the boundary pass on the second stream at the same time (both
-// wait for what precedes on the context stream); the context stream then
-// waits for the boundary pass, whose shares pend_out the next step adds.
 template <typename R, bool SEED>
-lbm_status reverse_step3(lbm3d_ctx* c, const R* S, const R* lam_in, R* lam_out, R* grad, const R* pend_in,
-                         R* pend_out, R w) {
+void reverse_step3(lbm3d_ctx* c, const R* S, const R* lam_in, R* lam_out, R* grad, R w) {
   const Mat3Ptrs<R> m = mat3_ptrs<R>(c);
-  const Consts3<R>& k = consts3<R>(c);
-  const bool open = !(c->g.flags & LBM_PERIODIC_X);
-  const int nrows = c->g.ny * c->g.nz;
-  if (open) {
-    if (hipEventRecord(c->ev_in, c->stream) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_in, 0) != hipSuccess)
-      return fail3(c, LBM_ERR_DEVICE, "boundary pass ordering failed");
-    hipLaunchKernelGGL((k3_adj_bnd<R, SEED>), dim3(unsigned((2 * nrows + 63) / 64)), dim3(64), 0, c->aux, S, lam_in,
-                       grad, pend_in, pend_out, m.phi, m.invk, m.d, k, w);
-    if (hipEventRecord(c->ev_bnd, c->aux) != hipSuccess) return fail3(c, LBM_ERR_DEVICE, "boundary pass event failed");
-  }
-  hipLaunchKernelGGL((k3_adj_step<R, SEED>), dim3(unsigned(c->L.nblocks_obs)), dim3(kBlock3), 0, c->stream, S, lam_in,
-                     lam_out, grad, open ? pend_in : nullptr, m.phi, m.invk, m.d, k, w);
-  if (open && hipStreamWaitEvent(c->stream, c->ev_bnd, 0) != hipSuccess)
-    return fail3(c, LBM_ERR_DEVICE, "boundary pass join failed");
-  return LBM_OK;
+  const dim3 grid(unsigned(row_blocks(c->g.nx, lbm::adj_lane_shift(c->g.nx)) * c->g.ny * c->g.nz));
+  hipLaunchKernelGGL((k3_adj_step<R, SEED>), grid, dim3(kBlock3), 0, c->stream, S, lam_in, lam_out, grad, m.phi,
+                     m.invk, m.d, consts3<R>(c), w);
+}
+
+// Steps 1 .. n from state 0 of the replay buffer, the last one into the
+// context's other state buffer.
+template <typename R>
+void forward_last_segment3(lbm3d_ctx* c, const AdjLayout3& A, int n) {
+  char* buf = c->adj_ws + A.off_replay;
+  for (int j = 1; j <= n; ++j)
+    launch_step3_kernel<R, MAT_FULL>(c, reinterpret_cast<const R*>(buf + size_t(j - 1) * A.state),
+                                     j < n ? reinterpret_cast<R*>(buf + size_t(j) * A.state)
+                                           : static_cast<R*>(c->state(c->cur ^ 1)));
+  c->cur ^= 1;
+  c->step += n;
 }
 
 template <typename R>
 lbm_status backward3_t(lbm3d_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_d) {
   const AdjLayout3 A = adj_layout3(c, c->adj_nsteps, c->adj_every);
   char* ws = c->adj_ws;
-  const Mat3Ptrs<R> m = mat3_ptrs<R>(c);
   const Consts3<R> k = consts3<R>(c);
-  const dim3 grid(unsigned(c->L.nblocks_obs));
   R* grad = reinterpret_cast<R*>(ws + A.off_grad);
-  const bool open = !(c->g.flags & LBM_PERIODIC_X);
-  const int64_t npend = int64_t(kPendVals) * c->g.ny * c->g.nz;
-  R* pend[2] = {reinterpret_cast<R*>(ws + A.off_pend),
-                reinterpret_cast<R*>(ws + A.off_pend + align3(size_t(npend) * c->L.esize))};
   R* lam[2] = {reinterpret_cast<R*>(ws + A.off_lam), reinterpret_cast<R*>(ws + A.off_lam + A.state)};
-  if (!c->aux) {
-    if (hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) != hipSuccess) {
-      c->aux = nullptr;
-      return fail3(c, LBM_ERR_DEVICE, "second stream creation failed");
-    }
-    if (hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_bnd, hipEventDisableTiming) != hipSuccess)
-      return fail3(c, LBM_ERR_DEVICE, "event creation failed");
-  }
   const int64_t ngrad = int64_t(3) * c->L.plane;
   hipLaunchKernelGGL(k3_fill<R>, dim3(unsigned((ngrad + kBlock3 - 1) / kBlock3)), dim3(kBlock3), 0, c->stream, grad,
                      ngrad, R(0));
-  if (open)  // shares never written (rows without an inlet, ...) stay zero
-    for (R* b : pend)
-      hipLaunchKernelGGL(k3_fill<R>, dim3(unsigned((npend + kBlock3 - 1) / kBlock3)), dim3(kBlock3), 0, c->stream, b,
-                         npend, R(0));
   // Seed: adjoint of J = mean over (x, y) of sum_CL 4 F C_ref s_c / dt * dx.
   const lbm_params& p = c->p;
   const double w = dJ * c->d.dx / (double(c->g.nx) * c->g.ny) * 4.0 * p.faraday * p.C_ref / c->d.dt;
-  if (lbm_status st = reverse_step3<R, true>(c, static_cast<const R*>(c->state(c->cur)), nullptr, lam[0], grad,
-                                             nullptr, pend[0], R(w));
-      st != LBM_OK)
-    return st;
-  int cur = 0, pc = 0;  // pend[pc]: the shares the next reverse step adds
+  reverse_step3<R, true>(c, static_cast<const R*>(c->state(c->cur)), nullptr, lam[0], grad, R(w));
+  int cur = 0;
+  char* replay = ws + A.off_replay;
   for (int seg = A.nck - 1; seg >= 0; --seg) {
     const int64_t start = int64_t(seg) * c->adj_every;
     const int len = int(std::min<int64_t>(c->adj_every, c->adj_nsteps - start));
-    char* replay = ws + A.off_replay;
-    if (hipMemcpyAsync(replay, ws + A.off_ck + size_t(seg) * A.state, A.state, hipMemcpyDeviceToDevice,
-                       c->stream) != hipSuccess)
-      return fail3(c, LBM_ERR_DEVICE, "replay restore failed");
-    for (int j = 1; j < len; ++j)
-      hipLaunchKernelGGL((k3_step<R, MAT_FULL>), grid, dim3(kBlock3), 0, c->stream,
-                         reinterpret_cast<const R*>(replay + size_t(j - 1) * A.state),
-                         reinterpret_cast<R*>(replay + size_t(j) * A.state), m.phi, m.invk, m.d, k);
+    if (!c->adj_last_resident) {
+      if (hipMemcpyAsync(replay, ws + A.off_ck + size_t(seg) * A.state, A.state, hipMemcpyDeviceToDevice,
+                         c->stream) != hipSuccess)
+        return fail3(c, LBM_ERR_DEVICE, "replay restore failed");
+      for (int j = 1; j < len; ++j)
+        launch_step3_kernel<R, MAT_FULL>(c, reinterpret_cast<const R*>(replay + size_t(j - 1) * A.state),
+                                         reinterpret_cast<R*>(replay + size_t(j) * A.state));
+    }
+    c->adj_last_resident = false;
     for (int j = len - 1; j >= 0; --j) {
-      if (lbm_status st = reverse_step3<R, false>(c, reinterpret_cast<const R*>(replay + size_t(j) * A.state),
-                                                  lam[cur], lam[cur ^ 1], grad, pend[pc], pend[pc ^ 1], R(0));
-          st != LBM_OK)
-        return st;
+      reverse_step3<R, false>(c, reinterpret_cast<const R*>(replay + size_t(j) * A.state), lam[cur], lam[cur ^ 1],
+                              grad, R(0));
       cur ^= 1;
-      pc ^= 1;
     }
   }
-  if (open)  // the last reverse step's boundary shares
-    hipLaunchKernelGGL(k3_adj_apply<R>, dim3(unsigned((34 * int64_t(c->g.ny) * c->g.nz + kBlock3 - 1) / kBlock3)),
-                       dim3(kBlock3), 0, c->stream, pend[pc], lam[cur], grad, k);
   hipLaunchKernelGGL(k3_adj_init<R>, c->grid3(), dim3(kBlock3), 0, c->stream, lam[cur], grad, k);
   void* outs[3] = {g_phi, g_invk, g_d};
   for (int i = 0; i < 3; ++i)
@@ -659,12 +630,22 @@ lbm_status lbm3d_forward_checkpointed(lbm3d_ctx* c, int64_t nsteps, int32_t ever
   c->adj_every = every;
   const size_t sb = size_t(33) * c->L.plane * c->L.esize;
   for (int seg = 0; seg < A.nck; ++seg) {
-    if (hipMemcpyAsync(c->adj_ws + A.off_ck + size_t(seg) * A.state, c->state(c->cur), sb, hipMemcpyDeviceToDevice,
-                       c->stream) != hipSuccess)
+    char* ck = c->adj_ws + A.off_ck + size_t(seg) * A.state;
+    char* replay = c->adj_ws + A.off_replay;
+    if (hipMemcpyAsync(ck, c->state(c->cur), sb, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
+        (seg == A.nck - 1 && hipMemcpyAsync(replay, ck, sb, hipMemcpyDeviceToDevice, c->stream) != hipSuccess))
       return fail3(c, LBM_ERR_DEVICE, "checkpoint copy failed");
     const int64_t n = std::min<int64_t>(every, nsteps - int64_t(seg) * every);
-    if (lbm_status s = lbm3d_step(c, n); s != LBM_OK) return s;
+    if (seg < A.nck - 1) {
+      if (lbm_status s = lbm3d_step(c, n); s != LBM_OK) return s;
+      continue;
+    }
+    // The last segment steps through the replay buffer (the same kernel, so
+    // the same states), where the first reverse sweep reads them.
+    if (c->g.precision == 64) forward_last_segment3<double>(c, A, int(n)); else forward_last_segment3<float>(c, A, int(n));
+    if (lbm_status s = check3(c, "forward_checkpointed"); s != LBM_OK) return s;
   }
+  c->adj_last_resident = true;
   lbm_obs o{};
   if (lbm_status s = lbm3d_observables(c, &o); s != LBM_OK) return s;
   if (J_out) *J_out = o.current_density;

@@ -53,6 +53,7 @@ struct Consts3 {
   R k_f, k_s, rhocp_f, rhocp_s, alpha_scale;
   R T_in, c_in, V_op, U0_slope, U0_icept, ln_k0, E_over_R, inv_T_arrh, aF_over_R, four_f_cref;
   R aFsum_over_R;  // (alpha_a + alpha_c) F / R, Butler-Volmer only
+  R aT_f, aT_s;    // sqrt(3) alpha_scale k_f and k_s (reverse step)
 };
 
 template <typename R>
@@ -75,8 +76,8 @@ __device__ __forceinline__ Mat3<R> material(const Consts3<R>& k, const R* __rest
     phi = phi_f[cell];
     if constexpr (MAT == MAT_PHI) {
       const R om = R(1) - phi;
-      invk = om * om * k.kc_inv / (phi * phi * phi);
-      d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * sqrt(phi) * k.D_f;
+      invk = lbm::div_(om * om * k.kc_inv, phi * phi * phi);
+      d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * lbm::sqrt_(phi) * k.D_f;
     } else {
       invk = invk_f[cell];
       d = d_f[cell];
@@ -86,73 +87,77 @@ __device__ __forceinline__ Mat3<R> material(const Consts3<R>& k, const R* __rest
   m.phi = phi;
   m.invk = invk;
   m.d = d;
-  m.sqk = sqrt(invk);
-  m.fphi = R(0.143) / (phi * sqrt(phi));
+  m.sqk = lbm::sqrt_(invk);
+  m.fphi = lbm::div_(R(0.143), phi * lbm::sqrt_(phi));
   m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
   m.l1 = phi * m.fphi * m.sqk * R(0.5);
   m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
-  const R alpha = (k.k_f * phi + k.k_s * (R(1) - phi)) * k.alpha_scale / m.rhocp;
+  const R alpha = lbm::div_((k.k_f * phi + k.k_s * (R(1) - phi)) * k.alpha_scale, m.rhocp);
   const R s3 = R(1.7320508075688772935);
   m.aT = s3 * alpha;
   m.aC = s3 * d;
   return m;
 }
 
-// UNIFORM: a wavefront whose nodes all lie one node or more inside the
-// lattice folds each population's plane and neighbour shift into a
-// wave-uniform buffer base (scalar registers) and adds one shared 32-bit
-// lane offset (used by the reverse step).
-template <typename R, bool UNIFORM = false>
-__device__ __forceinline__ void pull(const R* __restrict__ src, const Consts3<R>& k, int x, int y, int z,
-                                     R (&f)[33]) {
-  const int row = k.pitch * k.ny;
-  if (UNIFORM && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2 && z >= 1 && z <= k.nz - 2)) {
-    const uint32_t ob = uint32_t(z * row + y * k.pitch + x) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = 0; q < 33; ++q)
-      f[q] = lbm::buffer_load<R, 2>(
-          src + (int64_t(q) * k.plane - int64_t(EZ[q]) * row - int64_t(EY[q]) * k.pitch - EX[q]), ob);
-    return;
+// Wave-uniform bases of a 33-plane buffer at row (y, z), as
+// lbm::PlaneBuffer: the lane's x is the vector offset.
+template <typename R>
+struct Planes3 {
+  const R* p;
+  const Consts3<R>& k;
+  __device__ __forceinline__ Planes3(const R* base, const Consts3<R>& c, int y, int z)
+      : p(base + (int64_t(z) * c.ny + y) * c.pitch), k(c) {}
+  __device__ __forceinline__ const R* at(int q, int dx, int dy, int dz) const {
+    return p + (int64_t(q) * k.plane + (int64_t(dz) * k.ny + dy) * k.pitch + dx);
   }
-  const bool px = k.flags & F_PERIODIC_X, py = k.flags & F_PERIODIC_Y, pz = k.flags & F_PERIODIC_Z;
-#pragma unroll
-  for (int q = 0; q < 33; ++q) {
-    int xs = x - EX[q], ys = y - EY[q], zs = z - EZ[q];
-    if (px) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
-    if (py) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
-    if (pz) zs = zs < 0 ? zs + k.nz : (zs >= k.nz ? zs - k.nz : zs);
-    const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny && (unsigned)zs < (unsigned)k.nz;
-    const int off = in ? (q * k.plane + zs * row + ys * k.pitch + xs) : (OPP[q] * k.plane + z * row + y * k.pitch + x);
-    f[q] = __builtin_nontemporal_load(src + off);
+  template <int AUX>
+  __device__ __forceinline__ R load(int q, int dx, int dy, int dz, uint32_t ob) const {
+    return lbm::buffer_load<R, AUX>(at(q, dx, dy, dz), ob);
   }
+  template <int AUX>
+  __device__ __forceinline__ void store(int q, int dx, int dy, int dz, uint32_t ob, R v) const {
+    lbm::buffer_store<AUX>(const_cast<R*>(at(q, dx, dy, dz)), ob, v);
+  }
+};
+
+// Element offset the pull of population q at (x, y, z) reads (f*_q(x - e_q),
+// or the bounced-back f*_opp(q)(x) where the link crosses a wall), and the
+// reverse step's push writes.
+template <typename R>
+__device__ __forceinline__ int pull_offset(const Consts3<R>& k, int q, int x, int y, int z) {
+  int xs = x - EX[q], ys = y - EY[q], zs = z - EZ[q];
+  if (k.flags & F_PERIODIC_X) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
+  if (k.flags & F_PERIODIC_Y) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
+  if (k.flags & F_PERIODIC_Z) zs = zs < 0 ? zs + k.nz : (zs >= k.nz ? zs - k.nz : zs);
+  const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny && (unsigned)zs < (unsigned)k.nz;
+  return in ? (q * k.plane + (zs * k.ny + ys) * k.pitch + xs) : (OPP[q] * k.plane + (z * k.ny + y) * k.pitch + x);
 }
 
-// Pull of the planes [Q0, Q1) only, into f[0 .. Q1 - Q0) (as pull).  A
-// wavefront whose nodes all lie inside the lattice by one node or more
-// loads through wave-uniform buffer bases (one 32-bit lane offset for all
-// planes: no per-load 64-bit address registers).
-template <typename R, int Q0, int Q1>
+// A wavefront whose nodes all lie one node or more inside the lattice; y and
+// z are the same for all its lanes.
+template <typename R>
+__device__ __forceinline__ bool inside(const Consts3<R>& k, int x, int y, int z) {
+  return y >= 1 && y <= k.ny - 2 && z >= 1 && z <= k.nz - 2 && __all(x >= 1 && x <= k.nx - 2);
+}
+
+// Pull of the planes [Q0, Q1) of a wavefront of one row (y, z), into
+// f[0 .. Q1 - Q0).  NT: the non-temporal hint.
+template <typename R, int Q0, int Q1, bool NT>
 __device__ __forceinline__ void pull_range(const R* __restrict__ src, const Consts3<R>& k, int x, int y, int z,
                                            R* f) {
-  const int row = k.pitch * k.ny;
-  if (__all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2 && z >= 1 && z <= k.nz - 2)) {
-    const uint32_t ob = uint32_t(z * row + y * k.pitch + x) * uint32_t(sizeof(R));
+  if (inside(k, x, y, z)) {
+    const Planes3<R> b(src, k, y, z);
+    const uint32_t ob = uint32_t(x) * uint32_t(sizeof(R));
 #pragma unroll
-    for (int q = Q0; q < Q1; ++q)
-      f[q - Q0] = lbm::buffer_load<R, 2>(
-          src + (int64_t(q) * k.plane - int64_t(EZ[q]) * row - int64_t(EY[q]) * k.pitch - EX[q]), ob);
+    for (int q = Q0; q < Q1; ++q) f[q - Q0] = b.template load<NT ? 2 : 0>(q, -EX[q], -EY[q], -EZ[q], ob);
     return;
   }
-  const bool px = k.flags & F_PERIODIC_X, py = k.flags & F_PERIODIC_Y, pz = k.flags & F_PERIODIC_Z;
 #pragma unroll
   for (int q = Q0; q < Q1; ++q) {
-    int xs = x - EX[q], ys = y - EY[q], zs = z - EZ[q];
-    if (px) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
-    if (py) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
-    if (pz) zs = zs < 0 ? zs + k.nz : (zs >= k.nz ? zs - k.nz : zs);
-    const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny && (unsigned)zs < (unsigned)k.nz;
-    const int off = in ? (q * k.plane + zs * row + ys * k.pitch + xs) : (OPP[q] * k.plane + z * row + y * k.pitch + x);
-    f[q - Q0] = __builtin_nontemporal_load(src + off);
+    if constexpr (NT)
+      f[q - Q0] = __builtin_nontemporal_load(src + pull_offset(k, q, x, y, z));
+    else
+      f[q - Q0] = src[pull_offset(k, q, x, y, z)];
   }
 }
 
@@ -178,14 +183,15 @@ __device__ __forceinline__ Macro3<R> flow_macros(const R (&f)[N], const Mat3<R>&
     vx += R(0.5) * m.phi * k.ax;
     vy += R(0.5) * m.phi * k.ay;
   }
-  const R vm = sqrt(vx * vx + vy * vy + vz * vz);
-  const R den = m.l0 + sqrt(m.l0 * m.l0 + m.l1 * vm);
+  const R vm = lbm::sqrt_(vx * vx + vy * vy + vz * vz);
+  const R den = m.l0 + lbm::sqrt_(m.l0 * m.l0 + m.l1 * vm);
+  const R iden = lbm::rcp_seed(den);
   Macro3<R> o;
-  o.ux = vx / den;
-  o.uy = vy / den;
-  o.uz = vz / den;
+  o.ux = lbm::div_(vx, den, iden);
+  o.uy = lbm::div_(vy, den, iden);
+  o.uz = lbm::div_(vz, den, iden);
   const R u2 = o.ux * o.ux + o.uy * o.uy + o.uz * o.uz;
-  const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * sqrt(u2));
+  const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * lbm::sqrt_(u2));
   o.Fx = -drag * o.ux;
   o.Fy = -drag * o.uy;
   o.Fz = -drag * o.uz;
@@ -193,7 +199,7 @@ __device__ __forceinline__ Macro3<R> flow_macros(const R (&f)[N], const Mat3<R>&
     o.Fx += m.phi * k.ax;
     o.Fy += m.phi * k.ay;
   }
-  const R iphi = R(1) / m.phi;
+  const R iphi = lbm::rcp_(m.phi);
   o.p = (s - R(0.5) * u2 * iphi) * R(0.5) * iphi;
   return o;
 }
@@ -206,7 +212,7 @@ __device__ __forceinline__ R weight(int q) {
 // Add sgn * f_eq(p, u; phi) (shifted rest population) to f[0..18].
 template <typename R>
 __device__ __forceinline__ void add_feq(R p, R ux, R uy, R uz, R phi, R sgn, R* f) {
-  const R iphi = R(1) / phi;
+  const R iphi = lbm::rcp_(phi);
   const R u2 = ux * ux + uy * uy + uz * uz;
   f[0] += sgn * (R(-2) * phi * p - R(0.5) * u2 * iphi);
 #pragma unroll
@@ -287,7 +293,7 @@ __device__ __forceinline__ Mat3<R> pre_collision(const R* __restrict__ src, cons
   const bool inlet = open && x == 0 && z < k.nz_ch;
   const bool outlet = open && x == k.nx - 1;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
-  pull(src, k, xp, y, z, f);
+  pull_range<R, 0, 33, true>(src, k, xp, y, z, f);
   const Mat3<R> mp = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y, z);
   if (!(inlet || outlet)) return mp;
   Mat3<R> mb = material<R, MAT>(k, phi_f, invk_f, d_f, x, y, z);
@@ -306,7 +312,7 @@ using lbm::reaction;  // the CL reaction of Eqs. 12-17 (shared with 2D)
 // a: the node's macroscopic fields.
 template <typename R>
 __device__ __forceinline__ void collide_flow(R* f, const Macro3<R>& a, const Mat3<R>& mt, const Consts3<R>& k) {
-  const R iphi = R(1) / mt.phi;
+  const R iphi = lbm::rcp_(mt.phi);
   const R u2 = a.ux * a.ux + a.uy * a.uy + a.uz * a.uz;
   const R uF = a.ux * a.Fx + a.uy * a.Fy + a.uz * a.Fz;
   const R sp = k.s_plus, sm = k.s_minus;
@@ -390,19 +396,22 @@ __device__ __forceinline__ void collide(R (&f)[33], const Mat3<R>& mt, const Con
   collide_scalars(f + 19, a.ux, a.uy, a.uz, mt, k, cl);
 }
 
-// Store f[0 .. Q1 - Q0) into the planes [Q0, Q1) at element offset o, through
-// wave-uniform buffer bases (the 33 planes hold fewer than 2^31 elements).
-template <typename R, int Q0, int Q1>
-__device__ __forceinline__ void store_range(R* __restrict__ dst, const Consts3<R>& k, int o, const R* f) {
-  const uint32_t ob = uint32_t(o) * uint32_t(sizeof(R));
+// Store f[0 .. Q1 - Q0) into the planes [Q0, Q1) of node (x, y, z), y and z
+// the wavefront's.
+template <typename R, int Q0, int Q1, int AUX>
+__device__ __forceinline__ void store_range(R* __restrict__ dst, const Consts3<R>& k, int x, int y, int z,
+                                            const R* f) {
+  const Planes3<R> b(dst, k, y, z);
 #pragma unroll
-  for (int q = Q0; q < Q1; ++q) lbm::buffer_store(dst + int64_t(q) * k.plane, ob, f[q - Q0]);
+  for (int q = Q0; q < Q1; ++q)
+    b.template store<AUX>(q, 0, 0, 0, uint32_t(x) * uint32_t(sizeof(R)), f[q - Q0]);
 }
 
 // One time step of node (x, y, z) in two passes: the 19 flow populations
 // (pull, boundary extrapolation, collision, store), then the 14 scalar ones
 // with the node's velocity, so that at most 19 populations are held at once.
-template <typename R, int MAT>
+// STREAM: as k_step's.
+template <typename R, int MAT, bool STREAM>
 __device__ __forceinline__ void step_node(const R* __restrict__ src, R* __restrict__ dst, const R* __restrict__ phi_f,
                                           const R* __restrict__ invk_f, const R* __restrict__ d_f,
                                           const Consts3<R>& k, int x, int y, int z) {
@@ -413,15 +422,14 @@ __device__ __forceinline__ void step_node(const R* __restrict__ src, R* __restri
   const Mat3<R> mp = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y, z);
   Mat3<R> mt = mp;
   if (inlet || outlet) mt = material<R, MAT>(k, phi_f, invk_f, d_f, x, y, z);
-  const int o = (z * k.ny + y) * k.pitch + x;
   Macro3<R> a, nb{};
   {
     R f[19];
-    pull_range<R, 0, 19>(src, k, xp, y, z, f);
+    pull_range<R, 0, 19, STREAM>(src, k, xp, y, z, f);
     if (inlet || outlet) nb = boundary_flow(f, k, y, z, inlet, mp, mt);
     a = flow_macros(f, mt, k);
     collide_flow(f, a, mt, k);
-    store_range<R, 0, 19>(dst, k, o, f);
+    store_range<R, 0, 19, STREAM ? 0 : 16>(dst, k, x, y, z, f);
   }
   if (outlet) {  // scalar material of column nx-2 at the outlet
     mt.aT = mp.aT;
@@ -429,10 +437,10 @@ __device__ __forceinline__ void step_node(const R* __restrict__ src, R* __restri
     mt.rhocp = mp.rhocp;
   }
   R g[14];
-  pull_range<R, 19, 33>(src, k, xp, y, z, g);
+  pull_range<R, 19, 33, STREAM>(src, k, xp, y, z, g);
   if (inlet) boundary_scalars_inlet(g, k, y, z, nb, mp, mt);
   collide_scalars(g, a.ux, a.uy, a.uz, mt, k, z >= k.z_cl0 && !(k.flags & F_NO_REACTION));
-  store_range<R, 19, 33>(dst, k, o, g);
+  store_range<R, 19, 33, STREAM ? 0 : 16>(dst, k, x, y, z, g);
 }
 
 }  // namespace lbm3

@@ -10,34 +10,32 @@ namespace lbm3 {
 constexpr int kBlock3 = 256;
 constexpr int kObsQ3 = 9;
 
-// Row order of the launch.  Rows (y, z) are visited in chunks of `ty`
-// consecutive y: all z of the first chunk, then all z of the next, so the
-// rows a z-neighbour pull touches were loaded ty rows earlier (not ny).  The
-// eight XCDs receive consecutive workgroups round-robin; each gets one
-// contiguous range of this order, so z- and y-neighbours share an L2.
-__device__ __forceinline__ void row_of(int flat, int total, int nbx, int ny, int nz, int ty, int& bx, int& y,
-                                       int& z) {
-  const int xcd = flat & 7;
-  const int slot = flat >> 3;
-  const int full = total >> 3, rem = total & 7;
+// Node of a thread of the step kernels: a workgroup covers kBlock3
+// consecutive nodes of one row (thread t holds x = kBlock3 b + t - shift).
+// Rows (y, z) are visited in chunks of `ty` consecutive y: all z of the first
+// chunk, then all z of the next, so the rows a z-neighbour pull touches were
+// loaded ty rows earlier (not ny).  The eight XCDs receive consecutive
+// workgroups round-robin; each gets one contiguous range of this order, so z-
+// and y-neighbours share an L2.  False: no such node.  (Workgroups of four
+// consecutive wavefronts of the row order, which leave none idle at row
+// lengths that are no multiple of 256, were slower: 97x50x33 FP64 17.7 ->
+// 19.5 us, 160x80x40 FP32 25.8 -> 29.8.)
+inline __host__ __device__ int row_blocks(int nx, int shift) { return (nx + shift + kBlock3 - 1) / kBlock3; }
+template <typename R>
+__device__ __forceinline__ bool node_of(const Consts3<R>& k, int shift, int& x, int& y, int& z) {
+  const int flat = blockIdx.x, total = gridDim.x;
+  const int xcd = flat & 7, slot = flat >> 3, full = total >> 3, rem = total & 7;
   const int logical = xcd * full + (xcd < rem ? xcd : rem) + slot;
-  const int row = logical / nbx;
-  bx = logical - row * nbx;
-  const int per_chunk = ty * nz;
+  const int nbx = row_blocks(k.nx, shift), row = logical / nbx;
+  const int per_chunk = k.ty * k.nz;
   const int chunk = row / per_chunk;
-  const int y0 = chunk * ty;
-  const int h = (ny - y0) < ty ? (ny - y0) : ty;  // the last chunk may be short
+  const int y0 = chunk * k.ty;
+  const int h = (k.ny - y0) < k.ty ? (k.ny - y0) : k.ty;  // the last chunk may be short
   const int r = row - chunk * per_chunk;
   z = r / h;
   y = y0 + (r - z * h);
-}
-
-template <typename R>
-__device__ __forceinline__ void node_of(const Consts3<R>& k, int& x, int& y, int& z) {
-  const int nbx = (k.nx + kBlock3 - 1) / kBlock3;
-  int bx;
-  row_of(blockIdx.x, gridDim.x, nbx, k.ny, k.nz, k.ty, bx, y, z);
-  x = bx * kBlock3 + threadIdx.x;
+  x = (logical - row * nbx) * kBlock3 + int(threadIdx.x) - shift;
+  return (unsigned)x < (unsigned)k.nx;
 }
 
 // Waves per SIMD the FP32 step is compiled for: the flow and scalar passes
@@ -49,14 +47,13 @@ struct StepWaves3 {
   static constexpr int value = sizeof(R) == 4 ? 8 : 1;
 };
 
-template <typename R, int MAT>
+template <typename R, int MAT, bool STREAM>
 __global__ __launch_bounds__(kBlock3) __attribute__((amdgpu_waves_per_eu(StepWaves3<R>::value)))
 void k3_step(const R* __restrict__ src, R* __restrict__ dst, const R* __restrict__ phi_f,
              const R* __restrict__ invk_f, const R* __restrict__ d_f, Consts3<R> k) {
   int x, y, z;
-  node_of(k, x, y, z);
-  if (x >= k.nx) return;
-  step_node<R, MAT>(src, dst, phi_f, invk_f, d_f, k, x, y, z);
+  if (!node_of(k, 0, x, y, z)) return;
+  step_node<R, MAT, STREAM>(src, dst, phi_f, invk_f, d_f, k, x, y, z);
 }
 
 // Rest fluid at zero pressure (shifted f = 0), theta = 0, O2 at c_in.

@@ -97,6 +97,11 @@ __device__ __forceinline__ void outlet_scalar_adj_material(AdjMat<R>& mb, const 
   mb.isig = mp.isig;
 }
 
+// Lane shift of the reverse step: lane l of a row's first workgroup holds
+// x = l - shift, so that columns nx - 2 and nx - 1 share a wavefront (as
+// columns 0 and 1 do) at every width.
+__host__ __device__ inline int adj_lane_shift(int nx) { return ((nx - 1) & 63) == 0 ? 1 : 0; }
+
 // EXT: the instances of the reverse step that also cover Boussinesq
 // buoyancy, the energy equation with the heat-capacity ratio sigma, the
 // pressure-driven inlet and the thin-film CL; the default instances leave
@@ -406,7 +411,7 @@ __device__ __forceinline__ void flow_adj(const MacroTape<R>& t, const AdjMat<R>&
   const R d13 = la[1] - la[3], d24 = la[2] - la[4], d57 = la[5] - la[7], d68 = la[6] - la[8];
   const R lB = R(0.25) * (s57 + s68);
   const R lA = fma_(R(0.25), s13 + s24, -lB), lN = R(0.25) * (s13 - s24), lM2 = R(0.125) * (s57 - s68);
-  const R c6 = R(1.0 / 6.0);
+  const R c6 = R(1.0 / 6.0);  // rounded as in the forward step: j' = 6 fl(1/6) j there, and here
   const R gx = c6 * (d57 - d68), gy = c6 * (d57 + d68);
   const R ljx = fma_(c6, d13, gx), ljy = fma_(c6, d24, gy);
   const R lqx = fma_(-c6, d13, R(0.5) * gx), lqy = fma_(-c6, d24, R(0.5) * gy);

@@ -53,11 +53,6 @@ __device__ __forceinline__ R load_own(const R* __restrict__ p, const PlaneBuffer
   return k.near32 ? b.template load<0>(q, 0, 0, uint32_t(o) * uint32_t(sizeof(R))) : p[q * k.plane + o];
 }
 
-// Lane shift of the reverse step: lane l of a row's first workgroup holds
-// x = l - shift, so that columns nx - 2 and nx - 1 share a wavefront (as
-// columns 0 and 1 do) at every width.
-__host__ __device__ inline int adj_lane_shift(int nx) { return ((nx - 1) & 63) == 0 ? 1 : 0; }
-
 // One reverse step: lam_out = (dS'/dS)^T lam_in at the state S, gradients
 // accumulated into grad (planes phi, 1/K, D_eff).  SEED: lam_out = dJ/dS
 // (times w = dJ dx / nx * 4 F C_ref / dt), no lam_in.
@@ -73,13 +68,11 @@ __host__ __device__ inline int adj_lane_shift(int nx) { return ((nx - 1) & 63) =
 // Small lattices are bound by one wavefront's chain, large ones by HBM (in
 // FP32 S, lambda in and out, the gradient twice, the fields: 264 bytes a
 // node).  Holding all nineteen populations, the moment-matrix transposes and
-// 57 four-register buffer resources at once took 128 VGPRs and spilled: 544
+// the buffer resources of 57 planes at once took 128 VGPRs and spilled: 544
 // bytes of scratch per lane in FP64 and 482 scalar-register spills.  Now 71
 // (FP32) and 135 (FP64) VGPRs without a spill; per reverse step at 200x40
 // FP64 29.8 -> 9.2 us, at 1024x256 FP32 (beside the replay) 18.0 -> 17.2 us.
-// The compiler places spills of scalar registers into vector lanes, and the
-// spilled forms' gradients have differed from run to run; every instance
-// here, with and without the model options, is free of them.
+// (Gradients of the spilled forms have differed from run to run.)
 template <typename R, bool SEED, bool EXT = false>
 __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, const R* __restrict__ lam_in,
                                                      R* __restrict__ lam_out, R* __restrict__ grad,

@@ -41,7 +41,7 @@ struct Consts {
   uint32_t flags;
   int32_t plane;        // stride between population q and q + 1
   int32_t bv;           // nonzero: Butler-Volmer kinetics (anodic branch), else the printed Tafel form
-  int32_t near32;       // nonzero: the byte offsets of PlaneBuffer fit 32 bits (near_offsets)
+  int32_t near32;       // nonzero: the lane offsets of PlaneBuffer fit 32 bits (near_offset)
   // flow (Section 2.1)
   R s_e, s_q, nu;       // s_e: rate of rho, e, zeta, pxx, pxy; s_q: energy flux
   R u_in_coef;          // 6 U_avg / H_channel^2
@@ -213,52 +213,36 @@ __device__ __forceinline__ R buffer_load(const R* base, uint32_t byte_off) {
   }
 }
 
-template <typename R>
+template <int AUX = 0, typename R>
 __device__ __forceinline__ void buffer_store(R* base, uint32_t byte_off, R v) {
   if constexpr (sizeof(R) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), buffer_of(base), int(byte_off), 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), buffer_of(base), int(byte_off), 0, AUX);
   } else {
     using U2 = uint32_t __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), buffer_of(base), int(byte_off), 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), buffer_of(base), int(byte_off), 0, AUX);
   }
 }
 
-// Wave-uniform bases of one 19-plane buffer: five raw buffer resources of
-// four planes each, each based one row and one element
-// before row yb of its first plane so that every neighbour shift is a
-// non-negative scalar byte offset.  One 32-bit lane offset (of the node from
-// (0, yb)) serves all planes, and a plane costs one scalar register (its own
-// resource would cost four: at 57 planes that spilled scalar registers).
+// Wave-uniform bases of a 19-plane buffer at row yb: a plane and a neighbour
+// shift fold into the base of a raw buffer resource in scalar registers, and
+// one 32-bit lane offset (of the node from (0, yb)) serves all planes.  (One
+// resource for several planes with a scalar offset per plane saves scalar
+// registers, but such loads and stores are slower: 1024x256 FP32 single
+// steps 7.9 against 7.6 us, 4096x1024 in pairs 86.2 against 82.9.)
 template <typename R>
 struct PlaneBuffer {
-  __amdgpu_buffer_rsrc_t r[5];
-  uint32_t plane, pitch;  // bytes
-  __device__ __forceinline__ PlaneBuffer(const R* p, const Consts<R>& k, int yb = 0) {
-    p += int64_t(yb - 1) * k.pitch - 1;
-    plane = uint32_t(k.plane) * uint32_t(sizeof(R));
-    pitch = uint32_t(k.pitch) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int g = 0; g < 5; ++g) r[g] = buffer_of(p + int64_t(4 * g) * k.plane);
-  }
-  // byte offset of population q of the node displaced by (dx, dy)
-  __device__ __forceinline__ uint32_t off(int q, int dx, int dy) const {
-    return uint32_t(q & 3) * plane + uint32_t(1 + dy) * pitch + uint32_t(1 + dx) * uint32_t(sizeof(R));
-  }
+  const R* p;
+  const Consts<R>& k;
+  __device__ __forceinline__ PlaneBuffer(const R* base, const Consts<R>& c, int yb = 0)
+      : p(base + int64_t(yb) * c.pitch), k(c) {}
+  // population q of the node displaced by (dx, dy), of which ob is the byte offset
   template <int AUX>
   __device__ __forceinline__ R load(int q, int dx, int dy, uint32_t ob) const {
-    if constexpr (sizeof(R) == 4)
-      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
-    else
-      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(r[q >> 2], int(ob), int(off(q, dx, dy)), AUX));
+    return buffer_load<R, AUX>(p + (int64_t(q) * k.plane + int64_t(dy) * k.pitch + dx), ob);
   }
   template <int AUX = 0>
   __device__ __forceinline__ void store(int q, int dx, int dy, uint32_t ob, R v) const {
-    if constexpr (sizeof(R) == 4) {
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r[q >> 2], int(ob), int(off(q, dx, dy)), AUX);
-    } else {
-      using U2 = uint32_t __attribute__((ext_vector_type(2)));
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r[q >> 2], int(ob), int(off(q, dx, dy)), AUX);
-    }
+    buffer_store<AUX>(const_cast<R*>(p) + (int64_t(q) * k.plane + int64_t(dy) * k.pitch + dx), ob, v);
   }
 };
 

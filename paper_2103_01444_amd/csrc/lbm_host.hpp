@@ -38,13 +38,11 @@ inline int64_t plane_elems(int64_t pitched_cells) {
   return pitched_cells >= kPadMinCells ? pitched_cells + kPlanePad : pitched_cells;
 }
 
-// Whether every byte offset a PlaneBuffer adds to a base fits 32 bits: four
-// planes, a lane's offset (rows: the rows it may count over) and a row of
-// neighbour shift.  False only for states of about 16 GB, and batch cases of
-// rows of 400 000 nodes or more.
-inline int32_t near_offsets(int64_t plane, int64_t pitch, int64_t lane, size_t esize) {
-  return (4 * plane + 2 * pitch + lane) * int64_t(esize) < (int64_t(1) << 32);
-}
+// Whether a lane's byte offset from the first row of its wavefront or tile
+// fits 32 bits: over a whole plane in the planar layout (always: 19 planes
+// hold fewer than 2^31 elements), over 64 rows in the batch's (not for rows
+// of 400 000 nodes or more).
+inline int32_t near_offset(int64_t lane, size_t esize) { return lane * int64_t(esize) < (int64_t(1) << 32); }
 
 // Scalars derived from (geometry, params).
 struct Derived {
@@ -185,7 +183,7 @@ void fill_consts(Consts<R>& k, const lbm_geometry& g, const lbm_params& p, const
   k.flags = g.flags;
   k.plane = int32_t(plane_elems(int64_t(pitch) * g.ny));
   k.bv = p.kinetics == LBM_KINETICS_BUTLER_VOLMER;
-  k.near32 = near_offsets(k.plane, pitch, k.plane, sizeof(R));
+  k.near32 = near_offset(k.plane, sizeof(R));
   const double se = 1.0 / p.tau_f;
   k.s_e = R(se);
   k.s_q = R(8.0 * (2.0 - se) / (8.0 - se));
