@@ -6,11 +6,10 @@
 // adjoint of S is obtained per node x by
 //   mu_x  = (dC_x / d pre_x)^T lambda_x                       (collision)
 //   mu_xp += (dB / d pre_xp)^T mu_b     for the boundary node b fed by xp
-//   lambda_new[source of pull (x, q)] = mu_x[q]                (push)
-// Every element of the state is pulled by exactly one node, so the push
-// writes every element of lambda_new once; boundary nodes, whose pulled
-// values the forward step discards, write zeros.  Each node accumulates
-// only its own gradient with respect to (porosity, 1/K, D_eff).
+//   lambda_new[source of pull (x, q)] = mu_x[q]
+// Every element of the state is pulled by exactly one node; boundary nodes,
+// whose pulled values the forward step discards, have mu = 0.  Each node
+// accumulates only its own gradient with respect to (porosity, 1/K, D_eff).
 #pragma once
 
 #include "lbm_device.hpp"

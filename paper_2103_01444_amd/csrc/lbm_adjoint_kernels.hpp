@@ -1,13 +1,14 @@
 // Kernels of the reverse sweep (three per-cell fields: porosity, 1/K, D_eff).
 #pragma once
 
+#include <type_traits>
+
 #include "lbm_adjoint.hpp"
 #include "lbm_kernels2d.hpp"
 
 namespace lbm {
 
-// Element offset the pull of population q at (x, y) reads, and the push of
-// its adjoint writes.
+// Element offset the pull of population q at (x, y) reads.
 template <typename R>
 __device__ __forceinline__ int pull_offset(const Consts<R>& k, int q, int x, int y) {
   int xs = x - EX[q];
@@ -18,72 +19,87 @@ __device__ __forceinline__ int pull_offset(const Consts<R>& k, int q, int x, int
   return in ? (q * k.plane + ys * k.pitch + xs) : (OPP[q] * k.plane + y * k.pitch + x);
 }
 
-// Populations [Q0, Q1) of node (x, y): inner (the wavefront lies one node or
-// more inside the lattice) through the wave-uniform bases.
-template <typename R, int Q0, int Q1>
-__device__ __forceinline__ void pull_part(const R* __restrict__ S, const PlaneBuffer<R>& b, const Consts<R>& k,
-                                          bool inner, int x, int y, R* f) {
-  if (inner) {
-    const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = Q0; q < Q1; ++q) f[q - Q0] = b.template load<2>(q, -EX[q], -EY[q], ob);
-  } else {
-#pragma unroll
-    for (int q = Q0; q < Q1; ++q) f[q - Q0] = __builtin_nontemporal_load(S + pull_offset(k, q, x, y));
-  }
-}
-
-template <typename R, int Q0, int Q1>
-__device__ __forceinline__ void push_part(R* __restrict__ lam, const PlaneBuffer<R>& b, const Consts<R>& k,
-                                          bool inner, int x, int y, const R* mu) {
-  if (inner) {
-    const uint32_t ob = uint32_t(y * k.pitch + x) * uint32_t(sizeof(R));
-#pragma unroll
-    for (int q = Q0; q < Q1; ++q) b.store(q, -EX[q], -EY[q], ob, mu[q - Q0]);
-  } else {
-#pragma unroll
-    for (int q = Q0; q < Q1; ++q) lam[pull_offset(k, q, x, y)] = mu[q - Q0];
-  }
-}
-
-// Population q of the node at element offset o.
+// The adjoint of S is kept as each node's mu (the adjoint of what the node
+// pulled), in the same planes as a state.  Population q of node (x, y) was
+// pulled by (x + e_q), or, where that link crosses a wall, by the node itself
+// as its opposite: the element of mu that holds its adjoint.
 template <typename R>
-__device__ __forceinline__ R load_own(const R* __restrict__ p, const PlaneBuffer<R>& b, const Consts<R>& k, int q,
-                                      int o) {
-  return k.near32 ? b.template load<0>(q, 0, 0, uint32_t(o) * uint32_t(sizeof(R))) : p[q * k.plane + o];
+__device__ __forceinline__ int puller_offset(const Consts<R>& k, int q, int x, int y) {
+  int xs = x + EX[q];
+  int ys = y + EY[q];
+  if (k.flags & F_PERIODIC_X) xs = xs < 0 ? xs + k.nx : (xs >= k.nx ? xs - k.nx : xs);
+  if (k.flags & F_PERIODIC_Y) ys = ys < 0 ? ys + k.ny : (ys >= k.ny ? ys - k.ny : ys);
+  const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny;
+  return in ? (q * k.plane + ys * k.pitch + xs) : (OPP[q] * k.plane + y * k.pitch + x);
 }
 
-// One reverse step: lam_out = (dS'/dS)^T lam_in at the state S, gradients
-// accumulated into grad (planes phi, 1/K, D_eff).  SEED: lam_out = dJ/dS
-// (times w = dJ dx / nx * 4 F C_ref / dt), no lam_in.
+// Populations [Q0, Q1) of node (x, y), y the wavefront's row; inner: the
+// wavefront lies one node or more inside the lattice (wave-uniform bases).
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void pull_part(const R* __restrict__ S, const Consts<R>& k, bool inner, int x, int y,
+                                          R* f) {
+  if (inner) {
+    const PlaneBuffer<R> b(S, k, y);
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q)
+      f[q - Q0] = b.template load<0>(q, -EX[q], -EY[q], uint32_t(x) * uint32_t(sizeof(R)));
+  } else {
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) f[q - Q0] = S[pull_offset(k, q, x, y)];
+  }
+}
+
+// Adjoint of the post-collision populations [Q0, Q1) of node (x, y) from mu.
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void gather_part(const R* __restrict__ mu, const Consts<R>& k, bool inner, int x, int y,
+                                            R* la) {
+  if (inner) {
+    const PlaneBuffer<R> b(mu, k, y);
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q)
+      la[q - Q0] = b.template load<0>(q, EX[q], EY[q], uint32_t(x) * uint32_t(sizeof(R)));
+  } else {
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) la[q - Q0] = mu[puller_offset(k, q, x, y)];
+  }
+}
+
+// Store [Q0, Q1) of node (x, y), y the wavefront's row.
+template <typename R, int Q0, int Q1>
+__device__ __forceinline__ void store_part(R* __restrict__ mu, const Consts<R>& k, int x, int y, const R* v) {
+  const PlaneBuffer<R> b(mu, k, y);
+#pragma unroll
+  for (int q = Q0; q < Q1; ++q) b.template store<16>(q, 0, 0, uint32_t(x) * uint32_t(sizeof(R)), v[q - Q0]);
+}
+
+// The reverse step of one node: mu = (dS'/d pulled)^T lambda at the state S.
+// SEED: of J (times w = dJ dx / nx * 4 F C_ref / dt), no lambda.
+//
+// A wavefront holds consecutive nodes of row y, lane l the node x = xl + l;
+// both nodes of a boundary pair (0, 1) and (nx - 2, nx - 1) if it holds
+// either.  gather(q0, la) fills la with the adjoints of the populations from
+// q0 on (10 scalar ones from 9, 9 flow ones from 0); put(q0, mu) takes mu.
+// g0, g1, g2: the gradient with respect to the node's (phi, 1/K, D_eff).
 //
 // Two passes per node: the ten scalar populations (pull, adjoint of their
-// collisions, push), which leave the velocity's adjoint, then the nine flow
-// ones, so that about 30 values are live at once.  A boundary lane runs its
-// own node's collision adjoint in the common passes on its extrapolated
+// collisions), which leave the velocity's adjoint, then the nine flow ones,
+// so that about 30 values are live at once.  A boundary lane runs its own
+// node's collision adjoint in the common passes on its extrapolated
 // populations; the lane of the feeding column takes the boundary node's
 // result across lanes and runs the transposed extrapolation, while the
 // boundary lane keeps what belongs to its own material.
 //
-// Small lattices are bound by one wavefront's chain, large ones by HBM (in
-// FP32 S, lambda in and out, the gradient twice, the fields: 264 bytes a
-// node).  Holding all nineteen populations, the moment-matrix transposes and
-// the buffer resources of 57 planes at once took 128 VGPRs and spilled: 544
-// bytes of scratch per lane in FP64 and 482 scalar-register spills.  Now 71
-// (FP32) and 135 (FP64) VGPRs without a spill; per reverse step at 200x40
-// FP64 29.8 -> 9.2 us, at 1024x256 FP32 (beside the replay) 18.0 -> 17.2 us.
-// (Gradients of the spilled forms have differed from run to run.)
-template <typename R, bool SEED, bool EXT = false>
-__global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, const R* __restrict__ lam_in,
-                                                     R* __restrict__ lam_out, R* __restrict__ grad,
-                                                     const R* __restrict__ phi_f, const R* __restrict__ invk_f,
-                                                     const R* __restrict__ d_f, Consts<R> k, R w) {
-  int bx, by;
-  xcd_tile(gridDim.x, gridDim.y, bx, by);
-  const int shift = adj_lane_shift(k.nx);
-  const int x = bx * kBlock + int(threadIdx.x) - shift;
-  const int y = by;
-  if ((unsigned)x >= (unsigned)k.nx) return;
+// Small lattices are bound by one wavefront's chain, large ones by HBM.
+// Holding all nineteen populations, the moment-matrix transposes and the
+// buffer resources of 57 planes at once took 128 VGPRs and spilled: 544 bytes
+// of scratch per lane in FP64 and 482 scalar-register spills; in two passes
+// no instance spills vector registers.  Per reverse step at 200x40 FP64 29.8
+// -> 9.2 us.  (Gradients of the spilled forms have differed from run to run.)
+template <typename R, bool SEED, bool EXT, typename Gather, typename Put>
+__device__ __forceinline__ void reverse_node(const R* __restrict__ S, const R* __restrict__ phi_f,
+                                             const R* __restrict__ invk_f, const R* __restrict__ d_f,
+                                             const Consts<R>& k, int x, int y, int xl, bool inner, R w,
+                                             const Gather& gather, const Put& put, R& g0, R& g1, R& g2) {
   const bool open = !(k.flags & F_PERIODIC_X);
   const bool react = !(k.flags & F_NO_REACTION);
   const bool cl = react && y >= k.y_cl0;
@@ -92,18 +108,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   const bool outlet = open && x == k.nx - 1;
   const bool bnode = inlet || outlet;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
-  const int l0 = (x + shift) & ~63;  // first lane of the wavefront, as an x + shift
-  const bool w_in = in_row && l0 == 0, w_out = open && l0 == ((k.nx - 1 + shift) & ~63);
-  const int lane_out = (k.nx - 1 + shift) & 63;
+  const int lane_in = -xl, lane_out = k.nx - 1 - xl;  // lanes of columns 0 and nx - 1
+  const bool w_in = in_row && lane_in >= 0 && lane_in < 63, w_out = open && lane_out >= 1 && lane_out < 64;
   const bool pressure = EXT && (k.flags & F_PRESSURE_INLET);
-  const bool inner = k.near32 && __all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2);
-  const int o = y * k.pitch + x;
-  const PlaneBuffer<R> bS(S, k), bi(lam_in, k), bo(lam_out, k);
 
   AdjMat<R> m = adj_material<R>(k, phi_f, invk_f, d_f, xp, y);
   R f[9], g[10];
-  pull_part<R, 9, 19>(S, bS, k, inner, xp, y, g);
-  pull_part<R, 0, 9>(S, bS, k, inner, xp, y, f);
+  pull_part<R, 9, 19>(S, k, inner, xp, y, g);
+  pull_part<R, 0, 9>(S, k, inner, xp, y, f);
   // Thin-film CL (EXT): the bottom row's wall-crossing populations react as
   // the forward pull left them (column nx - 2's film for the outlet).
   const bool film = EXT && (k.flags & F_THIN_CL) && react && y == k.ny - 1;
@@ -151,8 +163,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
     }
   } else {
     R la[10];
-#pragma unroll
-    for (int q = 0; q < 10; ++q) la[q] = load_own(lam_in, bi, k, 9 + q, o);
+    gather(std::integral_constant<int, 9>{}, la);
     scalars_adj<R, EXT>(g, t.ux, t.uy, m, k, cl, la, mus, lux, luy, ma);
   }
   // With buoyancy the boundary nodes' temperature adjoint also has a share
@@ -166,8 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
       for (int q = 0; q < 9; ++q) muf[q] = R(0);
     } else {
       R la[9];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) la[q] = load_own(lam_in, bi, k, q, o);
+      gather(std::integral_constant<int, 0>{}, la);
       flow_adj<R, EXT>(t, m, k, la, lux, luy, muf, lth, ma);
       if (buoyant) {
         const R l = theta_adj<R, EXT>(lth, t.thb, m, k, ma);
@@ -183,8 +193,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   if (w_in) {
     R mub[10];
 #pragma unroll
-    for (int q = 0; q < 10; ++q) mub[q] = __shfl(mus[q], shift, 64);
-    const R uxp = __shfl(t.ux, shift + 1, 64), uyp = __shfl(t.uy, shift + 1, 64);
+    for (int q = 0; q < 10; ++q) mub[q] = __shfl(mus[q], lane_in, 64);
+    const R uxp = __shfl(t.ux, lane_in + 1, 64), uyp = __shfl(t.uy, lane_in + 1, 64);
     if (x <= 1) {
       MatAdj<R> axp{}, ab{};
       R lt1 = R(0), lc1 = R(0);
@@ -221,14 +231,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   }
   // A boundary node's pulled sources were never read by the forward step:
   // their adjoint is 0.
-  auto push_scalars = [&]() {
+  auto put_scalars = [&]() {
     if (bnode) {
 #pragma unroll
       for (int q = 0; q < 10; ++q) mus[q] = R(0);
     }
-    push_part<R, 9, 19>(lam_out, bo, k, inner, x, y, mus);
+    put(std::integral_constant<int, 9>{}, mus);
   };
-  if (!EXT) push_scalars();
+  if (!EXT) put_scalars();
 
   // ---- flow ----
   if (!EXT) flow_pass();
@@ -238,7 +248,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
       if (!(side == 0 ? w_in : w_out)) continue;
-      const int lb = side == 0 ? shift : lane_out, lp = side == 0 ? shift + 1 : lane_out - 1;
+      const int lb = side == 0 ? lane_in : lane_out, lp = side == 0 ? lane_in + 1 : lane_out - 1;
       R mub[9];
 #pragma unroll
       for (int q = 0; q < 9; ++q) mub[q] = __shfl(muf[q], lb, 64);
@@ -288,12 +298,12 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
     const R ls = SEED ? ((open && x == k.nx - 2) ? R(2) * w : w) : R(0);
     film_adj(ft, m, k, ls, mus[4], mus[9], ma);
   }
-  if (EXT) push_scalars();
+  if (EXT) put_scalars();
   if (bnode) {
 #pragma unroll
     for (int q = 0; q < 9; ++q) muf[q] = R(0);
   }
-  push_part<R, 0, 9>(lam_out, bo, k, inner, x, y, muf);
+  put(std::integral_constant<int, 0>{}, muf);
 
   // The gradient of this node's own material; the outlet's scalar-material
   // terms went to column nx - 2.
@@ -303,24 +313,120 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
     ma.rhocp = R(0);
     ma.sig = R(0);
   }
-  R g0 = R(0), g1 = R(0), g2 = R(0);
+  g0 = g1 = g2 = R(0);
   material_adj<R, EXT>(k, m, ma, g0, g1, g2);
+}
+
+// One reverse step, one launch: mu_out at the state S from mu_in, gradients
+// accumulated into grad (planes phi, 1/K, D_eff).
+template <typename R, bool SEED, bool EXT = false>
+__global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, const R* __restrict__ mu_in,
+                                                     R* __restrict__ mu_out, R* __restrict__ grad,
+                                                     const R* __restrict__ phi_f, const R* __restrict__ invk_f,
+                                                     const R* __restrict__ d_f, Consts<R> k, R w) {
+  int bx, y;
+  xcd_tile(gridDim.x, gridDim.y, bx, y);
+  const int x = bx * kBlock + int(threadIdx.x) - adj_lane_shift(k.nx);
+  if ((unsigned)x >= (unsigned)k.nx) return;
+  const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
+  R g0, g1, g2;
+  reverse_node<R, SEED, EXT>(
+      S, phi_f, invk_f, d_f, k, x, y, x - int(threadIdx.x & 63), inner, w,
+      [&](auto q0, auto& la) { gather_part<R, q0(), q0() + sizeof(la) / sizeof(R)>(mu_in, k, inner, x, y, la); },
+      [&](auto q0, const auto& mu) { store_part<R, q0(), q0() + sizeof(mu) / sizeof(R)>(mu_out, k, x, y, mu); }, g0,
+      g1, g2);
+  const int o = y * k.pitch + x;
   grad[o] += g0;
   grad[k.plane + o] += g1;
   grad[2 * k.plane + o] += g2;
 }
 
+// Two reverse steps in one launch, at the states S1 (first) and S0, with the
+// bits of two single ones.  A workgroup takes a tile of at most kAdjX columns
+// and ROWS - 2 rows.  The first step runs over the tile and a ring of one
+// node, extended to both nodes of a boundary pair where it holds one, a row
+// per wavefront, and leaves mu in LDS; the second gathers from there and
+// writes the tile's.  Of the 264 bytes a node that a single FP32 step moves
+// (S, mu in and out, the gradient twice, the fields) lambda's 152 and the
+// gradient's 24 are halved, and the ring adds a share of S and mu.  Reverse
+// sweep with its replay, per step, one -> two steps per launch: 1024x256 FP32
+// 24.5 -> 18.7 us.  ROWS = 8, or 4 on lattices of fewer than 2^17 nodes,
+// which leave CUs idle (200x40 FP64 13.3 -> 10.4, FP32 9.8 -> 9.3; 1024x256
+// FP32 18.7 with 8, 19.7 with 4, 19.0 with 12).  Lattices without periodic
+// axes.
+constexpr int kAdjX = 60;
+template <typename R, bool EXT, int ROWS>
+__global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S1, const R* __restrict__ S0,
+                                                             const R* __restrict__ mu_in, R* __restrict__ mu_out,
+                                                             R* __restrict__ grad, const R* __restrict__ phi_f,
+                                                             const R* __restrict__ invk_f,
+                                                             const R* __restrict__ d_f, Consts<R> k) {
+  __shared__ R lds[ROWS * 19 * 64];
+  int bx, by;
+  xcd_tile(gridDim.x, gridDim.y, bx, by);
+  // tiles equal within one column
+  const int x0 = int(int64_t(bx) * k.nx / gridDim.x), x1 = int(int64_t(bx + 1) * k.nx / gridDim.x);
+  int xl = x0 > 0 ? x0 - 1 : 0, xr = x1 < k.nx ? x1 + 1 : k.nx;  // the first step's columns
+  if (xl == 1) xl = 0;
+  if (xr == k.nx - 1) xr = k.nx;
+  const int i = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x = xl + i, y0 = by * (ROWS - 2), y = y0 - 1 + j;
+  const bool row = (unsigned)y < (unsigned)k.ny;
+  const bool own = x >= x0 && x < x1 && j >= 1 && j < ROWS - 1;
+  R ga[3] = {R(0), R(0), R(0)}, gb[3] = {R(0), R(0), R(0)};
+  if (row && x < xr) {
+    const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
+    R* p = lds + j * 19 * 64 + i;
+    reverse_node<R, false, EXT>(
+        S1, phi_f, invk_f, d_f, k, x, y, xl, inner, R(0),
+        [&](auto q0, auto& la) { gather_part<R, q0(), q0() + sizeof(la) / sizeof(R)>(mu_in, k, inner, x, y, la); },
+        [&](auto q0, const auto& mu) {
+#pragma unroll
+          for (int q = 0; q < int(sizeof(mu) / sizeof(R)); ++q) p[(q0() + q) * 64] = mu[q];
+        },
+        ga[0], ga[1], ga[2]);
+  }
+  __syncthreads();
+  // the second step: the tile, 30 columns or more wide (or the whole row), so
+  // that it holds both nodes of a boundary pair or neither
+  if (!(row && own)) return;
+  const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
+  const R* p = lds + j * 19 * 64 + i;
+  reverse_node<R, false, EXT>(
+      S0, phi_f, invk_f, d_f, k, x, y, xl, inner, R(0),
+      [&](auto q0, auto& la) {
+#pragma unroll
+        for (int n = 0; n < int(sizeof(la) / sizeof(R)); ++n) {
+          const int q = q0() + n;
+          const int xs = x + EX[q], ys = y + EY[q];
+          const bool in = inner || ((unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny);
+          la[n] = p[in ? (EY[q] * 19 + q) * 64 + EX[q] : OPP[q] * 64];
+        }
+      },
+      [&](auto q0, const auto& mu) {
+        store_part<R, q0(), q0() + sizeof(mu) / sizeof(R)>(mu_out, k, x, y, mu);
+      },
+      gb[0], gb[1], gb[2]);
+  const int o = y * k.pitch + x;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int n = c * k.plane + o;
+    grad[n] = (grad[n] + ga[c]) + gb[c];
+  }
+}
+
 // Gradient through the initial state: the O2 equilibrium at rest depends on
-// b_C = 20 sqrt(3) D - 4 (Eq. 10).
+// b_C = 20 sqrt(3) D - 4 (Eq. 10).  mu: the first step's.
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_adj_init(const R* __restrict__ lam0, R* __restrict__ grad, Consts<R> k) {
+__global__ __launch_bounds__(kBlock) void k_adj_init(const R* __restrict__ mu, R* __restrict__ grad, Consts<R> k) {
   const int x = blockIdx.x * kBlock + threadIdx.x;
   const int y = blockIdx.y;
   if (x >= k.nx) return;
-  const int o = y * k.pitch + x;
-  const R l0 = lam0[14 * k.plane + o];
-  const R l14 = lam0[15 * k.plane + o] + lam0[16 * k.plane + o] + lam0[17 * k.plane + o] + lam0[18 * k.plane + o];
-  grad[2 * k.plane + o] += R(34.64101615137754587) * k.c_in * (-l0 * R(0.2) + l14 * R(0.05));
+  R l[5];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) l[q] = mu[puller_offset(k, 14 + q, x, y)];
+  grad[2 * k.plane + y * k.pitch + x] +=
+      R(34.64101615137754587) * k.c_in * (-l[0] * R(0.2) + (l[1] + l[2] + l[3] + l[4]) * R(0.05));
 }
 
 // Pitched plane -> dense [ny][nx] caller array.

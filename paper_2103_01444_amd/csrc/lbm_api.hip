@@ -745,6 +745,15 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
   const dim3 grid((c->g.nx + kBlock - 1) / kBlock, c->g.ny);
   const dim3 agrid((c->g.nx + adj_lane_shift(c->g.nx) + kBlock - 1) / kBlock, c->g.ny);
   R* grad = reinterpret_cast<R*>(ws + A.off_grad);
+  auto pair = [&](auto ext_form, auto rows_form, const R* S1, const R* S0, const R* in, R* out) {
+    constexpr int rows = rows_form();
+    const dim3 pgrid((c->g.nx + kAdjX - 1) / kAdjX, (c->g.ny + rows - 3) / (rows - 2));
+    hipLaunchKernelGGL((k_adj_step2<R, ext_form(), rows>), pgrid, dim3(64 * rows), 0, c->stream, S1, S0, in, out, grad,
+                       m.phi, m.invk, m.d, k);
+  };
+  const bool small = int64_t(c->g.nx) * c->g.ny < kT2SmallCells;
+  using Rows4 = std::integral_constant<int, 4>;
+  using Rows8 = std::integral_constant<int, 8>;
   R* lam[2] = {reinterpret_cast<R*>(ws + A.off_lam), reinterpret_cast<R*>(ws + A.off_lam + A.state)};
   const int64_t ngrad = int64_t(3) * c->L.plane;
   hipLaunchKernelGGL(k_fill<R>, dim3(unsigned((ngrad + kBlock - 1) / kBlock)), dim3(kBlock), 0, c->stream, grad,
@@ -808,14 +817,29 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
     if (hipStreamWaitEvent(c->stream, c->ev_rep[b], 0) != hipSuccess)
       return fail(c, LBM_ERR_DEVICE, "replay join failed");
     const char* buf = ws + A.off_replay + size_t(b) * rbuf;
-    for (int j = seg_len(seg) - 1; j >= 0; --j) {
-      const R* S = reinterpret_cast<const R*>(buf + size_t(j) * A.state);
-      if (ext)
-        hipLaunchKernelGGL((k_adj_step<R, false, true>), agrid, dim3(kBlock), 0, c->stream, S, lam[cur],
-                           lam[cur ^ 1], grad, m.phi, m.invk, m.d, k, R(0));
-      else
-        hipLaunchKernelGGL((k_adj_step<R, false>), agrid, dim3(kBlock), 0, c->stream, S, lam[cur], lam[cur ^ 1], grad,
-                           m.phi, m.invk, m.d, k, R(0));
+    const auto state = [&](int j) { return reinterpret_cast<const R*>(buf + size_t(j) * A.state); };
+    for (int j = seg_len(seg) - 1; j >= 0;) {
+      if (j >= 1 && two_steps_per_launch(c)) {
+        const R *S1 = state(j), *S0 = state(j - 1), *in = lam[cur];
+        R* out = lam[cur ^ 1];
+        if (ext && small)
+          pair(std::true_type{}, Rows4{}, S1, S0, in, out);
+        else if (ext)
+          pair(std::true_type{}, Rows8{}, S1, S0, in, out);
+        else if (small)
+          pair(std::false_type{}, Rows4{}, S1, S0, in, out);
+        else
+          pair(std::false_type{}, Rows8{}, S1, S0, in, out);
+        j -= 2;
+      } else {
+        if (ext)
+          hipLaunchKernelGGL((k_adj_step<R, false, true>), agrid, dim3(kBlock), 0, c->stream, state(j), lam[cur],
+                             lam[cur ^ 1], grad, m.phi, m.invk, m.d, k, R(0));
+        else
+          hipLaunchKernelGGL((k_adj_step<R, false>), agrid, dim3(kBlock), 0, c->stream, state(j), lam[cur],
+                             lam[cur ^ 1], grad, m.phi, m.invk, m.d, k, R(0));
+        --j;
+      }
       cur ^= 1;
     }
     if (hipEventRecord(c->ev_rev[b], c->stream) != hipSuccess) return fail(c, LBM_ERR_DEVICE, "sweep event failed");

@@ -37,3 +37,29 @@ def test_gradient_at_lane_boundaries(nx, options):
         err = float((out[name].cpu()[4:] - ref).abs().max() / ref.abs().max().clamp_min(1e-300))
         print(f"nx {nx} d/d{name}: rel err {err:.2e}", flush=True)
         assert err < 1e-9, (name, err)
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int64 if t.dtype == torch.float64 else torch.int32)
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("shape", [(3, 3), (59, 4), (60, 5), (61, 6), (62, 7), (121, 12), (122, 13), (181, 3),
+                                   (2185, 60), (2186, 61), (541, 243)], ids=lambda s: f"{s[0]}x{s[1]}")
+def test_reverse_pairs_equal_single_reverse_steps(shape, precision):
+    """Two reverse steps per launch at the edges of their tiles (60 columns;
+    two rows below 2^17 nodes, six above) against a checkpoint at every step,
+    whose segments are swept one step at a time: the same gradient bits."""
+    from paper_2103_01444_amd import lbm
+    nx, ny = shape
+    ch = max(1, ny // 2)
+    w = W.adjoint2d(64, 16)
+    w.update(nx=nx, ny=ny, ny_channel=ch, ny_gdl=ny - ch - 1, ny_cl=1, Re=0.5, V_op=0.45, precision=precision)
+    phi = torch.as_tensor(W.porosity_field(w))
+    sims = [lbm.Cathode.from_workload(w, phi=phi, independent_fields=1) for _ in range(2)]
+    J = [s.forward_checkpointed(13, every) for s, every in zip(sims, (5, 1))]
+    assert J[0] == J[1]
+    a, b = (s.backward(1.0, permeability=False) for s in sims)
+    for name in ("inv_k", "phi", "d_eff"):
+        assert bool(torch.isfinite(a[name]).all()), name
+        assert torch.equal(_bits(a[name]), _bits(b[name])), name
