@@ -126,14 +126,16 @@ __global__ __launch_bounds__(BS) void k_batch_step(R* __restrict__ pool, const B
   batch_tile<R, MAT, ONE>(pool, cases, tiles[t], parity, tx, ty);
 }
 
-// Two steps per launch: one workgroup per tile of kT2X x kT2Y nodes, the
-// body of k_step2 on the tile's case.  Cases with periodic axes are not
-// scheduled so.
-template <typename R, int MAT>
-__global__ __launch_bounds__((Tile2<kT2X, kT2Y>::threads)) void k_batch_step2(
+// Three steps per launch: one workgroup per tile of kT3X x kT3Y nodes, the
+// body of k_step3 on the tile's case.  Cases with periodic axes are not
+// scheduled so.  Against pairs of steps in tiles of 48x8, 40 steps of 48
+// cases beyond the last-level cache take 3.15 against 3.66 ms; 200 steps of
+// 39 cases of 200x40, which fit it, 1.89 against 1.90.
+template <typename R, int MAT, int SAUX>
+__global__ __launch_bounds__((Tile3<kT3X, kT3Y>::threads)) void k_batch_step3(
     R* __restrict__ pool, const BatchCase<R>* __restrict__ cases, const Tile* __restrict__ tiles, int ntiles,
     int parity) {
-  __shared__ R lds[19 * Tile2<kT2X, kT2Y>::N];
+  __shared__ R lds[19 * Tile3<kT3X, kT3Y>::N];
   const int t = xcd_logical(blockIdx.x, gridDim.x);
   if (t >= ntiles) return;  // the whole workgroup: no thread reaches the barrier
   const Tile tl = tiles[t];
@@ -143,7 +145,7 @@ __global__ __launch_bounds__((Tile2<kT2X, kT2Y>::threads)) void k_batch_step2(
   const R* fields = MAT == MAT_LAYERED ? nullptr : pool + cases[tl.c].off[0] + int64_t(kFieldRow) * k.plane;
   const R* invk_f = MAT == MAT_LAYERED ? nullptr : fields + k.plane;
   const R* d_f = MAT == MAT_LAYERED ? nullptr : fields + 2 * k.plane;
-  step2_tile<R, MAT, kT2X, kT2Y, 16>(lds, src, nullptr, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
+  step3_tile<R, MAT, kT3X, kT3Y, SAUX>(lds, src, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
 }
 
 // Waves per SIMD the persistent kernel is compiled for (at least): the

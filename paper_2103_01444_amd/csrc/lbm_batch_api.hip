@@ -18,9 +18,10 @@ using namespace lbm;
 namespace {
 
 constexpr size_t kAlign = 256;
-// The schedule that asks for two steps per launch: its workgroup size and
-// tile shape name the form (the kernel's own tiles are kT2X x kT2Y).
+// The schedule that asks for several steps per launch: its workgroup size
+// and tile shape name the form (the kernel's own tiles are kT3X x kT3Y).
 constexpr int kTwoStepBlock = 960, kTwoStepX = 64, kTwoStepY = 12;
+constexpr int64_t kStreamPool = int64_t(256) << 20;  // pools beyond the last-level cache
 constexpr int kMaxGridY = 65535;
 constexpr int kObsCases = 256;  // cases per launch of the observables, at most (bounds their scratch)
 constexpr int kMinTileCells = 64;  // smallest tile the schedule accepts (sizes the tile table)
@@ -67,7 +68,7 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
       e += (L.rows * plane + 63) / 64 * 64;  // 256-byte aligned per buffer
     }
     L.max_tiles += std::max(int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells),
-                            ((g[i].nx + kT2X - 1) / kT2X) * ((g[i].ny + kT2Y - 1) / kT2Y));
+                            ((g[i].nx + kT3X - 1) / kT3X) * ((g[i].ny + kT3Y - 1) / kT3Y));
     L.max_obs_blocks = std::max(L.max_obs_blocks, ((g[i].nx + kBlock - 1) / kBlock) * g[i].ny);
   }
   L.pool_elems = e;
@@ -328,12 +329,17 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
     const dim3 grid(b->ntiles);
     int64_t s = 0;
     int odd_tx = tx, odd_ty = ty;
-    if (b->sched.block == kTwoStepBlock) {  // two steps per launch; an odd count ends with one step on the same tiles
-      odd_tx = kT2X;
-      odd_ty = kT2Y;
-      for (; s + 2 <= nsteps; s += 2) {
-        hipLaunchKernelGGL((k_batch_step2<R, MAT>), grid, dim3(Tile2<kT2X, kT2Y>::threads), 0, b->stream, pool, cases,
-                           tiles, b->ntiles, b->parity);
+    if (b->sched.block == kTwoStepBlock) {  // the one or two left over run on the same tiles
+      odd_tx = kT3X;
+      odd_ty = kT3Y;
+      const bool stream = int64_t(b->L.pool_elems) * int64_t(sizeof(R)) > kStreamPool;
+      for (; s + 3 <= nsteps; s += 3) {
+        if (stream)
+          hipLaunchKernelGGL((k_batch_step3<R, MAT, 0>), grid, dim3(Tile3<kT3X, kT3Y>::threads), 0, b->stream, pool,
+                             cases, tiles, b->ntiles, b->parity);
+        else
+          hipLaunchKernelGGL((k_batch_step3<R, MAT, 16>), grid, dim3(Tile3<kT3X, kT3Y>::threads), 0, b->stream, pool,
+                             cases, tiles, b->ntiles, b->parity);
         b->parity ^= 1;
       }
     }
@@ -379,8 +385,8 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
       if (b->g[i].flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y))
         return bfail(b, LBM_ERR_INVALID_ARG, "the two-step form needs walls and inlet / outlet columns (no periodic axis)");
   b->sched = s;
-  const bool two = s.block == kTwoStepBlock;
-  if (lbm_status st = build_tiles(b, two ? kT2X : s.tile_x, two ? kT2Y : s.tile_y); st != LBM_OK) return st;
+  const bool several = s.block == kTwoStepBlock;
+  if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y); st != LBM_OK) return st;
   if (s.persistent)
     return b->L.fields ? persistent_grid<R, MAT_FULL>(b, &b->persistent_grid)
                        : persistent_grid<R, MAT_LAYERED>(b, &b->persistent_grid);

@@ -90,13 +90,13 @@ constexpr int kT2X = 48, kT2Y = 8;              // lattices of kT2SmallCells nod
 constexpr int kT2SmallX = 16, kT2SmallY = 8;
 constexpr int64_t kT2SmallCells = int64_t(1) << 17;
 
-// Pull of node (x, y) from the step-one populations of the tile at (x0, y0).
-template <int TX, int TY, typename R>
-__device__ __forceinline__ void pull_tile(const R* __restrict__ lds, const Consts<R>& k, int x, int y, int x0,
-                                          int y0, R (&f)[19]) {
-  constexpr int W = Tile2<TX, TY>::W, N = Tile2<TX, TY>::N;
+// Pull of node (x, y), LDS node n of rows of W and planes of N nodes, from
+// the populations of the step before.
+template <int W, int N, typename R>
+__device__ __forceinline__ void pull_tile(const R* __restrict__ lds, const Consts<R>& k, int x, int y, int n,
+                                          R (&f)[19]) {
+  const R* p = lds + n;
   if (__all(x >= 1 && x <= k.nx - 2 && y >= 1 && y <= k.ny - 2)) {  // no wall link: constant offsets
-    const R* p = lds + (y - y0 + 1) * W + (x - x0 + 2);
 #pragma unroll
     for (int q = 0; q < 19; ++q) f[q] = p[q * N - EY[q] * W - EX[q]];
     return;
@@ -105,8 +105,7 @@ __device__ __forceinline__ void pull_tile(const R* __restrict__ lds, const Const
   for (int q = 0; q < 19; ++q) {
     const int xs = x - EX[q], ys = y - EY[q];
     const bool in = (unsigned)xs < (unsigned)k.nx && (unsigned)ys < (unsigned)k.ny;
-    const int n = in ? (ys - y0 + 1) * W + (xs - x0 + 2) : (y - y0 + 1) * W + (x - x0 + 2);
-    f[q] = lds[(in ? q : OPP[q]) * N + n];
+    f[q] = p[in ? q * N - EY[q] * W - EX[q] : OPP[q] * N];
   }
 }
 
@@ -142,7 +141,7 @@ __device__ __forceinline__ void step2_tile(R* __restrict__ lds, const R* __restr
   const bool outlet = x == k.nx - 1;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
   R f[19];
-  pull_tile<TX, TY>(lds, k, xp, y, x0, y0, f);
+  pull_tile<W, N>(lds, k, xp, y, (y - y0 + 1) * W + (xp - x0 + 2), f);
   Mat<R> mt = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y);
   thin_film(f, mt, k, y);
   if (inlet || outlet) {
@@ -164,6 +163,100 @@ __global__ __launch_bounds__((Tile2<TX, TY>::threads)) void k_step2(const R* __r
   int bx, by;
   xcd_tile(gridDim.x, gridDim.y, bx, by);
   step2_tile<R, MAT, TX, TY, SAUX>(lds, src, mid, dst, phi_f, invk_f, d_f, k, bx * TX, by * TY);
+}
+
+// Three time steps in one launch, where no state between them is asked for:
+// the state is read and written once for three steps.  Step one runs over
+// the tile and a halo of two (three columns on the left, where the outlet's
+// feeding columns can lie), one node per thread, as in k_step2; step two
+// runs in place over the tile and a halo of one, its nodes held in registers
+// until all have been pulled; step three pulls the tile's nodes and writes
+// `dst`.  A thread keeps its node throughout, so a node's material is read
+// and derived once.  The states are the bits of three single steps.
+//
+// The halo's extra nodes (512 computed for 27x12 = 324 kept) buy a third of
+// the memory traffic and of the launches.  Region rows are 32 nodes, two to
+// a wavefront.  Per step, k_step2 / 27x12 (us): FP32 1024x256 6.9 / 6.4,
+// 1537x431 12.5 / 12.0, 4096x1024 83.4 / 66.5; FP64 1024x256 10.5 / 9.6,
+// 2048x512 38.7 / 29.7, 4096x1024 144 / 108.  Lattices of fewer than 2^16
+// nodes leave CUs idle and take 27x4: 200x40 FP64 3.6 / 3.3 (27x12 there:
+// one workgroup on 32 of 256 CUs).  64 nodes a row (59x12, 1024 threads) is
+// slower: 4096x1024 80.7.  Stores write through where the two states fit the
+// last-level cache (FP32 1024x256 6.4 against 6.7) and are plain beyond it
+// (4096x1024 66.5 against 82, FP64 108 against 143).
+template <int TX, int TY>
+struct Tile3 {
+  static constexpr int W = TX + 5, N = W * (TY + 4);  // LDS: x0 - 3 .. x0 + TX + 1, y0 - 2 .. y0 + TY + 1
+  static constexpr int threads = (N + 63) / 64 * 64;
+  static_assert(threads <= 1024, "three-step tile: one node per thread");
+};
+constexpr int kT3X = 27, kT3Y = 12;
+constexpr int kT3SmallX = 27, kT3SmallY = 4;
+constexpr int64_t kT3SmallCells = int64_t(1) << 16;
+
+// The three steps of the tile at (x0, y0), called by every thread of a
+// Tile3::threads workgroup (it holds workgroup barriers).  SAUX: cache
+// policy of the final stores.
+template <typename R, int MAT, int TX, int TY, int SAUX>
+__device__ __forceinline__ void step3_tile(R* __restrict__ lds, const R* __restrict__ src, R* __restrict__ dst,
+                                           const R* __restrict__ phi_f, const R* __restrict__ invk_f,
+                                           const R* __restrict__ d_f, const Consts<R>& k, int x0, int y0) {
+  constexpr int W = Tile3<TX, TY>::W, N = Tile3<TX, TY>::N;
+  const int yb = y0 > 1 ? y0 - 2 : 0;
+  const int n = threadIdx.x, i = n % W, j = n / W;
+  const int x = x0 - 3 + i, y = y0 - 2 + j;
+  const bool node = n < N && (unsigned)x < (unsigned)k.nx && (unsigned)y < (unsigned)k.ny;
+  const bool own = node && i >= 3 && i < TX + 3 && j >= 2 && j < TY + 2;
+  const bool inlet = x == 0 && y < k.ny_ch, outlet = x == k.nx - 1;
+  const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
+  const bool cl = y >= k.y_cl0 && !(k.flags & F_NO_REACTION);
+  Mat<R> m;  // of the column whose populations the node pulls
+  R f[19];
+  auto finish = [&] {
+    thin_film(f, m, k, y);
+    Mat<R> mt = m;
+    if (inlet || outlet) {
+      mt = material<R, MAT>(k, phi_f, invk_f, d_f, x, y);
+      boundary_column(f, k, y, inlet, m, mt);
+      if (outlet) outlet_scalar_material(mt, m);
+    }
+    collide(f, mt, k, cl);
+  };
+  if (node) {
+    pull<R, false>(src, k, xp, y, f, yb);
+    m = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y);
+    finish();
+#pragma unroll
+    for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
+  }
+  __syncthreads();
+  const bool two = node && i >= 1 && i <= TX + 3 && j >= 1 && j <= TY + 2;
+  if (two) {
+    pull_tile<W, N>(lds, k, xp, y, n + xp - x, f);
+    finish();
+  }
+  __syncthreads();
+  if (two) {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
+  }
+  __syncthreads();
+  if (own) {
+    pull_tile<W, N>(lds, k, xp, y, n + xp - x, f);
+    finish();
+    store_node<SAUX>(dst, k, x, y, yb, f);
+  }
+}
+
+template <typename R, int MAT, int TX, int TY, int SAUX>
+__global__ __launch_bounds__((Tile3<TX, TY>::threads)) void k_step3(const R* __restrict__ src, R* __restrict__ dst,
+                                                                    const R* __restrict__ phi_f,
+                                                                    const R* __restrict__ invk_f,
+                                                                    const R* __restrict__ d_f, Consts<R> k) {
+  __shared__ R lds[19 * Tile3<TX, TY>::N];
+  int bx, by;
+  xcd_tile(gridDim.x, gridDim.y, bx, by);
+  step3_tile<R, MAT, TX, TY, SAUX>(lds, src, dst, phi_f, invk_f, d_f, k, bx * TX, by * TY);
 }
 
 // Equilibrium initial state: rest fluid at zero pressure (shifted f = 0),
