@@ -214,8 +214,8 @@ lbm_status lbm_init_equilibrium(lbm_ctx* ctx);
 
 /* Advance nsteps time steps (Eq. 1 and the scalar equation of Eq. 10 with
  * the CL source).  Lattices without periodic axes
- * advance two steps per kernel launch (an odd count ends with a single
- * step); the states are bit-identical to single steps.
+ * advance three steps per kernel launch (what is left over in launches of
+ * two or one); the states are bit-identical to single steps.
  * Async; never synchronizes. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t nsteps);
 
@@ -339,8 +339,9 @@ typedef struct lbm_schedule {
   int32_t block;           /* threads per workgroup of the per-step form: 0 or 256 (cells of a tile in a
                             * loop, or one per thread when the tile has 256), or 64 / 128 when the tile has
                             * exactly that many cells (one per thread); the persistent form uses 256.
-                            * 960 with 64 x 12 tiles and persistent = 0: two steps per launch (tiles and
-                            * their halos in LDS, of the library's own shape; an odd count ends with one step), for batches without
+                            * 960 with 64 x 12 tiles and persistent = 0: three steps per launch (tiles
+                            * and their halos in LDS, of the library's own shape; the one or two left over
+                            * run as single steps), for batches without
                             * periodic axes */
 } lbm_schedule;
 
