@@ -76,7 +76,7 @@ __device__ __forceinline__ Mat3<R> material(const Consts3<R>& k, const R* __rest
     phi = phi_f[cell];
     if constexpr (MAT == MAT_PHI) {
       const R om = R(1) - phi;
-      invk = lbm::div_(om * om * k.kc_inv, phi * phi * phi);
+      invk = om * om * k.kc_inv / (phi * phi * phi);
       d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * lbm::sqrt_(phi) * k.D_f;
     } else {
       invk = invk_f[cell];
@@ -88,7 +88,7 @@ __device__ __forceinline__ Mat3<R> material(const Consts3<R>& k, const R* __rest
   m.invk = invk;
   m.d = d;
   m.sqk = lbm::sqrt_(invk);
-  m.fphi = lbm::div_(R(0.143), phi * lbm::sqrt_(phi));
+  m.fphi = R(0.143) / (phi * lbm::sqrt_(phi));
   m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
   m.l1 = phi * m.fphi * m.sqk * R(0.5);
   m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
@@ -184,12 +184,12 @@ __device__ __forceinline__ Macro3<R> flow_macros(const R (&f)[N], const Mat3<R>&
     vy += R(0.5) * m.phi * k.ay;
   }
   const R vm = lbm::sqrt_(vx * vx + vy * vy + vz * vz);
-  const R den = m.l0 + lbm::sqrt_(m.l0 * m.l0 + m.l1 * vm);
-  const R iden = lbm::rcp_seed(den);
+  const R den = lbm::momentum_denominator(m.l0, m.l1, vm);
+  const R fden = lbm::below_inf(den), iden = lbm::rcp_seed(den, fden);
   Macro3<R> o;
-  o.ux = lbm::div_(vx, den, iden);
-  o.uy = lbm::div_(vy, den, iden);
-  o.uz = lbm::div_(vz, den, iden);
+  o.ux = lbm::div_(vx, fden, iden);
+  o.uy = lbm::div_(vy, fden, iden);
+  o.uz = lbm::div_(vz, fden, iden);
   const R u2 = o.ux * o.ux + o.uy * o.uy + o.uz * o.uz;
   const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * lbm::sqrt_(u2));
   o.Fx = -drag * o.ux;

@@ -16,41 +16,33 @@
 
 namespace lbm {
 
-// 1 / a and sqrt(a) from the hardware estimates and Newton steps.  The
-// compiler's IEEE forms also scale by powers of two for operands near the
-// ends of the exponent range; here 1 / a is taken of porosities, heat
-// capacities and momentum denominators (1e-3 .. 1e3), and the root's operand
-// is bounded from below: a root below the bound's root comes out too small,
-// never NaN, which no result can feel (it is a speed that is added to 1/2).
-// FP32: 3 and 6 instructions instead of 10 and 16, FP64: 5 and 11 instead of
-// 10 and 20; results within 1 ulp.  NaN and infinity come out as NaN.  Used
-// by the reverse step only: the forward step's roundings are IEEE's.
-__device__ __forceinline__ float fast_rcp(float a) {
-  const float y = __builtin_amdgcn_rcpf(a);
-  return __builtin_fmaf(__builtin_fmaf(-a, y, 1.0f), y, y);
-}
-__device__ __forceinline__ double fast_rcp(double a) {
-  double y = __builtin_amdgcn_rcp(a);
-  y = __builtin_fma(__builtin_fma(-a, y, 1.0), y, y);
-  return __builtin_fma(__builtin_fma(-a, y, 1.0), y, y);
-}
-__device__ __forceinline__ float fast_sqrt(float a) {
-  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(a, 1.17549435e-38f));
-  const float s = a * y;
+// 1 / a and sqrt(a) from the hardware estimates and Newton steps, within 1
+// ulp (the forward step's are IEEE's: lbm_device.hpp, where the range of the
+// operands is discussed).  A root below the bound of its operand's comes out
+// too small, which no result can feel (it is a speed that is added to 1/2);
+// 1 / infinity is 0, and sqrt(infinity) infinity with c = below_inf(a).
+// FP32: 4 and 6 instructions instead of 10 and 16, FP64: 6 and 11 instead of
+// 10 and 20.
+__device__ __forceinline__ float fast_rcp(float a) { return rcp_seed(a, below_inf(a)); }
+__device__ __forceinline__ double fast_rcp(double a) { return rcp_seed(a, below_inf(a)); }
+__device__ __forceinline__ float fast_sqrt(float a, float c) {
+  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(c, 1.17549435e-38f));
+  const float s = c * y;
   return __builtin_fmaf(__builtin_fmaf(-s, s, a), 0.5f * y, s);
 }
-__device__ __forceinline__ double fast_sqrt(double a) {
-  const double y = __builtin_amdgcn_rsq(__builtin_fmax(a, 1e-300));
-  double g = a * y, h = 0.5 * y;
+__device__ __forceinline__ double fast_sqrt(double a, double c) {
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(c, 1e-300));
+  double g = c * y, h = 0.5 * y;
   double r = __builtin_fma(-h, g, 0.5);
   g = __builtin_fma(g, r, g);
   h = __builtin_fma(h, r, h);
-  r = __builtin_fma(-g, g, a);
+  r = __builtin_fma(-g, g, c);
   g = __builtin_fma(r, h, g);
   r = __builtin_fma(-g, g, a);
   return __builtin_fma(r, h, g);
 }
-
+template <typename R>
+__device__ __forceinline__ R fast_sqrt(R a) { return fast_sqrt(a, a); }
 
 // Sum of the five populations g of a scalar lattice, and the temperature
 // rise from the five temperature populations (isig: 1 / sigma, 1 without the
@@ -171,7 +163,7 @@ __device__ __forceinline__ MacroTape<R> flow_macros_tape(const R* f, R th, const
     t.vy += R(0.5) * m.phi * t.ay;
   }
   t.vm = fast_sqrt(fma_(t.vx, t.vx, t.vy * t.vy));
-  const R r = fast_sqrt(fma_(m.l1, t.vm, m.l0 * m.l0));
+  const R q = fma_(m.l1, t.vm, m.l0 * m.l0), r = fast_sqrt(q, below_inf(q));
   t.ir = fast_rcp(r);
   t.iden = fast_rcp(m.l0 + r);
   t.ux = t.vx * t.iden;

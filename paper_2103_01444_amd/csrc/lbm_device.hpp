@@ -74,27 +74,42 @@ struct Mat {
 
 // a / b, 1 / b and sqrt(a) to the bits of IEEE's for operands whose result
 // and remainders stay clear of the ends of the exponent range: the steps of
-// the compiler's expansions without their scaling and special cases.
-// Operands here are porosities, heat capacities, drag and momentum sums of
-// order 1e-6 .. 1e6, and velocities: below 2^-100 (2^-900 in FP64), where
-// the remainders leave the range, a quotient or root may be off in its last
-// bits, and a root of less than the smallest normal number comes out too
-// small; no other quantity of the step can feel either (|v| is added to 1/2).
-// A zero denominator or an infinite operand gives NaN.  FP32: 8, 7 and 9
-// instructions instead of 10, 10 and 16.
+// the compiler's expansions without their scaling and special cases.  FP32:
+// 8, 7 and 9 instructions instead of 10, 10 and 16.
+//
+// From below: under 2^-100 (2^-900 in FP64), where the remainders leave the
+// range, a quotient or root may be off in its last bits, and a root of less
+// than the smallest normal number comes out too small.  Velocities may be
+// that small; no other quantity of the step can feel it (|v| is added to
+// 1/2).  Quotients by powers of the porosity, which may be denormal, are the
+// compiler's (base_fields, derive_material).  A zero denominator gives NaN.
+//
+// From above: nothing bounds 1/K (any finite number >= 0 is taken), and l0 =
+// 1/2 + phi nu / (4 K) squared overflows from 1/K of about 1e22 on in FP32
+// (1e156 in FP64).  The root of the infinite square is infinite and the
+// quotients by it are 0, as IEEE's (momentum_denominator, below_inf): such a
+// cell is at rest.  Elsewhere infinite operands give NaN; only a state that
+// has diverged has them.
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// Reciprocal of b as the quotients below take it.
-__device__ __forceinline__ float rcp_seed(float b) {
+// b, or the largest finite number for an infinite one.
+__device__ __forceinline__ float below_inf(float b) { return __builtin_fminf(b, 3.402823466e+38f); }
+__device__ __forceinline__ double below_inf(double b) { return __builtin_fmin(b, 1.7976931348623157e+308); }
+
+// Reciprocal of b as the quotients below take it.  With c = below_inf(b) an
+// infinite b gives 0, and div_(a, c, that) is then 0 too.
+__device__ __forceinline__ float rcp_seed(float b, float c) {
   const float y = __builtin_amdgcn_rcpf(b);
-  return fma_(fma_(-b, y, 1.0f), y, y);
+  return fma_(fma_(-c, y, 1.0f), y, y);
 }
-__device__ __forceinline__ double rcp_seed(double b) {
+__device__ __forceinline__ double rcp_seed(double b, double c) {
   double y = __builtin_amdgcn_rcp(b);
-  y = fma_(fma_(-b, y, 1.0), y, y);
-  return fma_(fma_(-b, y, 1.0), y, y);
+  y = fma_(fma_(-c, y, 1.0), y, y);
+  return fma_(fma_(-c, y, 1.0), y, y);
 }
+template <typename R>
+__device__ __forceinline__ R rcp_seed(R b) { return rcp_seed(b, b); }
 // a / b with y = rcp_seed(b), which quotients of one denominator share.
 __device__ __forceinline__ float div_(float a, float b, float y) {
   float q = a * y;
@@ -110,22 +125,32 @@ __device__ __forceinline__ R div_(R a, R b) { return div_(a, b, rcp_seed(b)); }
 template <typename R>
 __device__ __forceinline__ R rcp_(R b) { return div_(R(1), b, rcp_seed(b)); }
 
-__device__ __forceinline__ float sqrt_(float a) {
-  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(a, 1.17549435e-38f));
-  float s = a * y, h = 0.5f * y;
+// sqrt(a); c = below_inf(a) for an a that may be infinite, else a.
+__device__ __forceinline__ float sqrt_(float a, float c) {
+  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(c, 1.17549435e-38f));
+  float s = c * y, h = 0.5f * y;
   const float e = fma_(-h, s, 0.5f);
   s = fma_(s, e, s);
   h = fma_(h, e, h);
   return fma_(fma_(-s, s, a), h, s);
 }
-__device__ __forceinline__ double sqrt_(double a) {
-  const double y = __builtin_amdgcn_rsq(__builtin_fmax(a, 2.2250738585072014e-308));
-  double s = a * y, h = 0.5 * y;
+__device__ __forceinline__ double sqrt_(double a, double c) {
+  const double y = __builtin_amdgcn_rsq(__builtin_fmax(c, 2.2250738585072014e-308));
+  double s = c * y, h = 0.5 * y;
   const double e = fma_(-h, s, 0.5);
   s = fma_(s, e, s);
   h = fma_(h, e, h);
-  s = fma_(fma_(-s, s, a), h, s);
+  s = fma_(fma_(-s, s, c), h, s);
   return fma_(fma_(-s, s, a), h, s);
+}
+template <typename R>
+__device__ __forceinline__ R sqrt_(R a) { return sqrt_(a, a); }
+
+// l0 + sqrt(l0^2 + l1 |v|), infinite where the square overflows.
+template <typename R>
+__device__ __forceinline__ R momentum_denominator(R l0, R l1, R vmag) {
+  const R q = l0 * l0 + l1 * vmag;
+  return l0 + sqrt_(q, below_inf(q));
 }
 
 // Porous-medium properties of one cell.  Layered: clear channel (phi = 1,
@@ -146,7 +171,7 @@ __device__ __forceinline__ void base_fields(const Consts<R>& k, const R* __restr
     phi = phi_f[cell];
     if constexpr (MAT == MAT_PHI) {
       const R om = R(1) - phi;
-      invk = div_(om * om * k.kc_inv, phi * phi * phi);
+      invk = om * om * k.kc_inv / (phi * phi * phi);
       d = (porous && k.deff_ratio > R(0)) ? k.deff_ratio * k.D_f : phi * sqrt_(phi) * k.D_f;
     } else {
       invk = invk_f[cell];
@@ -162,7 +187,7 @@ __device__ __forceinline__ Mat<R> derive_material(const Consts<R>& k, R phi, R i
   m.phi = phi;
   m.invk = invk;
   m.sqk = sqrt_(invk);
-  m.fphi = div_(R(0.143), phi * sqrt_(phi));
+  m.fphi = R(0.143) / (phi * sqrt_(phi));
   m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
   m.l1 = phi * m.fphi * m.sqk * R(0.5);
   m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
@@ -328,11 +353,11 @@ __device__ __forceinline__ Macro<R> flow_macros(const R (&f)[19], const Mat<R>& 
     vy += R(0.5) * m.phi * ay;
   }
   const R vmag = sqrt_(vx * vx + vy * vy);
-  const R den = m.l0 + sqrt_(m.l0 * m.l0 + m.l1 * vmag);
-  const R iden = rcp_seed(den);
+  const R den = momentum_denominator(m.l0, m.l1, vmag);
+  const R fden = below_inf(den), iden = rcp_seed(den, fden);
   Macro<R> o;
-  o.ux = div_(vx, den, iden);
-  o.uy = div_(vy, den, iden);
+  o.ux = div_(vx, fden, iden);
+  o.uy = div_(vy, fden, iden);
   const R u2 = o.ux * o.ux + o.uy * o.uy;
   const R drag = m.phi * (k.nu * m.invk + m.fphi * m.sqk * sqrt_(u2));
   o.Fx = -drag * o.ux;
