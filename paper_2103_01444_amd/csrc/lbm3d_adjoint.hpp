@@ -18,6 +18,7 @@ namespace lbm3 {
 using lbm::fast_rcp;
 using lbm::fast_sqrt;
 using lbm::fma_;
+using lbm::nth;
 using lbm::ReactAdj;
 using lbm::reaction_tape;
 
@@ -224,9 +225,7 @@ __device__ __forceinline__ void flow_adj(const MacroTape3<R>& t, const AdjMat3<R
   const R hp = R(1) - R(0.5) * sp, hm = R(1) - R(0.5) * sm;
   const R iphi = mt.iphi;
   const Vec3<R> H = scale(iphi, axpy(R(9) * hp, t.F, scale(R(4.5) * sp, t.u)));
-  // weights in units of 1/36 (2 for an axis pair, 1 for a diagonal one); 3 w
-  // is then rounded as the forward step rounds it, whose small gain of the
-  // conserved momentum per step belongs to the gradient
+  // weights in units of 1/36 (2 for an axis pair, 1 for a diagonal one)
   Vec3<R> lH, lG, lT;
   R lC = R(0);
 #pragma unroll
@@ -244,7 +243,7 @@ __device__ __forceinline__ void flow_adj(const MacroTape3<R>& t, const AdjMat3<R
   const R c36 = R(1.0 / 36.0);
   lu = axpy(c36, lT, lu);
   lH = scale(c36, lH);
-  lG = scale(R(1.0 / 12.0), lG);  // three times the weighted sum
+  lG = {nth<12>(lG.x), nth<12>(lG.y), nth<12>(lG.z)};  // three times the weighted sum
   lC *= R(1.0 / 12.0);            // likewise
   const R uF = dot(t.u, t.F);
   const R lpp = sp * lC;

@@ -171,6 +171,8 @@ void fill_consts3(Consts3<R>& k, const lbm3d_geometry& g, const lbm_params& p, c
   k.aFsum_over_R = k2.aFsum_over_R;
   k.aT_f = k2.aT_f;
   k.aT_s = k2.aT_s;
+  k.kappa = k2.kappa;
+  k.ceq = k2.ceq;
 }
 
 template <typename R>

@@ -54,6 +54,7 @@ struct Consts3 {
   R T_in, c_in, V_op, U0_slope, U0_icept, ln_k0, E_over_R, inv_T_arrh, aF_over_R, four_f_cref;
   R aFsum_over_R;  // (alpha_a + alpha_c) F / R, Butler-Volmer only
   R aT_f, aT_s;    // sqrt(3) alpha_scale k_f and k_s (reverse step)
+  lbm::RateFromInlet<R> kappa, ceq;  // reverse step
 };
 
 template <typename R>

@@ -230,32 +230,44 @@ struct ReactAdj {
   R s_c, S_T, ehs, dsc_dc, dsc_dth;
 };
 
-// Tape of the CL reaction (Eqs. 12-17 as the forward step computes them,
-// Tafel or Butler-Volmer, printed or physical heat) and its derivatives:
-// s_c = -(c - c_eq) expm1(-kappa), c_eq = exp(alpha_sum F eta / (R T)) with
-// Butler-Volmer (0 with Tafel), S_T = 4 F C_ref s_c ehs / (rho c_p).  With
-// the printed heat ehs = eta + T dU0/dT = V - U0(0) does not depend on T;
-// with the physical heat ehs = -eta + T dU0/dT has dehs/dT = 2 dU0/dT, which
-// the callers add to the temperature adjoint.
+// A rate and its derivative in T, at x = (T - T_in) / T and dx = dx/dT.
+//
+// The exponents of the reaction are differences of numbers of order 50 whose
+// FP32 roundings are 2e-6 of the rate, the same in all cells of a catalyst
+// layer of one temperature.  The forward step has them (its bits are those of
+// the state); the reverse step starts from the value at T_in, computed on the
+// host, and is off by 1e-7.  Error of the reverse sweep itself (against the
+// 64-bit adjoint of the FP32 trajectory), 224x42 over 106 steps: d/dphi
+// 4.9e-6 -> 4.7e-7, d/dD_eff 6.3e-6 -> 6.6e-7.
+template <typename R>
+__device__ __forceinline__ R rate_at(const RateFromInlet<R>& r, R x, R dx, R& slope) {
+  const R v = r.fac * exp(fma_(r.d, x, r.ln));
+  slope = v * (r.d * dx);
+  return v;
+}
 
+// Tape of the CL reaction (Eqs. 12-17, Tafel or Butler-Volmer, printed or
+// physical heat) and its derivatives: s_c = -(c - c_eq) expm1(-kappa), c_eq =
+// exp(alpha_sum F eta / (R T)) with Butler-Volmer (0 with Tafel), S_T = 4 F
+// C_ref s_c ehs / (rho c_p).  With the printed heat ehs = eta + T dU0/dT = V -
+// U0(0) does not depend on T; with the physical heat ehs = -eta + T dU0/dT has
+// dehs/dT = 2 dU0/dT, which the callers add to the temperature adjoint.
 template <typename R, typename K>
 __device__ __forceinline__ ReactAdj<R> reaction_tape(R theta, R c, R rhocp, const K& k) {
   const R T = k.T_in + theta;
   const R iT = R(1) / T;
+  const R x = theta * iT, dx = k.T_in * iT * iT;
   const R eta = k.V_op - (k.U0_slope * T + k.U0_icept);
-  const R kappa = exp(k.ln_k0 - k.E_over_R * (iT - k.inv_T_arrh) - k.aF_over_R * eta * iT);
+  R dkappa, dceq = R(0);
+  const R kappa = rate_at(k.kappa, x, dx, dkappa);
+  const R ceq = k.bv ? rate_at(k.ceq, x, dx, dceq) : R(0);
   const R em = expm1(-kappa);
-  const R ceq = k.bv ? exp(k.aFsum_over_R * eta * iT) : R(0);
   ReactAdj<R> r;
   r.s_c = -(c - ceq) * em;
   r.ehs = ((k.flags & F_PHYSICAL_HEAT) ? -eta : eta) + T * k.U0_slope;
   r.S_T = k.four_f_cref * r.s_c * r.ehs / rhocp;
-  // dE/dT of the exponent E = ln_k0 - E/R (1/T - 1/T0) - aF/R eta / T, with
-  // deta/dT = -U0_slope; dc_eq/dT = -c_eq alpha_sum F/R (U0_slope / T + eta / T^2).
-  const R dE = k.E_over_R * iT * iT + k.aF_over_R * k.U0_slope * iT + k.aF_over_R * eta * iT * iT;
   r.dsc_dc = -em;
-  r.dsc_dth = (c - ceq) * (em + R(1)) * kappa * dE;
-  if (k.bv) r.dsc_dth -= em * ceq * k.aFsum_over_R * (k.U0_slope * iT + eta * iT * iT);
+  r.dsc_dth = (c - ceq) * (em + R(1)) * dkappa + em * dceq;
   return r;
 }
 
@@ -264,7 +276,7 @@ __device__ __forceinline__ ReactAdj<R> reaction_tape(R theta, R c, R rhocp, cons
 // and its derivatives with respect to the wall temperature T, g_c and a_c.
 template <typename R>
 struct FilmTape {
-  R a_t, T, s, S_T, ehs, em, ds_dT, ds_dac, dehs_dT;
+  R a_t, th, s, S_T, ehs, em, ds_dT, ds_dac, dehs_dT;
 };
 
 template <typename R>
@@ -272,23 +284,23 @@ __device__ __forceinline__ FilmTape<R> film_tape(R g_t, R g_c, const AdjMat<R>& 
   FilmTape<R> f;
   f.a_t = m.aT;
   const R a_c = m.aC;
-  f.T = k.T_in + g_t / f.a_t;
-  const R iT = R(1) / f.T;
-  const R eta = k.V_op - (k.U0_slope * f.T + k.U0_icept);
-  const R kappa_a =
-      exp(k.ln_k0 + k.ln_thin - k.E_over_R * (iT - k.inv_T_arrh) - k.aF_over_R * eta * iT) / a_c;
-  const R ceq = k.bv ? exp(k.aFsum_over_R * eta * iT) : R(0);
+  f.th = g_t / f.a_t;
+  const R T = k.T_in + f.th;
+  const R iT = R(1) / T;
+  const R x = f.th * iT, dx = k.T_in * iT * iT;
+  const R eta = k.V_op - (k.U0_slope * T + k.U0_icept);
+  R dkappa, dceq = R(0);
+  const R film = exp(k.ln_thin) / a_c;
+  const R kappa_a = rate_at(k.kappa, x, dx, dkappa) * film;
+  const R ceq = k.bv ? rate_at(k.ceq, x, dx, dceq) : R(0);
   f.em = expm1(-kappa_a);
   f.s = -(g_c - a_c * ceq) * f.em;
   const bool phys = k.flags & F_PHYSICAL_HEAT;
-  f.ehs = (phys ? -eta : eta) + f.T * k.U0_slope;
+  f.ehs = (phys ? -eta : eta) + T * k.U0_slope;
   f.S_T = k.four_f_cref * f.s * f.ehs / m.rhocp;
-  // ds/dkappa = (g_c - a_c c_eq)(em + 1); dkappa/dT = kappa dE/dT as in the
-  // volumetric tape; ds/dc_eq = a_c em with dc_eq/dT as there
-  const R dE = k.E_over_R * iT * iT + k.aF_over_R * k.U0_slope * iT + k.aF_over_R * eta * iT * iT;
+  // ds/dkappa = (g_c - a_c c_eq)(em + 1), ds/dc_eq = a_c em
   const R ds_dk = (g_c - a_c * ceq) * (f.em + R(1));
-  f.ds_dT = ds_dk * kappa_a * dE;
-  if (k.bv) f.ds_dT -= a_c * f.em * ceq * k.aFsum_over_R * (k.U0_slope * iT + eta * iT * iT);
+  f.ds_dT = ds_dk * (dkappa * film) + a_c * f.em * dceq;
   f.ds_dac = -ds_dk * kappa_a / a_c + ceq * f.em;
   f.dehs_dT = phys ? R(2) * k.U0_slope : R(0);
   return f;
@@ -313,7 +325,7 @@ __device__ __forceinline__ void film_adj(const FilmTape<R>& f, const AdjMat<R>& 
   l13 += lT / f.a_t;
   l18 += -ls * f.em;
   // T = T_in + g_t / a_t
-  ma.aT += -lT * (f.T - k.T_in) / f.a_t;
+  ma.aT += -lT * f.th / f.a_t;
   ma.aC += ls * f.ds_dac;
 }
 
@@ -388,6 +400,15 @@ __device__ __forceinline__ void flow_sums_adj(R l0, R lS, R lA, R lN, R lM, R lJ
   mu[8] = l68 - b68;
 }
 
+// a / N to the last bit or so.  The adjoint of a conserved moment passes
+// through every step unchanged; fl(1 / N) would scale it by 1 + 3e-8 (FP32)
+// at each.
+template <int N, typename R>
+__device__ __forceinline__ R nth(R a) {
+  const R c = R(1.0 / N), q = c * a;
+  return fma_(fma_(R(-N), q, a), c, q);
+}
+
 // Adjoint of the flow collision of one node in the sums of `collide`, S the
 // sum of its moving populations: la[0..8] the post-collision adjoints, lux,
 // luy the velocity's from the scalars; out: mu[0..8].
@@ -402,17 +423,11 @@ __device__ __forceinline__ void flow_adj(const MacroTape<R>& t, const AdjMat<R>&
   const R d13 = la[1] - la[3], d24 = la[2] - la[4], d57 = la[5] - la[7], d68 = la[6] - la[8];
   const R lB = R(0.25) * (s57 + s68);
   const R lA = fma_(R(0.25), s13 + s24, -lB), lN = R(0.25) * (s13 - s24), lM2 = R(0.125) * (s57 - s68);
-  const R c6 = R(1.0 / 6.0);  // rounded as in the forward step: j' = 6 fl(1/6) j there, and here
-  const R gx = c6 * (d57 - d68), gy = c6 * (d57 + d68);
-  const R ljx = fma_(c6, d13, gx), ljy = fma_(c6, d24, gy);
-  const R lqx = fma_(-c6, d13, R(0.5) * gx), lqy = fma_(-c6, d24, R(0.5) * gy);
-  // S' = S, A' = 4/5 S and f0' = -S at equilibrium go through p = fl(0.6) S18
-  // in the forward step, which makes each larger by fl(0.6) / 0.6; without
-  // that excess (r6, r8) the FP32 gradient of 1/K is 1.1e-6 off after 65
-  // steps of 197x72, with it 6.2e-7.
-  constexpr double r6 = double(R(0.6)) / 0.6 - 1.0, r8 = double(R(0.6)) / 0.75 / double(R(0.8)) - 1.0;
-  R lS = fma_(se, fma_(R(0.8), lA, -la[0]), lB);
-  lS = fma_(se, fma_(R(0.8 * r8), lA, R(r6) * (lB - la[0])), lS);
+  const R c6 = R(1.0 / 6.0);
+  const R gx = d57 - d68, gy = d57 + d68;
+  const R ljx = nth<6>(d13 + gx), ljy = nth<6>(d24 + gy);
+  const R lqx = c6 * fma_(R(0.5), gx, -d13), lqy = c6 * fma_(R(0.5), gy, -d24);
+  const R lS = fma_(se, fma_(R(0.8), lA, -la[0]), lB);
   const R lz = (R(4.0 / 3.0) * he) * (fma_(R(0.5), lA, lB) - la[0]);  // of (u F) / phi
   const R lw = R(-0.2) * se * lA;                                      // of u^2 / phi
   // N and M: u_i P_j with P = (s_e u + (2 - s_e) F) / phi

@@ -29,6 +29,13 @@ constexpr int EX[19] = {0, 1, 0, -1, 0, 1, -1, -1, 1, 0, 1, 0, -1, 0, 0, 1, 0, -
 constexpr int EY[19] = {0, 0, 1, 0, -1, 1, 1, -1, -1, 0, 0, 1, 0, -1, 0, 0, 1, 0, -1};
 constexpr int OPP[19] = {0, 3, 4, 1, 2, 7, 8, 5, 6, 9, 12, 13, 10, 11, 14, 17, 18, 15, 16};
 
+// exp(L(T)) of an exponent with L(T) - L(T_in) = d (T - T_in) / T, as a factor
+// of its value at the inlet temperature: fac exp(ln + d (T - T_in) / T).
+template <typename R>
+struct RateFromInlet {
+  R ln, fac, d;
+};
+
 // Per-launch constants, in the kernel's arithmetic type R.
 template <typename R>
 struct Consts {
@@ -64,6 +71,8 @@ struct Consts {
   R bx, by;             // buoyancy: acceleration per kelvin of temperature rise
   // reverse step: sqrt(3) alpha_scale k_f and k_s, 1 / rhocp_f
   R aT_f, aT_s, irc_f;
+  // reverse step: the reaction's rate factor kappa and c_eq
+  RateFromInlet<R> kappa, ceq;
 };
 
 template <typename R>

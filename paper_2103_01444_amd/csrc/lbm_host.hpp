@@ -221,6 +221,17 @@ void fill_consts(Consts<R>& k, const lbm_geometry& g, const lbm_params& p, const
   k.aT_f = R(std::sqrt(3.0) * d.alpha_scale * p.k_f);
   k.aT_s = R(std::sqrt(3.0) * d.alpha_scale * p.k_s);
   k.irc_f = R(1.0 / p.rhocp_f);
+  // The value at T_in is a factor, but for what an FP32 factor cannot hold.
+  const double eta_T = (p.V_op - (p.U0_slope * p.T_in_K + p.U0_icept)) / p.T_in_K;
+  const double aF = p.alpha_c * p.faraday / p.R_gas, aS = (p.alpha_a + p.alpha_c) * p.faraday / p.R_gas;
+  const auto rate = [](RateFromInlet<R>& r, double ln, double slope) {
+    r.ln = std::fabs(ln) > 60.0 ? R(ln) : R(0);
+    r.fac = R(std::exp(ln - double(r.ln)));
+    r.d = R(slope);
+  };
+  rate(k.kappa, d.ln_k0 - p.E_over_R * (1.0 / p.T_in_K - 1.0 / p.T_arrh) - aF * eta_T,
+       p.E_over_R / p.T_in_K + aF * (eta_T + p.U0_slope));
+  rate(k.ceq, aS * eta_T, -aS * (eta_T + p.U0_slope));
 }
 
 }  // namespace lbm
