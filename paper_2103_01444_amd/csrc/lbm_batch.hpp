@@ -126,12 +126,14 @@ __global__ __launch_bounds__(BS) void k_batch_step(R* __restrict__ pool, const B
   batch_tile<R, MAT, ONE>(pool, cases, tiles[t], parity, tx, ty);
 }
 
-// Three steps per launch: one workgroup per tile of kT3X x kT3Y nodes, the
-// body of k_step3 on the tile's case.  Cases with periodic axes are not
+// Three steps per launch, or the two left over: one workgroup per tile of
+// kT3X x kT3Y nodes, the body of k_step3 on the tile's case.  (A single step
+// left over is k_batch_step's, on rows of kBlock nodes: on these tiles it took
+// 217 us for the 64 cases, longer than two.)  Cases with periodic axes are not
 // scheduled so.  Against pairs of steps in tiles of 48x8, 40 steps of 48
 // cases beyond the last-level cache take 3.15 against 3.66 ms; 200 steps of
 // 39 cases of 200x40, which fit it, 1.89 against 1.90.
-template <typename R, int MAT, int SAUX>
+template <typename R, int MAT, int SAUX, int STEPS>
 __global__ __launch_bounds__((Tile3<kT3X, kT3Y>::threads)) void k_batch_step3(
     R* __restrict__ pool, const BatchCase<R>* __restrict__ cases, const Tile* __restrict__ tiles, int ntiles,
     int parity) {
@@ -145,7 +147,7 @@ __global__ __launch_bounds__((Tile3<kT3X, kT3Y>::threads)) void k_batch_step3(
   const R* fields = MAT == MAT_LAYERED ? nullptr : pool + cases[tl.c].off[0] + int64_t(kFieldRow) * k.plane;
   const R* invk_f = MAT == MAT_LAYERED ? nullptr : fields + k.plane;
   const R* d_f = MAT == MAT_LAYERED ? nullptr : fields + 2 * k.plane;
-  step3_tile<R, MAT, kT3X, kT3Y, SAUX>(lds, src, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
+  step3_tile<R, MAT, kT3X, kT3Y, SAUX, STEPS>(lds, src, dst, fields, invk_f, d_f, k, tl.x0, tl.y0);
 }
 
 // Waves per SIMD the persistent kernel is compiled for (at least): the

@@ -7,6 +7,7 @@
 #include <fstream>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm_batch.hpp"
@@ -53,6 +54,8 @@ bool batch_geometry_ok(const lbm_geometry* g, int n) {
   return true;
 }
 
+int tiles_of(const lbm_geometry& g, int tx, int ty) { return ((g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty); }
+
 BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
   BatchLayout L;
   L.esize = g[0].precision == 64 ? 8 : 4;
@@ -68,7 +71,7 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
       e += (L.rows * plane + 63) / 64 * 64;  // 256-byte aligned per buffer
     }
     L.max_tiles += std::max(int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells),
-                            ((g[i].nx + kT3X - 1) / kT3X) * ((g[i].ny + kT3Y - 1) / kT3Y));
+                            tiles_of(g[i], kT3X, kT3Y) + tiles_of(g[i], kBlock, 1));
     L.max_obs_blocks = std::max(L.max_obs_blocks, ((g[i].nx + kBlock - 1) / kBlock) * g[i].ny);
   }
   L.pool_elems = e;
@@ -108,6 +111,7 @@ struct lbm_batch {
   int64_t step = 0;
   lbm_schedule sched{256, 1, 0, 0};
   int ntiles = 0;
+  int nrow_tiles = 0;  // tiles of kBlock x 1 behind them, for a single step of the several-step form
   int persistent_grid = 0;
   long long barrier_limit = 0;  // wall-clock ticks a persistent barrier waits at most
   int wall_khz = 0;             // the device wall clock's rate
@@ -236,17 +240,23 @@ lbm_status upload_cases(lbm_batch* b) {
   return LBM_OK;
 }
 
-// Build the tile list for a tile shape; cases in order, rows then columns.
-lbm_status build_tiles(lbm_batch* b, int tx, int ty) {
+// Build the tile list for a tile shape (and, with `rows`, a list of kBlock x 1
+// tiles behind it); cases in order, rows then columns.
+lbm_status build_tiles(lbm_batch* b, int tx, int ty, bool rows) {
   std::vector<Tile> t;
-  for (int i = 0; i < b->n; ++i)
-    for (int y0 = 0; y0 < b->g[i].ny; y0 += ty)
-      for (int x0 = 0; x0 < b->g[i].nx; x0 += tx) t.push_back({i, x0, y0, 0});
+  const auto add = [&](int w, int h) {
+    for (int i = 0; i < b->n; ++i)
+      for (int y0 = 0; y0 < b->g[i].ny; y0 += h)
+        for (int x0 = 0; x0 < b->g[i].nx; x0 += w) t.push_back({i, x0, y0, 0});
+    return int(t.size());
+  };
+  const int ntiles = add(tx, ty), all = rows ? add(kBlock, 1) : ntiles;
   if (int(t.size()) > b->L.max_tiles) return bfail(b, LBM_ERR_INVALID_ARG, "tile too small");
   if (hipMemcpyAsync(b->tiles(), t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice, b->stream) != hipSuccess)
     return bfail(b, LBM_ERR_DEVICE, "tile table upload failed");
   if (hipStreamSynchronize(b->stream) != hipSuccess) return bfail(b, LBM_ERR_DEVICE, "tile table sync failed");
-  b->ntiles = int(t.size());
+  b->ntiles = ntiles;
+  b->nrow_tiles = all - ntiles;
   return LBM_OK;
 }
 
@@ -328,19 +338,27 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
     const int bs = b->sched.block == 64 || b->sched.block == 128 ? b->sched.block : kBlock;
     const dim3 grid(b->ntiles);
     int64_t s = 0;
-    int odd_tx = tx, odd_ty = ty;
-    if (b->sched.block == kTwoStepBlock) {  // the one or two left over run on the same tiles
-      odd_tx = kT3X;
-      odd_ty = kT3Y;
+    if (b->sched.block == kTwoStepBlock) {
       const bool stream = int64_t(b->L.pool_elems) * int64_t(sizeof(R)) > kStreamPool;
-      for (; s + 3 <= nsteps; s += 3) {
+      const auto launch = [&](auto steps) {
+        constexpr int n = decltype(steps)::value;
+        const dim3 threads(Tile3<kT3X, kT3Y>::threads);
         if (stream)
-          hipLaunchKernelGGL((k_batch_step3<R, MAT, 0>), grid, dim3(Tile3<kT3X, kT3Y>::threads), 0, b->stream, pool,
-                             cases, tiles, b->ntiles, b->parity);
+          hipLaunchKernelGGL((k_batch_step3<R, MAT, 0, n>), grid, threads, 0, b->stream, pool, cases, tiles, b->ntiles,
+                             b->parity);
         else
-          hipLaunchKernelGGL((k_batch_step3<R, MAT, 16>), grid, dim3(Tile3<kT3X, kT3Y>::threads), 0, b->stream, pool,
-                             cases, tiles, b->ntiles, b->parity);
+          hipLaunchKernelGGL((k_batch_step3<R, MAT, 16, n>), grid, threads, 0, b->stream, pool, cases, tiles,
+                             b->ntiles, b->parity);
         b->parity ^= 1;
+        s += n;
+      };
+      while (nsteps - s >= 3) launch(std::integral_constant<int, 3>{});
+      if (nsteps - s == 2) launch(std::integral_constant<int, 2>{});
+      if (nsteps - s == 1) {
+        hipLaunchKernelGGL((k_batch_step<R, MAT, true>), dim3(b->nrow_tiles), dim3(kBlock), 0, b->stream, pool, cases,
+                           tiles + b->ntiles, b->nrow_tiles, b->parity, kBlock, 1);
+        b->parity ^= 1;
+        s += 1;
       }
     }
     for (; s < nsteps; ++s) {
@@ -355,7 +373,7 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
                            b->ntiles, b->parity, tx, ty);
       else
         hipLaunchKernelGGL((k_batch_step<R, MAT, false>), grid, dim3(kBlock), 0, b->stream, pool, cases, tiles,
-                           b->ntiles, b->parity, odd_tx, odd_ty);
+                           b->ntiles, b->parity, tx, ty);
       b->parity ^= 1;
     }
     const hipError_t e = hipGetLastError();
@@ -386,7 +404,8 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
         return bfail(b, LBM_ERR_INVALID_ARG, "the two-step form needs walls and inlet / outlet columns (no periodic axis)");
   b->sched = s;
   const bool several = s.block == kTwoStepBlock;
-  if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y); st != LBM_OK) return st;
+  if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y, several); st != LBM_OK)
+    return st;
   if (s.persistent)
     return b->L.fields ? persistent_grid<R, MAT_FULL>(b, &b->persistent_grid)
                        : persistent_grid<R, MAT_LAYERED>(b, &b->persistent_grid);

@@ -194,10 +194,10 @@ constexpr int kT3X = 27, kT3Y = 12;
 constexpr int kT3SmallX = 27, kT3SmallY = 4;
 constexpr int64_t kT3SmallCells = int64_t(1) << 16;
 
-// The three steps of the tile at (x0, y0), called by every thread of a
-// Tile3::threads workgroup (it holds workgroup barriers).  SAUX: cache
-// policy of the final stores.
-template <typename R, int MAT, int TX, int TY, int SAUX>
+// The three steps (or two: what is left of a run on the same tiles) of the
+// tile at (x0, y0), called by every thread of a Tile3::threads workgroup (it
+// holds workgroup barriers).  SAUX: cache policy of the final stores.
+template <typename R, int MAT, int TX, int TY, int SAUX, int STEPS = 3>
 __device__ __forceinline__ void step3_tile(R* __restrict__ lds, const R* __restrict__ src, R* __restrict__ dst,
                                            const R* __restrict__ phi_f, const R* __restrict__ invk_f,
                                            const R* __restrict__ d_f, const Consts<R>& k, int x0, int y0) {
@@ -206,6 +206,8 @@ __device__ __forceinline__ void step3_tile(R* __restrict__ lds, const R* __restr
   const int n = threadIdx.x, i = n % W, j = n / W;
   const int x = x0 - 3 + i, y = y0 - 2 + j;
   const bool node = n < N && (unsigned)x < (unsigned)k.nx && (unsigned)y < (unsigned)k.ny;
+  // the nodes each of the last two steps runs over: the tile and a ring, the tile
+  const bool ring = node && i >= 1 && i <= TX + 3 && j >= 1 && j <= TY + 2;
   const bool own = node && i >= 3 && i < TX + 3 && j >= 2 && j < TY + 2;
   const bool inlet = x == 0 && y < k.ny_ch, outlet = x == k.nx - 1;
   const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
@@ -222,23 +224,25 @@ __device__ __forceinline__ void step3_tile(R* __restrict__ lds, const R* __restr
     }
     collide(f, mt, k, cl);
   };
-  if (node) {
+  static_assert(STEPS == 2 || STEPS == 3, "steps of a launch");
+  if (STEPS == 3 ? node : ring) {
     pull<R, false>(src, k, xp, y, f, yb);
     m = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y);
     finish();
 #pragma unroll
     for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
   }
-  __syncthreads();
-  const bool two = node && i >= 1 && i <= TX + 3 && j >= 1 && j <= TY + 2;
-  if (two) {
-    pull_tile<W, N>(lds, k, xp, y, n + xp - x, f);
-    finish();
-  }
-  __syncthreads();
-  if (two) {
+  if constexpr (STEPS == 3) {
+    __syncthreads();
+    if (ring) {
+      pull_tile<W, N>(lds, k, xp, y, n + xp - x, f);
+      finish();
+    }
+    __syncthreads();
+    if (ring) {
 #pragma unroll
-    for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
+      for (int q = 0; q < 19; ++q) lds[q * N + n] = f[q];
+    }
   }
   __syncthreads();
   if (own) {
