@@ -117,7 +117,7 @@ __device__ __forceinline__ MacroTape3<R> flow_macros_tape(const R* f, const AdjM
     t.v.y += R(0.5) * m.phi * k.ay;
   }
   t.vm = fast_sqrt(dot(t.v, t.v));
-  const R q = fma_(m.l1, t.vm, m.l0 * m.l0), r = fast_sqrt(q, lbm::below_inf(q));
+  const R r = lbm::fast_momentum_root(m.l0, m.l1, t.vm);
   t.ir = fast_rcp(r);
   t.iden = fast_rcp(m.l0 + r);
   t.u = scale(t.iden, t.v);

@@ -20,29 +20,25 @@ namespace lbm {
 // ulp (the forward step's are IEEE's: lbm_device.hpp, where the range of the
 // operands is discussed).  A root below the bound of its operand's comes out
 // too small, which no result can feel (it is a speed that is added to 1/2);
-// 1 / infinity is 0, and sqrt(infinity) infinity with c = below_inf(a).
-// FP32: 4 and 6 instructions instead of 10 and 16, FP64: 6 and 11 instead of
-// 10 and 20.
+// 1 / infinity is 0.  FP32: 4 and 6 instructions instead of 10 and 16, FP64:
+// 6 and 11 instead of 10 and 20.
 __device__ __forceinline__ float fast_rcp(float a) { return rcp_seed(a, below_inf(a)); }
 __device__ __forceinline__ double fast_rcp(double a) { return rcp_seed(a, below_inf(a)); }
-__device__ __forceinline__ float fast_sqrt(float a, float c) {
-  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(c, 1.17549435e-38f));
+__device__ __forceinline__ float fast_root(float a, float c, float y) {
   const float s = c * y;
-  return __builtin_fmaf(__builtin_fmaf(-s, s, a), 0.5f * y, s);
+  return fma_(fma_(-s, s, a), 0.5f * y, s);
 }
-__device__ __forceinline__ double fast_sqrt(double a, double c) {
-  const double y = __builtin_amdgcn_rsq(__builtin_fmax(c, 1e-300));
-  double g = c * y, h = 0.5 * y;
-  double r = __builtin_fma(-h, g, 0.5);
-  g = __builtin_fma(g, r, g);
-  h = __builtin_fma(h, r, h);
-  r = __builtin_fma(-g, g, c);
-  g = __builtin_fma(r, h, g);
-  r = __builtin_fma(-g, g, a);
-  return __builtin_fma(r, h, g);
+__device__ __forceinline__ double fast_root(double a, double c, double y) { return root_(a, c, y); }
+__device__ __forceinline__ float fast_sqrt(float a) {
+  return fast_root(a, a, rsq_(__builtin_fmaxf(a, 1.17549435e-38f)));
 }
+__device__ __forceinline__ double fast_sqrt(double a) { return fast_root(a, a, rsq_(__builtin_fmax(a, 1e-300))); }
+// sqrt(l0^2 + l1 |v|), as momentum_denominator's.
 template <typename R>
-__device__ __forceinline__ R fast_sqrt(R a) { return fast_sqrt(a, a); }
+__device__ __forceinline__ R fast_momentum_root(R l0, R l1, R vm) {
+  const R q = fma_(l1, vm, l0 * l0), c = below_inf(q);
+  return fast_root(q, c, rsq_(c));
+}
 
 // Sum of the five populations g of a scalar lattice, and the temperature
 // rise from the five temperature populations (isig: 1 / sigma, 1 without the
@@ -163,7 +159,7 @@ __device__ __forceinline__ MacroTape<R> flow_macros_tape(const R* f, R th, const
     t.vy += R(0.5) * m.phi * t.ay;
   }
   t.vm = fast_sqrt(fma_(t.vx, t.vx, t.vy * t.vy));
-  const R q = fma_(m.l1, t.vm, m.l0 * m.l0), r = fast_sqrt(q, below_inf(q));
+  const R r = fast_momentum_root(m.l0, m.l1, t.vm);
   t.ir = fast_rcp(r);
   t.iden = fast_rcp(m.l0 + r);
   t.ux = t.vx * t.iden;

@@ -134,17 +134,16 @@ __device__ __forceinline__ R div_(R a, R b) { return div_(a, b, rcp_seed(b)); }
 template <typename R>
 __device__ __forceinline__ R rcp_(R b) { return div_(R(1), b, rcp_seed(b)); }
 
-// sqrt(a); c = below_inf(a) for an a that may be infinite, else a.
-__device__ __forceinline__ float sqrt_(float a, float c) {
-  const float y = __builtin_amdgcn_rsqf(__builtin_fmaxf(c, 1.17549435e-38f));
+// sqrt(a) from the estimate y of 1 / sqrt(c); c: a, or below_inf(a) for an a
+// that may be infinite.
+__device__ __forceinline__ float root_(float a, float c, float y) {
   float s = c * y, h = 0.5f * y;
   const float e = fma_(-h, s, 0.5f);
   s = fma_(s, e, s);
   h = fma_(h, e, h);
   return fma_(fma_(-s, s, a), h, s);
 }
-__device__ __forceinline__ double sqrt_(double a, double c) {
-  const double y = __builtin_amdgcn_rsq(__builtin_fmax(c, 2.2250738585072014e-308));
+__device__ __forceinline__ double root_(double a, double c, double y) {
   double s = c * y, h = 0.5 * y;
   const double e = fma_(-h, s, 0.5);
   s = fma_(s, e, s);
@@ -152,14 +151,19 @@ __device__ __forceinline__ double sqrt_(double a, double c) {
   s = fma_(fma_(-s, s, c), h, s);
   return fma_(fma_(-s, s, a), h, s);
 }
-template <typename R>
-__device__ __forceinline__ R sqrt_(R a) { return sqrt_(a, a); }
+__device__ __forceinline__ float rsq_(float a) { return __builtin_amdgcn_rsqf(a); }
+__device__ __forceinline__ double rsq_(double a) { return __builtin_amdgcn_rsq(a); }
+__device__ __forceinline__ float sqrt_(float a) { return root_(a, a, rsq_(__builtin_fmaxf(a, 1.17549435e-38f))); }
+__device__ __forceinline__ double sqrt_(double a) {
+  return root_(a, a, rsq_(__builtin_fmax(a, 2.2250738585072014e-308)));
+}
 
-// l0 + sqrt(l0^2 + l1 |v|), infinite where the square overflows.
+// l0 + sqrt(l0^2 + l1 |v|): the operand is 1/4 or more, and infinite where
+// the square overflows.
 template <typename R>
 __device__ __forceinline__ R momentum_denominator(R l0, R l1, R vmag) {
-  const R q = l0 * l0 + l1 * vmag;
-  return l0 + sqrt_(q, below_inf(q));
+  const R q = l0 * l0 + l1 * vmag, c = below_inf(q);
+  return l0 + root_(q, c, rsq_(c));
 }
 
 // Porous-medium properties of one cell.  Layered: clear channel (phi = 1,
