@@ -307,6 +307,39 @@ __device__ __forceinline__ Mat3<R> pre_collision(const R* __restrict__ src, cons
   return mb;
 }
 
+// Pre-collision populations of node (x, y, z), boundary columns included, in
+// two passes as step_node takes them: flow(f, material) gets the 19 flow
+// populations, scalars(g, material) the 14 scalar ones.
+template <typename R, int MAT, typename Flow, typename Scalars>
+__device__ __forceinline__ void pre_collision_parts(const R* __restrict__ src, const Consts3<R>& k,
+                                                    const R* __restrict__ phi_f, const R* __restrict__ invk_f,
+                                                    const R* __restrict__ d_f, int x, int y, int z, const Flow& flow,
+                                                    const Scalars& scalars) {
+  const bool open = !(k.flags & F_PERIODIC_X);
+  const bool inlet = open && x == 0 && z < k.nz_ch;
+  const bool outlet = open && x == k.nx - 1;
+  const int xp = inlet ? 1 : (outlet ? k.nx - 2 : x);
+  const Mat3<R> mp = material<R, MAT>(k, phi_f, invk_f, d_f, xp, y, z);
+  Mat3<R> mt = mp;
+  if (inlet || outlet) mt = material<R, MAT>(k, phi_f, invk_f, d_f, x, y, z);
+  Macro3<R> nb{};
+  {
+    R f[19];
+    pull_range<R, 0, 19, true>(src, k, xp, y, z, f);
+    if (inlet || outlet) nb = boundary_flow(f, k, y, z, inlet, mp, mt);
+    flow(f, mt);
+  }
+  if (outlet) {  // scalar material of column nx-2 at the outlet (as in 2D)
+    mt.aT = mp.aT;
+    mt.aC = mp.aC;
+    mt.rhocp = mp.rhocp;
+  }
+  R g[14];
+  pull_range<R, 19, 33, true>(src, k, xp, y, z, g);
+  if (inlet) boundary_scalars_inlet(g, k, y, z, nb, mp, mt);
+  scalars(g, mt);
+}
+
 using lbm::reaction;  // the CL reaction of Eqs. 12-17 (shared with 2D)
 
 // Two-rate collision of the 19 flow populations with Guo's porous forcing;
