@@ -18,11 +18,17 @@ template <typename R>
 struct BatchCase {
   Consts<R> k;
   int64_t off[2];  // element offsets of the two state buffers in the pool
+  int32_t row0;    // index of the case's first row tile (below)
 };
 
 struct Tile {
   int32_t c, x0, y0, pad;
 };
+
+// Row tiles: tiles of kBlock x 1 nodes over every case, in case order, rows then
+// columns.  Kernels with one workgroup per kBlock nodes of a row (the initial
+// state, the observables, a single step of the several-step form) launch over
+// them, whatever the cases' sizes.
 
 // Per-cell fields of a batch whose cases carry them (MAT_FULL): rows 19, 20
 // and 21 of every lattice row of the case's first state buffer hold
@@ -71,39 +77,39 @@ __device__ __forceinline__ const R* case_fields(const R* pool, const BatchCase<R
   return MAT == MAT_LAYERED ? nullptr : pool + c.off[0] + int64_t(kFieldRow) * c.k.plane;
 }
 
-// Initial state of every case: blockIdx.y the case, blockIdx.x its blocks of
-// kBlock nodes of a row (a grid as wide as the largest case's; one launch
-// for the batch instead of one per case).
+// Initial state of every case (one launch for the batch, over the row tiles).
 template <typename R, int MAT>
-__global__ __launch_bounds__(kBlock) void k_batch_init(R* __restrict__ pool, const BatchCase<R>* __restrict__ cases) {
-  const BatchCase<R>& c = cases[blockIdx.y];
+__global__ __launch_bounds__(kBlock) void k_batch_init(R* __restrict__ pool, const BatchCase<R>* __restrict__ cases,
+                                                       const Tile* __restrict__ rows) {
+  const Tile t = rows[blockIdx.x];
+  const BatchCase<R>& c = cases[t.c];
   const Consts<R> k = c.k;
-  const int nbx = (k.nx + kBlock - 1) / kBlock, y = blockIdx.x / nbx, bx = blockIdx.x - y * nbx;
-  if (y >= k.ny) return;
   const R* f = case_fields<R, MAT>(pool, c);
-  init_node<R, MAT>(pool + c.off[0], f, f + k.plane, f + 2 * k.plane, k, bx * kBlock + int(threadIdx.x), y);
+  init_node<R, MAT>(pool + c.off[0], f, f + k.plane, f + 2 * k.plane, k, t.x0 + int(threadIdx.x), t.y0);
 }
 
-// Observable partials of every case, laid out and launched likewise:
-// partials of block b of case i at (i * gridDim.x + b) * kObsQ.
+// Observable partials of every case, kObsQ for each row tile, and their sums:
+// blockIdx.y the case.  (With a grid and partials of the largest case for each
+// of them, one 4096x1024 case among 255 of 200x40 took 302 MB more and 4.2
+// million workgroups, nearly all of which returned at once.)
 template <typename R, int MAT>
 __global__ __launch_bounds__(kBlock) void k_batch_obs(const R* __restrict__ pool,
-                                                      const BatchCase<R>* __restrict__ cases, int parity,
+                                                      const BatchCase<R>* __restrict__ cases,
+                                                      const Tile* __restrict__ rows, int parity,
                                                       double* __restrict__ partial) {
-  const BatchCase<R>& c = cases[blockIdx.y];
+  const Tile t = rows[blockIdx.x];
+  const BatchCase<R>& c = cases[t.c];
   const Consts<R> k = c.k;
-  const int nbx = (k.nx + kBlock - 1) / kBlock, y = blockIdx.x / nbx, bx = blockIdx.x - y * nbx;
-  if (y >= k.ny) return;  // the whole workgroup
   const R* f = case_fields<R, MAT>(pool, c);
-  obs_cells<R, MAT>(pool + c.off[parity], f, f + k.plane, f + 2 * k.plane, k, bx, y,
-                    partial + (size_t(blockIdx.y) * gridDim.x + blockIdx.x) * kObsQ);
+  obs_cells<R, MAT>(pool + c.off[parity], f, f + k.plane, f + 2 * k.plane, k, t.x0 / kBlock, t.y0,
+                    partial + size_t(blockIdx.x) * kObsQ);
 }
 template <typename R>
-__global__ __launch_bounds__(kFinal) void k_batch_obs_final(const double* __restrict__ partial, int stride,
+__global__ __launch_bounds__(kFinal) void k_batch_obs_final(const double* __restrict__ partial,
                                                             const BatchCase<R>* __restrict__ cases,
                                                             double* __restrict__ out) {
-  const Consts<R>& k = cases[blockIdx.y].k;
-  obs_final<kObsQ>(partial + size_t(blockIdx.y) * stride * kObsQ, (k.nx + kBlock - 1) / kBlock * k.ny, blockIdx.x,
+  const BatchCase<R>& c = cases[blockIdx.y];
+  obs_final<kObsQ>(partial + size_t(c.row0) * kObsQ, (c.k.nx + kBlock - 1) / kBlock * c.k.ny, blockIdx.x,
                    out + size_t(blockIdx.y) * kObsQ);
 }
 

@@ -24,19 +24,18 @@ constexpr size_t kAlign = 256;
 constexpr int kTwoStepBlock = 960, kTwoStepX = 64, kTwoStepY = 12;
 constexpr int64_t kStreamPool = int64_t(256) << 20;  // pools beyond the last-level cache
 constexpr int kMaxGridY = 65535;
-constexpr int kObsCases = 256;  // cases per launch of the observables, at most (bounds their scratch)
 constexpr int kMinTileCells = 64;  // smallest tile the schedule accepts (sizes the tile table)
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct BatchLayout {
   std::vector<int64_t> state_off[2];  // element offsets per case
   int64_t pool_elems = 0;
-  size_t off_pool = 0, off_backup = 0, off_cases = 0, off_tiles = 0, off_partial = 0, off_out = 0;
+  size_t off_pool = 0, off_backup = 0, off_cases = 0, off_tiles = 0, off_rows = 0, off_partial = 0, off_out = 0;
   size_t off_sync = 0;  // the persistent kernel's barrier: its counts (256 B apart), then the failure flag
   size_t total = 0;
   int max_tiles = 0;
-  int max_obs_blocks = 0;
-  int obs_cases = 0;  // cases one launch of the observables covers
+  std::vector<int32_t> row0;  // first row tile of each case
+  int nrows = 0;              // row tiles of all cases
   size_t esize = 4;
   int rows = 19;        // rows per lattice row of a state buffer: 19 populations (+ 3 field rows)
   bool fields = false;  // the cases carry per-cell fields (LBM_CELL_FIELDS)
@@ -64,6 +63,7 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
   int64_t e = 0;
   L.state_off[0].resize(n);
   L.state_off[1].resize(n);
+  L.row0.resize(n);
   for (int i = 0; i < n; ++i) {
     const int64_t plane = plane_elems(int64_t(pitch_of(g[i].nx)) * g[i].ny);
     for (int s = 0; s < 2; ++s) {
@@ -71,8 +71,9 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
       e += (L.rows * plane + 63) / 64 * 64;  // 256-byte aligned per buffer
     }
     L.max_tiles += std::max(int((int64_t(pitch_of(g[i].nx)) * g[i].ny + kMinTileCells - 1) / kMinTileCells),
-                            tiles_of(g[i], kT3X, kT3Y) + tiles_of(g[i], kBlock, 1));
-    L.max_obs_blocks = std::max(L.max_obs_blocks, ((g[i].nx + kBlock - 1) / kBlock) * g[i].ny);
+                            tiles_of(g[i], kT3X, kT3Y));
+    L.row0[i] = L.nrows;
+    L.nrows += tiles_of(g[i], kBlock, 1);
   }
   L.pool_elems = e;
   size_t o = 0;
@@ -84,11 +85,12 @@ BatchLayout make_batch_layout(const lbm_geometry* g, int n) {
   o += align_up(size_t(n) * (L.esize == 8 ? sizeof(BatchCase<double>) : sizeof(BatchCase<float>)));
   L.off_tiles = o;
   o += align_up(size_t(L.max_tiles) * sizeof(Tile));
-  L.obs_cases = std::min(n, kObsCases);
+  L.off_rows = o;
+  o += align_up(size_t(L.nrows) * sizeof(Tile));
   L.off_partial = o;
-  o += align_up(size_t(L.obs_cases) * L.max_obs_blocks * kObsQ * sizeof(double));
+  o += align_up(size_t(L.nrows) * kObsQ * sizeof(double));
   L.off_out = o;
-  o += align_up(size_t(L.obs_cases) * kObsQ * sizeof(double));
+  o += align_up(size_t(n) * kObsQ * sizeof(double));
   L.off_sync = o;
   o += align_up(size_t(kBarrierWords + 1) * 256);
   L.total = o;
@@ -111,7 +113,6 @@ struct lbm_batch {
   int64_t step = 0;
   lbm_schedule sched{256, 1, 0, 0};
   int ntiles = 0;
-  int nrow_tiles = 0;  // tiles of kBlock x 1 behind them, for a single step of the several-step form
   int persistent_grid = 0;
   long long barrier_limit = 0;  // wall-clock ticks a persistent barrier waits at most
   int wall_khz = 0;             // the device wall clock's rate
@@ -128,6 +129,7 @@ struct lbm_batch {
   // elements of one state buffer of case i
   size_t state_elems(int i) const { return size_t(L.rows) * plane_elems(int64_t(pitch_of(g[i].nx)) * g[i].ny); }
   Tile* tiles() { return reinterpret_cast<Tile*>(ws + L.off_tiles); }
+  Tile* rows() { return reinterpret_cast<Tile*>(ws + L.off_rows); }
   double* partial() { return reinterpret_cast<double*>(ws + L.off_partial); }
   double* out() { return reinterpret_cast<double*>(ws + L.off_out); }
   unsigned int* barrier_count() { return reinterpret_cast<unsigned int*>(ws + L.off_sync); }
@@ -232,6 +234,7 @@ lbm_status upload_cases(lbm_batch* b) {
     h[i].k = bconsts<R>(b, i);
     h[i].off[0] = b->L.state_off[0][i];
     h[i].off[1] = b->L.state_off[1][i];
+    h[i].row0 = b->L.row0[i];
   }
   if (hipMemcpyAsync(b->cases<R>(), h.data(), h.size() * sizeof(BatchCase<R>), hipMemcpyHostToDevice, b->stream) !=
       hipSuccess)
@@ -240,23 +243,18 @@ lbm_status upload_cases(lbm_batch* b) {
   return LBM_OK;
 }
 
-// Build the tile list for a tile shape (and, with `rows`, a list of kBlock x 1
-// tiles behind it); cases in order, rows then columns.
-lbm_status build_tiles(lbm_batch* b, int tx, int ty, bool rows) {
+// Upload the tile list of a tile shape to dst, which holds `room` tiles; cases
+// in order, rows then columns.
+lbm_status build_tiles(lbm_batch* b, int tx, int ty, Tile* dst, int room, int& count) {
   std::vector<Tile> t;
-  const auto add = [&](int w, int h) {
-    for (int i = 0; i < b->n; ++i)
-      for (int y0 = 0; y0 < b->g[i].ny; y0 += h)
-        for (int x0 = 0; x0 < b->g[i].nx; x0 += w) t.push_back({i, x0, y0, 0});
-    return int(t.size());
-  };
-  const int ntiles = add(tx, ty), all = rows ? add(kBlock, 1) : ntiles;
-  if (int(t.size()) > b->L.max_tiles) return bfail(b, LBM_ERR_INVALID_ARG, "tile too small");
-  if (hipMemcpyAsync(b->tiles(), t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice, b->stream) != hipSuccess)
+  for (int i = 0; i < b->n; ++i)
+    for (int y0 = 0; y0 < b->g[i].ny; y0 += ty)
+      for (int x0 = 0; x0 < b->g[i].nx; x0 += tx) t.push_back({i, x0, y0, 0});
+  if (int(t.size()) > room) return bfail(b, LBM_ERR_INVALID_ARG, "tile too small");
+  if (hipMemcpyAsync(dst, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice, b->stream) != hipSuccess)
     return bfail(b, LBM_ERR_DEVICE, "tile table upload failed");
   if (hipStreamSynchronize(b->stream) != hipSuccess) return bfail(b, LBM_ERR_DEVICE, "tile table sync failed");
-  b->ntiles = ntiles;
-  b->nrow_tiles = all - ntiles;
+  count = int(t.size());
   return LBM_OK;
 }
 
@@ -355,8 +353,8 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
       while (nsteps - s >= 3) launch(std::integral_constant<int, 3>{});
       if (nsteps - s == 2) launch(std::integral_constant<int, 2>{});
       if (nsteps - s == 1) {
-        hipLaunchKernelGGL((k_batch_step<R, MAT, true>), dim3(b->nrow_tiles), dim3(kBlock), 0, b->stream, pool, cases,
-                           tiles + b->ntiles, b->nrow_tiles, b->parity, kBlock, 1);
+        hipLaunchKernelGGL((k_batch_step<R, MAT, true>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, pool, cases,
+                           static_cast<const Tile*>(b->rows()), b->L.nrows, b->parity, kBlock, 1);
         b->parity ^= 1;
         s += 1;
       }
@@ -404,7 +402,9 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
         return bfail(b, LBM_ERR_INVALID_ARG, "the two-step form needs walls and inlet / outlet columns (no periodic axis)");
   b->sched = s;
   const bool several = s.block == kTwoStepBlock;
-  if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y, several); st != LBM_OK)
+  if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y, b->tiles(), b->L.max_tiles,
+                                  b->ntiles);
+      st != LBM_OK)
     return st;
   if (s.persistent)
     return b->L.fields ? persistent_grid<R, MAT_FULL>(b, &b->persistent_grid)
@@ -414,14 +414,12 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
 
 template <typename R>
 lbm_status init_t(lbm_batch* b) {
-  for (int i = 0; i < b->n; i += kMaxGridY) {
-    const dim3 grid(b->L.max_obs_blocks, std::min(b->n - i, kMaxGridY));
-    if (b->L.fields)
-      hipLaunchKernelGGL((k_batch_init<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(), b->cases<R>() + i);
-    else
-      hipLaunchKernelGGL((k_batch_init<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
-                         b->cases<R>() + i);
-  }
+  if (b->L.fields)
+    hipLaunchKernelGGL((k_batch_init<R, MAT_FULL>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, b->pool<R>(),
+                       b->cases<R>(), b->rows());
+  else
+    hipLaunchKernelGGL((k_batch_init<R, MAT_LAYERED>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, b->pool<R>(),
+                       b->cases<R>(), b->rows());
   hipLaunchKernelGGL(k_clear_barrier, dim3(1), dim3(64), 0, b->stream, b->barrier_count(), b->barrier_failed(), 1);
   b->parity = 0;
   b->step = 0;
@@ -429,9 +427,9 @@ lbm_status init_t(lbm_batch* b) {
   return e == hipSuccess ? LBM_OK : bfail(b, LBM_ERR_DEVICE, std::string("batch init: ") + hipGetErrorString(e));
 }
 
-// Observables of every case: one reduction over all of them (in groups of
-// kObsCases), one copy and one wait, where a launch, a copy and a wait per
-// case took 45 us each (48 cases: 2.0 ms, now 0.1).
+// Observables of every case: one reduction over all of them, one copy and one
+// wait, where a launch, a copy and a wait per case took 45 us each (48 cases:
+// 2.0 ms, now 0.1).
 template <typename R>
 lbm_status observables_t(lbm_batch* b, lbm_obs* out) {
   std::vector<double> host;
@@ -440,22 +438,19 @@ lbm_status observables_t(lbm_batch* b, lbm_obs* out) {
   } catch (const std::bad_alloc&) {
     return bfail(b, LBM_ERR_DEVICE, "out of host memory");
   }
-  for (int i0 = 0; i0 < b->n; i0 += b->L.obs_cases) {
-    const int n = std::min(b->n - i0, b->L.obs_cases);
-    const dim3 grid(b->L.max_obs_blocks, n);
-    if (b->L.fields)
-      hipLaunchKernelGGL((k_batch_obs<R, MAT_FULL>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
-                         b->cases<R>() + i0, b->parity, b->partial());
-    else
-      hipLaunchKernelGGL((k_batch_obs<R, MAT_LAYERED>), grid, dim3(kBlock), 0, b->stream, b->pool<R>(),
-                         b->cases<R>() + i0, b->parity, b->partial());
-    hipLaunchKernelGGL((k_batch_obs_final<R>), dim3(kObsQ, n), dim3(kFinal), 0, b->stream, b->partial(),
-                       b->L.max_obs_blocks, b->cases<R>() + i0, b->out());
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(host.data() + size_t(i0) * kObsQ, b->out(), size_t(n) * kObsQ * sizeof(double),
-                       hipMemcpyDeviceToHost, b->stream) != hipSuccess)
-      return bfail(b, LBM_ERR_DEVICE, "batch observables failed");
-  }
+  if (b->L.fields)
+    hipLaunchKernelGGL((k_batch_obs<R, MAT_FULL>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, b->pool<R>(),
+                       b->cases<R>(), b->rows(), b->parity, b->partial());
+  else
+    hipLaunchKernelGGL((k_batch_obs<R, MAT_LAYERED>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, b->pool<R>(),
+                       b->cases<R>(), b->rows(), b->parity, b->partial());
+  for (int i = 0; i < b->n; i += kMaxGridY)
+    hipLaunchKernelGGL((k_batch_obs_final<R>), dim3(kObsQ, std::min(b->n - i, kMaxGridY)), dim3(kFinal), 0, b->stream,
+                       b->partial(), b->cases<R>() + i, b->out() + size_t(i) * kObsQ);
+  if (hipGetLastError() != hipSuccess ||
+      hipMemcpyAsync(host.data(), b->out(), host.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream) !=
+          hipSuccess)
+    return bfail(b, LBM_ERR_DEVICE, "batch observables failed");
   if (lbm_status st = barrier_status(b); st != LBM_OK) return st;  // waits for the copies
   for (int i = 0; i < b->n; ++i) {
     const lbm_geometry& g = b->g[i];
@@ -691,6 +686,8 @@ lbm_status lbm_batch_create(const lbm_geometry* g, const lbm_params* p, int32_t 
           st != LBM_OK)
         return st;
   hipLaunchKernelGGL(k_clear_barrier, dim3(1), dim3(64), 0, b->stream, b->barrier_count(), b->barrier_failed(), 1);
+  int nrows = 0;
+  if (lbm_status st = build_tiles(b, kBlock, 1, b->rows(), b->L.nrows, nrows); st != LBM_OK) return st;
   lbm_schedule s{256, 1, 0, 0};
   return dbl ? set_schedule_t<double>(b, s) : set_schedule_t<float>(b, s);
 }
