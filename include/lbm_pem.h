@@ -376,10 +376,12 @@ lbm_status lbm_batch_get_schedule(const lbm_batch* b, lbm_schedule* s);
  * candidate whose grid barrier times out (lbm_batch_step) is skipped. */
 lbm_status lbm_batch_autotune(lbm_batch* b, int32_t trial_steps, lbm_schedule* best, double* best_ms_per_step);
 /* lbm_batch_autotune with a tuner cache file at cache_path (NULL: none): a
- * JSON object holding one schedule per line, keyed by GPU architecture,
- * precision and the case lattice sizes ("gfx950|fp32|256x64,512x128").  A
- * usable entry for this batch is set without trials (*from_cache = 1);
- * otherwise the trials run and the entry is added or replaced (the file is
+ * JSON object holding one schedule per line, keyed by GPU architecture, the
+ * library's step kernels and the material form ("k3", or "k3f" with
+ * LBM_CELL_FIELDS), precision and the case lattice sizes
+ * ("gfx950|k3|fp32|256x64,512x128").  A usable entry for this batch is set
+ * without trials (*from_cache = 1); entries of other kernels are kept and
+ * not used; otherwise the trials run and the entry is added or replaced (the file is
  * rewritten through a temporary file; concurrent writers are not
  * coordinated).  A file in any other form is left alone and not used
  * (lbm_batch_last_error says so; the status is that of the trials).

@@ -561,9 +561,12 @@ lbm_status autotune_t(lbm_batch* b, int trial_steps, lbm_schedule* best, double*
 }
 
 // Tuner cache file: a JSON object with one schedule per line,
-//   "gfx950|fp32|256x64,512x128": {"tile_x": 128, "tile_y": 1, "persistent": 0, "block": 0, "ms_per_step": 0.158}
-// keyed by the GPU architecture, the precision and the case lattice sizes in
-// case order.
+//   "gfx950|k3|fp32|256x64,512x128": {"tile_x": 128, "tile_y": 1, "persistent": 0, "block": 0, "ms_per_step": 0.158}
+// keyed by the GPU architecture, the step kernels a schedule stands for, the
+// material form ("k3f": per-cell fields), the precision and the case lattice
+// sizes in case order.  kTuneKernels changes with what a schedule runs or how
+// fast its kernels are: entries timed on others are then not used.
+constexpr const char* kTuneKernels = "k3";
 std::string tune_key(const lbm_batch* b) {
   std::string arch = "unknown";
   int dev = 0;
@@ -572,7 +575,7 @@ std::string tune_key(const lbm_batch* b) {
     arch = prop.gcnArchName;
     arch = arch.substr(0, arch.find(':'));
   }
-  std::string k = arch + "|fp" + std::to_string(b->g[0].precision) + "|";
+  std::string k = arch + "|" + kTuneKernels + (b->L.fields ? "f" : "") + "|fp" + std::to_string(b->g[0].precision) + "|";
   for (int i = 0; i < b->n; ++i) k += (i ? "," : "") + std::to_string(b->g[i].nx) + "x" + std::to_string(b->g[i].ny);
   return k;
 }

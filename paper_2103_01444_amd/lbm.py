@@ -547,7 +547,7 @@ class BatchedSweep:
     lbm_batch_*).  ``cases``: workload dictionaries (see ``workloads``), all
     of one precision.  The schedule (tile shape, per-step or persistent
     launch) is picked by ``autotune``, which the library caches in a JSON
-    file keyed by GPU architecture, precision and the case lattice sizes.  ``fields``: None
+    file keyed by GPU architecture, step kernels, precision and the case lattice sizes.  ``fields``: None
     (layered cases), or one entry per case, None or a dict with any of
     ``phi``, ``inv_k``, ``d_eff`` ([ny, nx] arrays): the cases then carry
     per-cell fields (missing ones derived from the layers) and each steps
@@ -623,7 +623,7 @@ class BatchedSweep:
     def autotune(self, trial_steps: int = 20, cache_path: str | None = None) -> dict:
         """Pick the fastest schedule (lbm_batch_autotune_cached: from the
         library's tuner cache file at ``cache_path`` when it holds one for
-        this GPU, precision and set of lattice sizes)."""
+        this GPU, these kernels, precision and set of lattice sizes)."""
         best = Schedule()
         ms = ctypes.c_double()
         hit = ctypes.c_int32()
