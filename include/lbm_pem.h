@@ -371,7 +371,8 @@ lbm_status lbm_batch_set_fields(lbm_batch* b, int32_t i, const void* phi, const 
                                 const void* d_eff);
 lbm_status lbm_batch_set_schedule(lbm_batch* b, const lbm_schedule* s);
 lbm_status lbm_batch_get_schedule(const lbm_batch* b, lbm_schedule* s);
-/* Time every candidate schedule for trial_steps steps from the current
+/* Time every candidate schedule for trial_steps steps (rounded up to whole
+ * launches for the three-step form) from the current
  * state; keep the fastest, restore the state.  Synchronous.  A persistent
  * candidate whose grid barrier times out (lbm_batch_step) is skipped. */
 lbm_status lbm_batch_autotune(lbm_batch* b, int32_t trial_steps, lbm_schedule* best, double* best_ms_per_step);

@@ -518,10 +518,13 @@ lbm_status autotune_t(lbm_batch* b, int trial_steps, lbm_schedule* best, double*
   for (const lbm_schedule& s : cand) {
     const int persistent = s.persistent;
     if (set_schedule_t<R>(b, s) != LBM_OK) continue;  // shape not usable here
-    st = launch_steps<R>(b, 2);                        // warm up
+    // the several-step form is warmed up and timed in whole launches of three
+    const bool threes = s.block == kTwoStepBlock;
+    const int64_t trial = threes ? (int64_t(trial_steps) + 2) / 3 * 3 : trial_steps;
+    st = launch_steps<R>(b, threes ? 3 : 2);  // warm up
     if (st != LBM_OK) break;
     (void)hipEventRecord(e0, b->stream);
-    st = launch_steps<R>(b, trial_steps);
+    st = launch_steps<R>(b, trial);
     if (st != LBM_OK) break;
     (void)hipEventRecord(e1, b->stream);
     if (hipEventSynchronize(e1) != hipSuccess) {
@@ -536,7 +539,7 @@ lbm_status autotune_t(lbm_batch* b, int trial_steps, lbm_schedule* best, double*
     }
     float ms = 0;
     (void)hipEventElapsedTime(&ms, e0, e1);
-    const double per = double(ms) / trial_steps;
+    const double per = double(ms) / double(trial);
     if (per < best_t) {
       best_t = per;
       best_s = s;

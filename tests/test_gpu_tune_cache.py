@@ -1,4 +1,4 @@
-"""Tuner cache entries belong to the kernels and the material form they were
+"""Tuner: trials time each form in its own launches.  Cache entries belong to the kernels and the material form they were
 timed on: an entry under an older key, or of the other form, is not used."""
 import json
 
@@ -36,3 +36,20 @@ def test_material_forms_have_entries_of_their_own(tmp_path):
     assert not _batch(fields=True)[0].autotune(trial_steps=3, cache_path=path)["cached"]
     assert _batch(fields=True)[0].autotune(trial_steps=3, cache_path=path)["cached"]
     assert _batch()[0].autotune(trial_steps=3, cache_path=path)["cached"]
+
+
+@pytest.mark.parametrize("trial_steps", [1, 2, 4])
+def test_short_trials_time_the_three_step_form(trial_steps):
+    """A trial that is no multiple of three is timed in launches of three, as
+    a run has them: on the 64-case sweep that form takes half of any other's
+    time a step."""
+    from paper_2103_01444_amd import lbm
+    b = lbm.BatchedSweep(W.batched_cases())
+    b.step(4)
+    before = [b.populations(i).clone() for i in (0, 31, 63)]
+    r = b.autotune(trial_steps=trial_steps)
+    print(r, flush=True)
+    assert r["block"] == 960
+    assert b.step_count == 4
+    for i, p in zip((0, 31, 63), before):
+        assert torch.equal(b.populations(i), p)
