@@ -451,7 +451,7 @@ __device__ __forceinline__ void flow_adj(const MacroTape<R>& t, const AdjMat<R>&
 // of xp's populations to lth1 and lc1 (per population) and of its velocity to
 // lux, luy, and the materials'.
 template <typename R, bool EXT>
-__device__ __forceinline__ void inlet_scalars_adj(const R (&mu_b)[10], R ux, R uy, R th1, R c1, R ubx, bool pressure,
+__device__ __forceinline__ void inlet_scalars_adj(const R (&mu_b)[10], R ux, R uy, R th1, R c1, bool pressure,
                                                   const AdjMat<R>& mxp, const Consts<R>& k, R& lux, R& luy, R& lth1,
                                                   R& lc1, MatAdj<R>& maxp, MatAdj<R>& mab) {
 #pragma unroll

@@ -198,8 +198,8 @@ __device__ __forceinline__ void reverse_node(const R* __restrict__ S, const R* _
     if (x <= 1) {
       MatAdj<R> axp{}, ab{};
       R lt1 = R(0), lc1 = R(0);
-      inlet_scalars_adj<R, EXT>(mub, uxp, uyp, theta_of(g, m.isig), sum5(g + 5), ubx, pressure, m, k, blx, bly, lt1,
-                                lc1, axp, ab);
+      inlet_scalars_adj<R, EXT>(mub, uxp, uyp, theta_of(g, m.isig), sum5(g + 5), pressure, m, k, blx, bly, lt1, lc1,
+                                axp, ab);
       if (x == 0) {
         ma.aC += ab.aC;
       } else {
@@ -344,9 +344,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
 // Two reverse steps in one launch, at the states S1 (first) and S0, with the
 // bits of two single ones.  A workgroup takes a tile of at most kAdjX columns
 // and ROWS - 2 rows.  The first step runs over the tile and a ring of one
-// node, extended to both nodes of a boundary pair where it holds one, a row
-// per wavefront, and leaves mu in LDS; the second gathers from there and
-// writes the tile's.  Of the 264 bytes a node that a single FP32 step moves
+// node, a row per wavefront, and leaves mu in LDS; the second gathers from
+// there and writes the tile's.  Of the 264 bytes a node that a single FP32 step moves
 // (S, mu in and out, the gradient twice, the fields) lambda's 152 and the
 // gradient's 24 are halved, and the ring adds a share of S and mu.  Reverse
 // sweep with its replay, per step, one -> two steps per launch: 1024x256 FP32
@@ -364,11 +363,9 @@ __global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S
   __shared__ R lds[ROWS * 19 * 64];
   int bx, by;
   xcd_tile(gridDim.x, gridDim.y, bx, by);
-  // tiles equal within one column
+  // tiles equal within one column: 30 columns or more wide, or the whole row
   const int x0 = int(int64_t(bx) * k.nx / gridDim.x), x1 = int(int64_t(bx + 1) * k.nx / gridDim.x);
-  int xl = x0 > 0 ? x0 - 1 : 0, xr = x1 < k.nx ? x1 + 1 : k.nx;  // the first step's columns
-  if (xl == 1) xl = 0;
-  if (xr == k.nx - 1) xr = k.nx;
+  const int xl = x0 > 0 ? x0 - 1 : 0, xr = x1 < k.nx ? x1 + 1 : k.nx;  // the first step's columns
   const int i = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int x = xl + i, y0 = by * (ROWS - 2), y = y0 - 1 + j;
   const bool row = (unsigned)y < (unsigned)k.ny;
