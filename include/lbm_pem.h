@@ -216,7 +216,10 @@ lbm_status lbm_init_equilibrium(lbm_ctx* ctx);
  * the CL source).  Lattices without periodic axes
  * advance three steps per kernel launch (what is left over in launches of
  * two or one); the states are bit-identical to single steps.
- * Async; never synchronizes. */
+ * Async; never synchronizes.  Captured into a HIP graph, an even nsteps ends
+ * in the state buffer it began in, so that every replay advances the state
+ * by nsteps (an odd one repeats the same steps); the step count is not
+ * advanced by replays. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t nsteps);
 
 /* Observables (Section 5) of the current state, reduced in double precision

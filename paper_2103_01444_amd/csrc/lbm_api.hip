@@ -217,16 +217,17 @@ void launch_step_mat(lbm_ctx* c, int64_t n) {
   const MatPtrs<R> m = mat_ptrs<R>(c);
   const Consts<R> k = consts<R>(c);
   if (two_steps_per_launch(c)) {
-    for (; n >= 3 && n != 4; n -= 3) {  // four: two pairs
+    for (; n >= 3 && n != 4; n -= 3) {
       launch_step_triple<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), static_cast<R*>(c->state(c->cur ^ 1)), m,
                                  k);
       c->cur ^= 1;
     }
-    for (; n >= 2; n -= 2) {
-      launch_step_pair<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), nullptr,
-                               static_cast<R*>(c->state(c->cur ^ 1)), m, k, c->stream);
-      c->cur ^= 1;
-    }
+    if (n == 4 || (n == 2 && !capturing(c->stream)))  // two pairs, or one
+      for (; n > 0; n -= 2) {
+        launch_step_pair<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), nullptr,
+                                 static_cast<R*>(c->state(c->cur ^ 1)), m, k, c->stream);
+        c->cur ^= 1;
+      }
   }
   for (int64_t i = 0; i < n; ++i) {
     launch_step_kernel<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), static_cast<R*>(c->state(c->cur ^ 1)), m,

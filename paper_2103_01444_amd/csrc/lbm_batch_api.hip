@@ -351,8 +351,8 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
         s += n;
       };
       while (nsteps - s >= 3) launch(std::integral_constant<int, 3>{});
-      if (nsteps - s == 2) launch(std::integral_constant<int, 2>{});
-      if (nsteps - s == 1) {
+      if (nsteps - s == 2 && !capturing(b->stream)) launch(std::integral_constant<int, 2>{});
+      while (s < nsteps) {
         hipLaunchKernelGGL((k_batch_step<R, MAT, true>), dim3(b->L.nrows), dim3(kBlock), 0, b->stream, pool, cases,
                            static_cast<const Tile*>(b->rows()), b->L.nrows, b->parity, kBlock, 1);
         b->parity ^= 1;

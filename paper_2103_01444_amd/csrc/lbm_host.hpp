@@ -44,6 +44,16 @@ inline int64_t plane_elems(int64_t pitched_cells) {
 // of 400 000 nodes or more).
 inline int32_t near_offset(int64_t lane, size_t esize) { return lane * int64_t(esize) < (int64_t(1) << 32); }
 
+// Whether the stream is being captured into a graph.  A graph of steps is
+// replayed from the buffer it was captured at, so one of an even number of
+// steps advances the state at every replay if its launches swap the two
+// buffers an even number of times, as single steps do: under capture a run
+// takes as many launches, modulo two, as it has steps.
+inline bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return stream && hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // Scalars derived from (geometry, params).
 struct Derived {
   double nu = 0, dx = 0, dt = 0, u_avg = 0, invk_gdl = 0, d_gdl = 0, alpha_scale = 0, ln_k0 = 0;
