@@ -199,8 +199,10 @@ lbm_status lbm_create(const lbm_geometry* g, void* dev_ws, size_t ws_bytes, void
  * and d_eff (O2 diffusivity, lattice units) are optional per-cell device
  * arrays [ny][nx]; NULL takes the layered value from *p (channel: phi = 1,
  * 1/K = 0, D = D_f_lat; GDL and CL: phi_gdl, Da_gdl or Kozeny-Carman,
- * deff_ratio_gdl or Bruggeman).  The arrays are copied; the caller may free
- * them afterwards.  Synchronous.  Errors: LBM_ERR_INVALID_ARG,
+ * deff_ratio_gdl or Bruggeman).  1/K may be any finite number >= 0; a cell
+ * where (1/2 + phi nu / (4 K))^2 overflows the precision (from 1/K of about
+ * 1e22 in FP32, 1e156 in FP64) is at rest and takes no drag.  The arrays are
+ * copied; the caller may free them afterwards.  Synchronous.  Errors: LBM_ERR_INVALID_ARG,
  * LBM_ERR_UNSTABLE_PARAMS (tau_f <= 0.5, a diffusivity outside
  * (0, 1/(4 sqrt 3)], porosity outside (0, 1], 1/K < 0, inlet peak velocity
  * above 0.1; with LBM_PRESSURE_INLET: the plane-Poiseuille peak velocity
@@ -343,8 +345,8 @@ typedef struct lbm_schedule {
                             * loop, or one per thread when the tile has 256), or 64 / 128 when the tile has
                             * exactly that many cells (one per thread); the persistent form uses 256.
                             * 960 with 64 x 12 tiles and persistent = 0: three steps per launch (tiles
-                            * and their halos in LDS, of the library's own shape; the one or two left over
-                            * run as single steps), for batches without
+                            * and their halos in LDS, of the library's own shape; two left over take one
+                            * launch of their own, one a single step), for batches without
                             * periodic axes */
 } lbm_schedule;
 

@@ -118,8 +118,8 @@ __device__ __forceinline__ MacroTape3<R> flow_macros_tape(const R* f, const AdjM
   }
   t.vm = fast_sqrt(dot(t.v, t.v));
   const R r = lbm::fast_momentum_root(m.l0, m.l1, t.vm);
-  t.ir = fast_rcp(r);
-  t.iden = fast_rcp(m.l0 + r);
+  t.ir = lbm::fast_rcp_inf(r);
+  t.iden = lbm::fast_rcp_inf(m.l0 + r);
   t.u = scale(t.iden, t.v);
   t.u2 = dot(t.u, t.u);
   t.drag = fma_(R(2) * m.l1, t.vm * t.iden, m.dl);

@@ -19,11 +19,14 @@ namespace lbm {
 // 1 / a and sqrt(a) from the hardware estimates and Newton steps, within 1
 // ulp (the forward step's are IEEE's: lbm_device.hpp, where the range of the
 // operands is discussed).  A root below the bound of its operand's comes out
-// too small, which no result can feel (it is a speed that is added to 1/2);
-// 1 / infinity is 0.  FP32: 4 and 6 instructions instead of 10 and 16, FP64:
-// 6 and 11 instead of 10 and 20.
-__device__ __forceinline__ float fast_rcp(float a) { return rcp_seed(a, below_inf(a)); }
-__device__ __forceinline__ double fast_rcp(double a) { return rcp_seed(a, below_inf(a)); }
+// too small, which no result can feel (it is a speed that is added to 1/2).
+// FP32: 3 and 6 instructions instead of 10 and 16, FP64: 5 and 11 instead of
+// 10 and 20.
+template <typename R>
+__device__ __forceinline__ R fast_rcp(R a) { return rcp_seed(a); }
+// 1 / a of an a that may be infinite: 0.
+template <typename R>
+__device__ __forceinline__ R fast_rcp_inf(R a) { return rcp_seed(a, below_inf(a)); }
 __device__ __forceinline__ float fast_root(float a, float c, float y) {
   const float s = c * y;
   return fma_(fma_(-s, s, a), 0.5f * y, s);
@@ -160,8 +163,8 @@ __device__ __forceinline__ MacroTape<R> flow_macros_tape(const R* f, R th, const
   }
   t.vm = fast_sqrt(fma_(t.vx, t.vx, t.vy * t.vy));
   const R r = fast_momentum_root(m.l0, m.l1, t.vm);
-  t.ir = fast_rcp(r);
-  t.iden = fast_rcp(m.l0 + r);
+  t.ir = fast_rcp_inf(r);
+  t.iden = fast_rcp_inf(m.l0 + r);
   t.ux = t.vx * t.iden;
   t.uy = t.vy * t.iden;
   t.u2 = fma_(t.ux, t.ux, t.uy * t.uy);

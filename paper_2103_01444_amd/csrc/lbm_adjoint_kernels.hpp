@@ -351,8 +351,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
 // sweep with its replay, per step, one -> two steps per launch: 1024x256 FP32
 // 24.5 -> 18.7 us.  ROWS = 8, or 4 on lattices of fewer than 2^17 nodes,
 // which leave CUs idle (200x40 FP64 13.3 -> 10.4, FP32 9.8 -> 9.3; 1024x256
-// FP32 18.7 with 8, 19.7 with 4, 19.0 with 12).  Lattices without periodic
-// axes.
+// FP32 18.7 with 8, 19.7 with 4, 19.0 with 12).  With the rates and sixths
+// that the FP32 gradient's error asked for (rate_at, nth) 19.2 -> 19.6 there,
+// 200x40 FP64 9.8 -> 9.9 (11.0 with all model options, 10.4 before).
+// Lattices without periodic axes.
 constexpr int kAdjX = 60;
 template <typename R, bool EXT, int ROWS>
 __global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S1, const R* __restrict__ S0,

@@ -170,8 +170,10 @@ void launch_step_kernel(lbm_ctx* c, const R* src, R* dst, const MatPtrs<R>& m, c
 
 // Lattices with walls and inlet / outlet columns advance three steps per
 // launch, or two where states between are kept or two are left (k_step3,
-// k_step2: the same states, bit for bit, as single steps), which is faster at
-// every size.  Three steps whose two middle states are stored as well are
+// k_step2: the same states, bit for bit, as single steps), which is faster
+// than single steps at every size; threes are faster than pairs at all but
+// FP32 lattices of about 2^20 nodes (2048x512: 17.0 against 16.4 us a step).
+// Three steps whose two middle states are stored as well are
 // slower than pairs (the 1024x256 gradient 11.8 against 11.6 ms, the 200x40
 // FP64 one 2.64 against 2.40).
 bool two_steps_per_launch(const lbm_ctx* c) { return !(c->g.flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y)); }

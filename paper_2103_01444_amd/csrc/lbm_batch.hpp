@@ -137,8 +137,9 @@ __global__ __launch_bounds__(BS) void k_batch_step(R* __restrict__ pool, const B
 // left over is k_batch_step's, on rows of kBlock nodes: on these tiles it took
 // 217 us for the 64 cases, longer than two.)  Cases with periodic axes are not
 // scheduled so.  Against pairs of steps in tiles of 48x8, 40 steps of 48
-// cases beyond the last-level cache take 3.15 against 3.66 ms; 200 steps of
-// 39 cases of 200x40, which fit it, 1.89 against 1.90.
+// cases beyond the last-level cache took 3.15 ms instead of 3.66 and 200 steps
+// of 39 cases of 200x40, which fit it, 1.89 instead of 1.90 (with restart and
+// observables; the steps alone, what is left over included, now 2.52 and 1.56).
 template <typename R, int MAT, int SAUX, int STEPS>
 __global__ __launch_bounds__((Tile3<kT3X, kT3Y>::threads)) void k_batch_step3(
     R* __restrict__ pool, const BatchCase<R>* __restrict__ cases, const Tile* __restrict__ tiles, int ntiles,

@@ -21,7 +21,7 @@ namespace {
 constexpr size_t kAlign = 256;
 // The schedule that asks for several steps per launch: its workgroup size
 // and tile shape name the form (the kernel's own tiles are kT3X x kT3Y).
-constexpr int kTwoStepBlock = 960, kTwoStepX = 64, kTwoStepY = 12;
+constexpr int kThreesBlock = 960, kThreesX = 64, kThreesY = 12;
 constexpr int64_t kStreamPool = int64_t(256) << 20;  // pools beyond the last-level cache
 constexpr int kMaxGridY = 65535;
 constexpr int kMinTileCells = 64;  // smallest tile the schedule accepts (sizes the tile table)
@@ -336,7 +336,7 @@ lbm_status launch_steps_mat(lbm_batch* b, int64_t nsteps) {
     const int bs = b->sched.block == 64 || b->sched.block == 128 ? b->sched.block : kBlock;
     const dim3 grid(b->ntiles);
     int64_t s = 0;
-    if (b->sched.block == kTwoStepBlock) {
+    if (b->sched.block == kThreesBlock) {
       const bool stream = int64_t(b->L.pool_elems) * int64_t(sizeof(R)) > kStreamPool;
       const auto launch = [&](auto steps) {
         constexpr int n = decltype(steps)::value;
@@ -392,16 +392,16 @@ lbm_status set_schedule_t(lbm_batch* b, const lbm_schedule& s) {
     return bfail(b, LBM_ERR_INVALID_ARG, "tile shape out of range");
   if (!(s.block == 0 || s.block == kBlock ||
         ((s.block == 64 || s.block == 128) && s.tile_x * s.tile_y == s.block && !s.persistent) ||
-        (s.block == kTwoStepBlock && s.tile_x == kTwoStepX && s.tile_y == kTwoStepY && !s.persistent)))
+        (s.block == kThreesBlock && s.tile_x == kThreesX && s.tile_y == kThreesY && !s.persistent)))
     return bfail(b, LBM_ERR_INVALID_ARG,
                  "workgroup size: 0 or 256, 64 / 128 for a per-step tile of as many cells, or 960 for the "
-                 "two-step form of 64 x 12 tiles");
-  if (s.block == kTwoStepBlock)
+                 "three-step form of 64 x 12 tiles");
+  if (s.block == kThreesBlock)
     for (int i = 0; i < b->n; ++i)
       if (b->g[i].flags & (LBM_PERIODIC_X | LBM_PERIODIC_Y))
-        return bfail(b, LBM_ERR_INVALID_ARG, "the two-step form needs walls and inlet / outlet columns (no periodic axis)");
+        return bfail(b, LBM_ERR_INVALID_ARG, "the three-step form needs walls and inlet / outlet columns (no periodic axis)");
   b->sched = s;
-  const bool several = s.block == kTwoStepBlock;
+  const bool several = s.block == kThreesBlock;
   if (lbm_status st = build_tiles(b, several ? kT3X : s.tile_x, several ? kT3Y : s.tile_y, b->tiles(), b->L.max_tiles,
                                   b->ntiles);
       st != LBM_OK)
@@ -514,12 +514,12 @@ lbm_status autotune_t(lbm_batch* b, int trial_steps, lbm_schedule* best, double*
       const int cells = sh[0] * sh[1];
       if (!persistent && (cells == 64 || cells == 128)) cand.push_back({sh[0], sh[1], 0, cells});
     }
-  cand.push_back({kTwoStepX, kTwoStepY, 0, kTwoStepBlock});
+  cand.push_back({kThreesX, kThreesY, 0, kThreesBlock});
   for (const lbm_schedule& s : cand) {
     const int persistent = s.persistent;
     if (set_schedule_t<R>(b, s) != LBM_OK) continue;  // shape not usable here
     // the several-step form is warmed up and timed in whole launches of three
-    const bool threes = s.block == kTwoStepBlock;
+    const bool threes = s.block == kThreesBlock;
     const int64_t trial = threes ? (int64_t(trial_steps) + 2) / 3 * 3 : trial_steps;
     st = launch_steps<R>(b, threes ? 3 : 2);  // warm up
     if (st != LBM_OK) break;

@@ -88,10 +88,12 @@ struct Mat {
 //
 // From below: under 2^-100 (2^-900 in FP64), where the remainders leave the
 // range, a quotient or root may be off in its last bits, and a root of less
-// than the smallest normal number comes out too small.  Velocities may be
-// that small; no other quantity of the step can feel it (|v| is added to
-// 1/2).  Quotients by powers of the porosity, which may be denormal, are the
-// compiler's (base_fields, derive_material).  A zero denominator gives NaN.
+// than the smallest normal number comes out too small (it is a speed that is
+// added to 1/2).  Velocities ahead of a front are that small: populations of
+// up to 1e-20 differ there from those of IEEE's forms in their last bits, and
+// no larger ones (60 steps from equilibrium, every model).  Quotients by
+// powers of the porosity, which may be denormal, are the compiler's
+// (base_fields, derive_material).  A zero denominator gives NaN.
 //
 // From above: nothing bounds 1/K (any finite number >= 0 is taken), and l0 =
 // 1/2 + phi nu / (4 K) squared overflows from 1/K of about 1e22 on in FP32

@@ -86,7 +86,7 @@ struct Tile2 {
   static constexpr int threads = (N + 63) / 64 * 64;
   static_assert(threads <= 1024 && TX * TY <= threads, "two-step tile");
 };
-constexpr int kT2X = 48, kT2Y = 8;              // lattices of kT2SmallCells nodes or more, and the batch
+constexpr int kT2X = 48, kT2Y = 8;              // lattices of kT2SmallCells nodes or more
 constexpr int kT2SmallX = 16, kT2SmallY = 8;
 constexpr int64_t kT2SmallCells = int64_t(1) << 17;
 
@@ -176,10 +176,11 @@ __global__ __launch_bounds__((Tile2<TX, TY>::threads)) void k_step2(const R* __r
 //
 // The halo's extra nodes (512 computed for 27x12 = 324 kept) buy a third of
 // the memory traffic and of the launches.  Region rows are 32 nodes, two to
-// a wavefront.  Per step, k_step2 / 27x12 (us): FP32 1024x256 6.9 / 6.4,
-// 1537x431 12.5 / 12.0, 4096x1024 83.4 / 66.5; FP64 1024x256 10.5 / 9.6,
-// 2048x512 38.7 / 29.7, 4096x1024 144 / 108.  Lattices of fewer than 2^16
-// nodes leave CUs idle and take 27x4: 200x40 FP64 3.6 / 3.3 (27x12 there:
+// a wavefront.  Per step with a porosity per cell, k_step2 / 27x12 (us): FP32
+// 1024x256 6.9 / 6.7, 1537x431 12.2 / 12.2, 2048x512 16.4 / 17.0, 4096x1024
+// 82.4 / 66.5; FP64 1024x256 10.6 / 10.2, 1537x431 20.8 / 19.0, 2048x512 39.0
+// / 29.6, 4096x1024 145 / 111.  Lattices of fewer than 2^16 nodes leave CUs
+// idle and take 27x4: 200x40 FP64 4.2 / 3.4, FP32 3.8 / 3.0 (27x12 there:
 // one workgroup on 32 of 256 CUs).  64 nodes a row (59x12, 1024 threads) is
 // slower: 4096x1024 80.7.  Stores write through where the two states fit the
 // last-level cache (FP32 1024x256 6.4 against 6.7) and are plain beyond it

@@ -616,7 +616,7 @@ class BatchedSweep:
         """Tiles of tile_x x tile_y nodes, one launch per step (persistent
         = 0) or one cooperative launch (1); block: workgroup size of the
         per-step form (0 or 256; 64 / 128 for tiles of that many cells; 960
-        with 64 x 12 tiles: two steps per launch)."""
+        with 64 x 12 tiles: three steps per launch)."""
         s = Schedule(tile_x, tile_y, persistent, block)
         self._check(self.lib.lbm_batch_set_schedule(self.h, ctypes.byref(s)))
 
