@@ -89,7 +89,7 @@ __device__ __forceinline__ Mat3<R> material(const Consts3<R>& k, const R* __rest
   m.invk = invk;
   m.d = d;
   m.sqk = lbm::sqrt_(invk);
-  m.fphi = R(0.143) / (phi * lbm::sqrt_(phi));
+  m.fphi = lbm::forchheimer(phi);
   m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
   m.l1 = phi * m.fphi * m.sqk * R(0.5);
   m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;

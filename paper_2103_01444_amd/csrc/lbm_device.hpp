@@ -91,9 +91,9 @@ struct Mat {
 // than the smallest normal number comes out too small (it is a speed that is
 // added to 1/2).  Velocities ahead of a front are that small: populations of
 // up to 1e-20 differ there from those of IEEE's forms in their last bits, and
-// no larger ones (60 steps from equilibrium, every model).  Quotients by
-// powers of the porosity, which may be denormal, are the compiler's
-// (base_fields, derive_material).  A zero denominator gives NaN.
+// no larger ones (60 steps from equilibrium, every model).  Powers of the
+// porosity may be denormal: forchheimer, and the compiler's quotient in
+// base_fields.  A zero denominator gives NaN.
 //
 // From above: nothing bounds 1/K (any finite number >= 0 is taken), and l0 =
 // 1/2 + phi nu / (4 K) squared overflows from 1/K of about 1e22 on in FP32
@@ -195,6 +195,16 @@ __device__ __forceinline__ void base_fields(const Consts<R>& k, const R* __restr
   }
 }
 
+// 0.143 phi^-3/2 to the bits of IEEE's quotient, also where the power is a
+// denormal number: both operands are scaled by a power of two.  (The
+// compiler's quotient in its place made the FP32 three-field step 3 % slower:
+// 1024x256 6.09 -> 6.26 us.)
+template <typename R>
+__device__ __forceinline__ R forchheimer(R phi) {
+  constexpr R up = sizeof(R) == 4 ? R(0x1p64) : R(0x1p512);
+  return div_(R(0.143) * up, phi * sqrt_(phi) * up);
+}
+
 // The quantities the update derives from a cell's porosity, 1/K and D_eff.
 template <typename R>
 __device__ __forceinline__ Mat<R> derive_material(const Consts<R>& k, R phi, R invk, R d) {
@@ -202,7 +212,7 @@ __device__ __forceinline__ Mat<R> derive_material(const Consts<R>& k, R phi, R i
   m.phi = phi;
   m.invk = invk;
   m.sqk = sqrt_(invk);
-  m.fphi = R(0.143) / (phi * sqrt_(phi));
+  m.fphi = forchheimer(phi);
   m.l0 = R(0.5) + phi * k.nu * invk * R(0.25);
   m.l1 = phi * m.fphi * m.sqk * R(0.5);
   m.rhocp = phi * k.rhocp_f + (R(1) - phi) * k.rhocp_s;
