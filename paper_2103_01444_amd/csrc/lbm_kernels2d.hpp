@@ -32,13 +32,13 @@ __device__ __forceinline__ void xcd_tile(int nbx, int nby, int& bx, int& by) {
 }
 
 // One time step: pull-stream, boundary columns, macros, flow collision,
-// reaction, scalar collisions, store.  STREAM: non-temporal loads and plain
-// stores, for a state larger than the 256 MB last-level cache; smaller ones
-// take cached loads and stores that write through to it (aux 16, sc1): the
-// lines are there for the next step, and the end of the kernel has no L2
-// write-back to wait for.  Per step, streaming -> cached: 1024x256 FP32 9.8
-// -> 8.3 us, 2048x512 FP32 31.6 -> 25.0, 200x40 FP64 4.92 -> 4.67; 4096x1024
-// FP32 102.6 -> 120.
+// reaction, scalar collisions, store.  STREAM: non-temporal loads, each lane
+// at its own addresses (see pull), and plain stores, for a state larger than
+// the 256 MB last-level cache; smaller ones take cached loads and stores that
+// write through to it (aux 16, sc1): the lines are there for the next step,
+// and the end of the kernel has no L2 write-back to wait for.  Per step,
+// streaming -> cached: 1024x256 FP32 9.8 -> 8.3 us, 2048x512 FP32 31.6 ->
+// 25.0, 200x40 FP64 4.92 -> 4.67; 4096x1024 FP32 102.6 -> 120.
 template <typename R, int MAT, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_step(const R* __restrict__ src, R* __restrict__ dst,
                                                  const R* __restrict__ phi_f,
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kBlock) void k_step(const R* __restrict__ src, R* _
   const int y = by;
   if (x >= k.nx) return;
   R f[19];
-  const Mat<R> mt = pre_collision<R, MAT, STREAM>(src, k, phi_f, invk_f, d_f, x, y, f, y);
+  const Mat<R> mt = pre_collision<R, MAT, STREAM, !STREAM>(src, k, phi_f, invk_f, d_f, x, y, f, y);
   const bool cl = y >= k.y_cl0 && !(k.flags & F_NO_REACTION);
   collide(f, mt, k, cl);
   store_node<STREAM ? 0 : 16>(dst, k, x, y, y, f);
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kBlock) void k_fields(const R* __restrict__ src,
   const int y = blockIdx.y;
   if (x >= k.nx) return;
   R f[19];
-  const Mat<R> mt = pre_collision<R, MAT, true>(src, k, phi_f, invk_f, d_f, x, y, f, y);
+  const Mat<R> mt = pre_collision<R, MAT, true, false>(src, k, phi_f, invk_f, d_f, x, y, f, y);
   const Macro<R> a = flow_macros(f, mt, k);
   const int o = y * k.nx + x;
   if (ux) ux[o] = a.ux;
