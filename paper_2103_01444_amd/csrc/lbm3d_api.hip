@@ -223,15 +223,17 @@ void by_mat(int mat, F&& f) {
   }
 }
 
-// One step src -> dst; a state beyond the 256 MB last-level cache streams
-// past it (per step, streaming -> cached: 97x50x33 FP64 21.9 -> 18.6 us,
-// 160x80x40 FP32 31.5 -> 25.8).
+// One step src -> dst; a state of which the 256 MB last-level cache would
+// hold little beside the other one streams past it (per step, streaming ->
+// cached: 97x50x33 FP64 21.9 -> 18.6 us, 160x80x40 FP32 31.5 -> 25.8, 160x80x80
+// FP32, 128 MB, 57.6 -> 54.2; but 160x100x100 FP32, 201 MB, 88.1 -> 90.6, and
+// 160x80x60 FP64, 193 MB, 85.4 -> 85.7, layered 81.8 -> 84.2).
 template <typename R, int MAT>
 void launch_step3_kernel(lbm3d_ctx* c, const R* src, R* dst) {
   const Mat3Ptrs<R> m = mat3_ptrs<R>(c);
   const Consts3<R>& k = consts3<R>(c);
   const dim3 grid(unsigned(row_blocks(c->g.nx, 0) * c->g.ny * c->g.nz));
-  if (c->L.state > (size_t(256) << 20))
+  if (c->L.state > (size_t(192) << 20))
     hipLaunchKernelGGL((k3_step<R, MAT, true>), grid, dim3(kBlock3), 0, c->stream, src, dst, m.phi, m.invk, m.d, k);
   else
     hipLaunchKernelGGL((k3_step<R, MAT, false>), grid, dim3(kBlock3), 0, c->stream, src, dst, m.phi, m.invk, m.d, k);

@@ -156,13 +156,20 @@ MatPtrs<R> mat_ptrs(lbm_ctx* c) {
 
 // A state beyond the 256 MB last-level cache.
 constexpr int64_t kStreamBytes = int64_t(256) << 20;
-bool streams(const lbm_ctx* c) { return int64_t(19) * c->L.plane * int64_t(c->L.esize) > kStreamBytes; }
+int64_t state_bytes(const lbm_ctx* c) { return int64_t(19) * c->L.plane * int64_t(c->L.esize); }
+bool streams(const lbm_ctx* c) { return state_bytes(c) > kStreamBytes; }
+
+// Single steps between two buffers stream from 192 MB a state, where little
+// of the other state is left in that cache (per step, cached -> streaming:
+// 3000x1000 FP32 with three fields, 217 MB, 99.0 -> 86.2 us, 2048x700 FP64,
+// 207 MB, 88.1 -> 86.1; but 2048x1024 FP32, 152 MB, 56.7 -> 61.5).
+constexpr int64_t kStepStreamBytes = int64_t(192) << 20;
 
 template <typename R, int MAT>
 void launch_step_kernel(lbm_ctx* c, const R* src, R* dst, const MatPtrs<R>& m, const Consts<R>& k,
-                        hipStream_t stream) {
+                        hipStream_t stream, int64_t stream_bytes) {
   const dim3 grid((c->g.nx + kBlock - 1) / kBlock, c->g.ny);
-  if (streams(c))
+  if (state_bytes(c) > stream_bytes)
     hipLaunchKernelGGL((k_step<R, MAT, true>), grid, dim3(kBlock), 0, stream, src, dst, m.phi, m.invk, m.d, k);
   else
     hipLaunchKernelGGL((k_step<R, MAT, false>), grid, dim3(kBlock), 0, stream, src, dst, m.phi, m.invk, m.d, k);
@@ -233,7 +240,7 @@ void launch_step_mat(lbm_ctx* c, int64_t n) {
   }
   for (int64_t i = 0; i < n; ++i) {
     launch_step_kernel<R, MAT>(c, static_cast<const R*>(c->state(c->cur)), static_cast<R*>(c->state(c->cur ^ 1)), m,
-                               k, c->stream);
+                               k, c->stream, kStepStreamBytes);
     c->cur ^= 1;
   }
 }
@@ -743,7 +750,8 @@ void launch_step_chain(lbm_ctx* c, Slot state, int n, hipStream_t stream) {
       launch_step_pair<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)),
                                     static_cast<R*>(state(j + 1)), m, k, stream);
   for (; j <= n; ++j)
-    launch_step_kernel<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)), m, k, stream);
+    launch_step_kernel<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)), m, k, stream,
+                                    kStepStreamBytes);
 }
 
 // The last segment of the checkpointed forward run steps through replay
