@@ -162,8 +162,13 @@ bool streams(const lbm_ctx* c) { return state_bytes(c) > kStreamBytes; }
 // Single steps between two buffers stream from 192 MB a state, where little
 // of the other state is left in that cache (per step, cached -> streaming:
 // 3000x1000 FP32 with three fields, 217 MB, 99.0 -> 86.2 us, 2048x700 FP64,
-// 207 MB, 88.1 -> 86.1; but 2048x1024 FP32, 152 MB, 56.7 -> 61.5).
+// 207 MB, 88.1 -> 86.1; but 2048x1024 FP32, 152 MB, 56.7 -> 61.5).  Along a
+// chain of states that are all kept (launch_step_chain), each written to memory
+// that the cache does not hold, from 40 MB (40 steps, then with the reverse
+// sweep: 1200x512 FP32, 44.5 MB, 1054 -> 899 us, 2177 -> 2103; 1024x256 FP64,
+// 38 MB, 700 -> 687, but 1842 -> 1937).
 constexpr int64_t kStepStreamBytes = int64_t(192) << 20;
+constexpr int64_t kChainStreamBytes = int64_t(40) << 20;
 
 template <typename R, int MAT>
 void launch_step_kernel(lbm_ctx* c, const R* src, R* dst, const MatPtrs<R>& m, const Consts<R>& k,
@@ -738,20 +743,28 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int32_t every) {
   return A;
 }
 
-// Steps from state(0) to state(n) of a chain of states, storing each: a
-// pair per launch where the lattice allows it, single steps otherwise.
+// Steps from state(0) to state(n) of a chain of states, storing each: a pair
+// per launch or single steps.  overlapped: the chain runs beside other work
+// (the adjoint's replay, on the second stream during a reverse sweep), where
+// pairs pay at any size: they store three states per two steps instead of
+// four, and the latency of a launch is hidden (1024x256 FP32, 60 steps forward
+// and back, pairs 1653, singles 1718 us).  Alone, pairs are faster only on
+// lattices below 2^17 nodes, which are bound by launches (40 steps, pairs /
+// singles, us: FP32 200x40 203 / 259, 400x200 280 / 277, 512x256 334 / 299,
+// 1024x256 532 / 392, 1537x431 1148 / 946, 2048x700 2383 / 1914, 4096x1024
+// 6522 / 4836; FP64 1024x256 859 / 700, 1537x431 1970 / 1747).
 template <typename R, typename Slot>
-void launch_step_chain(lbm_ctx* c, Slot state, int n, hipStream_t stream) {
+void launch_step_chain(lbm_ctx* c, Slot state, int n, hipStream_t stream, bool overlapped) {
   const MatPtrs<R> m = mat_ptrs<R>(c);
   const Consts<R> k = consts<R>(c);
   int j = 1;
-  if (two_steps_per_launch(c))
+  if (two_steps_per_launch(c) && (overlapped || int64_t(c->g.nx) * c->g.ny < kT2SmallCells))
     for (; j + 1 <= n; j += 2)
       launch_step_pair<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)),
                                     static_cast<R*>(state(j + 1)), m, k, stream);
   for (; j <= n; ++j)
     launch_step_kernel<R, MAT_FULL>(c, static_cast<const R*>(state(j - 1)), static_cast<R*>(state(j)), m, k, stream,
-                                    kStepStreamBytes);
+                                    kChainStreamBytes);
 }
 
 // The last segment of the checkpointed forward run steps through replay
@@ -765,7 +778,7 @@ lbm_status forward_last_segment(lbm_ctx* c, const AdjLayout& A, int64_t n) {
     return fail(c, LBM_ERR_DEVICE, "replay buffer copy failed");
   void* last = c->state(c->cur ^ 1);
   launch_step_chain<R>(c, [&](int64_t j) -> void* { return j < n ? buf + size_t(j) * A.state : last; }, int(n),
-                       c->stream);
+                       c->stream, false);
   c->cur ^= 1;
   c->step += n;
   return check_launch(c, "forward_checkpointed");
@@ -834,7 +847,7 @@ lbm_status backward_t(lbm_ctx* c, double dJ, void* g_invk, void* g_phi, void* g_
     if (hipMemcpyAsync(buf, ws + A.off_ck + size_t(seg) * A.state, A.state, hipMemcpyDeviceToDevice, c->aux) !=
         hipSuccess)
       return fail(c, LBM_ERR_DEVICE, "replay restore failed");
-    launch_step_chain<R>(c, [&](int j) -> void* { return buf + size_t(j) * A.state; }, seg_len(seg) - 1, c->aux);
+    launch_step_chain<R>(c, [&](int j) -> void* { return buf + size_t(j) * A.state; }, seg_len(seg) - 1, c->aux, true);
     if (hipEventRecord(c->ev_rep[b], c->aux) != hipSuccess) return fail(c, LBM_ERR_DEVICE, "replay event failed");
     return LBM_OK;
   };
