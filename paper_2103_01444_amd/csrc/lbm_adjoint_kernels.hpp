@@ -35,17 +35,23 @@ __device__ __forceinline__ int puller_offset(const Consts<R>& k, int q, int x, i
 
 // Populations [Q0, Q1) of node (x, y), y the wavefront's row; inner: the
 // wavefront lies one node or more inside the lattice (wave-uniform bases).
-template <typename R, int Q0, int Q1>
+// NT: the non-temporal hint.
+template <typename R, int Q0, int Q1, bool NT>
 __device__ __forceinline__ void pull_part(const R* __restrict__ S, const Consts<R>& k, bool inner, int x, int y,
                                           R* f) {
   if (inner) {
     const PlaneBuffer<R> b(S, k, y);
 #pragma unroll
     for (int q = Q0; q < Q1; ++q)
-      f[q - Q0] = b.template load<0>(q, -EX[q], -EY[q], uint32_t(x) * uint32_t(sizeof(R)));
+      f[q - Q0] = b.template load<NT ? 2 : 0>(q, -EX[q], -EY[q], uint32_t(x) * uint32_t(sizeof(R)));
   } else {
 #pragma unroll
-    for (int q = Q0; q < Q1; ++q) f[q - Q0] = S[pull_offset(k, q, x, y)];
+    for (int q = Q0; q < Q1; ++q) {
+      if constexpr (NT)
+        f[q - Q0] = __builtin_nontemporal_load(S + pull_offset(k, q, x, y));
+      else
+        f[q - Q0] = S[pull_offset(k, q, x, y)];
+    }
   }
 }
 
@@ -64,16 +70,16 @@ __device__ __forceinline__ void gather_part(const R* __restrict__ mu, const Cons
   }
 }
 
-// Store [Q0, Q1) of node (x, y), y the wavefront's row.
-template <typename R, int Q0, int Q1>
+// Store [Q0, Q1) of node (x, y), y the wavefront's row.  AUX: cache policy.
+template <typename R, int Q0, int Q1, int AUX>
 __device__ __forceinline__ void store_part(R* __restrict__ mu, const Consts<R>& k, int x, int y, const R* v) {
   const PlaneBuffer<R> b(mu, k, y);
 #pragma unroll
-  for (int q = Q0; q < Q1; ++q) b.template store<16>(q, 0, 0, uint32_t(x) * uint32_t(sizeof(R)), v[q - Q0]);
+  for (int q = Q0; q < Q1; ++q) b.template store<AUX>(q, 0, 0, uint32_t(x) * uint32_t(sizeof(R)), v[q - Q0]);
 }
 
 // The reverse step of one node: mu = (dS'/d pulled)^T lambda at the state S.
-// SEED: of J (times w = dJ dx / nx * 4 F C_ref / dt), no lambda.
+// SEED: of J (times w = dJ dx / nx * 4 F C_ref / dt), no lambda.  NT: of S.
 //
 // A wavefront holds consecutive nodes of row y, lane l the node x = xl + l;
 // both nodes of a boundary pair (0, 1) and (nx - 2, nx - 1) if it holds
@@ -95,7 +101,7 @@ __device__ __forceinline__ void store_part(R* __restrict__ mu, const Consts<R>& 
 // of scratch per lane in FP64 and 482 scalar-register spills; in two passes
 // no instance spills vector registers.  Per reverse step at 200x40 FP64 29.8
 // -> 9.2 us.  (Gradients of the spilled forms have differed from run to run.)
-template <typename R, bool SEED, bool EXT, typename Gather, typename Put>
+template <typename R, bool SEED, bool EXT, bool NT, typename Gather, typename Put>
 __device__ __forceinline__ void reverse_node(const R* __restrict__ S, const R* __restrict__ phi_f,
                                              const R* __restrict__ invk_f, const R* __restrict__ d_f,
                                              const Consts<R>& k, int x, int y, int xl, bool inner, R w,
@@ -114,8 +120,8 @@ __device__ __forceinline__ void reverse_node(const R* __restrict__ S, const R* _
 
   AdjMat<R> m = adj_material<R>(k, phi_f, invk_f, d_f, xp, y);
   R f[9], g[10];
-  pull_part<R, 9, 19>(S, k, inner, xp, y, g);
-  pull_part<R, 0, 9>(S, k, inner, xp, y, f);
+  pull_part<R, 9, 19, NT>(S, k, inner, xp, y, g);
+  pull_part<R, 0, 9, NT>(S, k, inner, xp, y, f);
   // Thin-film CL (EXT): the bottom row's wall-crossing populations react as
   // the forward pull left them (column nx - 2's film for the outlet).
   const bool film = EXT && (k.flags & F_THIN_CL) && react && y == k.ny - 1;
@@ -318,7 +324,12 @@ __device__ __forceinline__ void reverse_node(const R* __restrict__ S, const R* _
 }
 
 // One reverse step, one launch: mu_out at the state S from mu_in, gradients
-// accumulated into grad (planes phi, 1/K, D_eff).
+// accumulated into grad (planes phi, 1/K, D_eff).  S is one state of a chain,
+// read once here: non-temporal loads and plain stores leave the last-level
+// cache to mu (41 steps back on lattices periodic in x, cached S and written
+// through -> this, us: FP32 1537x431 1591 -> 1455, 2048x700 3028 -> 2387, FP64
+// 1537x431 3043 -> 2308; with the checkpoints' replay beside it FP32 1024x256,
+// 60 steps, 1311 -> 1236).
 template <typename R, bool SEED, bool EXT = false>
 __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, const R* __restrict__ mu_in,
                                                      R* __restrict__ mu_out, R* __restrict__ grad,
@@ -330,10 +341,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R* __restrict__ S, co
   if ((unsigned)x >= (unsigned)k.nx) return;
   const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
   R g0, g1, g2;
-  reverse_node<R, SEED, EXT>(
+  reverse_node<R, SEED, EXT, true>(
       S, phi_f, invk_f, d_f, k, x, y, x - int(threadIdx.x & 63), inner, w,
       [&](auto q0, auto& la) { gather_part<R, q0(), q0() + sizeof(la) / sizeof(R)>(mu_in, k, inner, x, y, la); },
-      [&](auto q0, const auto& mu) { store_part<R, q0(), q0() + sizeof(mu) / sizeof(R)>(mu_out, k, x, y, mu); }, g0,
+      [&](auto q0, const auto& mu) { store_part<R, q0(), q0() + sizeof(mu) / sizeof(R), 0>(mu_out, k, x, y, mu); }, g0,
       g1, g2);
   const int o = y * k.pitch + x;
   grad[o] += g0;
@@ -376,7 +387,7 @@ __global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S
   if (row && x < xr) {
     const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
     R* p = lds + j * 19 * 64 + i;
-    reverse_node<R, false, EXT>(
+    reverse_node<R, false, EXT, false>(
         S1, phi_f, invk_f, d_f, k, x, y, xl, inner, R(0),
         [&](auto q0, auto& la) { gather_part<R, q0(), q0() + sizeof(la) / sizeof(R)>(mu_in, k, inner, x, y, la); },
         [&](auto q0, const auto& mu) {
@@ -391,7 +402,7 @@ __global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S
   if (!(row && own)) return;
   const bool inner = __all(x >= 1 && x <= k.nx - 2) && y >= 1 && y <= k.ny - 2;
   const R* p = lds + j * 19 * 64 + i;
-  reverse_node<R, false, EXT>(
+  reverse_node<R, false, EXT, false>(
       S0, phi_f, invk_f, d_f, k, x, y, xl, inner, R(0),
       [&](auto q0, auto& la) {
 #pragma unroll
@@ -403,7 +414,7 @@ __global__ __launch_bounds__(64 * ROWS) void k_adj_step2(const R* __restrict__ S
         }
       },
       [&](auto q0, const auto& mu) {
-        store_part<R, q0(), q0() + sizeof(mu) / sizeof(R)>(mu_out, k, x, y, mu);
+        store_part<R, q0(), q0() + sizeof(mu) / sizeof(R), 16>(mu_out, k, x, y, mu);
       },
       gb[0], gb[1], gb[2]);
   const int o = y * k.pitch + x;
